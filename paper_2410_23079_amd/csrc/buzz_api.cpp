@@ -93,9 +93,10 @@ inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 struct Layout {
-    size_t K, V, score, pos, logit[2], stat[2], ticket, part_ml, part_o, sel, stK, stV, stScore, stPos, pscore, obs_stats, total;
+    size_t K, V, score, pos, logit[2], stat[2], ticket, part_ml, part_o, sel, stK, stV, stScore, stPos, pscore, obs_stats, obs_partial, total;
     int32_t cap, old_cap, ring_cap, ring_base, s_cap, sel_stride, st_rows;
     int32_t units, G, elem, row_bytes, old_stride, keep;
+    size_t obs_stats_cap, obs_partial_cap;   // elements ((max, sum) pairs, column sums) of the two scoring arrays
 };
 
 int make_layout(const buzz_config_t* c, Layout* L)
@@ -189,8 +190,13 @@ int make_layout(const buzz_config_t* c, Layout* L)
     L->pscore = take((size_t)units * c->max_context * 4);
     {   // prefill scoring statistics: what the vector path (fp32) or the matrix-core path (16-bit) needs
         const size_t vec = (size_t)units * ceil_div(c->max_context, kObsKeyBlock) * kObsRows * 2 * 4;
-        const size_t mma = (size_t)c->batch * c->n_q_heads * kObsKeySplits * kObsPassRows * 2 * 4;
-        L->obs_stats = take(c->kv_dtype == BUZZ_FP32 ? vec : mma);
+        size_t mma = (size_t)c->batch * c->n_q_heads * (c->max_context < kObsPassRows ? c->max_context : kObsPassRows);
+        const size_t sums = (size_t)units * c->max_context * kObsItemParts;
+        const size_t cut = mma * kObsKeyParts < kObsPartElems ? mma * kObsKeyParts : kObsPartElems;
+        L->obs_stats_cap = mma = mma < cut ? cut : mma;         // (uncut, every query leaves one pair)
+        L->obs_stats = take(c->kv_dtype == BUZZ_FP32 ? vec : mma * 2 * 4);
+        L->obs_partial_cap = c->kv_dtype == BUZZ_FP32 ? 0 : sums < kObsPartElems ? sums : kObsPartElems;
+        L->obs_partial = take(L->obs_partial_cap * 4);
     }
     L->total = off;
     return BUZZ_OK;
@@ -586,8 +592,9 @@ int buzz_prefill(buzz_cache_t* c, const void* kp, const void* vp, int64_t N, con
         float* ps = c->at<float>(L.pscore);
         if (int rc = probe_die_placement(st)) return rc;
         if (hipError_t e = launch_fill_f32(c->at<float>(L.ticket), nullptr, L.units, st)) return hip_rc(e);
-        // starting scores, one row of N per unit
-        if (hipError_t e = launch_fill_f32(ps, init_score, (int64_t)L.units * N, st)) return hip_rc(e);
+        // starting scores, one row of N per unit; with observed queries the scoring itself starts from them
+        if (n_obs == 0)
+            if (hipError_t e = launch_fill_f32(ps, init_score, (int64_t)L.units * N, st)) return hip_rc(e);
         if (n_obs > 0) {
             const int G = L.G;
             const int max_q = obs_pass_queries(cfg.kv_dtype, G);   // queries of one head per pass
@@ -599,13 +606,10 @@ int buzz_prefill(buzz_cache_t* c, const void* kp, const void* vp, int64_t N, con
                 oa.Hq = cfg.n_q_heads; oa.Hkv = cfg.n_kv_heads;
                 oa.scale_log2 = c->scale * 1.4426950408889634f;
                 oa.log_n = (cfg.flags & BUZZ_FLAG_LOG_N) ? 1 : 0;
-                {   // few observed queries leave the row-statistics step with fewer blocks than compute units:
-                    // then up to kObsKeySplits blocks share a query group's keys (at least 512 keys each)
-                    const int64_t blocks = (int64_t)cfg.batch * cfg.n_q_heads * ceil_div(oa.t_count, 256);
-                    int64_t ks = ceil_div(3 * (int64_t)compute_units(), blocks);
-                    if (ks > N / 512) ks = N / 512;
-                    oa.key_splits = (int32_t)(ks < 1 ? 1 : (ks > kObsKeySplits ? kObsKeySplits : ks));
-                }
+                oa.init = init_score; oa.first_pass = t0 == 0 ? 1 : 0;
+                oa.partial = c->at<float>(L.obs_partial);
+                oa.stats_cap = L.obs_stats_cap; oa.partial_cap = L.obs_partial_cap;
+                oa.compute_units = compute_units();
                 if (hipError_t e = launch_obs_scores(cfg.kv_dtype, cfg.head_dim, G, oa, L.units, st)) return hip_rc(e);
             }
         }

@@ -45,6 +45,12 @@ __device__ inline float query_scale(const ObsArgs& a, int pos)
     return a.log_n ? a.scale_log2 * (logf((float)(pos + 1)) * (1.0f / 6.2383246250395077f)) : a.scale_log2;
 }
 
+// the prompt scores a pass of step 2 adds to: the caller's starting scores (or 0) before the first pass
+__device__ inline float score_so_far(const ObsArgs& a, size_t i)
+{
+    return a.first_pass ? (a.init ? a.init[i] : 0.f) : a.score[i];
+}
+
 template <int DT> struct Vec { static constexpr int N = DT == BUZZ_FP32 ? 4 : 8; };
 
 constexpr int kTile = 32;   // rows staged in LDS per trip
@@ -186,7 +192,7 @@ __global__ __launch_bounds__(256) void obs_col_sums_kernel(const ObsArgs a, cons
             col += p;
         }
     }
-    if (j < a.N) a.score[(size_t)unit * a.N + j] += col;
+    if (j < a.N) a.score[(size_t)unit * a.N + j] = score_so_far(a, (size_t)unit * a.N + j) + col;
 }
 
 
@@ -222,6 +228,29 @@ template <> __device__ inline f32x4 mma16<BUZZ_FP16>(const u32x4& a, const u32x4
 
 constexpr int kMmaCols = 64;            // stationary vectors per wave
 constexpr int kMmaBlockCols = 256;      // ... per block of four waves
+
+// Causal work is a triangle: the blocks of the last 256 queries (step 1) and of the first 256 keys (step 2)
+// stream the whole prompt, the others proportionally less, and a layer with few heads has fewer blocks than the
+// chip holds.  So a block streams at most `part_len` of its moving rows (in chunks; step 2: items of one chunk of
+// one head), every group of stationary vectors is served by as many blocks as that takes, and all blocks but each
+// group's last are equally long.  (The rule of the launch is at launch_obs_mfma_t.)
+// How many parts the stationary queries of the block that holds query t (step 1) have: its latest query sees most.
+__device__ inline int stat_parts(const ObsArgs& a, int t, int chunk_rows)
+{
+    const int block_end = min(t - (t - a.t_begin) % kMmaBlockCols + kMmaBlockCols, a.t_begin + a.t_count);
+    const int chunks = (a.N - a.n_obs + block_end - 1) / chunk_rows + 1;
+    return (chunks + a.key_part_len - 1) / a.key_part_len;
+}
+
+// Step 2: the chunks of queries, on the grid anchored at t_begin, that see the keys of the block starting at key
+// j_block; *t_lo is the first one's first query.
+__host__ __device__ inline int seeing_chunks(const ObsArgs& a, int j_block, int chunk_rows, int* t_lo)
+{
+    const int shift = a.N - a.n_obs, t_end = a.t_begin + a.t_count;
+    const int t_first = j_block - shift > a.t_begin ? j_block - shift : a.t_begin;
+    *t_lo = a.t_begin + (t_first - a.t_begin) / chunk_rows * chunk_rows;
+    return *t_lo < t_end ? (t_end - *t_lo + chunk_rows - 1) / chunk_rows : 0;
+}
 
 // The moving rows of one chunk in LDS.  A row occupies its D * 2 bytes plus 16: with that pitch the 16
 // lanes that read the same piece of 16 different rows fall on 16 different groups of four banks.
@@ -293,16 +322,16 @@ __global__ __launch_bounds__(256) void obs_mfma_kernel(const ObsArgs a)
         const int unit = b * a.Hkv + h / G;
         // the latest queries see the most keys: their blocks go first, for all heads, so that the launch
         // ends with the short blocks (blockIdx.x, which the dispatcher advances first, is the head)
-        // blockIdx.y = (group of 256 queries, part of its keys): a.key_splits blocks share a group
-        const int q_blocks = (int)gridDim.y / a.key_splits;
-        const int part = (int)blockIdx.y % a.key_splits;
-        const int t_block = a.t_begin + (q_blocks - 1 - (int)blockIdx.y / a.key_splits) * kMmaBlockCols;
+        // blockIdx.y = (group of 256 queries, part of its keys): up to a.key_parts blocks share a group
+        const int q_blocks = (int)gridDim.y / a.key_parts;
+        const int part = (int)blockIdx.y % a.key_parts;
+        const int t_block = a.t_begin + (q_blocks - 1 - (int)blockIdx.y / a.key_parts) * kMmaBlockCols;
         if (t_block >= t_end) return;
         const int t_base = t_block + wave * kMmaCols;
         const bool active = t_base < t_end;                // a wave without queries still copies and synchronises
         const char* Qb = (const char*)a.q_obs + (size_t)head * a.n_obs * ROWB;
         const char* Kb = (const char*)a.K + (size_t)unit * a.N * ROWB;
-        constexpr float kRefStart = -1.0e30f, kRefSlack = 1073741824.0f;   // 2^30
+        constexpr float kRefStart = -3.402823466e38f, kRefSlack = 1073741824.0f;   // lowest float, 2^30
         u32x4 qf[CT][QP];
         int pos[CT];
         float scale[CT], m[CT], l[CT];
@@ -320,17 +349,17 @@ __global__ __launch_bounds__(256) void obs_mfma_kernel(const ObsArgs a)
         const int k_free = shift + t_base;                 // keys up to here are visible to every query of the wave
         const int k_last_block = shift + min(t_block + kMmaBlockCols, t_end) - 1;
         const int n_chunks = k_last_block / CH + 1;
-        const int per_part = (n_chunks + a.key_splits - 1) / a.key_splits;
-        const int c_begin = part * per_part, c_end = min(n_chunks, c_begin + per_part);   // this block's chunks
+        const int c_begin = part * a.key_part_len, c_end = min(n_chunks, c_begin + a.key_part_len);   // this block's chunks
+        if (c_begin >= c_end) return;                      // the group has fewer parts
         // Lazy reference: a lane sums exp2(s * scale - ref) against a reference that only moves when it has
         // to.  A chunk costs one fma, one exp2 and one add per element, straight-line code per 16 x 64 tile
         // (four independent chains of matrix instructions and the vector work on their results) with none
         // of the maximum bookkeeping, and one test at its end: if a sum of the wave has grown past kRefSlack
         // (or overflowed), the sums go back to their values before the chunk and the chunk is redone the
         // classic way, tile by tile: the reference rises to the running maximum and the sum so far is
-        // rescaled.  The reference starts so low that the first chunk with a visible key always takes the
-        // classic path; after it the test fails only when a logit exceeds its lane's reference by about 30
-        // (log2 units).  m[] holds the reference in scaled (log2) units.
+        // rescaled.  The block's first chunk goes the classic way at once (the reference starts at the lowest
+        // float, so trying it otherwise would only be thrown away); after it the test fails only when a logit
+        // exceeds its lane's reference by about 30 (log2 units).  m[] holds the reference in scaled (log2) units.
         auto products = [&](const u32x4 (&kf)[QP], int ct) {
             f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -376,26 +405,30 @@ __global__ __launch_bounds__(256) void obs_mfma_kernel(const ObsArgs a)
                 float l_in[CT];
 #pragma unroll
                 for (int ct = 0; ct < CT; ++ct) l_in[ct] = l[ct];
-                // (head_dim <= 128) the operand of tile i + 1 leaves LDS while tile i is computed; reading
-                // past the wave's last tile stays inside the buffer and is never used
                 u32x4 kf[2][QP];
-                MC::fetch(kf[0], sm_rows[c & 1], 0, j, q);
+                bool classic = c == c_begin;
+                if (!classic) {
+                    // (head_dim <= 128) the operand of tile i + 1 leaves LDS while tile i is computed; reading
+                    // past the wave's last tile stays inside the buffer and is never used
+                    MC::fetch(kf[0], sm_rows[c & 1], 0, j, q);
 #pragma unroll
-                for (int tile = 0; tile < CH / 16; ++tile) {
-                    const int k0 = c * CH + 16 * tile;
-                    if (AHEAD && tile + 1 < CH / 16) MC::fetch(kf[(tile + 1) & 1], sm_rows[c & 1], tile + 1, j, q);
-                    if (!AHEAD && tile > 0) MC::fetch(kf[0], sm_rows[c & 1], tile, j, q);
-                    if (k0 <= k_last) {
-                        // wave-uniform: does a causal boundary or the end of the query list cross this tile?
-                        if (k0 + 15 > k_free || t_base + kMmaCols > t_end) add_tile(kf[AHEAD ? tile & 1 : 0], k0, std::true_type{});
-                        else add_tile(kf[AHEAD ? tile & 1 : 0], k0, std::false_type{});
+                    for (int tile = 0; tile < CH / 16; ++tile) {
+                        const int k0 = c * CH + 16 * tile;
+                        if (AHEAD && tile + 1 < CH / 16) MC::fetch(kf[(tile + 1) & 1], sm_rows[c & 1], tile + 1, j, q);
+                        if (!AHEAD && tile > 0) MC::fetch(kf[0], sm_rows[c & 1], tile, j, q);
+                        if (k0 <= k_last) {
+                            // wave-uniform: does a causal boundary or the end of the query list cross this tile?
+                            if (k0 + 15 > k_free || t_base + kMmaCols > t_end) add_tile(kf[AHEAD ? tile & 1 : 0], k0, std::true_type{});
+                            else add_tile(kf[AHEAD ? tile & 1 : 0], k0, std::false_type{});
+                        }
                     }
+                    // the sums are nonnegative: their total passes the test only if each of them does; !(<=) also
+                    // catches a sum that overflowed or is not a number
+                    const float total = (l[0] + l[1]) + (l[2] + l[3]);
+                    static_assert(CT == 4, "the test adds four sums");
+                    classic = __builtin_amdgcn_ballot_w64(!(total <= kRefSlack)) != 0;
                 }
-                // the sums are nonnegative: their total passes the test only if each of them does; !(<=) also
-                // catches a sum that overflowed or is not a number
-                const float total = (l[0] + l[1]) + (l[2] + l[3]);
-                static_assert(CT == 4, "the test adds four sums");
-                if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(total <= kRefSlack)) != 0, 0)) {
+                if (__builtin_expect(classic, 0)) {
 #pragma unroll
                     for (int ct = 0; ct < CT; ++ct) l[ct] = l_in[ct];
 #pragma unroll 1
@@ -422,15 +455,22 @@ __global__ __launch_bounds__(256) void obs_mfma_kernel(const ObsArgs a)
             }
             const int t = t_base + 16 * ct + j;
             if (q == 0 && t < t_end) {                     // (a part without visible keys leaves (kRefStart, 0))
-                float* st = a.stats + (((size_t)head * a.key_splits + part) * kObsPassRows + (t - a.t_begin)) * 2;
+                float* st = a.stats + (((size_t)head * a.key_parts + part) * a.t_count + (t - a.t_begin)) * 2;
                 st[0] = m[ct];                             // reference of the scaled logits (at most their maximum)
-                st[1] = l[ct];
+                st[1] = a.key_parts > 1 ? l[ct] : 1.0f / l[ct];
             }
         }
     } else {
         const int unit = blockIdx.x;                       // the earliest keys are seen by the most queries: they go first
+        const int part = (int)blockIdx.y % a.item_parts;   // blockIdx.y = (block of 256 keys, part of its items)
         const int b = unit / a.Hkv, kvh = unit - b * a.Hkv;
-        const int j_block = blockIdx.y * kMmaBlockCols;
+        const int j_block = (int)blockIdx.y / a.item_parts * kMmaBlockCols;
+        // the block streams the queries from the first one that sees its first key, for every head of the group in
+        // turn: item i = (head i / n_chunks, chunk i % n_chunks), and of these its own part
+        int t_lo;
+        const int n_chunks = seeing_chunks(a, j_block, CH, &t_lo);
+        const int item0 = part * a.item_part_len, n_items = min(n_chunks * G, item0 + a.item_part_len);
+        if (part > 0 && item0 >= n_items) return;          // fewer parts here (part 0 carries the scores over)
         const int j_base = j_block + wave * kMmaCols;
         const bool active = j_base < a.N;
         const char* Kb = (const char*)a.K + (size_t)unit * a.N * ROWB;
@@ -443,33 +483,14 @@ __global__ __launch_bounds__(256) void obs_mfma_kernel(const ObsArgs a)
             for (int p = 0; p < QP; ++p) kf[ct][p] = piece(row, p);
             col[ct] = 0.f;
         }
-        // the block streams the queries from the first one that sees its first key, on the chunk grid
-        // anchored at t_begin, for every head of the group in turn: item i = (head i / n_chunks, chunk i % n_chunks)
-        const int t_first = max(j_block - shift, a.t_begin);
-        const int t_lo = a.t_begin + (t_first - a.t_begin) / CH * CH;
-        const int n_chunks = t_lo < t_end ? (t_end - t_lo + CH - 1) / CH : 0;
-        const int n_items = n_chunks * G;
         const int head0 = b * a.Hq + kvh * G;
         float2 staged_stat = make_float2(0.f, 0.f);
         auto request = [&](int item) {
             const int g = item / n_chunks, t0 = t_lo + (item - g * n_chunks) * CH;
             MC::request(staged, (const char*)a.q_obs + (size_t)(head0 + g) * a.n_obs * ROWB, t0, a.n_obs - 1);
-            if (threadIdx.x < CH) {                        // merge the parts: (reference, sum) -> (reference, 1 / sum)
-                const float* st = a.stats + ((size_t)(head0 + g) * a.key_splits * kObsPassRows +
-                                             (min(t0 + (int)threadIdx.x, t_end - 1) - a.t_begin)) * 2;
-                float2 part[kObsKeySplits];
-#pragma unroll
-                for (int k = 0; k < kObsKeySplits; ++k)
-                    part[k] = *(const float2*)(st + (size_t)min(k, a.key_splits - 1) * kObsPassRows * 2);
-                float ref = part[0].x;
-#pragma unroll
-                for (int k = 1; k < kObsKeySplits; ++k) ref = fmaxf(ref, part[k].x);   // part 0 holds key 0: finite, l > 0
-                float sum = 0.f;
-#pragma unroll
-                for (int k = 0; k < kObsKeySplits; ++k)
-                    if (k < a.key_splits) sum = fmaf(part[k].y, __builtin_amdgcn_exp2f(part[k].x - ref), sum);
-                staged_stat = make_float2(ref, 1.0f / sum);
-            }
+            if (threadIdx.x < CH)                          // the reference and 1 / sum of the chunk's queries
+                staged_stat = *(const float2*)(a.stats + ((size_t)(head0 + g) * a.key_parts * a.t_count +
+                                                          (min(t0 + (int)threadIdx.x, t_end - 1) - a.t_begin)) * 2);
         };
         auto store = [&](int buf) {
             MC::store(sm_rows[buf], staged);
@@ -499,12 +520,12 @@ __global__ __launch_bounds__(256) void obs_mfma_kernel(const ObsArgs a)
                 }
             }
         };
-        if (n_items > 0) {
-            request(0);
-            store(0);
+        if (item0 < n_items) {
+            request(item0);
+            store(item0 & 1);
         }
         __syncthreads();
-        for (int item = 0; item < n_items; ++item) {
+        for (int item = item0; item < n_items; ++item) {
             const bool more = item + 1 < n_items;
             if (more) request(item + 1);
             if (active) {
@@ -538,22 +559,108 @@ __global__ __launch_bounds__(256) void obs_mfma_kernel(const ObsArgs a)
             float c = col[ct] + __shfl_xor(col[ct], 16);
             c += __shfl_xor(c, 32);
             const int key = j_base + 16 * ct + j;
-            if (q == 0 && key < a.N) a.score[(size_t)unit * a.N + key] += c;
+            if (q == 0 && key < a.N) {
+                const size_t at = (size_t)unit * a.N + key;
+                if (a.item_parts == 1) a.score[at] = score_so_far(a, at) + c;
+                else a.partial[(size_t)part * gridDim.x * a.N + at] = c;
+            }
         }
     }
 }
 
-template <int DT, int D>
-hipError_t launch_obs_mfma_t(const ObsArgs& a, int units, hipStream_t st, Timing tm)
+// Merges the parts of a query's row statistics into its part 0: (reference, sum) of every part -> (reference,
+// 1 / sum).  (Done by the blocks of step 2 as they stage a chunk, the arithmetic waits for loads that are
+// otherwise in flight across a chunk's tiles: step 2 of 256 heads of 128, 256 queries, 4096 keys: 120 us with the merge inside, 98 us
+// without, 5 us for this kernel.)
+__global__ __launch_bounds__(256) void obs_merge_stats_kernel(const ObsArgs a, int chunk_rows)
 {
-    const int heads = units / a.Hkv * a.Hq;
-    const dim3 g1(heads, (a.t_count + kMmaBlockCols - 1) / kMmaBlockCols * a.key_splits), g2(units, (a.N + kMmaBlockCols - 1) / kMmaBlockCols);
+    const int r = blockIdx.x * 256 + threadIdx.x, head = blockIdx.y;
+    if (r >= a.t_count) return;
+    float2* st = (float2*)a.stats + (size_t)head * a.key_parts * a.t_count + r;
+    const int parts = stat_parts(a, a.t_begin + r, chunk_rows);
+    float2 got[kObsKeyParts];
+#pragma unroll
+    for (int k = 0; k < kObsKeyParts; ++k) got[k] = st[(size_t)min(k, parts - 1) * a.t_count];
+    float ref = got[0].x;                                  // part 0 holds key 0: finite, sum > 0
+#pragma unroll
+    for (int k = 1; k < kObsKeyParts; ++k) ref = fmaxf(ref, got[k].x);
+    float sum = got[0].y * __builtin_amdgcn_exp2f(got[0].x - ref);
+#pragma unroll
+    for (int k = 1; k < kObsKeyParts; ++k)
+        if (k < parts) sum = fmaf(got[k].y, __builtin_amdgcn_exp2f(got[k].x - ref), sum);
+    st[0] = make_float2(ref, 1.0f / sum);
+}
+
+// Adds the parts of a key block's column sums to the prompt scores, in part order (the same bits every time).
+// Latency-bound, 5 us at 16 units of 4001 keys, against 290 us that the cut of step 2 saves there.
+__global__ __launch_bounds__(256) void obs_sum_parts_kernel(const ObsArgs a, int chunk_rows)
+{
+    const int j = blockIdx.x * 256 + threadIdx.x, unit = blockIdx.y;
+    if (j >= a.N) return;
+    int t_lo;
+    const int items = seeing_chunks(a, j / kMmaBlockCols * kMmaBlockCols, chunk_rows, &t_lo) * (a.Hq / a.Hkv);
+    const int parts = (items + a.item_part_len - 1) / a.item_part_len;
+    const size_t at = (size_t)unit * a.N + j;
+    float got[kObsItemParts];
+#pragma unroll
+    for (int p = 0; p < kObsItemParts; ++p) got[p] = p < parts ? a.partial[(size_t)p * gridDim.y * a.N + at] : 0.f;
+    float s = score_so_far(a, at);
+#pragma unroll
+    for (int p = 0; p < kObsItemParts; ++p) s += got[p];
+    a.score[at] = s;
+}
+
+template <int DT, int D>
+hipError_t launch_obs_mfma_t(ObsArgs a, int units, hipStream_t st, Timing tm)
+{
+    constexpr int CH = MovingChunk<D>::ROWS;
+    const int heads = units / a.Hkv * a.Hq, G = a.Hq / a.Hkv;
+    const int q_blocks = (a.t_count + kMmaBlockCols - 1) / kMmaBlockCols;
+    const int k_blocks = (a.N + kMmaBlockCols - 1) / kMmaBlockCols;
+    // A step whose longest block is no more than its share of two blocks per compute unit stays whole: the long
+    // blocks start first and have the SIMDs more and more to themselves, and parts would only repeat the blocks'
+    // prologue (64 heads of 128, 4096 queries: 347 us whole, 385 us cut).  Below that it is cut for four blocks
+    // per compute unit (16 heads on 4 kv heads, 4001 queries: 622 us whole, 369 us cut; six or eight: the same).
+    auto split = [&](int64_t total, int longest, int most, int* parts, int* len) {
+        const int64_t cus = a.compute_units;
+        int64_t l = longest <= (total + 2 * cus - 1) / (2 * cus) ? longest : (total + 4 * cus - 1) / (4 * cus);
+        if (l < (longest + most - 1) / most) l = (longest + most - 1) / most;
+        *len = (int)(l < 1 ? 1 : l);
+        *parts = longest > 0 ? (int)((longest + *len - 1) / *len) : 1;
+    };
+    int64_t total = 0;
+    int longest = 0;
+    for (int b = 0; b < q_blocks; ++b) {
+        const int end = (b + 1) * kMmaBlockCols < a.t_count ? (b + 1) * kMmaBlockCols : a.t_count;
+        const int chunks = (a.N - a.n_obs + a.t_begin + end - 1) / CH + 1;
+        total += (int64_t)chunks * heads;
+        longest = chunks;
+    }
+    int most = (int)(a.stats_cap / ((size_t)heads * a.t_count));       // what the statistics array holds
+    split(total, longest, most < kObsKeyParts ? (most < 1 ? 1 : most) : kObsKeyParts, &a.key_parts, &a.key_part_len);
+    total = 0;
+    int t_lo;
+    for (int b = 0; b < k_blocks; ++b) total += (int64_t)seeing_chunks(a, b * kMmaBlockCols, CH, &t_lo) * G * units;
+    longest = seeing_chunks(a, 0, CH, &t_lo) * G;
+    most = (int)(a.partial_cap / ((size_t)units * a.N));
+    split(total, longest, most < kObsItemParts ? (most < 1 ? 1 : most) : kObsItemParts, &a.item_parts, &a.item_part_len);
+    const dim3 g1(heads, q_blocks * a.key_parts), g2(units, k_blocks * a.item_parts);
+    if (g1.y > 65535 || g2.y > 65535) return hipErrorInvalidValue;
     if (a.log_n) BUZZ_LAUNCH((obs_mfma_kernel<DT, D, 1, true>), g1, dim3(256), 0, st, tm, a);
     else BUZZ_LAUNCH((obs_mfma_kernel<DT, D, 1, false>), g1, dim3(256), 0, st, tm, a);
     if (hipError_t e = hipGetLastError()) return e;
+    if (a.key_parts > 1) {
+        BUZZ_LAUNCH(obs_merge_stats_kernel, dim3((a.t_count + 255) / 256, heads), dim3(256), 0, st, tm, a, CH);
+        if (hipError_t e = hipGetLastError()) return e;
+    }
     if (a.log_n) BUZZ_LAUNCH((obs_mfma_kernel<DT, D, 2, true>), g2, dim3(256), 0, st, tm, a);
     else BUZZ_LAUNCH((obs_mfma_kernel<DT, D, 2, false>), g2, dim3(256), 0, st, tm, a);
-    return hipGetLastError();
+    if (hipError_t e = hipGetLastError()) return e;
+    if (a.item_parts > 1) {
+        BUZZ_LAUNCH(obs_sum_parts_kernel, dim3((a.N + 255) / 256, units), dim3(256), 0, st, tm, a, CH);
+        return hipGetLastError();
+    }
+    return hipSuccess;
 }
 
 template <int DT>
