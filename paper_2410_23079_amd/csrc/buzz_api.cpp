@@ -188,14 +188,13 @@ int make_layout(const buzz_config_t* c, Layout* L)
     L->stScore = take(strows * 4);
     L->stPos = take(strows * 4);
     L->pscore = take((size_t)units * c->max_context * 4);
-    {   // prefill scoring statistics: what the vector path (fp32) or the matrix-core path (16-bit) needs
-        const size_t vec = (size_t)units * ceil_div(c->max_context, kObsKeyBlock) * kObsRows * 2 * 4;
+    {   // prefill scoring: the queries' statistics and the column sums of steps that are cut into parts
         size_t mma = (size_t)c->batch * c->n_q_heads * (c->max_context < kObsPassRows ? c->max_context : kObsPassRows);
         const size_t sums = (size_t)units * c->max_context * kObsItemParts;
         const size_t cut = mma * kObsKeyParts < kObsPartElems ? mma * kObsKeyParts : kObsPartElems;
         L->obs_stats_cap = mma = mma < cut ? cut : mma;         // (uncut, every query leaves one pair)
-        L->obs_stats = take(c->kv_dtype == BUZZ_FP32 ? vec : mma * 2 * 4);
-        L->obs_partial_cap = c->kv_dtype == BUZZ_FP32 ? 0 : sums < kObsPartElems ? sums : kObsPartElems;
+        L->obs_stats = take(mma * 2 * 4);
+        L->obs_partial_cap = sums < kObsPartElems ? sums : kObsPartElems;
         L->obs_partial = take(L->obs_partial_cap * 4);
     }
     L->total = off;
@@ -596,8 +595,7 @@ int buzz_prefill(buzz_cache_t* c, const void* kp, const void* vp, int64_t N, con
         if (n_obs == 0)
             if (hipError_t e = launch_fill_f32(ps, init_score, (int64_t)L.units * N, st)) return hip_rc(e);
         if (n_obs > 0) {
-            const int G = L.G;
-            const int max_q = obs_pass_queries(cfg.kv_dtype, G);   // queries of one head per pass
+            const int max_q = kObsPassRows;                     // queries of one head per pass
             for (int64_t t0 = 0; t0 < n_obs; t0 += max_q) {
                 ObsArgs oa{};
                 oa.K = kp; oa.q_obs = q_obs; oa.score = ps; oa.stats = c->at<float>(L.obs_stats);
@@ -610,7 +608,7 @@ int buzz_prefill(buzz_cache_t* c, const void* kp, const void* vp, int64_t N, con
                 oa.partial = c->at<float>(L.obs_partial);
                 oa.stats_cap = L.obs_stats_cap; oa.partial_cap = L.obs_partial_cap;
                 oa.compute_units = compute_units();
-                if (hipError_t e = launch_obs_scores(cfg.kv_dtype, cfg.head_dim, G, oa, L.units, st)) return hip_rc(e);
+                if (hipError_t e = launch_obs_scores(cfg.kv_dtype, cfg.head_dim, oa, L.units, st)) return hip_rc(e);
             }
         }
         GatherArgs g{};

@@ -151,31 +151,28 @@ struct ObsArgs {               // prefill scoring: causal attention of observed 
     const void* q_obs;         // [B][Hq][n_obs][D]; query t sits at prompt position N - n_obs + t
     float* score;              // [units][N]   the prompt scores, written by the first pass, added to by later ones
     const float* init;         // [units][N]   starting scores, NULL: zeros
-    float* stats;              // vector path: [units][key_blocks][kObsRows][2] per key-block (max, sum) of every query
-                               // row; matrix-core path: [B * Hq][key_parts][t_count][2] (reference, sum) of
-                               // every query over each part of its keys
-    float* partial;            // matrix-core path: [item_parts][units][N] column sums, each over a part of the queries
+    float* stats;              // [B * Hq][key_parts][t_count][2] (reference, sum) of every query over each part of its keys
+    float* partial;            // [item_parts][units][N] column sums, each over a part of the queries
     size_t stats_cap;          // (reference, sum) pairs the statistics array holds
     size_t partial_cap;        // column sums the partial array holds
     int32_t N, n_obs;
-    int32_t t_begin, t_count;  // queries scored by this pass; at most obs_pass_queries()
+    int32_t t_begin, t_count;  // queries scored by this pass; at most kObsPassRows
     int32_t Hq, Hkv;
     int32_t log_n;             // 1: a query at prompt position i is scaled by log(i + 1) / log(512) (Sec. 3.5)
     int32_t first_pass;        // 1: the scores start from `init`
     int32_t compute_units;
-    // matrix-core path, set by the launch: blocks that share the keys of one group of 256 queries and the chunks of
-    // keys each takes; blocks that share the queries of one block of 256 keys and the (head, chunk) items each takes
+    // set by the launch: blocks that share the keys of one group of queries and the chunks of keys each takes;
+    // blocks that share the queries of one block of keys and the (head, chunk) items each takes
     int32_t key_parts, key_part_len, item_parts, item_part_len;
+    int32_t heads, units;      // B * Hq, B * Hkv (set by the launch)
     float scale_log2;
 };
 
-constexpr int kObsRows = 256;        // query rows (query x group member) per pass = threads per block
-constexpr int kObsKeyBlock = 1024;   // keys per block of the row-statistics kernel
-constexpr int kObsPassRows = 4096;   // matrix-core scoring: queries per head and pass
-constexpr int kObsKeyParts = 8;      // ... and the most blocks that share one query group's keys
+constexpr int kObsPassRows = 4096;   // prompt scoring: queries per head and pass
+constexpr int kObsKeyParts = 16;     // ... and the most blocks that share one query group's keys
 constexpr int kObsItemParts = 16;    // ... or one key block's queries
 // Elements of the two arrays that hold the parts' results: what the launch's rule can ask for.  It cuts a step
-// with fewer than 4 blocks (of 256 stationary vectors) per compute unit into at most 8 per unit and one remainder
+// with fewer than 4 blocks (of at most 256 stationary vectors) per compute unit into at most 8 per unit and one remainder
 // per uncut block, so 12 blocks of 256 results per compute unit are enough and never bind.
 constexpr size_t kObsPartElems = (size_t)12 * kDefaultCUs * 256;
 
@@ -196,8 +193,7 @@ hipError_t launch_gather_rows(const GatherArgs& a, int units, hipStream_t st, Ti
 hipError_t launch_fill_f32(float* dst, const float* src, int64_t n, hipStream_t st);  // src NULL => zeros
 hipError_t launch_plain_copy(void* dst, const void* src, size_t bytes, hipStream_t st);
 hipError_t launch_evict_new_rows(const EvictArgs& a, int units, hipStream_t st, Timing tm = {});
-hipError_t launch_obs_scores(int dtype, int D, int G, const ObsArgs& a, int units, hipStream_t st, Timing tm = {});
-int obs_pass_queries(int dtype, int G);   // queries of one head a single scoring pass covers
+hipError_t launch_obs_scores(int dtype, int D, const ObsArgs& a, int units, hipStream_t st, Timing tm = {});
 int attn_tile_rows(int dtype, int D, int G);   // rows one block consumes per loop trip (split sizes are multiples)
 bool attn_supported(int dtype, int D, int G);
 

@@ -2,19 +2,9 @@
 // prompt queries (the last n_obs positions) and the query heads of its kv head, of the causal
 // attention probability it receives (eq. 3 applied to prompt queries; the score "A" of Alg. 2).
 //
-// Two kernels per pass of at most kObsRows query rows (row = one query of one group member):
-//   obs_row_stats : thread = query row (q kept in registers), keys streamed through LDS tiles;
-//                   writes the (max, sum) of the row's logits per block of kObsKeyBlock keys;
-//   obs_col_sums  : thread = key (k kept in registers), query rows streamed through LDS tiles;
-//                   merges the row statistics, recomputes the logits and adds the column sums of
-//                   the probabilities to the prompt scores.
-// Both form a logit as an fma chain over the head dimension in the same order, so the two passes
-// see identical logits.  Plain fp32 vector arithmetic; used for fp32 caches.
-//
-// 16-bit caches take the matrix-core pair below instead (obs_mfma_kernel<.., 1> and <.., 2>): the same two
-// steps, but q.K^T runs on 16x16x32 MFMA tiles and a pass covers up to kObsPassRows queries per head, so
-// scoring with every prompt query (n_obs = N) costs two launches per 4096 queries instead of two per 256
-// query rows.
+// Two steps per pass of up to kObsPassRows queries per head, both on the matrix cores (obs_mfma_kernel<.., 1> and
+// <.., 2>): the first computes every query's softmax reference and sum over the keys it sees, the second forms the
+// logits again and adds up every key's probabilities.
 #include "buzz_internal.h"
 
 #include <type_traits>
@@ -22,193 +12,24 @@
 namespace buzz {
 namespace {
 
-typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
-
-template <int DT> __device__ inline void cvt16B(const uint4& r, float* f);   // 16 bytes -> 4 or 8 floats
-template <> __device__ inline void cvt16B<BUZZ_FP32>(const uint4& r, float* f) {
-    f[0] = __uint_as_float(r.x); f[1] = __uint_as_float(r.y); f[2] = __uint_as_float(r.z); f[3] = __uint_as_float(r.w);
-}
-template <> __device__ inline void cvt16B<BUZZ_BF16>(const uint4& r, float* f) {
-    const uint32_t w[4] = {r.x, r.y, r.z, r.w};
-#pragma unroll
-    for (int i = 0; i < 4; ++i) { f[2 * i] = __uint_as_float(w[i] << 16); f[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u); }
-}
-template <> __device__ inline void cvt16B<BUZZ_FP16>(const uint4& r, float* f) {
-    const uint32_t w[4] = {r.x, r.y, r.z, r.w};
-#pragma unroll
-    for (int i = 0; i < 4; ++i) { const half2_t h = __builtin_bit_cast(half2_t, w[i]); f[2 * i] = (float)h.x; f[2 * i + 1] = (float)h.y; }
-}
-
-// softmax scale (log2 units) of the query at prompt position `pos`; Sec. 3.5 multiplies it by log_512(pos + 1)
-__device__ inline float query_scale(const ObsArgs& a, int pos)
-{
-    return a.log_n ? a.scale_log2 * (logf((float)(pos + 1)) * (1.0f / 6.2383246250395077f)) : a.scale_log2;
-}
-
 // the prompt scores a pass of step 2 adds to: the caller's starting scores (or 0) before the first pass
 __device__ inline float score_so_far(const ObsArgs& a, size_t i)
 {
     return a.first_pass ? (a.init ? a.init[i] : 0.f) : a.score[i];
 }
 
-template <int DT> struct Vec { static constexpr int N = DT == BUZZ_FP32 ? 4 : 8; };
-
-constexpr int kTile = 32;   // rows staged in LDS per trip
-
-// cooperative load of `rows` rows of D elements (row r at src + row_off(r)) into fp32 LDS [kTile][D]
-template <int DT, int D, typename RowPtr, typename RowScale>
-__device__ inline void stage_rows(float* lds, int rows, RowScale row_scale, RowPtr row_ptr)
-{
-    constexpr int VEC = Vec<DT>::N, CH = D / VEC;         // 16-byte chunks per row
-    for (int i = threadIdx.x; i < kTile * CH; i += 256) {
-        const int r = i / CH, ch = i - r * CH;
-        float f[VEC];
-        float scale = 0.f;
-        if (r < rows) {
-            const uint4 raw = *(const uint4*)(row_ptr(r) + (size_t)ch * 16);
-            cvt16B<DT>(raw, f);
-            scale = row_scale(r);
-        } else {
-#pragma unroll
-            for (int v = 0; v < VEC; ++v) f[v] = 0.f;
-        }
-#pragma unroll
-        for (int v = 0; v < VEC; ++v) lds[r * D + ch * VEC + v] = f[v] * scale;
-    }
-}
-
-template <int D> __device__ inline float dot_lds(const float* reg, const float* lds_row)
-{
-    float s = 0.f;
-#pragma unroll
-    for (int d4 = 0; d4 < D / 4; ++d4) {
-        const float4 x = *(const float4*)(lds_row + d4 * 4);
-        s = fmaf(reg[d4 * 4 + 0], x.x, s);
-        s = fmaf(reg[d4 * 4 + 1], x.y, s);
-        s = fmaf(reg[d4 * 4 + 2], x.z, s);
-        s = fmaf(reg[d4 * 4 + 3], x.w, s);
-    }
-    return s;
-}
-
-template <int DT, int D>
-__global__ __launch_bounds__(256) void obs_row_stats_kernel(const ObsArgs a)
-{
-    const int G = a.Hq / a.Hkv;
-    constexpr int VEC = Vec<DT>::N, ROWB = D * (DT == BUZZ_FP32 ? 4 : 2);
-    __shared__ __attribute__((aligned(16))) float tile[kTile * D];
-    const int kb = blockIdx.x, unit = blockIdx.y, r = threadIdx.x;
-    const int b = unit / a.Hkv, kvh = unit - b * a.Hkv;
-    const int R = a.t_count * G;
-    const bool live = r < R;
-    const int t = a.t_begin + (live ? r / G : 0), g = live ? r % G : 0;
-    const int limit = a.N - a.n_obs + t;                       // last key this query may see
-    const float qscale = query_scale(a, limit);
-    float qreg[D];
-    {
-        const char* qp = (const char*)a.q_obs + ((size_t)(b * a.Hq + kvh * G + g) * a.n_obs + t) * ROWB;
-#pragma unroll
-        for (int ch = 0; ch < D / VEC; ++ch) {
-            float f[VEC];
-            cvt16B<DT>(*(const uint4*)(qp + ch * 16), f);
-#pragma unroll
-            for (int v = 0; v < VEC; ++v) qreg[ch * VEC + v] = f[v] * qscale;
-        }
-    }
-    const int kbeg = kb * kObsKeyBlock, kend = min(a.N, kbeg + kObsKeyBlock);
-    const char* Kb = (const char*)a.K + (size_t)unit * a.N * ROWB;
-    float m = -INFINITY, l = 0.f;
-    for (int k0 = kbeg; k0 < kend; k0 += kTile) {
-        const int rows = min(kTile, kend - k0);
-        __syncthreads();
-        stage_rows<DT, D>(tile, rows, [](int) { return 1.0f; }, [&](int rr) { return Kb + (size_t)(k0 + rr) * ROWB; });
-        __syncthreads();
-#pragma unroll 2
-        for (int kk = 0; kk < rows; ++kk) {
-            if (k0 + kk > limit) break;                        // causal: later keys are invisible to this query
-            const float d = dot_lds<D>(qreg, tile + kk * D);
-            const float mn = fmaxf(m, d);
-            l = fmaf(l, __builtin_amdgcn_exp2f(m - mn), __builtin_amdgcn_exp2f(d - mn));
-            m = mn;
-        }
-    }
-    float* st = a.stats + (((size_t)unit * gridDim.x + kb) * kObsRows + r) * 2;
-    st[0] = m;
-    st[1] = l;
-}
-
-template <int DT, int D>
-__global__ __launch_bounds__(256) void obs_col_sums_kernel(const ObsArgs a, const int key_blocks)
-{
-    const int G = a.Hq / a.Hkv;
-    constexpr int VEC = Vec<DT>::N, ROWB = D * (DT == BUZZ_FP32 ? 4 : 2);
-    __shared__ __attribute__((aligned(16))) float tile[kTile * D];
-    __shared__ float sM[kObsRows], sInvL[kObsRows];
-    const int unit = blockIdx.y, tid = threadIdx.x;
-    const int j = blockIdx.x * 256 + tid;                      // this thread's key
-    const int b = unit / a.Hkv, kvh = unit - b * a.Hkv;
-    const int R = a.t_count * G;
-    {   // merge the per-key-block statistics of query row `tid`
-        float M = -INFINITY;
-        const float* st = a.stats + ((size_t)unit * key_blocks * kObsRows + tid) * 2;
-        for (int kb = 0; kb < key_blocks; ++kb) M = fmaxf(M, st[(size_t)kb * kObsRows * 2]);
-        float L = 0.f;
-        for (int kb = 0; kb < key_blocks; ++kb) {
-            const float mk = st[(size_t)kb * kObsRows * 2];
-            L = fmaf(st[(size_t)kb * kObsRows * 2 + 1], __builtin_amdgcn_exp2f(mk - M), L);   // key 0 is always visible: M finite
-        }
-        sM[tid] = M;
-        sInvL[tid] = 1.0f / L;
-    }
-    float kreg[D];
-    {
-        const int jj = j < a.N ? j : a.N - 1;
-        const char* kp = (const char*)a.K + ((size_t)unit * a.N + jj) * ROWB;
-#pragma unroll
-        for (int ch = 0; ch < D / VEC; ++ch) {
-            float f[VEC];
-            cvt16B<DT>(*(const uint4*)(kp + ch * 16), f);
-#pragma unroll
-            for (int v = 0; v < VEC; ++v) kreg[ch * VEC + v] = f[v];
-        }
-    }
-    float col = 0.f;
-    for (int r0 = 0; r0 < R; r0 += kTile) {
-        const int rows = min(kTile, R - r0);
-        __syncthreads();
-        stage_rows<DT, D>(tile, rows,
-                          [&](int rr) { return query_scale(a, a.N - a.n_obs + a.t_begin + (r0 + rr) / G); },
-                          [&](int rr) {
-                              const int r = r0 + rr, t = a.t_begin + r / G, g = r % G;
-                              return (const char*)a.q_obs + ((size_t)(b * a.Hq + kvh * G + g) * a.n_obs + t) * ROWB;
-                          });
-        __syncthreads();
-#pragma unroll 4
-        for (int rr = 0; rr < kTile; ++rr) {
-            const int r = r0 + rr;
-            const float d = dot_lds<D>(kreg, tile + rr * D);
-            const int limit = a.N - a.n_obs + a.t_begin + r / G;
-            const float p = (rr < rows && j <= limit) ? __builtin_amdgcn_exp2f(d - sM[r]) * sInvL[r] : 0.f;
-            col += p;
-        }
-    }
-    if (j < a.N) a.score[(size_t)unit * a.N + j] = score_so_far(a, (size_t)unit * a.N + j) + col;
-}
-
-
 // ---------------------------------------------------------------------------------------------------
-// Matrix-core prefill scoring (16-bit caches).
-//
-// One template serves both steps.  A wave keeps 64 "stationary" vectors in registers as the B operand of
-// v_mfma_f32_16x16x32 (4 column tiles of 16) and streams tiles of 16 "moving" vectors through the A
+// One template serves both steps and all types.  A wave keeps 64 (fp32: 32) "stationary" vectors in registers as the
+// B operand (column tiles of 16) and streams tiles of 16 "moving" vectors through the A
 // operand; lane (j, q) = (lane % 16, lane / 16) holds, of vector j of a tile, the 16-byte pieces 4p + q
 // (a permutation of the contraction index that both operands share), and receives the four products of
-// moving vectors 4q .. 4q+3 with stationary vector j.
-//   step 1 (row statistics): stationary = 64 queries of one head, moving = the keys they may see;
+// moving vectors 4q .. 4q+3 with stationary vector j.  A 16-byte piece is one v_mfma_f32_16x16x32 of 16-bit elements
+// or four v_mfma_f32_16x16x4 of fp32 ones (one per element, in full precision).
+//   step 1 (row statistics): stationary = queries of one head, moving = the keys they may see;
 //           every lane keeps a (reference, sum) of its query over its keys; merged over q at the end.
-//   step 2 (column sums):    stationary = 64 keys, moving = the queries that may see them, head after
+//   step 2 (column sums):    stationary = keys, moving = the queries that may see them, head after
 //           head of the group; every lane adds exp2(s - reference_i) / sum_i of its key over its queries.
-// The four waves of a block take adjacent groups of 64 stationary vectors and share the moving rows: the
+// The four waves of a block take adjacent groups of stationary vectors and share the moving rows: the
 // block copies them, kChunk rows at a time, into one of two LDS buffers while it computes on the other
 // (global loads of chunk c + 1 are issued before the tiles of chunk c and stored after them, one barrier
 // per chunk).  A wave reading its tiles straight from memory, one tile ahead, spent more than half its
@@ -226,8 +47,21 @@ template <> __device__ inline f32x4 mma16<BUZZ_FP16>(const u32x4& a, const u32x4
     return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_t, a), __builtin_bit_cast(f16x8_t, b), c, 0, 0, 0);
 }
 
-constexpr int kMmaCols = 64;            // stationary vectors per wave
-constexpr int kMmaBlockCols = 256;      // ... per block of four waves
+template <> __device__ inline f32x4 mma16<BUZZ_FP32>(const u32x4& a, const u32x4& b, f32x4 c) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        c = __builtin_amdgcn_mfma_f32_16x16x4f32(__builtin_bit_cast(float, (unsigned)a[e]), __builtin_bit_cast(float, (unsigned)b[e]), c, 0, 0, 0);
+    return c;
+}
+
+// Stationary vectors: 16-bit types take 64 per wave, so that an operand fetched from LDS feeds four column tiles and
+// the vector work on them hides behind matrix instructions.  fp32 tiles are bound by the matrix pipe alone (16
+// instructions of 32 cycles per 16 x 16 x 64 products); 32 vectors keep head_dim 256 in registers and give a
+// small layer twice the blocks.
+// (8 heads of 64, 2048 fp32 queries: scoring 3033 us with one vector-ALU thread per query or key and 256 queries per
+// pass, 80 us here: 33-42 us per step against 14 us that its matrix instructions alone take with every SIMD busy.)
+template <int DT> constexpr int col_tiles() { return DT == BUZZ_FP32 ? 2 : 4; }
+template <int DT> constexpr int block_cols() { return 4 * 16 * col_tiles<DT>(); }   // per block of four waves
 
 // Causal work is a triangle: the blocks of the last 256 queries (step 1) and of the first 256 keys (step 2)
 // stream the whole prompt, the others proportionally less, and a layer with few heads has fewer blocks than the
@@ -235,9 +69,9 @@ constexpr int kMmaBlockCols = 256;      // ... per block of four waves
 // one head), every group of stationary vectors is served by as many blocks as that takes, and all blocks but each
 // group's last are equally long.  (The rule of the launch is at launch_obs_mfma_t.)
 // How many parts the stationary queries of the block that holds query t (step 1) have: its latest query sees most.
-__device__ inline int stat_parts(const ObsArgs& a, int t, int chunk_rows)
+__device__ inline int stat_parts(const ObsArgs& a, int t, int chunk_rows, int cols)
 {
-    const int block_end = min(t - (t - a.t_begin) % kMmaBlockCols + kMmaBlockCols, a.t_begin + a.t_count);
+    const int block_end = min(t - (t - a.t_begin) % cols + cols, a.t_begin + a.t_count);
     const int chunks = (a.N - a.n_obs + block_end - 1) / chunk_rows + 1;
     return (chunks + a.key_part_len - 1) / a.key_part_len;
 }
@@ -252,12 +86,12 @@ __host__ __device__ inline int seeing_chunks(const ObsArgs& a, int j_block, int 
     return *t_lo < t_end ? (t_end - *t_lo + chunk_rows - 1) / chunk_rows : 0;
 }
 
-// The moving rows of one chunk in LDS.  A row occupies its D * 2 bytes plus 16: with that pitch the 16
+// The moving rows of one chunk in LDS.  A row occupies its bytes plus 16: with that pitch the 16
 // lanes that read the same piece of 16 different rows fall on 16 different groups of four banks.
-template <int D>
+template <int ROWB_>
 struct MovingChunk {
-    static constexpr int ROWB = D * 2, PIECES = ROWB / 16, PITCH = ROWB + 16;
-    static constexpr int ROWS = D == 256 ? 32 : 64;                   // two buffers stay within 64 KB of LDS
+    static constexpr int ROWB = ROWB_, PIECES = ROWB / 16, PITCH = ROWB + 16;
+    static constexpr int ROWS = ROWB <= 256 ? 64 : 16384 / ROWB;      // two buffers stay within 64 KB of LDS
     static constexpr int PER_THREAD = ROWS * PIECES / 256;            // 16-byte pieces a thread copies per chunk
     static_assert(ROWS * PIECES % 256 == 0, "the block copies whole rounds of 256 pieces");
     // issue the loads of rows row0 .. row0 + ROWS - 1 (clamped to last_row) of the array at `base`; rows are
@@ -286,11 +120,11 @@ struct MovingChunk {
         }
     }
     // A operand of tile `tile` (16 rows) of the chunk for this lane
-    static __device__ inline void fetch(u32x4 (&f)[D / 32], const char* buf, int tile, int j, int q)
+    static __device__ inline void fetch(u32x4 (&f)[ROWB / 64], const char* buf, int tile, int j, int q)
     {
         const char* row = buf + (16 * tile + j) * PITCH + q * 16;
 #pragma unroll
-        for (int p = 0; p < D / 32; ++p) f[p] = *(const u32x4*)(row + p * 64);
+        for (int p = 0; p < ROWB / 64; ++p) f[p] = *(const u32x4*)(row + p * 64);
     }
 };
 
@@ -302,9 +136,10 @@ __global__ __launch_bounds__(256) void obs_mfma_kernel(const ObsArgs a)
     auto qscale = [&](int pos) {
         return LOGN ? a.scale_log2 * (logf((float)(pos + 1)) * (1.0f / 6.2383246250395077f)) : a.scale_log2;
     };
-    using MC = MovingChunk<D>;
-    constexpr int ROWB = D * 2, QP = D / 32, CT = kMmaCols / 16, CH = MC::ROWS;
-    constexpr bool AHEAD = D <= 128;                       // a second operand buffer fits the register budget
+    constexpr int ROWB = D * (DT == BUZZ_FP32 ? 4 : 2);
+    using MC = MovingChunk<ROWB>;
+    constexpr int QP = ROWB / 64, CT = col_tiles<DT>(), COLS = 16 * CT, BLOCK_COLS = block_cols<DT>(), CH = MC::ROWS;
+    constexpr bool AHEAD = ROWB <= 256;                    // a second operand buffer fits the register budget
     __shared__ __align__(16) char sm_rows[2][CH * MC::PITCH];
     __shared__ float2 sm_stat[2][CH];                      // step 2: (reference, 1 / sum) of the chunk's queries
     const int lane = threadIdx.x & 63;
@@ -317,17 +152,14 @@ __global__ __launch_bounds__(256) void obs_mfma_kernel(const ObsArgs a)
     u32x4 staged[MC::PER_THREAD];
 
     if constexpr (STEP == 1) {
-        const int head = blockIdx.x;                       // b * Hq + h
+        // the latest queries see the most keys: their blocks go first, for all heads, so that the launch
+        // ends with the short blocks (the grid is linear, the head advances first, then the part, then the group)
+        const int head = blockIdx.x % a.heads, slot = blockIdx.x / a.heads;   // b * Hq + h
+        const int part = slot % a.key_parts, group = slot / a.key_parts;
         const int b = head / a.Hq, h = head - b * a.Hq;
         const int unit = b * a.Hkv + h / G;
-        // the latest queries see the most keys: their blocks go first, for all heads, so that the launch
-        // ends with the short blocks (blockIdx.x, which the dispatcher advances first, is the head)
-        // blockIdx.y = (group of 256 queries, part of its keys): up to a.key_parts blocks share a group
-        const int q_blocks = (int)gridDim.y / a.key_parts;
-        const int part = (int)blockIdx.y % a.key_parts;
-        const int t_block = a.t_begin + (q_blocks - 1 - (int)blockIdx.y / a.key_parts) * kMmaBlockCols;
-        if (t_block >= t_end) return;
-        const int t_base = t_block + wave * kMmaCols;
+        const int t_block = a.t_begin + ((a.t_count - 1) / BLOCK_COLS - group) * BLOCK_COLS;
+        const int t_base = t_block + wave * COLS;
         const bool active = t_base < t_end;                // a wave without queries still copies and synchronises
         const char* Qb = (const char*)a.q_obs + (size_t)head * a.n_obs * ROWB;
         const char* Kb = (const char*)a.K + (size_t)unit * a.N * ROWB;
@@ -345,15 +177,15 @@ __global__ __launch_bounds__(256) void obs_mfma_kernel(const ObsArgs a)
             for (int p = 0; p < QP; ++p) qf[ct][p] = piece(row, p);
             m[ct] = kRefStart; l[ct] = 0.f;
         }
-        const int k_last = shift + min(t_base + kMmaCols, t_end) - 1;   // the wave's latest query sees keys 0 .. k_last
+        const int k_last = shift + min(t_base + COLS, t_end) - 1;   // the wave's latest query sees keys 0 .. k_last
         const int k_free = shift + t_base;                 // keys up to here are visible to every query of the wave
-        const int k_last_block = shift + min(t_block + kMmaBlockCols, t_end) - 1;
+        const int k_last_block = shift + min(t_block + BLOCK_COLS, t_end) - 1;
         const int n_chunks = k_last_block / CH + 1;
         const int c_begin = part * a.key_part_len, c_end = min(n_chunks, c_begin + a.key_part_len);   // this block's chunks
         if (c_begin >= c_end) return;                      // the group has fewer parts
         // Lazy reference: a lane sums exp2(s * scale - ref) against a reference that only moves when it has
-        // to.  A chunk costs one fma, one exp2 and one add per element, straight-line code per 16 x 64 tile
-        // (four independent chains of matrix instructions and the vector work on their results) with none
+        // to.  A chunk costs one fma, one exp2 and one add per element, straight-line code per tile
+        // (independent chains of matrix instructions and the vector work on their results) with none
         // of the maximum bookkeeping, and one test at its end: if a sum of the wave has grown past kRefSlack
         // (or overflowed), the sums go back to their values before the chunk and the chunk is redone the
         // classic way, tile by tile: the reference rises to the running maximum and the sum so far is
@@ -408,7 +240,7 @@ __global__ __launch_bounds__(256) void obs_mfma_kernel(const ObsArgs a)
                 u32x4 kf[2][QP];
                 bool classic = c == c_begin;
                 if (!classic) {
-                    // (head_dim <= 128) the operand of tile i + 1 leaves LDS while tile i is computed; reading
+                    // (rows up to 256 bytes) the operand of tile i + 1 leaves LDS while tile i is computed; reading
                     // past the wave's last tile stays inside the buffer and is never used
                     MC::fetch(kf[0], sm_rows[c & 1], 0, j, q);
 #pragma unroll
@@ -418,14 +250,15 @@ __global__ __launch_bounds__(256) void obs_mfma_kernel(const ObsArgs a)
                         if (!AHEAD && tile > 0) MC::fetch(kf[0], sm_rows[c & 1], tile, j, q);
                         if (k0 <= k_last) {
                             // wave-uniform: does a causal boundary or the end of the query list cross this tile?
-                            if (k0 + 15 > k_free || t_base + kMmaCols > t_end) add_tile(kf[AHEAD ? tile & 1 : 0], k0, std::true_type{});
+                            if (k0 + 15 > k_free || t_base + COLS > t_end) add_tile(kf[AHEAD ? tile & 1 : 0], k0, std::true_type{});
                             else add_tile(kf[AHEAD ? tile & 1 : 0], k0, std::false_type{});
                         }
                     }
                     // the sums are nonnegative: their total passes the test only if each of them does; !(<=) also
                     // catches a sum that overflowed or is not a number
-                    const float total = (l[0] + l[1]) + (l[2] + l[3]);
-                    static_assert(CT == 4, "the test adds four sums");
+                    float total = l[0];
+#pragma unroll
+                    for (int ct = 1; ct < CT; ++ct) total += l[ct];
                     classic = __builtin_amdgcn_ballot_w64(!(total <= kRefSlack)) != 0;
                 }
                 if (__builtin_expect(classic, 0)) {
@@ -461,17 +294,18 @@ __global__ __launch_bounds__(256) void obs_mfma_kernel(const ObsArgs a)
             }
         }
     } else {
-        const int unit = blockIdx.x;                       // the earliest keys are seen by the most queries: they go first
-        const int part = (int)blockIdx.y % a.item_parts;   // blockIdx.y = (block of 256 keys, part of its items)
+        // the earliest keys are seen by the most queries: they go first (linear grid: unit, part, block of keys)
+        const int unit = blockIdx.x % a.units, slot = blockIdx.x / a.units;
+        const int part = slot % a.item_parts;
         const int b = unit / a.Hkv, kvh = unit - b * a.Hkv;
-        const int j_block = (int)blockIdx.y / a.item_parts * kMmaBlockCols;
+        const int j_block = slot / a.item_parts * BLOCK_COLS;
         // the block streams the queries from the first one that sees its first key, for every head of the group in
         // turn: item i = (head i / n_chunks, chunk i % n_chunks), and of these its own part
         int t_lo;
         const int n_chunks = seeing_chunks(a, j_block, CH, &t_lo);
         const int item0 = part * a.item_part_len, n_items = min(n_chunks * G, item0 + a.item_part_len);
         if (part > 0 && item0 >= n_items) return;          // fewer parts here (part 0 carries the scores over)
-        const int j_base = j_block + wave * kMmaCols;
+        const int j_base = j_block + wave * COLS;
         const bool active = j_base < a.N;
         const char* Kb = (const char*)a.K + (size_t)unit * a.N * ROWB;
         u32x4 kf[CT][QP];
@@ -545,7 +379,7 @@ __global__ __launch_bounds__(256) void obs_mfma_kernel(const ObsArgs a)
 #pragma unroll
                         for (int v = 0; v < 4; ++v) st[v] = sm_stat[item & 1][16 * tile + 4 * q + v];
                         // wave-uniform: unmasked if every query of the tile exists and sees every key of the wave
-                        if (t0 + 16 > t_end || shift + t0 < j_base + kMmaCols - 1) consume_as(qf[AHEAD ? tile & 1 : 0], st, t0, std::true_type{});
+                        if (t0 + 16 > t_end || shift + t0 < j_base + COLS - 1) consume_as(qf[AHEAD ? tile & 1 : 0], st, t0, std::true_type{});
                         else consume_as(qf[AHEAD ? tile & 1 : 0], st, t0, std::false_type{});
                     }
                 }
@@ -562,7 +396,7 @@ __global__ __launch_bounds__(256) void obs_mfma_kernel(const ObsArgs a)
             if (q == 0 && key < a.N) {
                 const size_t at = (size_t)unit * a.N + key;
                 if (a.item_parts == 1) a.score[at] = score_so_far(a, at) + c;
-                else a.partial[(size_t)part * gridDim.x * a.N + at] = c;
+                else a.partial[(size_t)part * a.units * a.N + at] = c;
             }
         }
     }
@@ -572,12 +406,12 @@ __global__ __launch_bounds__(256) void obs_mfma_kernel(const ObsArgs a)
 // 1 / sum).  (Done by the blocks of step 2 as they stage a chunk, the arithmetic waits for loads that are
 // otherwise in flight across a chunk's tiles: step 2 of 256 heads of 128, 256 queries, 4096 keys: 120 us with the merge inside, 98 us
 // without, 5 us for this kernel.)
-__global__ __launch_bounds__(256) void obs_merge_stats_kernel(const ObsArgs a, int chunk_rows)
+__global__ __launch_bounds__(256) void obs_merge_stats_kernel(const ObsArgs a, int chunk_rows, int cols)
 {
     const int r = blockIdx.x * 256 + threadIdx.x, head = blockIdx.y;
     if (r >= a.t_count) return;
     float2* st = (float2*)a.stats + (size_t)head * a.key_parts * a.t_count + r;
-    const int parts = stat_parts(a, a.t_begin + r, chunk_rows);
+    const int parts = stat_parts(a, a.t_begin + r, chunk_rows, cols);
     float2 got[kObsKeyParts];
 #pragma unroll
     for (int k = 0; k < kObsKeyParts; ++k) got[k] = st[(size_t)min(k, parts - 1) * a.t_count];
@@ -593,17 +427,17 @@ __global__ __launch_bounds__(256) void obs_merge_stats_kernel(const ObsArgs a, i
 
 // Adds the parts of a key block's column sums to the prompt scores, in part order (the same bits every time).
 // Latency-bound, 5 us at 16 units of 4001 keys, against 290 us that the cut of step 2 saves there.
-__global__ __launch_bounds__(256) void obs_sum_parts_kernel(const ObsArgs a, int chunk_rows)
+__global__ __launch_bounds__(256) void obs_sum_parts_kernel(const ObsArgs a, int chunk_rows, int cols)
 {
     const int j = blockIdx.x * 256 + threadIdx.x, unit = blockIdx.y;
     if (j >= a.N) return;
     int t_lo;
-    const int items = seeing_chunks(a, j / kMmaBlockCols * kMmaBlockCols, chunk_rows, &t_lo) * (a.Hq / a.Hkv);
+    const int items = seeing_chunks(a, j / cols * cols, chunk_rows, &t_lo) * (a.Hq / a.Hkv);
     const int parts = (items + a.item_part_len - 1) / a.item_part_len;
     const size_t at = (size_t)unit * a.N + j;
     float got[kObsItemParts];
 #pragma unroll
-    for (int p = 0; p < kObsItemParts; ++p) got[p] = p < parts ? a.partial[(size_t)p * gridDim.y * a.N + at] : 0.f;
+    for (int p = 0; p < kObsItemParts; ++p) got[p] = p < parts ? a.partial[(size_t)p * a.units * a.N + at] : 0.f;
     float s = score_so_far(a, at);
 #pragma unroll
     for (int p = 0; p < kObsItemParts; ++p) s += got[p];
@@ -613,10 +447,11 @@ __global__ __launch_bounds__(256) void obs_sum_parts_kernel(const ObsArgs a, int
 template <int DT, int D>
 hipError_t launch_obs_mfma_t(ObsArgs a, int units, hipStream_t st, Timing tm)
 {
-    constexpr int CH = MovingChunk<D>::ROWS;
+    constexpr int CH = MovingChunk<D * (DT == BUZZ_FP32 ? 4 : 2)>::ROWS, COLS = block_cols<DT>();
     const int heads = units / a.Hkv * a.Hq, G = a.Hq / a.Hkv;
-    const int q_blocks = (a.t_count + kMmaBlockCols - 1) / kMmaBlockCols;
-    const int k_blocks = (a.N + kMmaBlockCols - 1) / kMmaBlockCols;
+    a.heads = heads; a.units = units;
+    const int q_blocks = (a.t_count + COLS - 1) / COLS;
+    const int k_blocks = (a.N + COLS - 1) / COLS;
     // A step whose longest block is no more than its share of two blocks per compute unit stays whole: the long
     // blocks start first and have the SIMDs more and more to themselves, and parts would only repeat the blocks'
     // prologue (64 heads of 128, 4096 queries: 347 us whole, 385 us cut).  Below that it is cut for four blocks
@@ -631,7 +466,7 @@ hipError_t launch_obs_mfma_t(ObsArgs a, int units, hipStream_t st, Timing tm)
     int64_t total = 0;
     int longest = 0;
     for (int b = 0; b < q_blocks; ++b) {
-        const int end = (b + 1) * kMmaBlockCols < a.t_count ? (b + 1) * kMmaBlockCols : a.t_count;
+        const int end = (b + 1) * COLS < a.t_count ? (b + 1) * COLS : a.t_count;
         const int chunks = (a.N - a.n_obs + a.t_begin + end - 1) / CH + 1;
         total += (int64_t)chunks * heads;
         longest = chunks;
@@ -640,24 +475,25 @@ hipError_t launch_obs_mfma_t(ObsArgs a, int units, hipStream_t st, Timing tm)
     split(total, longest, most < kObsKeyParts ? (most < 1 ? 1 : most) : kObsKeyParts, &a.key_parts, &a.key_part_len);
     total = 0;
     int t_lo;
-    for (int b = 0; b < k_blocks; ++b) total += (int64_t)seeing_chunks(a, b * kMmaBlockCols, CH, &t_lo) * G * units;
+    for (int b = 0; b < k_blocks; ++b) total += (int64_t)seeing_chunks(a, b * COLS, CH, &t_lo) * G * units;
     longest = seeing_chunks(a, 0, CH, &t_lo) * G;
     most = (int)(a.partial_cap / ((size_t)units * a.N));
     split(total, longest, most < kObsItemParts ? (most < 1 ? 1 : most) : kObsItemParts, &a.item_parts, &a.item_part_len);
-    const dim3 g1(heads, q_blocks * a.key_parts), g2(units, k_blocks * a.item_parts);
-    if (g1.y > 65535 || g2.y > 65535) return hipErrorInvalidValue;
+    const int64_t blocks1 = (int64_t)heads * q_blocks * a.key_parts, blocks2 = (int64_t)units * k_blocks * a.item_parts;
+    if (blocks1 > INT32_MAX / 256 || blocks2 > INT32_MAX / 256) return hipErrorInvalidValue;   // (far beyond any GPU's memory)
+    const dim3 g1((unsigned)blocks1), g2((unsigned)blocks2);
     if (a.log_n) BUZZ_LAUNCH((obs_mfma_kernel<DT, D, 1, true>), g1, dim3(256), 0, st, tm, a);
     else BUZZ_LAUNCH((obs_mfma_kernel<DT, D, 1, false>), g1, dim3(256), 0, st, tm, a);
     if (hipError_t e = hipGetLastError()) return e;
     if (a.key_parts > 1) {
-        BUZZ_LAUNCH(obs_merge_stats_kernel, dim3((a.t_count + 255) / 256, heads), dim3(256), 0, st, tm, a, CH);
+        BUZZ_LAUNCH(obs_merge_stats_kernel, dim3((a.t_count + 255) / 256, heads), dim3(256), 0, st, tm, a, CH, COLS);
         if (hipError_t e = hipGetLastError()) return e;
     }
     if (a.log_n) BUZZ_LAUNCH((obs_mfma_kernel<DT, D, 2, true>), g2, dim3(256), 0, st, tm, a);
     else BUZZ_LAUNCH((obs_mfma_kernel<DT, D, 2, false>), g2, dim3(256), 0, st, tm, a);
     if (hipError_t e = hipGetLastError()) return e;
     if (a.item_parts > 1) {
-        BUZZ_LAUNCH(obs_sum_parts_kernel, dim3((a.N + 255) / 256, units), dim3(256), 0, st, tm, a, CH);
+        BUZZ_LAUNCH(obs_sum_parts_kernel, dim3((a.N + 255) / 256, units), dim3(256), 0, st, tm, a, CH, COLS);
         return hipGetLastError();
     }
     return hipSuccess;
@@ -674,40 +510,14 @@ hipError_t launch_obs_mfma_d(int D, const ObsArgs& a, int units, hipStream_t st,
     return hipErrorInvalidValue;
 }
 
-template <int DT, int D>
-hipError_t launch_obs_t(const ObsArgs& a, int units, hipStream_t st)
-{
-    const int key_blocks = (a.N + kObsKeyBlock - 1) / kObsKeyBlock;
-    hipLaunchKernelGGL((obs_row_stats_kernel<DT, D>), dim3(key_blocks, units), dim3(256), 0, st, a);
-    if (hipError_t e = hipGetLastError()) return e;
-    hipLaunchKernelGGL((obs_col_sums_kernel<DT, D>), dim3((a.N + 255) / 256, units), dim3(256), 0, st, a, key_blocks);
-    return hipGetLastError();
-}
-
-template <int DT>
-hipError_t launch_obs_d(int D, const ObsArgs& a, int units, hipStream_t st)
-{
-    switch (D) {
-        case 64: return launch_obs_t<DT, 64>(a, units, st);
-        case 128: return launch_obs_t<DT, 128>(a, units, st);
-        case 256: return launch_obs_t<DT, 256>(a, units, st);
-    }
-    return hipErrorInvalidValue;
-}
-
 }  // namespace
 
-int obs_pass_queries(int dtype, int G)
-{
-    return dtype == BUZZ_FP32 ? kObsRows / G : kObsPassRows;
-}
 
-
-hipError_t launch_obs_scores(int dtype, int D, int /*G*/, const ObsArgs& a, int units, hipStream_t st, Timing tm)
+hipError_t launch_obs_scores(int dtype, int D, const ObsArgs& a, int units, hipStream_t st, Timing tm)
 {
     if (a.N <= 0 || a.t_count <= 0) return hipSuccess;
     switch (dtype) {
-        case BUZZ_FP32: return launch_obs_d<BUZZ_FP32>(D, a, units, st);
+        case BUZZ_FP32: return launch_obs_mfma_d<BUZZ_FP32>(D, a, units, st, tm);
         case BUZZ_FP16: return launch_obs_mfma_d<BUZZ_FP16>(D, a, units, st, tm);
         case BUZZ_BF16: return launch_obs_mfma_d<BUZZ_BF16>(D, a, units, st, tm);
     }

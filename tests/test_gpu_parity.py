@@ -206,10 +206,12 @@ def test_prefill_scores_from_every_prompt_query_wide_rows(dtype):
 
 @pytest.mark.parametrize("dtype,D,G,prompt,n_obs", [
     ("bf16", 128, 4, 1537, 1537), ("fp16", 64, 1, 1025, 1025), ("bf16", 64, 3, 2049, 1), ("fp16", 128, 2, 4097, 257),
-    ("bf16", 256, 2, 511, 300), ("fp16", 128, 1, 65, 65)])
+    ("bf16", 256, 2, 511, 300), ("fp16", 128, 1, 65, 65),
+    ("fp32", 64, 1, 1025, 1025), ("fp32", 64, 3, 2050, 1), ("fp32", 128, 2, 700, 129), ("fp32", 256, 2, 385, 385),
+    ("fp32", 64, 1, 4300, 4200), ("fp32", 128, 1, 33, 33)])
 def test_prompt_scoring_cut_into_parts(dtype, D, G, prompt, n_obs):
-    """Few heads: both scoring steps are cut into several blocks per group of 256 queries / block of 256 keys, with
-    ragged last parts, groups of fewer parts than others, one query, one chunk."""
+    """Few heads: both scoring steps are cut into several blocks per group of queries / block of keys, with ragged
+    last parts, groups of fewer parts than others, one query, one chunk, a second pass; fp32 and 16-bit operands."""
     wl = small(batch=1, n_kv_heads=2, n_q_heads=2 * G, head_dim=D, dtype=dtype, prompt=prompt, decode_steps=1,
                sink=4, window=prompt // 4, segment=16, keep=2, evict_every=8, n_obs=n_obs)
     run(wl)
