@@ -302,7 +302,7 @@ GatherArgs cache_gather_base(const buzz_cache_t* c)
     g.srcK = c->at<char>(c->L.K); g.srcV = c->at<char>(c->L.V);
     g.srcScore = c->at<float>(c->L.score); g.srcPos = c->at<int32_t>(c->L.pos);
     g.src_unit_rows = c->L.cap;
-    g.src_step = 1; g.sel_step = 1;
+    g.src_step = 1;
     g.dstK = c->at<char>(c->L.K); g.dstV = c->at<char>(c->L.V);
     g.dstScore = c->at<float>(c->L.score); g.dstPos = c->at<int32_t>(c->L.pos);
     g.dst_unit_rows = c->L.cap;
@@ -393,7 +393,7 @@ int evict_impl(buzz_cache_t* c, hipStream_t st)
             if (hipError_t e = launch_segment_topk(sa, L.units, st, prof_pair(c, 2))) return hip_rc(e);
             GatherArgs g = cache_gather_base(c);
             g.src_map = c->map();
-            g.sel = c->at<int32_t>(L.sel); g.sel_stride = L.sel_stride; g.sel_start = 0; g.sel_step = 1;
+            g.sel = c->at<int32_t>(L.sel); g.sel_stride = L.sel_stride; g.sel_step = 1; g.sel_hi = (int32_t)new2;
             g.dstK = c->at<char>(L.stK); g.dstV = c->at<char>(L.stV);
             g.dstScore = c->at<float>(L.stScore); g.dstPos = c->at<int32_t>(L.stPos);
             g.dst_unit_rows = L.st_rows; g.dst_start = 0; g.n_rows = (int32_t)new2;
@@ -462,7 +462,7 @@ int evict_impl(buzz_cache_t* c, hipStream_t st)
             if (hipError_t e = launch_segment_topk(sa, L.units, st, prof_pair(c, 2))) return hip_rc(e);
             GatherArgs g = cache_gather_base(c);
             g.src_map = c->map();
-            g.sel = c->at<int32_t>(L.sel); g.sel_stride = L.sel_stride; g.sel_start = 0; g.sel_step = 1;
+            g.sel = c->at<int32_t>(L.sel); g.sel_stride = L.sel_stride; g.sel_step = 1; g.sel_hi = (int32_t)new2;
             g.dst_start = (int32_t)(k + old2); g.n_rows = (int32_t)new2;
             if (hipError_t e = launch_gather_rows(g, L.units, st, prof_pair(c, 2))) return hip_rc(e);
         }
@@ -588,17 +588,14 @@ int buzz_prefill(buzz_cache_t* c, const void* kp, const void* vp, int64_t N, con
     if (selected > L.sel_stride || sink_rows + survivors > L.ring_base) return BUZZ_ECAPACITY;
 
     if (!c->dry) {
-        float* ps = c->at<float>(L.pscore);
         if (int rc = probe_die_placement(st)) return rc;
-        if (hipError_t e = launch_fill_f32(c->at<float>(L.ticket), nullptr, L.units, st)) return hip_rc(e);
-        // starting scores, one row of N per unit; with observed queries the scoring itself starts from them
-        if (n_obs == 0)
-            if (hipError_t e = launch_fill_f32(ps, init_score, (int64_t)L.units * N, st)) return hip_rc(e);
+        // prompt scores, one row of N per unit: what the scoring leaves, or the caller's (NULL: all zero)
+        const float* ps = n_obs > 0 ? c->at<float>(L.pscore) : init_score;
         if (n_obs > 0) {
             const int max_q = kObsPassRows;                     // queries of one head per pass
             for (int64_t t0 = 0; t0 < n_obs; t0 += max_q) {
                 ObsArgs oa{};
-                oa.K = kp; oa.q_obs = q_obs; oa.score = ps; oa.stats = c->at<float>(L.obs_stats);
+                oa.K = kp; oa.q_obs = q_obs; oa.score = c->at<float>(L.pscore); oa.stats = c->at<float>(L.obs_stats);
                 oa.N = (int32_t)N; oa.n_obs = (int32_t)n_obs;
                 oa.t_begin = (int32_t)t0; oa.t_count = (int32_t)((n_obs - t0) < max_q ? (n_obs - t0) : max_q);
                 oa.Hq = cfg.n_q_heads; oa.Hkv = cfg.n_kv_heads;
@@ -611,41 +608,31 @@ int buzz_prefill(buzz_cache_t* c, const void* kp, const void* vp, int64_t N, con
                 if (hipError_t e = launch_obs_scores(cfg.kv_dtype, cfg.head_dim, oa, L.units, st)) return hip_rc(e);
             }
         }
+        // one launch places every row: sink, survivors behind it, the tail at the start of the ring
         GatherArgs g{};
-        g.srcK = kp; g.srcV = vp; g.srcScore = ps; g.srcPos = nullptr;
-        g.src_unit_rows = N; g.src_step = 1; g.sel_step = 1;
+        g.srcK = kp; g.srcV = vp; g.srcScore = ps;
+        g.src_unit_rows = N; g.src_step = 1;
         g.dstK = c->at<char>(L.K); g.dstV = c->at<char>(L.V);
         g.dstScore = c->at<float>(L.score); g.dstPos = c->at<int32_t>(L.pos);
         g.dst_unit_rows = L.cap; g.row_bytes = L.row_bytes;
-        // sink
-        GatherArgs gs = g;
-        gs.src_start = 0; gs.dst_start = 0; gs.n_rows = (int32_t)sink_rows;
-        if (hipError_t e = launch_gather_rows(gs, L.units, st)) return hip_rc(e);
-        if (sample) {
-            if (survivors > 0) {
-                SelectArgs sa{};
-                sa.score = ps; sa.unit_stride = N;
-                sa.map = RingMap{0, 0, 0, 0};
-                sa.lo = (int32_t)k; sa.new_count = (int32_t)M;
-                sa.segment = global ? (int32_t)(M > kMaxWaveSegment ? M : kMaxWaveSegment) : cfg.segment;
-                sa.keep = L.keep;
-                sa.ignore_scores = (cfg.flags & BUZZ_FLAG_INTERVAL_NEW) ? 1 : 0;
-                sa.sel = c->at<int32_t>(L.sel); sa.sel_stride = L.sel_stride;
-                if (hipError_t e = launch_segment_topk(sa, L.units, st)) return hip_rc(e);
-                GatherArgs gv = g;
-                gv.sel = c->at<int32_t>(L.sel); gv.sel_stride = L.sel_stride; gv.sel_start = 0;
-                gv.sel_step = (int32_t)sel_step;
-                gv.dst_start = (int32_t)k; gv.n_rows = (int32_t)survivors;
-                if (hipError_t e = launch_gather_rows(gv, L.units, st)) return hip_rc(e);
-            }
-            GatherArgs gw = g;
-            gw.src_start = (int32_t)(N - w); gw.dst_start = L.ring_base; gw.n_rows = (int32_t)w;
-            if (hipError_t e = launch_gather_rows(gw, L.units, st)) return hip_rc(e);
-        } else {
-            GatherArgs gt = g;
-            gt.src_start = (int32_t)sink_rows; gt.dst_start = L.ring_base; gt.n_rows = (int32_t)tail_rows;
-            if (hipError_t e = launch_gather_rows(gt, L.units, st)) return hip_rc(e);
+        g.dst_map = RingMap{(int32_t)(sink_rows + survivors), L.ring_base, 0, L.ring_cap};
+        g.ticket = c->at<int32_t>(L.ticket);
+        g.n_rows = (int32_t)(sink_rows + survivors + tail_rows);
+        g.sel_lo = (int32_t)sink_rows; g.sel_hi = (int32_t)(sink_rows + survivors);
+        g.tail_shift = (int32_t)(N - tail_rows - sink_rows - survivors);
+        if (survivors > 0) {
+            SelectArgs sa{};
+            sa.score = ps; sa.unit_stride = N;
+            sa.map = RingMap{0, 0, 0, 0};
+            sa.lo = (int32_t)k; sa.new_count = (int32_t)M;
+            sa.segment = global ? (int32_t)(M > kMaxWaveSegment ? M : kMaxWaveSegment) : cfg.segment;
+            sa.keep = L.keep;
+            sa.ignore_scores = ((cfg.flags & BUZZ_FLAG_INTERVAL_NEW) || !ps) ? 1 : 0;   // no scores: all equal
+            sa.sel = c->at<int32_t>(L.sel); sa.sel_stride = L.sel_stride;
+            if (hipError_t e = launch_segment_topk(sa, L.units, st)) return hip_rc(e);
+            g.sel = c->at<int32_t>(L.sel); g.sel_stride = L.sel_stride; g.sel_step = (int32_t)sel_step;
         }
+        if (hipError_t e = launch_gather_rows(g, L.units, st)) return hip_rc(e);
     }
     c->pending = false;
     c->sink_filled = sink_rows;
@@ -811,10 +798,14 @@ int buzz_cache_export(buzz_cache_t* c, void* k, void* v, float* score, int32_t* 
     if (!alive(c)) return BUZZ_EINVAL;
     if (!c->ready) return BUZZ_ESTATE;
     if (c->dry) return BUZZ_OK;
-    if (int rc = flush_scores(c, (hipStream_t)hip_stream)) return rc;
     GatherArgs g = cache_gather_base(c);
     g.src_map = c->map();
     g.src_start = 0; g.src_step = 1;
+    if (c->pending) {                                          // applied to the rows that leave; the cache keeps it pending
+        g.logit_prev = c->at<float>(c->L.logit[c->last_buf]);
+        g.stat_prev = c->at<float>(c->L.stat[c->last_buf]);
+        g.G = c->L.G;
+    }
     g.dstK = k; g.dstV = v; g.dstScore = score; g.dstPos = pos;
     g.dst_unit_rows = c->n(); g.dst_start = 0; g.n_rows = (int32_t)c->n();
     return hip_rc(launch_gather_rows(g, c->L.units, (hipStream_t)hip_stream));
@@ -836,19 +827,17 @@ int buzz_cache_import(buzz_cache_t* c, const void* k, const void* v, const float
     if (!c->dry) {
         hipStream_t st = (hipStream_t)hip_stream;
         if (int rc = probe_die_placement(st)) return rc;
-        if (hipError_t e = launch_fill_f32(c->at<float>(L.ticket), nullptr, L.units, st)) return hip_rc(e);
         GatherArgs g{};
         g.srcK = k; g.srcV = v; g.srcScore = score; g.srcPos = pos;
-        g.src_unit_rows = n; g.src_step = 1; g.sel_step = 1;
+        g.src_unit_rows = n; g.src_step = 1;
         g.dstK = c->at<char>(L.K); g.dstV = c->at<char>(L.V);
         g.dstScore = c->at<float>(L.score); g.dstPos = c->at<int32_t>(L.pos);
         g.dst_unit_rows = L.cap; g.row_bytes = L.row_bytes;
-        GatherArgs front = g;                                  // sink and old rows: the linear region
-        front.src_start = 0; front.dst_start = 0; front.n_rows = (int32_t)(sink_rows + n_old);
-        if (hipError_t e = launch_gather_rows(front, L.units, st)) return hip_rc(e);
-        GatherArgs ring = g;                                   // buffered new rows and the window: the ring, from its base
-        ring.src_start = (int32_t)(sink_rows + n_old); ring.dst_start = L.ring_base; ring.n_rows = (int32_t)tail_rows;
-        if (hipError_t e = launch_gather_rows(ring, L.units, st)) return hip_rc(e);
+        // sink and old rows: the linear region; buffered new rows and the window: the ring, from its base
+        g.dst_map = RingMap{(int32_t)(sink_rows + n_old), L.ring_base, 0, L.ring_cap};
+        g.ticket = c->at<int32_t>(L.ticket);
+        g.n_rows = (int32_t)n;
+        if (hipError_t e = launch_gather_rows(g, L.units, st)) return hip_rc(e);
     }
     c->pending = false;
     c->sink_filled = sink_rows;

@@ -132,18 +132,27 @@ struct EvictArgs {
     int32_t cap, row_bytes, G;
 };
 
+// Copies rows r = 0 .. n_rows - 1 of every unit.  Source of row r: sel[(r - sel_lo) * sel_step] for
+// sel_lo <= r < sel_hi (sel NULL: none), else src_start + r * src_step, plus tail_shift from r = sel_hi on.
 struct GatherArgs {
-    const void* srcK; const void* srcV; const float* srcScore; const int32_t* srcPos;  // srcPos NULL => pos = source row
+    const void* srcK; const void* srcV;
+    const float* srcScore;     // NULL: zeros
+    const int32_t* srcPos;     // NULL: the source row itself
+    const float* logit_prev;   // [units][G][src_unit_rows] logits of a score update to apply on the way, NULL: none
+    const float* stat_prev;    // [units][G][2] its (max, 1 / sum)
     int64_t src_unit_rows;     // rows between units in the source arrays
     RingMap src_map;           // ring_cap == 0: identity
-    const int32_t* sel;        // NULL => affine source rows
-    int32_t sel_stride, sel_start, sel_step;
-    int32_t src_start, src_step;
+    const int32_t* sel;
+    int32_t sel_stride, sel_step, sel_lo, sel_hi;
+    int32_t src_start, src_step, tail_shift;
     void* dstK; void* dstV; float* dstScore; int32_t* dstPos;    // any may be NULL
+    int32_t* ticket;           // [units] arrival counters of the decode step to clear, NULL: none
     int64_t dst_unit_rows;
+    RingMap dst_map;           // ring_cap == 0: identity
     int32_t dst_start;
     int32_t n_rows;
     int32_t row_bytes;         // D * sizeof(element)
+    int32_t G;
 };
 
 struct ObsArgs {               // prefill scoring: causal attention of observed prompt queries (one pass)

@@ -10,6 +10,8 @@
 namespace buzz {
 namespace {
 
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+
 constexpr int kSelWaves = 4;
 
 __global__ __launch_bounds__(256) void segment_topk_kernel(const SelectArgs a)
@@ -218,29 +220,49 @@ __global__ __launch_bounds__(256) void evict_new_rows_kernel(const EvictArgs a)
     }
 }
 
-constexpr int kGatherRowsPerBlock = 64;
-
-__global__ __launch_bounds__(256) void gather_rows_kernel(const GatherArgs a)
+// Row copies: bound by memory traffic, or by latency where there are few rows.  A thread moves ONE 16-byte piece of K
+// and one of V, both requested before either is stored; rows are spread over as many blocks as that takes.  That is the
+// shape in which a copy is fastest on this chip (1 GB device to device: one piece per thread 6.2 TB/s, four 5.7,
+// eight 4.2); with 64 rows per block and four dependent load-store rounds per thread this kernel moved 5.0 TB/s.
+// Nothing of a copy is read twice: non-temporal loads and stores (32 units of 7668 rows of 512 bytes, copied in and out:
+// 111 us with ordinary accesses, 102 with non-temporal stores, 98 with both; no size was slower, from 8 x 1512 rows up).
+// The block's first threads carry the rows' scores and positions, one row each.
+__global__ __launch_bounds__(256) void gather_rows_kernel(const GatherArgs a, const int lpr_log2)
 {
     const int unit = blockIdx.y, tid = threadIdx.x;
-    const int lpr = a.row_bytes >> 4;              // 16-byte lanes per row
-    const int c = tid % lpr, rr = tid / lpr, rows_per_pass = 256 / lpr;
-    const int rbeg = blockIdx.x * kGatherRowsPerBlock;
-    const int rend = min(a.n_rows, rbeg + kGatherRowsPerBlock);
+    const int rows = 256 >> lpr_log2;              // rows per block, 1 << lpr_log2 pieces each
+    const int r0 = blockIdx.x * rows;
     const size_t sbase = (size_t)unit * a.src_unit_rows, dbase = (size_t)unit * a.dst_unit_rows;
-    for (int r = rbeg + rr; r < rend; r += rows_per_pass) {
-        const int src = a.sel ? a.sel[(size_t)unit * a.sel_stride + a.sel_start + (size_t)r * a.sel_step]
-                              : a.src_start + r * a.src_step;
-        const int sp = a.src_map.ring_cap ? a.src_map.phys(src) : src;
-        const size_t so = (sbase + sp) * a.row_bytes + c * 16;
-        const size_t dro = dbase + a.dst_start + r;
-        const size_t dof = dro * a.row_bytes + c * 16;
-        if (a.dstK) *(uint4*)((char*)a.dstK + dof) = *(const uint4*)((const char*)a.srcK + so);
-        if (a.dstV) *(uint4*)((char*)a.dstV + dof) = *(const uint4*)((const char*)a.srcV + so);
-        if (c == 0) {
-            if (a.dstScore) a.dstScore[dro] = a.srcScore[sbase + sp];
-            if (a.dstPos) a.dstPos[dro] = a.srcPos ? a.srcPos[sbase + sp] : src;
+    auto source = [&](int r) {
+        if (a.sel && r >= a.sel_lo && r < a.sel_hi)
+            return a.sel[(size_t)unit * a.sel_stride + (size_t)(r - a.sel_lo) * a.sel_step];
+        return a.src_start + r * a.src_step + (r >= a.sel_hi ? a.tail_shift : 0);
+    };
+    auto place = [&](int r) { return a.dst_map.ring_cap ? a.dst_map.phys(a.dst_start + r) : a.dst_start + r; };
+    if (a.ticket && blockIdx.x == 0 && tid == 0) a.ticket[unit] = 0;
+    const int r = r0 + (tid >> lpr_log2);
+    if (r < a.n_rows) {
+        const int src = source(r), sp = a.src_map.ring_cap ? a.src_map.phys(src) : src;
+        const int c = (tid & ((1 << lpr_log2) - 1)) * 16;
+        const size_t so = (sbase + sp) * a.row_bytes + c, dof = (dbase + place(r)) * a.row_bytes + c;
+        u32x4 k, v;
+        if (a.dstK) k = __builtin_nontemporal_load((const u32x4*)((const char*)a.srcK + so));
+        if (a.dstV) v = __builtin_nontemporal_load((const u32x4*)((const char*)a.srcV + so));
+        if (a.dstK) __builtin_nontemporal_store(k, (u32x4*)((char*)a.dstK + dof));
+        if (a.dstV) __builtin_nontemporal_store(v, (u32x4*)((char*)a.dstV + dof));
+    }
+    if (tid < rows && r0 + tid < a.n_rows) {
+        const int src = source(r0 + tid), sp = a.src_map.ring_cap ? a.src_map.phys(src) : src;
+        const size_t d = dbase + place(r0 + tid);
+        if (a.dstScore) {
+            float v = a.srcScore ? a.srcScore[sbase + sp] : 0.f;
+            if (a.logit_prev)
+                for (int g = 0; g < a.G; ++g)
+                    v = add_probability(v, a.logit_prev[(sbase * a.G) + (size_t)g * a.src_unit_rows + sp],
+                                        a.stat_prev[((size_t)unit * a.G + g) * 2], a.stat_prev[((size_t)unit * a.G + g) * 2 + 1]);
+            a.dstScore[d] = v;
         }
+        if (a.dstPos) a.dstPos[d] = a.srcPos ? a.srcPos[sbase + sp] : src;
     }
 }
 
@@ -296,9 +318,13 @@ hipError_t launch_segment_topk(const SelectArgs& a, int units, hipStream_t st, T
 
 hipError_t launch_gather_rows(const GatherArgs& a, int units, hipStream_t st, Timing tm)
 {
-    if (a.n_rows <= 0) return hipSuccess;
-    dim3 grid((a.n_rows + kGatherRowsPerBlock - 1) / kGatherRowsPerBlock, units), block(256);
-    BUZZ_LAUNCH(gather_rows_kernel, grid, block, 0, st, tm, a);
+    if (a.n_rows <= 0 && !a.ticket) return hipSuccess;
+    int lpr_log2 = 0;                              // 16-byte pieces per row: a power of two, at most 64
+    while ((16 << lpr_log2) < a.row_bytes) ++lpr_log2;
+    if ((16 << lpr_log2) != a.row_bytes || lpr_log2 > 6) return hipErrorInvalidValue;
+    const int rows = 256 >> lpr_log2;
+    dim3 grid(a.n_rows > 0 ? (a.n_rows + rows - 1) / rows : 1, units), block(256);
+    BUZZ_LAUNCH(gather_rows_kernel, grid, block, 0, st, tm, a, lpr_log2);
     return hipGetLastError();
 }
 

@@ -151,6 +151,30 @@ def test_export_then_import_resumes_the_cache(G, dtype, old_stride):
             assert torch.equal(x, y)
 
 
+@pytest.mark.parametrize("G,dtype,old_stride", [(1, "fp32", 1), (4, "bf16", 1), (1, "fp16", 0), (3, "fp32", 0)])
+def test_export_does_not_disturb_the_cache(G, dtype, old_stride):
+    """The score update a step leaves pending is applied to the exported copy only: a cache that is exported after
+    every step gives bit for bit what one that is exported once does, and an export repeats itself."""
+    from paper_2410_23079_amd import FLAG_AUTO_EVICT, FLAG_DETERMINISTIC, BuzzCache
+    ls = lockstep()
+    wl = small(batch=1, n_kv_heads=3, n_q_heads=3 * G, head_dim=64, dtype=dtype, prompt=300, decode_steps=41,
+               sink=4, window=37, segment=16, keep=2, evict_every=16, old_stride=old_stride, n_obs=24)
+    p, d = prompt_inputs(wl, device="cuda"), decode_inputs(wl, device="cuda")
+    a, b = (BuzzCache(ls.buzz_config(wl, flags=FLAG_AUTO_EVICT | FLAG_DETERMINISTIC)) for _ in range(2))
+    out_a, out_b = (torch.empty(wl.batch, wl.n_q_heads, wl.head_dim, dtype=torch.float32, device="cuda") for _ in range(2))
+    for c in (a, b):
+        c.prefill(p["K"], p["V"], q_obs=p["q_obs"])
+    for t in range(wl.decode_steps):
+        a.decode_step(d["q"][t], d["k"][t], d["v"][t], out_a)
+        b.decode_step(d["q"][t], d["k"][t], d["v"][t], out_b)
+        assert torch.equal(out_a, out_b)
+        first = b.export()
+        for x, y in zip(first, b.export()):
+            assert torch.equal(x, y)
+    for x, y in zip(a.export(), b.export()):
+        assert torch.equal(x, y)
+
+
 def test_die_local_merge_refuses_blocks_on_an_unexpected_die():
     """The guard of the die-local merge, forced from the host: with a wrong record of which die serves which
     launch-order number every block reports a mismatch and the outputs of the step are NaN, not numbers; the
