@@ -54,9 +54,6 @@ typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 #ifndef BUZZ_U_G8
 #define BUZZ_U_G8 2
 #endif
-#ifndef BUZZ_MFMA_TR
-#define BUZZ_MFMA_TR 1   // 16-row tiles a wave of the matrix-core kernel has in flight
-#endif
 #ifndef BUZZ_MIN_BLOCKS
 #define BUZZ_MIN_BLOCKS 1  // second argument of __launch_bounds__
 #endif
@@ -65,8 +62,8 @@ typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 // block b holds the wall clock (100 MHz) at which the block passed point s of the last launch.
 #if defined(BUZZ_TRACE) && BUZZ_TU == 2
 __device__ unsigned long long g_trace[kMaxBlocks * 16];
-#define BUZZ_STAMP(slot) do { g_trace[(size_t)(blockIdx.y * gridDim.x + blockIdx.x) * 16 + (slot)] = wall_clock64(); } while (0)
-#define BUZZ_STAMP_VALUE(slot, v) do { g_trace[(size_t)(blockIdx.y * gridDim.x + blockIdx.x) * 16 + (slot)] = (v); } while (0)
+#define BUZZ_STAMP(slot) do { g_trace[(size_t)((blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x) * 16 + (slot)] = wall_clock64(); } while (0)
+#define BUZZ_STAMP_VALUE(slot, v) do { g_trace[(size_t)((blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x) * 16 + (slot)] = (v); } while (0)
 #else
 #define BUZZ_STAMP(slot) do { } while (0)
 #define BUZZ_STAMP_VALUE(slot, v) do { } while (0)
@@ -191,10 +188,10 @@ template <bool LOCAL> constexpr int merge_scope() { return LOCAL ? __HIP_MEMORY_
 template <bool LOCAL> __device__ inline void publish(float* p, float v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, merge_scope<LOCAL>()); }
 template <bool LOCAL> __device__ inline float acquire(const float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, merge_scope<LOCAL>()); }
 
-// Where a block works: logical rows [j0, j1) of one unit.  The range is cut into at most four physically
-// contiguous runs (linear region, ring before the wrap, ring after the wrap, the row being appended).
+// Where a block works: logical rows [j0, j1) of one unit.  The range is cut into at most three physically
+// contiguous runs of stored rows (linear region, ring before the wrap, ring after the wrap) and the row being appended.
 struct SplitCtx {
-    int split, unit, b, kvh;
+    int split, unit;
     int home;            // die-local merge: launch-order block number mod 8, which decides the die
     int j0, j1, jl1, wrap;
     size_t ubase;
@@ -207,14 +204,12 @@ __device__ inline SplitCtx make_ctx(const AttnArgs& a)
     x.home = 0;
     if (a.xcd_local) {
         // The hardware deals the blocks of a grid to the dies (XCDs) round-robin in launch order: block b runs
-        // on die b mod 8.  Renumber so that the n_splits blocks of a unit share b mod 8 (units is a multiple of
-        // 8 here): die d gets units d * units/8 ... and, in launch order, their splits.
-        const int b = blockIdx.y * gridDim.x + blockIdx.x, die = b & 7, slot = b >> 3;
-        x.unit = die * (gridDim.y >> 3) + slot / (int)gridDim.x;
-        x.split = slot % (int)gridDim.x;
-        x.home = die;
+        // on die b mod 8.  The grid is (8, n_splits, units / 8), x first in launch order, so the n_splits blocks of a
+        // unit share b mod 8 = blockIdx.x (units is a multiple of 8 here) and die d gets units d * units/8 ...
+        x.home = blockIdx.x;
+        x.split = blockIdx.y;
+        x.unit = blockIdx.x * gridDim.z + blockIdx.z;
     }
-    x.b = x.unit / a.Hkv; x.kvh = x.unit - x.b * a.Hkv;
     x.j0 = x.split * a.rows_per_split;
     x.j1 = min(a.n, x.j0 + a.rows_per_split);
     x.jl1 = min(x.j1, a.n - 1);                           // rows already stored in the arena end here
@@ -223,54 +218,41 @@ __device__ inline SplitCtx make_ctx(const AttnArgs& a)
     return x;
 }
 
-// run r covers logical rows [lo, hi) stored at physical rows phys0 ...; run 3 is the row being appended
-__device__ inline void run_bounds(const AttnArgs& a, const SplitCtx& x, int run, int& lo, int& hi, int& phys0)
-{
-    if (run == 0) { lo = x.j0; hi = min(x.jl1, a.map.front); phys0 = lo; }
-    else if (run == 1) { lo = max(x.j0, a.map.front); hi = min(x.jl1, x.wrap); phys0 = a.map.ring_base + a.map.ring_head + (lo - a.map.front); }
-    else if (run == 2) { lo = max(x.j0, x.wrap); hi = x.jl1; phys0 = a.map.ring_base + (lo - x.wrap); }
-    else { lo = a.n - 1; hi = (x.j1 == a.n && x.j0 < a.n) ? a.n : lo; phys0 = a.new_phys; }
-}
-
-// Everything a block does once its waves have put their (max, sum, unnormalised output) into LDS.
-// The order hides as much latency as it can behind work that does not depend on it:
-//   2. merge the waves, publish the split's partial (write-through stores);
-//   3. wait for the published stores, synchronise, take the ticket;
-//   4. the block that drew the last ticket requests the partials (upper half of its waves);
-//   5. side phase: this step's logits leave LDS, the previous step's score update is applied
-//      (off the critical path: in the last block it runs under the latency of step 4's loads);
-//   6. the last block merges the splits and writes the output.
-// The tiles of a split, numbered across its (up to three) stored runs.  Inside a run tiles sit on a grid
-// anchored at a physical multiple of WROWS: `lead` rows before the run's first row are masked, `cnt` is
-// the run length measured from the anchor.  A block's waves do not own fixed tiles: apart from the first
-// one each, a wave claims its next tile from a counter in LDS when it has issued the loads of the current
-// one.  (With fixed round-robin tiles the waves launched first -- which the memory pipeline serves first
+// The tiles of a split: WROWS consecutive rows each, numbered across its (up to three) stored runs from each run's
+// first row on; the row being appended, which comes from the caller's buffer, is a tile of its own at the end.
+// A block's waves do not own fixed tiles: apart from the first one each, a wave claims its next tile from a counter
+// in LDS.  (With fixed round-robin tiles the waves launched first -- which the memory pipeline serves first
 // -- ended 15% earlier than the others, and the block waited for the slowest.)
+struct Tile { int lo, phys, cnt, base; bool fresh; };     // run: first logical and physical row, length; first row in it
+
 template <int WROWS>
 struct TileMap {
-    int lo0, lo1, lo2, ph0, ph1, ph2, ld0, ld1, ld2, c0, c1, c2, f1, f2, n_tiles;
+    int lo0, lo1, lo2, ph0, ph1, ph2, c0, c1, c2, f1, f2, f3, n_tiles, n;
     __device__ inline TileMap(const AttnArgs& a, const SplitCtx& x)
     {
-        int h;
-        run_bounds(a, x, 0, lo0, h, ph0); ld0 = ph0 & (WROWS - 1); c0 = h > lo0 ? h - lo0 + ld0 : 0;
-        run_bounds(a, x, 1, lo1, h, ph1); ld1 = ph1 & (WROWS - 1); c1 = h > lo1 ? h - lo1 + ld1 : 0;
-        run_bounds(a, x, 2, lo2, h, ph2); ld2 = ph2 & (WROWS - 1); c2 = h > lo2 ? h - lo2 + ld2 : 0;
-        f1 = (c0 + WROWS - 1) / WROWS;
-        f2 = f1 + (c1 + WROWS - 1) / WROWS;
-        n_tiles = f2 + (c2 + WROWS - 1) / WROWS;
+        n = a.n;
+        lo0 = x.j0; ph0 = lo0; c0 = min(x.jl1, a.map.front) - lo0;
+        lo1 = max(x.j0, a.map.front); ph1 = a.map.ring_base + a.map.ring_head + (lo1 - a.map.front); c1 = min(x.jl1, x.wrap) - lo1;
+        lo2 = max(x.j0, x.wrap); ph2 = a.map.ring_base + (lo2 - x.wrap); c2 = x.jl1 - lo2;
+        f1 = (max(c0, 0) + WROWS - 1) / WROWS;
+        f2 = f1 + (max(c1, 0) + WROWS - 1) / WROWS;
+        f3 = f2 + (max(c2, 0) + WROWS - 1) / WROWS;
+        n_tiles = f3 + (x.j1 == a.n && x.j0 < a.n ? 1 : 0);
     }
     __device__ inline int total() const { return n_tiles; }
-    // tile t -> its run's (lo, phys0, lead, cnt) and the tile's first row measured from the anchor
-    __device__ inline void locate(int t, int& l, int& p, int& ld, int& c, int& base) const
+    __device__ inline Tile locate(int t) const
     {
         // (sums of "difference or 0" rather than nested selects between members: the latter turn into
         // an indexed read of the structure and push it into private memory)
         const bool r1 = t >= f1, r2 = t >= f2;
-        l = lo0 + (r1 ? lo1 - lo0 : 0) + (r2 ? lo2 - lo1 : 0);
-        p = ph0 + (r1 ? ph1 - ph0 : 0) + (r2 ? ph2 - ph1 : 0);
-        ld = ld0 + (r1 ? ld1 - ld0 : 0) + (r2 ? ld2 - ld1 : 0);
-        c = c0 + (r1 ? c1 - c0 : 0) + (r2 ? c2 - c1 : 0);
-        base = (t - (r1 ? f1 : 0) - (r2 ? f2 - f1 : 0)) * WROWS;
+        Tile k;
+        k.fresh = t >= f3;
+        k.lo = lo0 + (r1 ? lo1 - lo0 : 0) + (r2 ? lo2 - lo1 : 0);
+        k.phys = ph0 + (r1 ? ph1 - ph0 : 0) + (r2 ? ph2 - ph1 : 0);
+        k.cnt = c0 + (r1 ? c1 - c0 : 0) + (r2 ? c2 - c1 : 0);
+        k.base = (t - (r1 ? f1 : 0) - (r2 ? f2 - f1 : 0)) * WROWS;
+        if (k.fresh) { k.lo = n - 1; k.cnt = 1; k.base = 0; }
+        return k;
     }
 };
 
@@ -288,127 +270,310 @@ __device__ inline int next_tile(const AttnArgs& a, int* counter, int last, int n
     return a.fixed_tiles ? last + nw : claim_tile(counter);
 }
 
-// The previous step's softmax statistics of one unit (global maximum and 1/sum per head), which turn its
-// stored logits into probabilities.  A kernel requests them when it starts: they come from memory, and a
-// request made where they are needed would stall the end of the block for a full round trip.
-template <int G> struct PrevStat { float M[G], iL[G]; };
+// A wave's way through the tiles.  TWO: two tile buffers, the next tile's loads are issued before the current tile is
+// consumed.  (The compiler waits for both at once, because the next tile may not exist.  With the loads
+// issued unconditionally, and the loop shaped so that it waits for the older half only, the stream was no faster -- 52
+// us of 62 on one sequence of 23.6k rows by 32 heads, 7.4 TB/s either way -- and waves with one tile paid for loads of
+// tiles that do not exist: 8 units of 1500 rows, 4 heads each, 10.1 instead of 8.0 us per step.)
+template <bool TWO, typename Buf, typename Load, typename Compute>
+__device__ inline void stream_tiles(const AttnArgs& a, int* counter, int wave, int nw, int total, Load load, Compute compute)
+{
+    int t = wave;
+    if constexpr (TWO) {
+        Buf first, second;
+        if (t < total) load(first, t);
+        int tn = next_tile(a, counter, t, nw);
+        while (t < total) {
+            if (tn < total) load(second, tn);
+            int t2 = next_tile(a, counter, tn, nw);
+            compute(first, t);
+            t = tn; tn = t2;
+            if (t >= total) break;
+            if (tn < total) load(first, tn);
+            t2 = next_tile(a, counter, tn, nw);
+            compute(second, t);
+            t = tn; tn = t2;
+        }
+    } else {
+        while (t < total) {
+            Buf buf;
+            load(buf, t);
+            const int tn = next_tile(a, counter, t, nw);
+            compute(buf, t);
+            t = tn;
+        }
+    }
+}
+
+// A barrier that orders LDS only: loads from memory that are in flight stay in flight across it.
+__device__ inline void lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// The side phase: per row of the split, this step's logits out, and the score with the previous step's probability
+// added (one step late, because a probability needs the maximum and sum over all splits).  A thread takes the rows
+// tid, tid + NTHR, ...: every access of a wave is one contiguous piece whatever the row's place in the arena is.
+// The first SR rows of a thread are requested when the kernel starts and consumed after the streaming loop, so that
+// their latency is never exposed; longer splits take further rounds of SR rows.
+template <int G> constexpr int side_rows() { return G == 1 ? 8 : (G <= 4 ? 4 : 2); }
+
+template <int G> struct SideRows {
+    float M[G], iL[G];                                    // the previous step's softmax statistics of the unit
+    float sc[side_rows<G>()], lp[side_rows<G>()][G];      // old scores and the previous step's logits
+    u32x4 fresh;                                          // one of the new row's pieces (K's, then V's), last split only
+};
+
+// eq. 2: the caller's new row joins the cache.  Its pieces are requested when the kernel starts and stored in the
+// side phase (stores between the streaming loop's loads would make the compiler wait for more than it needs).
+template <int ROWB>
+__device__ inline bool fresh_piece(const AttnArgs& a, const SplitCtx& x) { return x.j1 == a.n && x.j0 < a.n && (int)threadIdx.x < 2 * (ROWB / 16); }
+template <int ROWB, int G>
+__device__ inline void request_fresh_row(const AttnArgs& a, const SplitCtx& x, SideRows<G>& p)
+{
+    constexpr int P = ROWB / 16;
+    const int i = threadIdx.x;
+    if (fresh_piece<ROWB>(a, x)) p.fresh = *(const u32x4*)((const char*)(i < P ? a.k_new : a.v_new) + (size_t)x.unit * ROWB + (i < P ? i : i - P) * 16);
+}
+template <int ROWB, int G>
+__device__ inline void store_fresh_row(const AttnArgs& a, const SplitCtx& x, const SideRows<G>& p)
+{
+    constexpr int P = ROWB / 16;
+    const int i = threadIdx.x;
+    if (fresh_piece<ROWB>(a, x)) {
+        *(u32x4*)((char*)(i < P ? a.K : a.V) + (x.ubase + a.new_phys) * ROWB + (i < P ? i : i - P) * 16) = p.fresh;
+        if (i == 0) a.pos[x.ubase + a.new_phys] = a.new_pos;
+    }
+}
+
+template <int G, int NTHR>
+__device__ inline void request_side_rows(const AttnArgs& a, const SplitCtx& x, int first, SideRows<G>& p)
+{
+    if (!a.pending) return;
+    const float* score_u = a.score + x.ubase;
+    const float* logit_prev_u = a.logit_prev + x.ubase * G;
+#pragma unroll
+    for (int i = 0; i < side_rows<G>(); ++i) {
+        if (x.j0 + first + i * NTHR >= x.jl1) break;
+        const int j = x.j0 + first + (int)threadIdx.x + i * NTHR;
+        if (j < x.jl1) {
+            const int ph = a.map.phys(j);
+            p.sc[i] = score_u[ph];
+#pragma unroll
+            for (int g = 0; g < G; ++g) p.lp[i][g] = logit_prev_u[(size_t)g * a.cap + ph];
+        }
+    }
+}
 
 template <int G>
-__device__ inline PrevStat<G> load_prev_stat(const AttnArgs& a, int unit)
+__device__ inline void request_prev_stat(const AttnArgs& a, int unit, SideRows<G>& p)
 {
-    PrevStat<G> p;
 #pragma unroll
     for (int g = 0; g < G; ++g) {
-        p.M[g] = a.pending ? a.stat_prev[((size_t)unit * G + g) * 2] : 0.f;
-        p.iL[g] = a.pending ? a.stat_prev[((size_t)unit * G + g) * 2 + 1] : 0.f;
-    }
-    return p;
-}
-
-// What a thread needs for the first pass of its side phase (4 consecutive physical rows in each stored
-// run of the split): the old scores and the previous step's logits.  Requested when the kernel starts and
-// consumed after the streaming loop, so that their latency is never exposed.
-// (They occupy 12 (G + 1) registers through the whole streaming loop; where that would spill -- 8 heads
-// per row, or 4 heads of 256 columns -- the request is made after the loop instead.)
-template <int G> struct SideRows { float4 sc[3], lp[3][G]; };
-template <int G, int D> constexpr bool early_side() { return G <= 4 && G * D <= 512; }
-
-template <int G>
-__device__ inline void request_side_rows(const AttnArgs& a, const SplitCtx& x, SideRows<G>& p)
-{
-    const int tid = threadIdx.x;
-    const float* logit_prev_u = a.logit_prev + x.ubase * G;
-    const float* score_u = a.score + x.ubase;
-#pragma unroll
-    for (int run = 0; run < 3; ++run) {
-        int lo, hi, phys0;
-        run_bounds(a, x, run, lo, hi, phys0);
-        const int lead = phys0 & 3, pa = phys0 - lead, cnt = hi - lo + lead;
-        if (a.pending && hi - lo > 0 && 4 * tid < cnt) {
-            p.sc[run] = *(const float4*)(score_u + pa + 4 * tid);
-#pragma unroll
-            for (int g = 0; g < G; ++g) p.lp[run][g] = *(const float4*)(logit_prev_u + (size_t)g * a.cap + pa + 4 * tid);
-        }
+        p.M[g] = a.stat_prev[((size_t)unit * G + g) * 2];       // (read but not used where nothing is pending)
+        p.iL[g] = a.stat_prev[((size_t)unit * G + g) * 2 + 1];
     }
 }
 
-// new score = old score + sum over heads of the previous step's probability (lazy update, one step late)
-template <int G>
-__device__ inline void first_pass_scores(const AttnArgs& a, const SplitCtx& x, const PrevStat<G>& prev, SideRows<G>& p)
+template <int G, int NTHR>
+__device__ inline void store_side_rows(const AttnArgs& a, const SplitCtx& x, int first, const SideRows<G>& p, const float* stage)
 {
-    const int tid = threadIdx.x;
+    float* score_u = a.score + x.ubase;
+    float* logit_u = a.logit + x.ubase * G;               // [G][cap] for this unit, written by this step
 #pragma unroll
-    for (int run = 0; run < 3; ++run) {
-        int lo, hi, phys0;
-        run_bounds(a, x, run, lo, hi, phys0);
-        const int lead = phys0 & 3, cnt = hi - lo + lead;
-        if (a.pending && hi - lo > 0 && 4 * tid < cnt) {
+    for (int i = 0; i < side_rows<G>(); ++i) {
+        if (x.j0 + first + i * NTHR >= x.j1) break;
+        const int r = first + (int)threadIdx.x + i * NTHR, j = x.j0 + r;
+        if (j < x.j1) {
+            const int ph = a.map.phys(j);
 #pragma unroll
-            for (int g = 0; g < G; ++g) {
-                p.sc[run].x = add_probability(p.sc[run].x, p.lp[run][g].x, prev.M[g], prev.iL[g]);
-                p.sc[run].y = add_probability(p.sc[run].y, p.lp[run][g].y, prev.M[g], prev.iL[g]);
-                p.sc[run].z = add_probability(p.sc[run].z, p.lp[run][g].z, prev.M[g], prev.iL[g]);
-                p.sc[run].w = add_probability(p.sc[run].w, p.lp[run][g].w, prev.M[g], prev.iL[g]);
+            for (int g = 0; g < G; ++g) logit_u[(size_t)g * a.cap + ph] = stage[g * a.rows_per_split + r];
+            if (j == a.n - 1) {
+                score_u[ph] = 0.f;                        // the appended row starts from score 0
+            } else if (a.pending) {
+                float sc = p.sc[i];
+#pragma unroll
+                for (int g = 0; g < G; ++g) sc = add_probability(sc, p.lp[i][g], p.M[g], p.iL[g]);
+                score_u[ph] = sc;
             }
         }
     }
 }
 
-template <int G, int D, int NW, bool LOCAL>
-__device__ inline void finish_split_scoped(const AttnArgs& a, const SplitCtx& x, const PrevStat<G>& prev,
-                                    const float4 (&pre_sc)[3], const float* stage,
-                                    float (*sm_m)[G], float (*sm_l)[G], float (*sm_acc)[G][D], int* sm_ticket)
+// The running results of a block's waves in LDS.
+template <int G, int D, int NW> struct WaveResults {
+    float2 ml[G][NW];                                     // (max, sum)
+    float acc[NW][G][D];                                  // unnormalised output
+    int ticket, next_tile;
+};
+
+__device__ inline float lane_value(float v, int lane)     // of a wave-uniform lane
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane));
+}
+
+// Maximum and sum over the wave, in every lane: 16 lanes by DPP, the four rows through scalar registers.
+__device__ inline float wave_max(float v)
+{
+    v = fmaxf(v, dpp_move<0xB1>(v));
+    v = fmaxf(v, dpp_move<0x4E>(v));
+    v = fmaxf(v, dpp_move<0x141>(v));
+    v = fmaxf(v, dpp_move<0x140>(v));
+    return fmaxf(fmaxf(lane_value(v, 0), lane_value(v, 16)), fmaxf(lane_value(v, 32), lane_value(v, 48)));
+}
+__device__ inline float wave_sum(float v)
+{
+    v = row_sum<16>(v);
+    return (lane_value(v, 0) + lane_value(v, 16)) + (lane_value(v, 32) + lane_value(v, 48));
+}
+
+// The last block of a unit merges the partials of its S splits, 64 output elements (of one head) per wave and group:
+// lane s fetches the (max, sum) pair of split s and turns it into that split's weight, every lane fetches its element
+// of the splits' outputs, GB groups and 8 (GB <= 2: 16) splits at a time in one round of loads without a branch in
+// between, and the weights reach the lanes as scalars: one exponential per wave and split instead of one per
+// element, half the loads of a pair per element, one round trip for up to 16 splits.  What counts here is the
+// number of instructions the waves have to issue between the ticket and the output: with a branch-free burst of
+// pairs and elements per thread, and two rounds of it, a step of 8 units, 12 splits, 4 heads of 128 took 9.3 us
+// instead of 8.0.  (Spreading the splits over all waves of the block and their sums through LDS: 8.2.)
+template <int G, int D, int NM>
+__device__ inline void merge_splits(const AttnArgs& a, int unit, int wave, bool poisoned, float* outp)
+{
+    constexpr int NG = G * D / 64, NMW = NM / 64;         // groups of 64 elements, merging waves
+    constexpr int PER = (NG + NMW - 1) / NMW, GB = PER < 4 ? PER : 4, CH = GB <= 2 ? 16 : 8;
+    const int S = a.n_splits, lane = threadIdx.x & 63;
+    const unsigned long long* ml = (const unsigned long long*)(a.part_ml + (size_t)unit * a.s_cap * G * 2);
+    const float* po = a.part_o + (size_t)unit * a.s_cap * G * D;
+#pragma unroll 1
+    for (int gr0 = wave; gr0 < NG; gr0 += NMW * GB) {
+        float M[GB], L[GB], o[GB];
+#pragma unroll
+        for (int b = 0; b < GB; ++b) { M[b] = -INFINITY; L[b] = 0.f; o[b] = 0.f; }
+        // 16 (8) splits per round; the running maximum moves from round to round
+#pragma unroll 1
+        for (int s0 = 0; s0 < S; s0 += CH) {
+            unsigned long long pair[GB];
+            float xr[GB][CH];
+            auto request = [&](auto local) {
+                constexpr bool LOCAL = decltype(local)::value;
+#pragma unroll
+                for (int b = 0; b < GB; ++b)
+                    pair[b] = __hip_atomic_load(ml + min(s0 + (lane & (CH - 1)), S - 1) * G + min(gr0 + b * NMW, NG - 1) * 64 / D, __ATOMIC_RELAXED, merge_scope<LOCAL>());
+#pragma unroll
+                for (int half = 0; half < CH; half += 8) {
+                    if (half > 0 && s0 + half >= S) break;
+#pragma unroll
+                    for (int b = 0; b < GB; ++b) {
+#pragma unroll
+                        for (int e = half; e < half + 8; ++e) xr[b][e] = acquire<LOCAL>(po + (size_t)min(s0 + e, S - 1) * (G * D) + min(gr0 + b * NMW, NG - 1) * 64 + lane);
+                    }
+                }
+            };
+            if (a.xcd_local) request(std::true_type{}); else request(std::false_type{});
+            const bool have = lane < CH && s0 + lane < S;
+            float w[GB];
+#pragma unroll
+            for (int b = 0; b < GB; ++b) {
+                const float m = have ? __uint_as_float((unsigned)pair[b]) : -INFINITY;
+                const float mx = fmaxf(M[b], wave_max(m));   // finite: the appended row is always present
+                const float keep = fast_exp2(M[b] - mx);     // 0 in the first round
+                w[b] = fast_exp2(m - mx);
+                L[b] = fmaf(L[b], keep, wave_sum(have ? w[b] * __uint_as_float((unsigned)(pair[b] >> 32)) : 0.f));
+                o[b] *= keep;
+                M[b] = mx;
+            }
+#pragma unroll
+            for (int half = 0; half < CH; half += 8) {
+                if (half > 0 && s0 + half >= S) break;
+#pragma unroll
+                for (int b = 0; b < GB; ++b) {
+#pragma unroll
+                    for (int e = half; e < half + 8; ++e) o[b] = fmaf(lane_value(w[b], e), s0 + e < S ? xr[b][e] : 0.f, o[b]);
+                }
+            }
+        }
+#pragma unroll
+        for (int b = 0; b < GB; ++b) {
+            const int gr = gr0 + b * NMW;
+            if (gr >= NG) continue;
+            outp[gr * 64 + lane] = poisoned ? __builtin_nanf("") : o[b] / L[b];
+            if (gr * 64 % D == 0 && lane == 0) {
+                a.stat[((size_t)unit * G + gr * 64 / D) * 2] = M[b];
+                a.stat[((size_t)unit * G + gr * 64 / D) * 2 + 1] = 1.0f / L[b];
+            }
+        }
+    }
+}
+
+// Everything a block does once its waves have put their (max, sum, unnormalised output) into LDS:
+//   1. merge the waves; the only split of a unit writes the result, else publish the split's partial;
+//   2. wait for the published stores, synchronise, take the ticket;
+//   3. in the block that drew the last ticket the upper half of the waves merges the splits and writes the output;
+//   4. side phase: this step's logits leave LDS, the previous step's score update is applied.  (The read
+//      stream of the block is over by then.  Doing the score update at the start of the block instead, under the
+//      latency of the first K/V loads, was measured 8% slower: its writes then compete with the ramping stream.
+//      Between 1 and 2 it delays the tickets: 8 units, 12 splits: 8.4 instead of 8.0 us per step.)
+template <int G, int D, int NW, int ROWB>
+__device__ inline void finish_split(const AttnArgs& a, const SplitCtx& x, SideRows<G>& side, const float* stage, WaveResults<G, D, NW>& sm)
 {
     constexpr int NTHR = NW * 64;                         // threads per block
-    const int tid = threadIdx.x;
-    const int unit = x.unit, j0 = x.j0;
+    const int tid = threadIdx.x, unit = x.unit;
     const int S = a.n_splits;
-    float* logit_u = a.logit + x.ubase * G;               // [G][cap] for this unit, written by this step
-    const float* logit_prev_u = a.logit_prev + x.ubase * G;   // the previous step's logits
-    float* score_u = a.score + x.ubase;
-    const float (&Mp)[G] = prev.M;
-    const float (&iLp)[G] = prev.iL;
-
-    // 2. merge the waves; the only split writes the result, otherwise publish the partial
-    __syncthreads();
-    float* outp = a.out + (size_t)(x.b * a.Hq + x.kvh * G) * D;
-    const size_t pbase = ((size_t)unit * a.s_cap + x.split) * G;
-    for (int i = tid; i < G * D; i += NTHR) {
-        const int g = i / D, d = i - g * D;
-        float M = sm_m[0][g];
+    // the NW results in LDS -> emit(element, head, column, max, sum, output)
+    auto merge_waves = [&](auto emit) {
+        for (int i = tid; i < G * D; i += NTHR) {
+            const int g = i / D, d = i - g * D;
+            float2 ml[NW];
+            float av[NW];
 #pragma unroll
-        for (int w = 1; w < NW; ++w) M = fmaxf(M, sm_m[w][g]);
-        const float mref = (M == -INFINITY) ? 0.f : M;
-        float o = 0.f, L = 0.f;
+            for (int w = 0; w < NW; ++w) { ml[w] = sm.ml[g][w]; av[w] = sm.acc[w][g][d]; }
+            float M = ml[0].x;
 #pragma unroll
-        for (int w = 0; w < NW; ++w) {
-            const float wgt = fast_exp2(sm_m[w][g] - mref);
-            o = fmaf(wgt, sm_acc[w][g][d], o);
-            L = fmaf(wgt, sm_l[w][g], L);
-        }
-        if (S == 1) {
-            outp[(size_t)g * D + d] = o / L;
-            if (d == 0) {
-                a.stat[((size_t)unit * G + g) * 2] = M;
-                a.stat[((size_t)unit * G + g) * 2 + 1] = 1.0f / L;
+            for (int w = 1; w < NW; ++w) M = fmaxf(M, ml[w].x);
+            const float mref = (M == -INFINITY) ? 0.f : M;
+            float o = 0.f, L = 0.f;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) {
+                const float wgt = fast_exp2(ml[w].x - mref);
+                o = fmaf(wgt, av[w], o);
+                L = fmaf(wgt, ml[w].y, L);
             }
-        } else {
-            publish<LOCAL>(a.part_o + (pbase + g) * D + d, o);
-            if (d == 0) {
-                publish<LOCAL>(a.part_ml + (pbase + g) * 2, M);
-                publish<LOCAL>(a.part_ml + (pbase + g) * 2 + 1, L);
-            }
+            emit(i, g, d, M, L, o);
         }
-    }
+    };
+    float* outp = a.out + (size_t)unit * G * D;           // heads of a unit are consecutive: unit * G = b * Hq + kvh * G
+    auto write = [&](int i, int g, int d, float M, float L, float o) {
+        outp[i] = o / L;
+        if (d == 0) {
+            a.stat[((size_t)unit * G + g) * 2] = M;
+            a.stat[((size_t)unit * G + g) * 2 + 1] = 1.0f / L;
+        }
+    };
+    lds_barrier();
+    if (S == 1) {
+        merge_waves(write);
+        if (tid == 0) BUZZ_STAMP(2);
+    } else {
+        const size_t pbase = ((size_t)unit * a.s_cap + x.split) * G;
+        float* part_o = a.part_o + pbase * D;
+        float* part_ml = a.part_ml + pbase * 2;
+        if (a.xcd_local)
+            merge_waves([&](int i, int g, int d, float M, float L, float o) {
+                publish<true>(part_o + i, o);
+                if (d == 0) { publish<true>(part_ml + 2 * g, M); publish<true>(part_ml + 2 * g + 1, L); }
+            });
+        else
+            merge_waves([&](int i, int g, int d, float M, float L, float o) {
+                publish<false>(part_o + i, o);
+                if (d == 0) { publish<false>(part_ml + 2 * g, M); publish<false>(part_ml + 2 * g + 1, L); }
+            });
+        if (tid == 0) BUZZ_STAMP(2);
 
-    if (tid == 0) BUZZ_STAMP(2);
-
-    // 3. ticket: the block that arrives last for this unit sees every split's partial.  Every wave first
-    // waits until its own published stores have been acknowledged (vmcnt(0)), then the block synchronises,
-    // then one thread takes the ticket: the ticket can never overtake a partial (the argument is written out
-    // above merge_scope).  No cache maintenance is involved.
-    bool last = false;
-    if (S > 1) {
+        // Ticket: the block that arrives last for this unit sees every split's partial.  Every wave first
+        // waits until its own published stores have been acknowledged (vmcnt(0)), then the block synchronises,
+        // then one thread takes the ticket: the ticket can never overtake a partial (the argument is written out
+        // above merge_scope).  No cache maintenance is involved.
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
         __builtin_amdgcn_s_waitcnt(0x0F70);               // vmcnt(0), expcnt / lgkmcnt untouched
         __syncthreads();
@@ -416,151 +581,41 @@ __device__ inline void finish_split_scoped(const AttnArgs& a, const SplitCtx& x,
             // A die-local merge is only right if this block really runs where its number says: the host has
             // recorded which die served block numbers 0..7 (die_map, 4 bits each); a block that finds itself
             // elsewhere says so in the ticket's upper half, and the merging block sees every earlier arrival's.
-            int add = 1;
-            if (LOCAL && (__builtin_amdgcn_s_getreg((31 << 11) | 20) & 7u) != ((a.die_map >> (4 * x.home)) & 15u)) add += 0x10000;   // XCC_ID
-            const int before = __hip_atomic_fetch_add(a.ticket + unit, add, __ATOMIC_RELAXED, merge_scope<LOCAL>());
-            *sm_ticket = before + (add & 0x10000);
+            int add = 1, before;
+            if (a.xcd_local) {
+                if ((__builtin_amdgcn_s_getreg((31 << 11) | 20) & 7u) != ((a.die_map >> (4 * x.home)) & 15u)) add += 0x10000;   // XCC_ID
+                before = __hip_atomic_fetch_add(a.ticket + unit, add, __ATOMIC_RELAXED, merge_scope<true>());
+            } else {
+                before = __hip_atomic_fetch_add(a.ticket + unit, add, __ATOMIC_RELAXED, merge_scope<false>());
+            }
+            sm.ticket = before + (add & 0x10000);
         }
         __syncthreads();
-        last = (*sm_ticket & 0xffff) == S - 1;
         if (tid == 0) BUZZ_STAMP(4);
+        const int arrival = __builtin_amdgcn_readfirstlane(sm.ticket);
+        if ((arrival & 0xffff) == S - 1) {
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+            constexpr int NM = NTHR / 2;                  // merging threads: the lower half starts its side phase
+            if (tid >= NM) {
+                // A die-local merge with a block on an unexpected die may have missed partials: its output is NaN
+                // rather than plausible numbers.
+                merge_splits<G, D, NM>(a, unit, __builtin_amdgcn_readfirstlane((tid - NM) >> 6), (arrival >> 16) != 0, outp);
+                if (tid == NM) {                          // ready for the next step
+                    if (a.xcd_local) __hip_atomic_store(a.ticket + unit, 0, __ATOMIC_RELAXED, merge_scope<true>());
+                    else __hip_atomic_store(a.ticket + unit, 0, __ATOMIC_RELAXED, merge_scope<false>());
+                }
+                if (tid == NM) BUZZ_STAMP(5);
+            }
+        }
     }
-
-    // 4. in the last block the upper half of the waves merges the splits; each of those threads owns OPT
-    // output elements and requests, for the first CH splits, the element itself and the (max, sum) pair of
-    // its head -- everything in ONE round of device-scope loads with no branch in between.  The answers
-    // arrive while the block does its side phase, which for up to 4 * NTHR / 2 rows per split keeps only
-    // the lower half of the waves busy.
-    constexpr int NM = NTHR / 2;                          // merging threads
-    constexpr int OPT = (G * D + NM - 1) / NM;            // output elements per merging thread
-    constexpr int CH = OPT >= 16 ? 2 : (OPT >= 8 ? 4 : 8);   // splits per round of loads
-    const bool merger = last && tid >= NM;
-    const unsigned long long* ml = (const unsigned long long*)(a.part_ml + (size_t)unit * a.s_cap * G * 2);
-    const float* po = a.part_o + (size_t)unit * a.s_cap * G * D;
-    unsigned long long mlr[OPT][CH];
-    float xr[OPT][CH];
-    auto request = [&](int s0) {
-#pragma unroll
-        for (int r = 0; r < OPT; ++r) {
-            const int i = min(tid - NM + NM * r, G * D - 1);
-            const int g = i / D;
-#pragma unroll
-            for (int e = 0; e < CH; ++e) {
-                const int sp = min(s0 + e, S - 1);
-                mlr[r][e] = __hip_atomic_load(ml + sp * G + g, __ATOMIC_RELAXED, merge_scope<LOCAL>());
-                xr[r][e] = acquire<LOCAL>(po + (size_t)sp * G * D + i);
-            }
-        }
-    };
-    if (last) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-    if (merger) request(0);
-
-    // 5. dense side phase, after the read stream of this block is over (the logits staged by all waves are
-    // visible after the barriers above).  Four consecutive physical rows per thread, 16-byte accesses where
-    // the whole group belongs to this split; the appended row starts from score 0.
-    // (Doing the score update at the start of the block instead, under the latency of the first K/V
-    // loads, was measured 8% slower: its writes then compete with the ramping read stream.)
-#pragma unroll
-    for (int run = 0; run < 4; ++run) {
-        int lo, hi, phys0;
-        run_bounds(a, x, run, lo, hi, phys0);
-        if (hi - lo <= 0) continue;
-        const bool fresh = run == 3;
-        const bool upd = a.pending && !fresh;
-        const int lead = phys0 & 3, pa = phys0 - lead, cnt = hi - lo + lead;
-        for (int r0 = 4 * tid; r0 < cnt; r0 += 4 * NTHR) {
-            const int ph = pa + r0;
-            float4 sc = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (upd) {
-                if (run < 3 && r0 == 4 * tid) {           // first pass: worked out in step 2b
-                    sc = pre_sc[run < 3 ? run : 0];
-                } else {
-                    float4 lp[G];
-                    sc = *(const float4*)(score_u + ph);
-#pragma unroll
-                    for (int g = 0; g < G; ++g) lp[g] = *(const float4*)(logit_prev_u + (size_t)g * a.cap + ph);
-#pragma unroll
-                    for (int g = 0; g < G; ++g) {
-                        sc.x = add_probability(sc.x, lp[g].x, Mp[g], iLp[g]);
-                        sc.y = add_probability(sc.y, lp[g].y, Mp[g], iLp[g]);
-                        sc.z = add_probability(sc.z, lp[g].z, Mp[g], iLp[g]);
-                        sc.w = add_probability(sc.w, lp[g].w, Mp[g], iLp[g]);
-                    }
-                }
-            }
-            const int sj = lo - j0 + r0 - lead;           // staging index of the group's first row
-            if (r0 >= lead && r0 + 3 < cnt) {
-#pragma unroll
-                for (int g = 0; g < G; ++g) {
-                    const float* sg = stage + g * a.rows_per_split + sj;
-                    *(float4*)(logit_u + (size_t)g * a.cap + ph) = make_float4(sg[0], sg[1], sg[2], sg[3]);
-                }
-                if (upd || fresh) *(float4*)(score_u + ph) = sc;
-            } else {                                      // ragged edge of the run: row by row
-                const float scv[4] = {sc.x, sc.y, sc.z, sc.w};
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    if (r0 + e >= lead && r0 + e < cnt) {
-#pragma unroll
-                        for (int g = 0; g < G; ++g) logit_u[(size_t)g * a.cap + ph + e] = stage[g * a.rows_per_split + sj + e];
-                        if (upd || fresh) score_u[ph + e] = scv[e];
-                    }
-                }
-            }
-        }
+    store_fresh_row<ROWB, G>(a, x, side);
+    store_side_rows<G, NTHR>(a, x, 0, side, stage);
+#pragma unroll 1
+    for (int first = side_rows<G>() * NTHR; x.j0 + first < x.j1; first += side_rows<G>() * NTHR) {
+        request_side_rows<G, NTHR>(a, x, first, side);
+        store_side_rows<G, NTHR>(a, x, first, side, stage);
     }
     if (tid == 0) BUZZ_STAMP(3);
-    if (!merger) return;
-
-    // 6. merge the splits: a running (max, sum, output) per owned element, CH splits per round.
-    // A die-local merge with a block on an unexpected die may have missed partials: its output is NaN rather
-    // than plausible numbers.
-    const float poison = (*sm_ticket >> 16) ? __builtin_nanf("") : 0.f;
-    float Mr[OPT], Lr[OPT], Or[OPT];
-#pragma unroll
-    for (int r = 0; r < OPT; ++r) { Mr[r] = -INFINITY; Lr[r] = 0.f; Or[r] = 0.f; }
-    for (int s0 = 0; s0 < S; s0 += CH) {
-        if (s0 > 0) request(s0);
-#pragma unroll
-        for (int r = 0; r < OPT; ++r) {
-            float mx = Mr[r];
-#pragma unroll
-            for (int e = 0; e < CH; ++e)
-                if (s0 + e < S) mx = fmaxf(mx, __uint_as_float((unsigned)mlr[r][e]));   // finite: the appended row is always present
-            const float keep = fast_exp2(Mr[r] - mx);    // 0 in the first round
-            Lr[r] *= keep; Or[r] *= keep; Mr[r] = mx;
-#pragma unroll
-            for (int e = 0; e < CH; ++e) {
-                if (s0 + e < S) {
-                    const float w = fast_exp2(__uint_as_float((unsigned)mlr[r][e]) - mx);
-                    Lr[r] = fmaf(__uint_as_float((unsigned)(mlr[r][e] >> 32)), w, Lr[r]);
-                    Or[r] = fmaf(w, xr[r][e], Or[r]);
-                }
-            }
-        }
-    }
-#pragma unroll
-    for (int r = 0; r < OPT; ++r) {
-        const int i = tid - NM + NM * r;
-        if (i >= G * D) continue;
-        const int g = i / D;
-        outp[i] = Or[r] / Lr[r] + poison;
-        if (i - g * D == 0) {
-            a.stat[((size_t)unit * G + g) * 2] = Mr[r];
-            a.stat[((size_t)unit * G + g) * 2 + 1] = 1.0f / Lr[r];
-        }
-    }
-    if (tid == NM) __hip_atomic_store(a.ticket + unit, 0, __ATOMIC_RELAXED, merge_scope<LOCAL>());   // ready for the next step
-    if (tid == NM) BUZZ_STAMP(5);
-}
-
-template <int G, int D, int NW>
-__device__ inline void finish_split(const AttnArgs& a, const SplitCtx& x, const PrevStat<G>& prev,
-                                    const float4 (&pre_sc)[3], const float* stage,
-                                    float (*sm_m)[G], float (*sm_l)[G], float (*sm_acc)[G][D], int* sm_ticket)
-{
-    if (a.xcd_local) finish_split_scoped<G, D, NW, true>(a, x, prev, pre_sc, stage, sm_m, sm_l, sm_acc, sm_ticket);
-    else finish_split_scoped<G, D, NW, false>(a, x, prev, pre_sc, stage, sm_m, sm_l, sm_acc, sm_ticket);
 }
 
 // Vector-ALU streaming kernel (any dtype; the choice for one query head per kv head).
@@ -574,25 +629,25 @@ __global__ __launch_bounds__(NW * 64, BUZZ_MIN_BLOCKS) void attn_split_kernel(co
     constexpr int ROWB = D * (int)sizeof(T);
     constexpr int WROWS = RPW * U;        // rows one wave consumes per trip
     static_assert(LPR >= 8 && LPR <= 64, "row must span 8..64 lanes");
-    static_assert((WROWS & (WROWS - 1)) == 0, "tiles anchor at multiples of WROWS");
 
     extern __shared__ float stage[];                      // [G][rows_per_split] logits of this split's rows
-    __shared__ float sm_m[NW][G], sm_l[NW][G];
-    __shared__ float sm_acc[NW][G][D];
-    __shared__ int sm_ticket, sm_next;
+    __shared__ WaveResults<G, D, NW> sm;
 
     const SplitCtx x = make_ctx(a);
-    const int unit = x.unit, b = x.b, kvh = x.kvh, j0 = x.j0, j1 = x.j1;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int unit = x.unit, j0 = x.j0;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // tile numbers and addresses stay in scalar registers
     const int c = lane % LPR, rs = lane / LPR;
-    const PrevStat<G> prev = load_prev_stat<G>(a, unit);
-    SideRows<G> side;
-    if constexpr (early_side<G, D>()) request_side_rows<G>(a, x, side);
     if (tid == 0) { BUZZ_STAMP(0); BUZZ_STAMP_VALUE(6, __builtin_amdgcn_s_getreg((31 << 11) | 4)); BUZZ_STAMP_VALUE(7, __builtin_amdgcn_s_getreg((31 << 11) | 20)); }
+    if (tid == 0) sm.next_tile = NW;                      // tiles 0 .. NW-1 are the waves' first tiles
+    SideRows<G> side;
+    request_prev_stat<G>(a, unit, side);
+    request_side_rows<G, NW * 64>(a, x, 0, side);
+    request_fresh_row<ROWB, G>(a, x, side);
 
     u32x4 qr[G];                                          // this lane's 16 bytes of every query head, raw
     {
-        const char* qb = (const char*)a.q + (size_t)(b * a.Hq + kvh * G) * ROWB + c * 16;
+        const char* qb = (const char*)a.q + (size_t)unit * G * ROWB + c * 16;
 #pragma unroll
         for (int g = 0; g < G; ++g) qr[g] = *(const u32x4*)(qb + (size_t)g * ROWB);
     }
@@ -610,29 +665,32 @@ __global__ __launch_bounds__(NW * 64, BUZZ_MIN_BLOCKS) void attn_split_kernel(co
         for (int v = 0; v < VEC; ++v) acc[g][v] = 0.f;
     }
 
-    // Work split inside a block.  A split's logical row range is cut into at most four physically
-    // contiguous runs; inside a run, tiles of WROWS rows sit on a grid anchored at a physical multiple
-    // of WROWS (`lead` rows before the run's first row are masked), and the block's waves take the tiles
-    // of all runs one after another (TileMap).  The streaming phase only reads: logits are staged in LDS,
-    // and all per-row side traffic (this step's logits out, the previous step's logits and the old score
-    // in, the new score out) happens in one dense phase at the end of the block.  Writes that trickle
-    // into a saturated read stream were measured to cost ~5% of the kernel per 1% of extra bytes.
-    auto load_tile = [&](u32x4 (&kr)[U], u32x4 (&vr)[U], const char* kp, const char* vp, int base, int lead, int cnt) {
+    // The streaming phase only reads: logits are staged in LDS, and all per-row side traffic (this step's logits out,
+    // the previous step's logits and the old score in, the new score out) happens in one dense phase at the end of
+    // the block.  Writes that trickle into a saturated read stream were measured to cost ~5% of the kernel per 1% of
+    // extra bytes.
+    struct Buf { u32x4 k[U], v[U]; };
+    const TileMap<WROWS> tiles(a, x);
+    const int total = tiles.total();
+    auto load_t = [&](u32x4 (&kr)[U], u32x4 (&vr)[U], int t) {
+        const Tile k = tiles.locate(t);
+        const char* kp = k.fresh ? (const char*)a.k_new + (size_t)unit * ROWB : Kb + (size_t)k.phys * ROWB;
+        const char* vp = k.fresh ? (const char*)a.v_new + (size_t)unit * ROWB : Vb + (size_t)k.phys * ROWB;
 #pragma unroll
-        for (int u = 0; u < U; ++u) {      // masked lanes re-read a valid row of the run
-            const unsigned off = (unsigned)(min(max(base + u * RPW + rs, lead), cnt - 1) - lead) * ROWB + lane_off;
+        for (int u = 0; u < U; ++u) {      // lanes past the run's end re-read its last row
+            const unsigned off = (unsigned)min(k.base + u * RPW + rs, k.cnt - 1) * ROWB + lane_off;
             kr[u] = load16<NT>(kp + off);
             vr[u] = load16<NT>(vp + off);
         }
     };
 
-    // `stg` = staging index (row relative to the split's first row) of the tile's first row
-    auto compute_tile = [&](const u32x4 (&kr)[U], const u32x4 (&vr)[U], int base, int lead, int cnt, int stg) {
+    auto compute_t = [&](const u32x4 (&kr)[U], const u32x4 (&vr)[U], int t) {
+        const Tile k = tiles.locate(t);
+        const int stg = k.lo - j0 + k.base;               // staging index (row relative to the split's first row)
         float s[G][U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int r = base + u * RPW + rs;
-            const bool ok = r >= lead && r < cnt;
+            const bool ok = k.base + u * RPW + rs < k.cnt;
 #pragma unroll
             for (int g = 0; g < G; ++g) {
                 const float d = row_sum<LPR>(E::dot(qr[g], kr[u])) * a.scale_log2;
@@ -672,65 +730,10 @@ __global__ __launch_bounds__(NW * 64, BUZZ_MIN_BLOCKS) void attn_split_kernel(co
         }
     };
 
-    if (tid == 0) sm_next = NW;                           // tiles 0 .. NW-1 are the waves' first tiles
-    __syncthreads();
-
-    // eq. 2: the new row comes from the caller, joins the cache, and is attended to like any other row
-    if (x.j1 == a.n && x.j0 < a.n && wave == 0) {
-        const char* kp = (const char*)a.k_new + (size_t)unit * ROWB;
-        const char* vp = (const char*)a.v_new + (size_t)unit * ROWB;
-        if (rs == 0) {
-            *(u32x4*)(Kb + (size_t)a.new_phys * ROWB + lane_off) = *(const u32x4*)(kp + lane_off);
-            *(u32x4*)(Vb + (size_t)a.new_phys * ROWB + lane_off) = *(const u32x4*)(vp + lane_off);
-            if (c == 0) a.pos[ubase + a.new_phys] = a.new_pos;
-        }
-        u32x4 kr[U], vr[U];
-        load_tile(kr, vr, kp, vp, 0, 0, 1);
-        compute_tile(kr, vr, 0, 0, 1, a.n - 1 - j0);
-    }
-
-    const TileMap<WROWS> tiles(a, x);
-    const int total = tiles.total();
-    auto load_t = [&](u32x4 (&kr)[U], u32x4 (&vr)[U], int t) {
-        int lo, phys0, lead, cnt, base;
-        tiles.locate(t, lo, phys0, lead, cnt, base);
-        load_tile(kr, vr, Kb + (size_t)phys0 * ROWB, Vb + (size_t)phys0 * ROWB, base, lead, cnt);
-    };
-    auto compute_t = [&](const u32x4 (&kr)[U], const u32x4 (&vr)[U], int t) {
-        int lo, phys0, lead, cnt, base;
-        tiles.locate(t, lo, phys0, lead, cnt, base);
-        compute_tile(kr, vr, base, lead, cnt, lo - j0 + base - lead);
-    };
-    if constexpr (G == 1) {
-        // two tile buffers: the next tile's loads are issued before the current tile is consumed
-        u32x4 ka[U], va[U], kb[U], vb[U];
-        int t = wave, tn = next_tile(a, &sm_next, t, NW);
-        if (t < total) load_t(ka, va, t);
-        while (t < total) {
-            if (tn < total) load_t(kb, vb, tn);
-            int tnn = next_tile(a, &sm_next, tn, NW);
-            compute_t(ka, va, t);
-            t = tn; tn = tnn;
-            if (t >= total) break;
-            if (tn < total) load_t(ka, va, tn);
-            tnn = next_tile(a, &sm_next, tn, NW);
-            compute_t(kb, vb, t);
-            t = tn; tn = tnn;
-        }
-    } else {
-        int t = wave;
-        while (t < total) {
-            u32x4 kr[U], vr[U];
-            load_t(kr, vr, t);
-            const int tn = next_tile(a, &sm_next, t, NW);
-            compute_t(kr, vr, t);
-            t = tn;
-        }
-    }
+    lds_barrier();
+    stream_tiles<G == 1, Buf>(a, &sm.next_tile, wave, NW, total, [&](Buf& b, int t) { load_t(b.k, b.v, t); }, [&](Buf& b, int t) { compute_t(b.k, b.v, t); });
 
     if (lane == 0) BUZZ_STAMP(8 + (wave & 7));
-    if constexpr (!early_side<G, D>()) request_side_rows<G>(a, x, side);
-    first_pass_scores<G>(a, x, prev, side);
 
     // merge the RPW lane groups of this wave (same columns, different rows)
 #pragma unroll
@@ -752,20 +755,20 @@ __global__ __launch_bounds__(NW * 64, BUZZ_MIN_BLOCKS) void attn_split_kernel(co
         }
     }
 
-    // merge the waves of the block through LDS and emit this split's partial
+    // this wave's result into LDS
     if (rs == 0) {
 #pragma unroll
         for (int g = 0; g < G; ++g) {
 #pragma unroll
-            for (int v = 0; v < VEC; ++v) sm_acc[wave][g][c * VEC + v] = acc[g][v];
+            for (int v = 0; v < VEC; v += 4)
+                *(f32x4*)&sm.acc[wave][g][c * VEC + v] = f32x4{acc[g][v], acc[g][v + 1], acc[g][v + 2], acc[g][v + 3]};
         }
         if (c == 0) {
 #pragma unroll
-            for (int g = 0; g < G; ++g) { sm_m[wave][g] = m[g]; sm_l[wave][g] = l[g]; }
+            for (int g = 0; g < G; ++g) sm.ml[g][wave] = make_float2(m[g], l[g]);
         }
     }
-    (void)j1;
-    finish_split<G, D, NW>(a, x, prev, side.sc, stage, sm_m, sm_l, sm_acc, &sm_ticket);
+    finish_split<G, D, NW, ROWB>(a, x, side, stage, sm);
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -825,28 +828,28 @@ __global__ __launch_bounds__(NW * 64) void attn_split_mfma_kernel(const AttnArgs
     constexpr int QP = NCH / 4;                           // K / Q chunks per lane
     constexpr int VS = (NCH + 15) / 16;                   // sets of 16 column chunks
     constexpr int WROWS = 16;
-    constexpr int TR = BUZZ_MFMA_TR;                      // tiles a wave loads before it computes
     static_assert(G >= 2 && G <= 16 && NCH % 4 == 0, "grouped queries, head_dim multiple of 32");
 
     extern __shared__ float stage[];                      // [G][rows_per_split] logits of this split's rows
-    __shared__ float sm_m[NW][G], sm_l[NW][G];
-    __shared__ float sm_acc[NW][G][D];
-    __shared__ int sm_ticket, sm_next;
+    __shared__ WaveResults<G, D, NW> sm;
 
     const SplitCtx x = make_ctx(a);
     const int unit = x.unit, j0 = x.j0;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // tile numbers and addresses stay in scalar registers
     const int j = lane & 15, q = lane >> 4;
-    const PrevStat<G> prev = load_prev_stat<G>(a, unit);
-    SideRows<G> side;
-    if constexpr (early_side<G, D>()) request_side_rows<G>(a, x, side);
     if (tid == 0) { BUZZ_STAMP(0); BUZZ_STAMP_VALUE(6, __builtin_amdgcn_s_getreg((31 << 11) | 4)); BUZZ_STAMP_VALUE(7, __builtin_amdgcn_s_getreg((31 << 11) | 20)); }
+    if (tid == 0) sm.next_tile = NW;                      // tiles 0 .. NW-1 are the waves' first tiles
+    SideRows<G> side;
+    request_prev_stat<G>(a, unit, side);
+    request_side_rows<G, NW * 64>(a, x, 0, side);
+    request_fresh_row<ROWB, G>(a, x, side);
 
     u32x4 qb[QP];                                         // Q operand: head j, chunks 4p + q
 #pragma unroll
     for (int p = 0; p < QP; ++p) {
         qb[p] = u32x4{0u, 0u, 0u, 0u};
-        if (j < G) qb[p] = *(const u32x4*)((const char*)a.q + (size_t)(x.b * a.Hq + x.kvh * G + j) * ROWB + (4 * p + q) * 16);
+        if (j < G) qb[p] = *(const u32x4*)((const char*)a.q + (size_t)(unit * G + j) * ROWB + (4 * p + q) * 16);
     }
 
     char* Kb = (char*)a.K + x.ubase * ROWB;
@@ -860,19 +863,27 @@ __global__ __launch_bounds__(NW * 64) void attn_split_mfma_kernel(const AttnArgs
         for (int mcol = 0; mcol < 8; ++mcol) O[t][mcol] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
 
-    auto load_tile = [&](u32x4 (&kk)[QP], u32x4 (&vv)[VS][4], const char* kp, const char* vp, int base, int lead, int cnt) {
-        const unsigned krow = (unsigned)(min(max(base + j, lead), cnt - 1) - lead) * ROWB;
+    struct Buf { u32x4 k[QP], v[VS][4]; };
+    const TileMap<WROWS> tiles(a, x);
+    const int total = tiles.total();
+    auto load_t = [&](u32x4 (&kk)[QP], u32x4 (&vv)[VS][4], int t) {
+        const Tile k = tiles.locate(t);
+        const char* kp = k.fresh ? (const char*)a.k_new + (size_t)unit * ROWB : Kb + (size_t)k.phys * ROWB;
+        const char* vp = k.fresh ? (const char*)a.v_new + (size_t)unit * ROWB : Vb + (size_t)k.phys * ROWB;
+        const unsigned krow = (unsigned)min(k.base + j, k.cnt - 1) * ROWB;   // past the run's end: its last row again
 #pragma unroll
         for (int p = 0; p < QP; ++p) kk[p] = load16<NT>(kp + krow + (4 * p + q) * 16);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const unsigned vrow = (unsigned)(min(max(base + 4 * q + e, lead), cnt - 1) - lead) * ROWB;
+            const unsigned vrow = (unsigned)min(k.base + 4 * q + e, k.cnt - 1) * ROWB;
 #pragma unroll
-            for (int t = 0; t < VS; ++t) vv[t][e] = load16<NT>(vp + vrow + ((16 * t + j) % NCH) * 16);
+            for (int t2 = 0; t2 < VS; ++t2) vv[t2][e] = load16<NT>(vp + vrow + ((16 * t2 + j) % NCH) * 16);
         }
     };
 
-    auto compute_tile = [&](const u32x4 (&kk)[QP], const u32x4 (&vv)[VS][4], int base, int lead, int cnt, int stg) {
+    auto compute_t = [&](const u32x4 (&kk)[QP], const u32x4 (&vv)[VS][4], int t) {
+        const Tile k = tiles.locate(t);
+        const int stg = k.lo - j0 + k.base;               // staging index (row relative to the split's first row)
         f32x4 sacc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int p = 0; p < QP; ++p) sacc = Mma<T>::qk(kk[p], qb[p], sacc);
@@ -880,8 +891,7 @@ __global__ __launch_bounds__(NW * 64) void attn_split_mfma_kernel(const AttnArgs
         float tmax = -INFINITY;
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            const int r = base + 4 * q + v;
-            const bool ok = r >= lead && r < cnt;
+            const bool ok = k.base + 4 * q + v < k.cnt;
             const float d = sacc[v] * a.scale_log2;
             s[v] = ok ? d : -INFINITY;
             if (ok && j < G) stage[j * a.rows_per_split + stg + 4 * q + v] = d;
@@ -932,65 +942,28 @@ __global__ __launch_bounds__(NW * 64) void attn_split_mfma_kernel(const AttnArgs
         }
     };
 
-    if (tid == 0) sm_next = NW;                           // tiles 0 .. NW-1 are the waves' first tiles
-    __syncthreads();
-
-    // eq. 2: the new row comes from the caller, joins the cache, and is attended to like any other row
-    if (x.j1 == a.n && x.j0 < a.n && wave == 0) {
-        const char* kp = (const char*)a.k_new + (size_t)unit * ROWB;
-        const char* vp = (const char*)a.v_new + (size_t)unit * ROWB;
-        if (tid < NCH) {
-            *(u32x4*)(Kb + (size_t)a.new_phys * ROWB + tid * 16) = *(const u32x4*)(kp + tid * 16);
-            *(u32x4*)(Vb + (size_t)a.new_phys * ROWB + tid * 16) = *(const u32x4*)(vp + tid * 16);
-            if (tid == 0) a.pos[x.ubase + a.new_phys] = a.new_pos;
-        }
-        u32x4 kk[QP], vv[VS][4];
-        load_tile(kk, vv, kp, vp, 0, 0, 1);
-        compute_tile(kk, vv, 0, 0, 1, a.n - 1 - j0);
-    }
-
-    // groups of TR tiles: all loads of a group are in flight before its first tile is used
-    const TileMap<WROWS * TR> tiles(a, x);
-    const int total = tiles.total();
-    int t = wave;
-    while (t < total) {
-        int lo, phys0, lead, cnt, base;
-        tiles.locate(t, lo, phys0, lead, cnt, base);
-        const char* kp = Kb + (size_t)phys0 * ROWB;
-        const char* vp = Vb + (size_t)phys0 * ROWB;
-        u32x4 kk[TR][QP], vv[TR][VS][4];
-#pragma unroll
-        for (int u = 0; u < TR; ++u)
-            if (u == 0 || base + u * WROWS < cnt) load_tile(kk[u], vv[u], kp, vp, base + u * WROWS, lead, cnt);
-        const int tn = next_tile(a, &sm_next, t, NW);
-#pragma unroll
-        for (int u = 0; u < TR; ++u)
-            if (u == 0 || base + u * WROWS < cnt)
-                compute_tile(kk[u], vv[u], base + u * WROWS, lead, cnt, lo - j0 + base + u * WROWS - lead);
-        t = tn;
-    }
+    lds_barrier();
+    stream_tiles<false, Buf>(a, &sm.next_tile, wave, NW, total, [&](Buf& b, int t) { load_t(b.k, b.v, t); }, [&](Buf& b, int t) { compute_t(b.k, b.v, t); });
 
     if (lane == 0) BUZZ_STAMP(8 + (wave & 7));
-    if constexpr (!early_side<G, D>()) request_side_rows<G>(a, x, side);
-    first_pass_scores<G>(a, x, prev, side);
-    // this wave's result into LDS in the layout finish_split expects
+    // this wave's result into LDS
     float l_tot = l_run + __shfl_xor(l_run, 16);
     l_tot += __shfl_xor(l_tot, 32);
-    if (q == 0 && j < G) { sm_m[wave][j] = m_run; sm_l[wave][j] = l_tot; }
+    if (q == 0 && j < G) sm.ml[j][wave] = make_float2(m_run, l_tot);
 #pragma unroll
-    for (int t = 0; t < VS; ++t) {
-        if (16 * t + j < NCH) {
+    for (int t2 = 0; t2 < VS; ++t2) {
+        if (16 * t2 + j < NCH) {
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                const int head = 4 * q + v;
-                if (head < G) {
-#pragma unroll
-                    for (int mcol = 0; mcol < 8; ++mcol) sm_acc[wave][head][8 * (16 * t + j) + mcol] = O[t][mcol][v];
+                if (4 * q + v < G) {
+                    float* dst = &sm.acc[wave][4 * q + v][8 * (16 * t2 + j)];
+                    *(f32x4*)dst = f32x4{O[t2][0][v], O[t2][1][v], O[t2][2][v], O[t2][3][v]};
+                    *(f32x4*)(dst + 4) = f32x4{O[t2][4][v], O[t2][5][v], O[t2][6][v], O[t2][7][v]};
                 }
             }
         }
     }
-    finish_split<G, D, NW>(a, x, prev, side.sc, stage, sm_m, sm_l, sm_acc, &sm_ticket);
+    finish_split<G, D, NW, ROWB>(a, x, side, stage, sm);
 }
 
 constexpr int kScoreRowsPerBlock = 2048;
@@ -1027,7 +1000,7 @@ template <int G, bool NT> constexpr int unroll_for()
 template <typename T, int D, int G>
 hipError_t launch_split_t(const AttnArgs& a, int units, hipStream_t st, Timing tm)
 {
-    dim3 grid(a.n_splits, units), block(a.waves * 64);
+    const dim3 grid = a.xcd_local ? dim3(8, a.n_splits, units / 8) : dim3(a.n_splits, units), block(a.waves * 64);
     const size_t lds = (size_t)G * a.rows_per_split * sizeof(float);   // logit staging
     if constexpr (G >= 2 && !std::is_same<T, float>::value) {   // grouped queries on a 16-bit cache: matrix cores
         if (a.waves == 8) {

@@ -37,12 +37,12 @@ int static_scratch_ptr(char** out)
     return BUZZ_OK;
 }
 
-// Which die (XCD) a block runs on, for every block of a small 2-D grid: the evidence for placing a unit's
+// Which die (XCD) a block runs on, for every block of a small grid: the evidence for placing a unit's
 // splits on one die by block number (see die_local_ok).
 __global__ void die_probe_kernel(int32_t* out)
 {
     if (threadIdx.x == 0)
-        out[blockIdx.y * gridDim.x + blockIdx.x] = (int32_t)(__builtin_amdgcn_s_getreg((31 << 11) | 20) & 7u);   // XCC_ID
+        out[(blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x] = (int32_t)(__builtin_amdgcn_s_getreg((31 << 11) | 20) & 7u);   // XCC_ID
 }
 
 int g_die_local[kMaxDevices];          // per GPU: 0 not probed yet, 1 blocks b and b + 8 share a die, 2 they do not
@@ -63,7 +63,7 @@ int probe_die_placement(hipStream_t st)
     int32_t* buf = (int32_t*)(sp + kStaticTicketBytes);                  // the partials area of the static scratch
     constexpr int kA = 8 * 64, kB = 3 * 40;
     int32_t host[kA + kB];
-    hipLaunchKernelGGL(die_probe_kernel, dim3(8, 64), dim3(64), 0, st, buf);
+    hipLaunchKernelGGL(die_probe_kernel, dim3(8, 16, 4), dim3(64), 0, st, buf);   // the decode kernel's shape
     hipLaunchKernelGGL(die_probe_kernel, dim3(3, 40), dim3(64), 0, st, buf + kA);
     if (hipGetLastError() != hipSuccess) return BUZZ_EHIP;
     if (hipMemcpyAsync(host, buf, sizeof(host), hipMemcpyDeviceToHost, st) != hipSuccess) return BUZZ_EHIP;

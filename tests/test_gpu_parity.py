@@ -108,6 +108,17 @@ def test_split_counts(splits):
     run(wl, splits=splits, check_auto=False)
 
 
+@pytest.mark.parametrize("G,D,dtype,splits,prompt", [
+    (1, 64, "bf16", 17, 900), (3, 64, "fp32", 9, 900), (8, 256, "bf16", 9, 700), (5, 128, "fp16", 33, 900),
+    (4, 128, "bf16", 100, 1900), (1, 64, "fp16", 1, 5000), (2, 64, "bf16", 1, 3100)])
+def test_split_merge_rounds_and_side_rounds(G, D, dtype, splits, prompt):
+    """Merges of more splits than one round of loads covers (8 or 16), groups of 64 outputs that do not divide over
+    the merging waves, and single splits with more rows than a thread requests ahead."""
+    wl = small(batch=1, n_kv_heads=2, n_q_heads=2 * G, head_dim=D, dtype=dtype, prompt=prompt, decode_steps=9,
+               sink=3, window=prompt - 77, segment=16, keep=3, evict_every=16, n_obs=8)
+    run(wl, splits=splits)
+
+
 @pytest.mark.parametrize("device_merge", [False, True])
 @pytest.mark.parametrize("G,dtype,heads", [(1, "fp16", 8), (4, "bf16", 8), (2, "fp32", 16), (8, "bf16", 8)])
 def test_split_merge_through_one_die_or_device_memory(G, dtype, heads, device_merge):
