@@ -14,9 +14,49 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kSelWaves = 4;
 
+// Ranks the len scores that a wave has put into its LDS slice (padded with -inf to `slice` entries, a multiple of four,
+// 16-byte aligned) and calls emit(rank among the survivors, offset) for its `take` best: score descending, ties to the
+// lowest offset, survivors numbered in offset order.  A row survives if fewer than `take` rows are larger: one
+// comparison and one addition per pair of rows, four rows per LDS read.  That keeps too many rows only where equal
+// scores straddle the boundary, which the count of kept rows shows; then (and only then) the comparison with the
+// offsets as tie-breakers runs.  Bound by these comparisons: with the tie-breaker in every pair, 448 segments of 64
+// in each of 32 units took 12.7 us, now 9 us (prefill and export of that prompt: 97.7 -> 93.9 us).
+template <typename Emit>
+__device__ inline void rank_segment(const float* sc, int len, int slice, int take, int lane, Emit emit)
+{
+    for (int exact = 0; exact < 2; ++exact) {
+        int running = 0;
+        for (int e0 = 0; e0 < len; e0 += 64) {
+            const int e = e0 + lane;
+            const float v = e < len ? sc[e] : 0.f;
+            int before = 0;                        // rows of the segment that rank before row e
+            if (!exact) {
+                for (int i = 0; i < slice; i += 4) {
+                    const float4 x = *(const float4*)(sc + i);
+                    before += x.x > v; before += x.y > v; before += x.z > v; before += x.w > v;
+                }
+            } else {
+                for (int i = 0; i < len; ++i) {
+                    const float vi = sc[i];
+                    before += (vi > v) || (vi == v && i < e);
+                }
+            }
+            const bool kp = e < len && before < take;
+            const unsigned long long mask = __ballot(kp);
+            const int r = running + __popcll(mask & ((1ull << lane) - 1ull));
+            if (kp && r < take) emit(r, e);
+            running += __popcll(mask);
+        }
+        if (running == take) break;                // no ties across the boundary (the exact pass always ends here)
+    }
+}
+
+// The slice of a segment in LDS, in floats: a multiple of four.
+__host__ __device__ inline int segment_slice(int segment) { return (segment + 3) & ~3; }
+
 __global__ __launch_bounds__(256) void segment_topk_kernel(const SelectArgs a)
 {
-    extern __shared__ float lds[];                 // [kSelWaves][segment]
+    extern __shared__ __attribute__((aligned(16))) float lds[];   // [kSelWaves][segment_slice]
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int seg = blockIdx.x * kSelWaves + wave, unit = blockIdx.y;
     const int n_seg = (a.new_count + a.segment - 1) / a.segment;
@@ -24,36 +64,25 @@ __global__ __launch_bounds__(256) void segment_topk_kernel(const SelectArgs a)
     const int start = seg * a.segment;
     const int len = active ? min(a.segment, a.new_count - start) : 0;
     const int take = min(a.keep, len);
-    float* sc = lds + wave * a.segment;
+    const int slice = segment_slice(a.segment);
+    float* sc = lds + wave * slice;
     const float* base = a.score + (size_t)unit * a.unit_stride;
-    for (int e = lane; e < len; e += 64) {
+    int* out = a.sel + (size_t)unit * a.sel_stride + seg * a.keep;
+    if (a.ignore_scores) {                         // all equal: the lowest indices win
+        for (int e = lane; e < take; e += 64) out[e] = a.lo + start + e;
+        return;
+    }
+    if (!active) return;                           // no block-wide barrier below: a wave only reads what it wrote
+    for (int e = lane; e < slice; e += 64) {
         const int row = a.lo + start + e;
-        float v = a.ignore_scores ? 0.f : base[a.map.ring_cap ? a.map.phys(row) : row];   // all equal: lowest indices win
+        float v = e < len ? base[a.map.ring_cap ? a.map.phys(row) : row] : -INFINITY;
         if (v != v) v = -INFINITY;                 // NaN ranks below everything
         sc[e] = v;
     }
-    __syncthreads();
-    if (!active) return;
-    int running = 0;
-    for (int e0 = 0; e0 < len; e0 += 64) {
-        const int e = e0 + lane;
-        bool kp = false;
-        if (e < len) {
-            const float v = sc[e];
-            int before = 0;                        // rows of the segment that rank strictly before row e
-            for (int i = 0; i < len; ++i) {
-                const float vi = sc[i];
-                before += (vi > v) || (vi == v && i < e);
-            }
-            kp = before < take;
-        }
-        const unsigned long long mask = __ballot(kp);
-        if (kp) {
-            const int r = running + __popcll(mask & ((1ull << lane) - 1ull));
-            a.sel[(size_t)unit * a.sel_stride + seg * a.keep + r] = a.lo + start + e;
-        }
-        running += __popcll(mask);
-    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    rank_segment(sc, len, slice, take, lane, [&](int r, int e) { out[r] = a.lo + start + e; });
 }
 
 // Segments too long for one wave's slice of the LDS (and the single segment of the H2O-style variant, which
@@ -154,7 +183,7 @@ __global__ __launch_bounds__(kTopkBlock) void segment_topk_block_kernel(const Se
 // adds exactly 0 for it.
 __global__ __launch_bounds__(256) void evict_new_rows_kernel(const EvictArgs a)
 {
-    extern __shared__ float lds[];                 // [kSelWaves][segment] scores, then [kSelWaves][keep] kept offsets
+    extern __shared__ __attribute__((aligned(16))) float lds[];   // [kSelWaves][segment_slice] scores, [kSelWaves][keep] kept offsets
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int seg = blockIdx.x * kSelWaves + wave, unit = blockIdx.y;
     const int n_seg = (a.new_count + a.segment - 1) / a.segment;
@@ -162,8 +191,9 @@ __global__ __launch_bounds__(256) void evict_new_rows_kernel(const EvictArgs a)
     const int start = seg * a.segment;
     const int len = min(a.segment, a.new_count - start);
     const int take = min(a.keep, len);
-    float* sc = lds + wave * a.segment;
-    int* kept = (int*)(lds + kSelWaves * a.segment) + wave * a.keep;
+    const int slice = segment_slice(a.segment);
+    float* sc = lds + wave * slice;
+    int* kept = (int*)(lds + kSelWaves * slice) + wave * a.keep;
     const size_t ubase = (size_t)unit * a.cap;
     const float* logit_u = a.logit_prev ? a.logit_prev + ubase * a.G : nullptr;
     auto current_score = [&](int ph) {             // the row's score with the pending update applied
@@ -174,31 +204,15 @@ __global__ __launch_bounds__(256) void evict_new_rows_kernel(const EvictArgs a)
                                     a.stat_prev[((size_t)unit * a.G + g) * 2 + 1]);
         return v;
     };
-    for (int e = lane; e < len; e += 64) {
-        float v = a.ignore_scores ? 0.f : current_score(a.map.phys(a.lo + start + e));   // all equal: lowest indices win
+    for (int e = lane; e < slice; e += 64) {
+        float v = e >= len ? -INFINITY : a.ignore_scores ? 0.f : current_score(a.map.phys(a.lo + start + e));   // all equal: lowest indices win
         if (v != v) v = -INFINITY;                 // NaN ranks below everything
         sc[e] = v;
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    int running = 0;
-    for (int e0 = 0; e0 < len; e0 += 64) {
-        const int e = e0 + lane;
-        bool kp = false;
-        if (e < len) {
-            const float v = sc[e];
-            int before = 0;                        // rows of the segment that rank strictly before row e
-            for (int i = 0; i < len; ++i) {
-                const float vi = sc[i];
-                before += (vi > v) || (vi == v && i < e);
-            }
-            kp = before < take;
-        }
-        const unsigned long long mask = __ballot(kp);
-        if (kp) kept[running + __popcll(mask & ((1ull << lane) - 1ull))] = e;
-        running += __popcll(mask);
-    }
+    rank_segment(sc, len, slice, take, lane, [&](int r, int e) { kept[r] = e; });
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -296,7 +310,7 @@ hipError_t launch_evict_new_rows(const EvictArgs& a, int units, hipStream_t st, 
     if (n_seg <= 0 || a.keep <= 0) return hipSuccess;
     if (a.row_bytes > 1024 || (a.row_bytes & 15) || 64 % (a.row_bytes >> 4)) return hipErrorInvalidValue;
     const dim3 grid((n_seg + kSelWaves - 1) / kSelWaves, units);
-    const size_t lds = (size_t)kSelWaves * (a.segment + a.keep) * sizeof(float);
+    const size_t lds = (size_t)kSelWaves * (segment_slice(a.segment) + a.keep) * sizeof(float);
     BUZZ_LAUNCH(evict_new_rows_kernel, grid, dim3(256), lds, st, tm, a);
     return hipGetLastError();
 }
@@ -311,7 +325,7 @@ hipError_t launch_segment_topk(const SelectArgs& a, int units, hipStream_t st, T
         return hipGetLastError();
     }
     dim3 grid((n_seg + kSelWaves - 1) / kSelWaves, units), block(256);
-    const size_t lds = (size_t)kSelWaves * a.segment * sizeof(float);
+    const size_t lds = (size_t)kSelWaves * segment_slice(a.segment) * sizeof(float);
     BUZZ_LAUNCH(segment_topk_kernel, grid, block, lds, st, tm, a);
     return hipGetLastError();
 }

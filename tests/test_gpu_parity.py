@@ -422,6 +422,18 @@ def test_nan_and_infinite_scores_rank_as_stated(keep, old_stride):
     assert st["evictions"] == 3
 
 
+@pytest.mark.parametrize("segment,keep,old_stride", [(1, 1, 1), (5, 2, 1), (63, 7, 1), (64, 64, 1), (65, 9, 0), (131, 70, 1),
+                                                      (4093, 3, 1), (4093, 4, 1)])
+def test_equal_scores_across_the_survivors_boundary(segment, keep, old_stride):
+    """Starting scores of three values only: nearly every segment has equal scores on both sides of its boundary, which
+    the lowest indices win; segments of one row to the longest, lengths that are no multiple of four, the LDS limit."""
+    def plant(ps):
+        ps.copy_(torch.floor(torch.rand(ps.shape, generator=torch.Generator().manual_seed(segment)) * 3.0).to(ps))
+    wl = small(batch=1, n_kv_heads=2, n_q_heads=2, head_dim=64, dtype="fp16", prompt=3 * segment + 200, decode_steps=6,
+               sink=3, window=40, segment=segment, keep=keep, evict_every=4, old_stride=old_stride, n_obs=0)
+    run(wl, plant=plant)
+
+
 @pytest.mark.parametrize("segment,keep", [(5000, 7), (9000, 300)])
 def test_segments_longer_than_one_wave_can_rank(segment, keep):
     """Segments beyond 4096 rows take the block-wide selection (radix select + prefix sum): two full segments and a
