@@ -746,7 +746,7 @@ int decode_step_impl(buzz_cache_t* c, const void* q, const void* k_new, const vo
             a.part_ml = (float*)(sp + kStaticTicketBytes);
             a.part_o = (float*)(sp + kStaticTicketBytes + ml_bytes);
             a.s_cap = a.n_splits;
-            if (hipError_t e = launch_fill_f32((float*)sp, nullptr, L.units, st)) return hip_rc(e);
+            if (hipError_t e = launch_clear_f32((float*)sp, L.units, st)) return hip_rc(e);
         }
         // about 8 waves per compute unit; 4-wave blocks also where 8 waves' partial outputs would not fit the LDS
         a.waves = ((int64_t)L.units * a.n_splits <= cus && L.G * cfg.head_dim < kWideBlockMaxGD) ? 8 : 4;

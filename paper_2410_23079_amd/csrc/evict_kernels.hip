@@ -280,10 +280,10 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(const GatherArgs a, co
     }
 }
 
-__global__ __launch_bounds__(256) void fill_f32_kernel(float* dst, const float* src, int64_t n)
+__global__ __launch_bounds__(256) void clear_f32_kernel(float* dst, int64_t n)
 {
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) dst[i] = src ? src[i] : 0.f;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) dst[i] = 0.f;
 }
 
 __global__ __launch_bounds__(256) void plain_copy_kernel(uint4* dst, const uint4* src, size_t n16)
@@ -342,12 +342,12 @@ hipError_t launch_gather_rows(const GatherArgs& a, int units, hipStream_t st, Ti
     return hipGetLastError();
 }
 
-hipError_t launch_fill_f32(float* dst, const float* src, int64_t n, hipStream_t st)
+hipError_t launch_clear_f32(float* dst, int64_t n, hipStream_t st)
 {
     if (n <= 0) return hipSuccess;
     int64_t blocks = (n + 255) / 256;
     if (blocks > 65536) blocks = 65536;
-    hipLaunchKernelGGL(fill_f32_kernel, dim3((unsigned)blocks), dim3(256), 0, st, dst, src, n);
+    hipLaunchKernelGGL(clear_f32_kernel, dim3((unsigned)blocks), dim3(256), 0, st, dst, n);
     return hipGetLastError();
 }
 
