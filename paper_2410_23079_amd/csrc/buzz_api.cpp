@@ -174,21 +174,19 @@ int make_layout(const buzz_config_t* c, Layout* L)
     L->V = take(rows * L->row_bytes);
     L->score = take(rows * 4);
     L->pos = take(rows * 4);
+    L->ticket = take((size_t)units * 4);
+    const size_t shared = off;                                  // scratch of the decode steps ...
     L->logit[0] = take(rows * G * 4);
     L->logit[1] = take(rows * G * 4);
     L->stat[0] = take((size_t)units * G * 2 * 4);
     L->stat[1] = take((size_t)units * G * 2 * 4);
-    L->ticket = take((size_t)units * 4);
     L->part_ml = take((size_t)units * s_cap * G * 2 * 4);
     L->part_o = take((size_t)units * s_cap * G * c->head_dim * 4);
-    L->sel = take((size_t)units * L->sel_stride * 4);
-    const size_t strows = (size_t)units * L->st_rows;
-    L->stK = take(strows * L->row_bytes);
-    L->stV = take(strows * L->row_bytes);
-    L->stScore = take(strows * 4);
-    L->stPos = take(strows * 4);
-    L->pscore = take((size_t)units * c->max_context * 4);
-    {   // prefill scoring: the queries' statistics and the column sums of steps that are cut into parts
+    const size_t decode_end = off;
+    off = shared;                                               // ... shares its place with that of the prompt scoring: a
+    {                                                           // prefill leaves no score update pending, and a step
+                                                                // writes its partial results before they are read
+        // the queries' statistics and the column sums of scoring steps that are cut into parts
         size_t mma = (size_t)c->batch * c->n_q_heads * (c->max_context < kObsPassRows ? c->max_context : kObsPassRows);
         const size_t sums = (size_t)units * c->max_context * kObsItemParts;
         const size_t cut = mma * kObsKeyParts < kObsPartElems ? mma * kObsKeyParts : kObsPartElems;
@@ -197,6 +195,14 @@ int make_layout(const buzz_config_t* c, Layout* L)
         L->obs_partial_cap = sums < kObsPartElems ? sums : kObsPartElems;
         L->obs_partial = take(L->obs_partial_cap * 4);
     }
+    if (off < decode_end) off = decode_end;
+    L->sel = take((size_t)units * L->sel_stride * 4);
+    const size_t strows = (size_t)units * L->st_rows;
+    L->stK = take(strows * L->row_bytes);
+    L->stV = take(strows * L->row_bytes);
+    L->stScore = take(strows * 4);
+    L->stPos = take(strows * 4);
+    L->pscore = take((size_t)units * c->max_context * 4);
     L->total = off;
     return BUZZ_OK;
 }
