@@ -348,9 +348,10 @@ __global__ __launch_bounds__(256) void obs_mfma_kernel(const ObsArgs a)
                 const int key = j_base + 16 * ct + j;
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
-                    float e = __builtin_amdgcn_exp2f(fmaf(acc[v], sc[v], -st[v].x));
-                    if (MASKED && key > posq[v]) e = 0.f;
-                    col[ct] = fmaf(e, st[v].y, col[ct]);
+                    // an invisible key takes nothing, not 0 times the query's 1 / sum, which may not be a number
+                    const float e = __builtin_amdgcn_exp2f(fmaf(acc[v], sc[v], -st[v].x));
+                    const float with = fmaf(e, st[v].y, col[ct]);
+                    col[ct] = MASKED && key > posq[v] ? col[ct] : with;
                 }
             }
         };

@@ -252,6 +252,30 @@ def test_prompt_scoring_cut_into_parts(dtype, D, G, prompt, n_obs):
     run(wl)
 
 
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("D,G,prompt,n_obs", [(64, 1, 200, 200), (128, 2, 700, 333), (256, 1, 90, 41)])
+def test_a_query_that_is_not_a_number_stays_with_the_keys_it_sees(dtype, D, G, prompt, n_obs):
+    """One observed query holds a NaN, another an infinity: the scores of every key they see are NaN, those of the keys
+    behind them (in the same tiles, too) are what the other queries leave there."""
+    from oracle.buzz_oracle import OracleCache
+    ls = lockstep()
+    wl = small(batch=1, n_kv_heads=2, n_q_heads=2 * G, head_dim=D, dtype=dtype, prompt=prompt, decode_steps=1, sink=4,
+               window=prompt // 4, segment=16, keep=2, evict_every=8, n_obs=n_obs)
+    p = prompt_inputs(wl, device="cuda")
+    p["q_obs"][0, 0, n_obs // 2, 3] = float("nan")
+    p["q_obs"][0, G, n_obs // 3, D - 1] = float("inf")
+    print(f"[odd queries] {dtype} D{D} G{G} N{prompt} n_obs{n_obs}", flush=True)
+    got = ls.gpu_prompt_scores(wl, p, n_obs).double().cpu().numpy()
+    units = [(0, 0), (0, 1)]
+    o = OracleCache(ls.oracle_config(wl, 2, sink=0, window=prompt + 1, old_stride=1))
+    o.prefill(ls.unit_slices(p["K"], units, 1), ls.unit_slices(p["V"], units, 1), q_obs=ls.unit_slices(p["q_obs"], units, G))
+    want = o.export()[2][:, 0]
+    last = [prompt - n_obs + n_obs // 2, prompt - n_obs + n_obs // 3]         # positions of the two queries
+    for h in range(2):
+        assert np.isnan(want[h, :last[h] + 1]).all() and np.isfinite(want[h, last[h] + 1:]).all()
+    assert ls.score_err(got[0], want) <= ls.SCORE_TOL
+
+
 @pytest.mark.parametrize("G", [1, 2])
 def test_prefill_scores_when_logits_jump(G):
     """Key rows of growing norm late in the prompt: the scaled logits of one query jump by ~20, then by far more
