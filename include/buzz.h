@@ -23,7 +23,9 @@
  *     One exception: the first buzz_prefill of a process on a GPU waits once
  *     for a short probe launch on `hip_stream` (see buzz_prefill).
  *   - Returns BUZZ_OK (0) or a negative buzz_status.  Arguments are validated
- *     before anything is enqueued: a failed call leaves the cache unchanged.
+ *     before anything is enqueued: a failed call leaves the cache unchanged
+ *     (BUZZ_EHIP out of a prefill with observed queries excepted: the cache then
+ *     holds nothing, and waits for the next prefill or import).
  *     Every call also checks, before it enqueues anything, that the rows it is
  *     about to touch lie inside the regions of the workspace layout, and
  *     returns BUZZ_ECAPACITY otherwise: no kernel is handed a row the

@@ -598,6 +598,7 @@ int buzz_prefill(buzz_cache_t* c, const void* kp, const void* vp, int64_t N, con
         // prompt scores, one row of N per unit: what the scoring leaves, or the caller's (NULL: all zero)
         const float* ps = n_obs > 0 ? c->at<float>(L.pscore) : init_score;
         if (n_obs > 0) {
+            c->ready = c->pending = false;                      // from here on the scoring overwrites the logits of the last step
             const int max_q = kObsPassRows;                     // queries of one head per pass
             for (int64_t t0 = 0; t0 < n_obs; t0 += max_q) {
                 ObsArgs oa{};

@@ -1,0 +1,82 @@
+"""What the host side enqueues, looked at on the CPU: the library's own objects linked against a recorder that takes
+kernel launches in place of the HIP runtime (tests/launch_recorder.cpp).  Device pointers are made up; nothing runs."""
+import ctypes
+import os
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2410_23079_amd import FLAG_AUTO_EVICT, BuzzConfig
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+HERE = os.path.join(ROOT, "tests")
+WS, KP, VP, QP, SP, PP, OUT = (0x100000 * i for i in (1, 2, 3, 4, 5, 6, 7))     # made-up device addresses
+
+pytestmark = pytest.mark.skipif(shutil.which("hipcc") is None, reason="hipcc not on PATH")
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    from paper_2410_23079_amd.build import CSRC, SOURCES, build
+    objs = [os.path.join(CSRC, stem + ".o") for _, stem, _ in SOURCES]
+    if not all(os.path.exists(o) for o in objs):             # objects are left by the in-tree build
+        build()
+    tmp = tmp_path_factory.mktemp("recorder")
+    rec, so = str(tmp / "launch_recorder.o"), str(tmp / "libbuzz_recorded.so")
+    subprocess.run(["hipcc", "-x", "hip", "--cuda-host-only", "-std=c++17", "-O1", "-fPIC", "-I", os.path.join(ROOT, "include"),
+                    "-I", CSRC, "-c", os.path.join(HERE, "launch_recorder.cpp"), "-o", rec], check=True, capture_output=True)
+    subprocess.run(["g++", "-shared", "-Wl,-Bsymbolic", "-Wl,--no-undefined", "-o", so, rec, *objs], check=True, capture_output=True)
+    lib = ctypes.CDLL(so)
+    P, I64 = ctypes.c_void_p, ctypes.c_int64
+    lib.buzz_prefill.argtypes = [P, P, P, I64, P, I64, P, P]
+    lib.buzz_decode_step.argtypes = [P] * 6
+    lib.buzz_cache_export.argtypes = [P] * 6
+    lib.buzz_cache_import.argtypes = [P, P, P, P, P, I64, I64, I64, P]
+    lib.buzz_evict.argtypes = [P, P]
+    lib.buzz_cache_destroy.argtypes = [P]
+    lib.rec_kernel.restype = ctypes.c_char_p
+    lib.rec_value.restype = ctypes.c_longlong
+    lib.rec_value.argtypes = [ctypes.c_int, ctypes.c_char_p]
+    return lib
+
+
+def config(**kw):
+    base = dict(batch=2, n_q_heads=8, n_kv_heads=2, head_dim=128, kv_dtype="bf16", sink=4, window=64, segment=16,
+                keep=2, evict_every=16, max_context=4096, old_stride=1, flags=FLAG_AUTO_EVICT)
+    base.update(kw)
+    return BuzzConfig(**base)
+
+
+def create(lib, cfg):
+    h, raw = ctypes.c_void_p(), cfg.to_c()
+    assert lib.buzz_cache_create(ctypes.byref(raw), ctypes.c_void_p(WS), ctypes.c_size_t(1 << 60), ctypes.byref(h)) == 0
+    return h
+
+
+def recorded(lib):
+    return [(lib.rec_kernel(i).decode(), i) for i in range(lib.rec_count())]
+
+
+@pytest.mark.parametrize("dtype,n_obs", [("bf16", 300), ("fp32", 40)])
+def test_a_prefill_that_fails_while_it_scores_leaves_no_cache_behind(lib, dtype, n_obs):
+    """The scratch of the prompt scoring overlays the logits that a pending score update needs: whatever launch of a
+    prefill with observed queries fails, no later call may read the old rows' update from it."""
+    h = create(lib, config(kv_dtype=dtype))
+    lib.rec_reset(-1)
+    assert lib.buzz_prefill(h, KP, VP, 600, QP, n_obs, None, None) == 0
+    lib.rec_reset(-1)
+    assert lib.buzz_prefill(h, KP, VP, 600, QP, n_obs, None, None) == 0
+    count = lib.rec_count()
+    assert count >= 4                                        # two scoring steps, selection, placement
+    for fail in range(count):
+        for _ in range(3):                                   # leaves a score update pending
+            assert lib.buzz_decode_step(h, QP, KP, VP, OUT, None) == 0
+        lib.rec_reset(fail)
+        assert lib.buzz_prefill(h, KP, VP, 600, QP, n_obs, None, None) == -4
+        lib.rec_reset(-1)
+        assert lib.buzz_decode_step(h, QP, KP, VP, OUT, None) == -3
+        assert lib.buzz_evict(h, None) == -3 and lib.buzz_cache_export(h, KP, VP, SP, PP, None) == -3
+        assert lib.rec_count() == 0
+        assert lib.buzz_prefill(h, KP, VP, 600, QP, n_obs, None, None) == 0
+    assert lib.buzz_cache_destroy(h) == 0
