@@ -15,6 +15,7 @@
 //    the rows it ranks and leaves the rest pending.
 //  - The block that finishes last for a unit (atomic ticket, nobody waits) merges the split partials
 //    into the attention output and publishes (M, 1/L) for the next step's score update.
+#include <stddef.h>
 #include <type_traits>
 
 #include "buzz_internal.h"
@@ -408,10 +409,10 @@ __device__ inline void store_side_rows(const AttnArgs& a, const SplitCtx& x, int
     }
 }
 
-// The running results of a block's waves in LDS.
+// The running results of a block's waves in LDS; acc is written 16 bytes at a time.
 template <int G, int D, int NW> struct WaveResults {
+    alignas(16) float acc[NW][G][D];                      // unnormalised output
     float2 ml[G][NW];                                     // (max, sum)
-    float acc[NW][G][D];                                  // unnormalised output
     int ticket, next_tile;
 };
 
@@ -638,6 +639,7 @@ __global__ __launch_bounds__(NW * 64, BUZZ_MIN_BLOCKS) void attn_split_kernel(co
 
     extern __shared__ float stage[];                      // [G][rows_per_split] logits of this split's rows
     __shared__ WaveResults<G, D, NW> sm;
+    static_assert(alignof(decltype(sm)) >= 16 && offsetof(decltype(sm), acc) % 16 == 0 && D % 4 == 0, "16-byte stores into acc");
 
     const SplitCtx x = make_ctx(a);
     const int unit = x.unit, j0 = x.j0;
@@ -838,6 +840,7 @@ __global__ __launch_bounds__(NW * 64) void attn_split_mfma_kernel(const AttnArgs
 
     extern __shared__ float stage[];                      // [G][rows_per_split] logits of this split's rows
     __shared__ WaveResults<G, D, NW> sm;
+    static_assert(alignof(decltype(sm)) >= 16 && offsetof(decltype(sm), acc) % 16 == 0 && D % 4 == 0, "16-byte stores into acc");
 
     const SplitCtx x = make_ctx(a);
     const int unit = x.unit, j0 = x.j0;
