@@ -14,49 +14,95 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kSelWaves = 4;
 
-// Ranks the len scores that a wave has put into its LDS slice (padded with -inf to `slice` entries, a multiple of four,
-// 16-byte aligned) and calls emit(rank among the survivors, offset) for its `take` best: score descending, ties to the
-// lowest offset, survivors numbered in offset order.  A row survives if fewer than `take` rows are larger: one
-// comparison and one addition per pair of rows, four rows per LDS read.  That keeps too many rows only where equal
-// scores straddle the boundary, which the count of kept rows shows; then (and only then) the comparison with the
-// offsets as tie-breakers runs.  Bound by these comparisons: with the tie-breaker in every pair, 448 segments of 64
-// in each of 32 units took 12.7 us, now 9 us (prefill and export of that prompt: 97.7 -> 93.9 us).
+// The ranking reads four scores at a time: `n` floats of LDS rounded up to that.
+__host__ __device__ inline int padded_length(int n) { return (n + 3) & ~3; }
+
+// Ranks the len scores that a wave has put into its LDS slice (16-byte aligned, padded with -inf to a
+// multiple of four) and calls emit(rank among the survivors, offset) for its `take` >= 1 best: score descending, ties to
+// the lowest offset, survivors numbered in offset order.  (A rank may be given out twice; the last one counts.)  A row
+// survives if fewer than `take` rows are larger: one comparison and one addition per pair of rows, which is what bounds
+// the kernel.  That count keeps too many rows only where equal scores straddle the boundary.  The last survivor's score
+// is then the one that the most rows are larger than among the kept, its equals share the places that the larger rows
+// leave, and a pass that only compares with that score numbers them: a tie costs one step per 64 rows.
+// 448 segments of 64 in each of 32 units: 12.7 us with the tie-breaker in every comparison, 9 us now.  Prefill of 16
+// segments of 1000 in each of 32 units: 253 us with distinct scores, 716 with equal ones when ties took a second pass of
+// comparisons, 165 with either now.
 template <typename Emit>
-__device__ inline void rank_segment(const float* sc, int len, int slice, int take, int lane, Emit emit)
+__device__ inline void rank_segment(const float* sc, int len, int padded, int take, int lane, Emit emit)
 {
-    for (int exact = 0; exact < 2; ++exact) {
-        int running = 0;
-        for (int e0 = 0; e0 < len; e0 += 64) {
-            const int e = e0 + lane;
-            const float v = e < len ? sc[e] : 0.f;
-            int before = 0;                        // rows of the segment that rank before row e
-            if (!exact) {
-                for (int i = 0; i < slice; i += 4) {
-                    const float4 x = *(const float4*)(sc + i);
-                    before += x.x > v; before += x.y > v; before += x.z > v; before += x.w > v;
-                }
-            } else {
-                for (int i = 0; i < len; ++i) {
-                    const float vi = sc[i];
-                    before += (vi > v) || (vi == v && i < e);
-                }
-            }
-            const bool kp = e < len && before < take;
-            const unsigned long long mask = __ballot(kp);
-            const int r = running + __popcll(mask & ((1ull << lane) - 1ull));
-            if (kp && r < take) emit(r, e);
-            running += __popcll(mask);
+    const unsigned long long below = (1ull << lane) - 1ull;
+    const int rows = __builtin_amdgcn_readfirstlane(len);
+    auto larger_than = [&](float v) {              // rows of the segment
+        int n = 0;
+        auto count = [&](const float4& x) { n += x.x > v; n += x.y > v; n += x.z > v; n += x.w > v; };
+        int i = 0;
+#pragma unroll 1
+        for (; i + 16 <= padded; i += 16) {        // four reads in flight: a wave is often alone on its SIMD
+            float4 x[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) x[u] = *(const float4*)(sc + i + 4 * u);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) count(x[u]);
         }
-        if (running == take) break;                // no ties across the boundary (the exact pass always ends here)
+#pragma unroll 1
+        for (; i < padded; i += 4) count(*(const float4*)(sc + i));
+        return n;
+    };
+    auto wave_max = [](int v) {
+        for (int off = 32; off; off >>= 1) v = max(v, __shfl_xor(v, off));
+        return v;
+    };
+    if (padded <= 64) {
+        const int larger = larger_than(lane < len ? sc[lane] : 0.f);
+        bool kp = lane < len && larger < take;
+        unsigned long long mask = __ballot(kp);
+        if (__popcll(mask) != take) {              // equal scores across the boundary: the first of them fill it
+            const int top = wave_max(kp ? larger : -1);
+            const unsigned long long ties = __ballot(kp && larger == top);
+            kp = kp && (larger < top || __popcll(ties & below) < take - top);
+            mask = __ballot(kp);
+        }
+        if (kp) emit(__popcll(mask & below), lane);
+        return;
+    }
+    int kept = 0, most = -1;                       // of the rows that this lane would keep, the one with most larger rows:
+    float last = 0.f;                              // ... how many, and its score
+#pragma unroll 1
+    for (int e0 = 0; e0 < rows; e0 += 64) {
+        const int e = e0 + lane;
+        const float v = e < len ? sc[e] : 0.f;
+        const int larger = larger_than(v);
+        const bool kp = e < len && larger < take;
+        const unsigned long long mask = __ballot(kp);
+        const int r = kept + __popcll(mask & below);
+        if (kp && r < take) emit(r, e);
+        if (kp && larger > most) { most = larger; last = v; }
+        kept += __popcll(mask);
+    }
+    if (kept == take) return;
+    // equal scores across the boundary: every survivor again
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    const int top = wave_max(most);
+    const float bound = __shfl(last, __ffsll(__ballot(most == top)) - 1);
+    const int room = take - top;                   // rows that equal the bound and survive
+    int equal = 0;
+    kept = 0;
+#pragma unroll 1
+    for (int e0 = 0; e0 < rows; e0 += 64) {
+        const int e = e0 + lane;
+        const float v = e < len ? sc[e] : -INFINITY;
+        const unsigned long long ties = __ballot(e < len && v == bound);
+        const bool kp = e < len && (v > bound || (v == bound && equal + __popcll(ties & below) < room));
+        const unsigned long long mask = __ballot(kp);
+        if (kp) emit(kept + __popcll(mask & below), e);
+        kept += __popcll(mask);
+        equal += __popcll(ties);
     }
 }
 
-// The slice of a segment in LDS, in floats: a multiple of four.
-__host__ __device__ inline int segment_slice(int segment) { return (segment + 3) & ~3; }
-
 __global__ __launch_bounds__(256) void segment_topk_kernel(const SelectArgs a)
 {
-    extern __shared__ __attribute__((aligned(16))) float lds[];   // [kSelWaves][segment_slice]
+    extern __shared__ __attribute__((aligned(16))) float lds[];   // [kSelWaves][padded_length(segment)]
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int seg = blockIdx.x * kSelWaves + wave, unit = blockIdx.y;
     const int n_seg = (a.new_count + a.segment - 1) / a.segment;
@@ -64,7 +110,7 @@ __global__ __launch_bounds__(256) void segment_topk_kernel(const SelectArgs a)
     const int start = seg * a.segment;
     const int len = active ? min(a.segment, a.new_count - start) : 0;
     const int take = min(a.keep, len);
-    const int slice = segment_slice(a.segment);
+    const int slice = padded_length(a.segment);
     float* sc = lds + wave * slice;
     const float* base = a.score + (size_t)unit * a.unit_stride;
     int* out = a.sel + (size_t)unit * a.sel_stride + seg * a.keep;
@@ -183,7 +229,7 @@ __global__ __launch_bounds__(kTopkBlock) void segment_topk_block_kernel(const Se
 // adds exactly 0 for it.
 __global__ __launch_bounds__(256) void evict_new_rows_kernel(const EvictArgs a)
 {
-    extern __shared__ __attribute__((aligned(16))) float lds[];   // [kSelWaves][segment_slice] scores, [kSelWaves][keep] kept offsets
+    extern __shared__ __attribute__((aligned(16))) float lds[];   // [kSelWaves][padded_length(segment)] scores, [kSelWaves][keep] kept offsets
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int seg = blockIdx.x * kSelWaves + wave, unit = blockIdx.y;
     const int n_seg = (a.new_count + a.segment - 1) / a.segment;
@@ -191,7 +237,7 @@ __global__ __launch_bounds__(256) void evict_new_rows_kernel(const EvictArgs a)
     const int start = seg * a.segment;
     const int len = min(a.segment, a.new_count - start);
     const int take = min(a.keep, len);
-    const int slice = segment_slice(a.segment);
+    const int slice = padded_length(a.segment);
     float* sc = lds + wave * slice;
     int* kept = (int*)(lds + kSelWaves * slice) + wave * a.keep;
     const size_t ubase = (size_t)unit * a.cap;
@@ -310,7 +356,7 @@ hipError_t launch_evict_new_rows(const EvictArgs& a, int units, hipStream_t st, 
     if (n_seg <= 0 || a.keep <= 0) return hipSuccess;
     if (a.row_bytes > 1024 || (a.row_bytes & 15) || 64 % (a.row_bytes >> 4)) return hipErrorInvalidValue;
     const dim3 grid((n_seg + kSelWaves - 1) / kSelWaves, units);
-    const size_t lds = (size_t)kSelWaves * (segment_slice(a.segment) + a.keep) * sizeof(float);
+    const size_t lds = (size_t)kSelWaves * (padded_length(a.segment) + a.keep) * sizeof(float);
     BUZZ_LAUNCH(evict_new_rows_kernel, grid, dim3(256), lds, st, tm, a);
     return hipGetLastError();
 }
@@ -325,7 +371,7 @@ hipError_t launch_segment_topk(const SelectArgs& a, int units, hipStream_t st, T
         return hipGetLastError();
     }
     dim3 grid((n_seg + kSelWaves - 1) / kSelWaves, units), block(256);
-    const size_t lds = (size_t)kSelWaves * segment_slice(a.segment) * sizeof(float);
+    const size_t lds = (size_t)kSelWaves * padded_length(a.segment) * sizeof(float);
     BUZZ_LAUNCH(segment_topk_kernel, grid, block, lds, st, tm, a);
     return hipGetLastError();
 }

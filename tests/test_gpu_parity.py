@@ -458,6 +458,39 @@ def test_equal_scores_across_the_survivors_boundary(segment, keep, old_stride):
     run(wl, plant=plant)
 
 
+def eviction_time(segment, keep, new, scores, flags=0):
+    """Shortest of several explicit evictions (device time, ms) of `new` buffered rows on 32 units."""
+    from paper_2410_23079_amd import BuzzCache, BuzzConfig
+    H, D, w, old = 32, 64, 64, 1
+    n = 4 + old + new + w
+    c = BuzzCache(BuzzConfig(1, H, H, D, "fp16", 4, w, segment, keep, max(new, segment) + 8, 4 * n + 4 * segment, old_stride=1, flags=flags))
+    k = torch.zeros(1, H, n, D, dtype=torch.float16, device="cuda")
+    sc = scores(H, n).to("cuda", torch.float32).contiguous()
+    pos = torch.arange(n, dtype=torch.int32, device="cuda").expand(1, H, n).contiguous()
+    times = []
+    for _ in range(8):
+        c.import_rows(k, k, sc, pos, old, n)
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        c.evict()
+        b.record()
+        b.synchronize()
+        times.append(a.elapsed_time(b))
+    return min(times)
+
+
+def distinct(H, n):
+    return torch.rand(1, H, n, generator=torch.Generator().manual_seed(7))
+
+
+def test_equal_scores_rank_as_fast_as_distinct_ones():
+    """Whatever the scores are, a segment costs one comparison per pair of rows: ranking by a second such pass where equal
+    scores straddle the survivors' boundary took 2.8 times as long."""
+    some, same = eviction_time(1000, 100, 1000, distinct), eviction_time(1000, 100, 1000, lambda H, n: torch.zeros(1, H, n))
+    print(f"[rank] distinct {some * 1e3:.1f} us, equal {same * 1e3:.1f} us", flush=True)
+    assert same <= 1.5 * some
+
+
 @pytest.mark.parametrize("segment,keep", [(5000, 7), (9000, 300)])
 def test_segments_longer_than_one_wave_can_rank(segment, keep):
     """Segments beyond 4096 rows take the block-wide selection (radix select + prefix sum): two full segments and a
