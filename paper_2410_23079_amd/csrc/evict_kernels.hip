@@ -17,8 +17,8 @@ constexpr int kSelWaves = 4;
 // The ranking reads four scores at a time: `n` floats of LDS rounded up to that.
 __host__ __device__ inline int padded_length(int n) { return (n + 3) & ~3; }
 
-// Ranks the len scores that a wave has put into its LDS slice (16-byte aligned, padded with -inf to a
-// multiple of four) and calls emit(rank among the survivors, offset) for its `take` >= 1 best: score descending, ties to
+// Ranks the len scores that a wave has put into its LDS slice (16-byte aligned, padded with -inf to
+// padded_length(len)) and calls emit(rank among the survivors, offset) for its `take` >= 1 best: score descending, ties to
 // the lowest offset, survivors numbered in offset order.  (A rank may be given out twice; the last one counts.)  A row
 // survives if fewer than `take` rows are larger: one comparison and one addition per pair of rows, which is what bounds
 // the kernel.  That count keeps too many rows only where equal scores straddle the boundary.  The last survivor's score
@@ -28,10 +28,10 @@ __host__ __device__ inline int padded_length(int n) { return (n + 3) & ~3; }
 // segments of 1000 in each of 32 units: 253 us with distinct scores, 716 with equal ones when ties took a second pass of
 // comparisons, 165 with either now.
 template <typename Emit>
-__device__ inline void rank_segment(const float* sc, int len, int padded, int take, int lane, Emit emit)
+__device__ inline void rank_segment(const float* sc, int len, int take, int lane, Emit emit)
 {
     const unsigned long long below = (1ull << lane) - 1ull;
-    const int rows = __builtin_amdgcn_readfirstlane(len);
+    const int rows = __builtin_amdgcn_readfirstlane(len), padded = padded_length(rows);   // the slice may be longer
     auto larger_than = [&](float v) {              // rows of the segment
         int n = 0;
         auto count = [&](const float4& x) { n += x.x > v; n += x.y > v; n += x.z > v; n += x.w > v; };
@@ -119,7 +119,7 @@ __global__ __launch_bounds__(256) void segment_topk_kernel(const SelectArgs a)
         return;
     }
     if (!active) return;                           // no block-wide barrier below: a wave only reads what it wrote
-    for (int e = lane; e < slice; e += 64) {
+    for (int e = lane; e < padded_length(len); e += 64) {
         const int row = a.lo + start + e;
         float v = e < len ? base[a.map.ring_cap ? a.map.phys(row) : row] : -INFINITY;
         if (v != v) v = -INFINITY;                 // NaN ranks below everything
@@ -128,7 +128,7 @@ __global__ __launch_bounds__(256) void segment_topk_kernel(const SelectArgs a)
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    rank_segment(sc, len, slice, take, lane, [&](int r, int e) { out[r] = a.lo + start + e; });
+    rank_segment(sc, len, take, lane, [&](int r, int e) { out[r] = a.lo + start + e; });
 }
 
 // Segments too long for one wave's slice of the LDS (and the single segment of the H2O-style variant, which
@@ -250,7 +250,7 @@ __global__ __launch_bounds__(256) void evict_new_rows_kernel(const EvictArgs a)
                                     a.stat_prev[((size_t)unit * a.G + g) * 2 + 1]);
         return v;
     };
-    for (int e = lane; e < slice; e += 64) {
+    for (int e = lane; e < padded_length(len); e += 64) {
         float v = e >= len ? -INFINITY : a.ignore_scores ? 0.f : current_score(a.map.phys(a.lo + start + e));   // all equal: lowest indices win
         if (v != v) v = -INFINITY;                 // NaN ranks below everything
         sc[e] = v;
@@ -258,7 +258,7 @@ __global__ __launch_bounds__(256) void evict_new_rows_kernel(const EvictArgs a)
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    rank_segment(sc, len, slice, take, lane, [&](int r, int e) { kept[r] = e; });
+    rank_segment(sc, len, take, lane, [&](int r, int e) { kept[r] = e; });
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");

@@ -491,6 +491,14 @@ def test_equal_scores_rank_as_fast_as_distinct_ones():
     assert same <= 1.5 * some
 
 
+def test_few_rows_rank_as_fast_in_a_long_segment_as_in_a_short_one():
+    """An explicit eviction (or a ragged last segment) of 100 rows costs what 100 rows cost, whatever the configured
+    segment is: ranked against a whole segment of 4000 it took ten times as long."""
+    short, long = eviction_time(100, 3, 100, distinct), eviction_time(4000, 3, 100, distinct)
+    print(f"[rank] 100 rows in a segment of 100: {short * 1e3:.1f} us, of 4000: {long * 1e3:.1f} us", flush=True)
+    assert long <= 2 * short
+
+
 @pytest.mark.parametrize("segment,keep", [(5000, 7), (9000, 300)])
 def test_segments_longer_than_one_wave_can_rank(segment, keep):
     """Segments beyond 4096 rows take the block-wide selection (radix select + prefix sum): two full segments and a
