@@ -343,7 +343,7 @@ bool evict_sizes(const buzz_cache_t* c, int64_t n, int64_t n_old, EvictSizes* z)
 bool evict_uses_one_launch(const buzz_cache_t* c, int64_t n_old, const EvictSizes& z)
 {
     return !(c->cfg.flags & BUZZ_FLAG_GLOBAL_TOPK) && z.old2 == n_old &&
-           (((int64_t)c->cfg.segment + 3) / 4 * 4 + c->L.keep) * (int64_t)(4 * sizeof(float)) <= 65536;
+           ((int64_t)c->cfg.segment + c->L.keep) * (int64_t)(4 * sizeof(float)) <= 65536;   // four waves' slices
 }
 bool evict_fits(const buzz_cache_t* c, int64_t n_old, const EvictSizes& z)
 {

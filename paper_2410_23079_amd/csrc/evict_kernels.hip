@@ -14,11 +14,11 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kSelWaves = 4;
 
-// The ranking reads four scores at a time: `n` floats of LDS rounded up to that.
-__host__ __device__ inline int padded_length(int n) { return (n + 3) & ~3; }
+// A wave's slice of the LDS, in floats: the ranking reads four scores at a time.
+__host__ __device__ inline int wave_slice(int floats) { return (floats + 3) & ~3; }
 
-// Ranks the len scores that a wave has put into its LDS slice (16-byte aligned, padded with -inf to
-// padded_length(len)) and calls emit(rank among the survivors, offset) for its `take` >= 1 best: score descending, ties to
+// Ranks the len scores that a wave has put into its LDS slice (16-byte aligned; up to three more
+// floats are read behind them and not used) and calls emit(rank among the survivors, offset) for its `take` >= 1 best: score descending, ties to
 // the lowest offset, survivors numbered in offset order.  (A rank may be given out twice; the last one counts.)  A row
 // survives if fewer than `take` rows are larger: one comparison and one addition per pair of rows, which is what bounds
 // the kernel.  That count keeps too many rows only where equal scores straddle the boundary.  The last survivor's score
@@ -31,13 +31,13 @@ template <typename Emit>
 __device__ inline void rank_segment(const float* sc, int len, int take, int lane, Emit emit)
 {
     const unsigned long long below = (1ull << lane) - 1ull;
-    const int rows = __builtin_amdgcn_readfirstlane(len), padded = padded_length(rows);   // the slice may be longer
+    const int rows = __builtin_amdgcn_readfirstlane(len);
     auto larger_than = [&](float v) {              // rows of the segment
         int n = 0;
         auto count = [&](const float4& x) { n += x.x > v; n += x.y > v; n += x.z > v; n += x.w > v; };
         int i = 0;
 #pragma unroll 1
-        for (; i + 16 <= padded; i += 16) {        // four reads in flight: a wave is often alone on its SIMD
+        for (; i + 16 <= rows; i += 16) {        // four reads in flight: a wave is often alone on its SIMD
             float4 x[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) x[u] = *(const float4*)(sc + i + 4 * u);
@@ -45,14 +45,20 @@ __device__ inline void rank_segment(const float* sc, int len, int take, int lane
             for (int u = 0; u < 4; ++u) count(x[u]);
         }
 #pragma unroll 1
-        for (; i < padded; i += 4) count(*(const float4*)(sc + i));
+        for (; i + 4 <= rows; i += 4) count(*(const float4*)(sc + i));
+        if (i < rows) {
+            const float4 x = *(const float4*)(sc + i);
+            n += x.x > v;
+            if (i + 1 < rows) n += x.y > v;
+            if (i + 2 < rows) n += x.z > v;
+        }
         return n;
     };
     auto wave_max = [](int v) {
         for (int off = 32; off; off >>= 1) v = max(v, __shfl_xor(v, off));
         return v;
     };
-    if (padded <= 64) {
+    if (rows <= 64) {
         const int larger = larger_than(lane < len ? sc[lane] : 0.f);
         bool kp = lane < len && larger < take;
         unsigned long long mask = __ballot(kp);
@@ -102,7 +108,7 @@ __device__ inline void rank_segment(const float* sc, int len, int take, int lane
 
 __global__ __launch_bounds__(256) void segment_topk_kernel(const SelectArgs a)
 {
-    extern __shared__ __attribute__((aligned(16))) float lds[];   // [kSelWaves][padded_length(segment)]
+    extern __shared__ __attribute__((aligned(16))) float lds[];   // [kSelWaves][wave_slice(segment)]
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int seg = blockIdx.x * kSelWaves + wave, unit = blockIdx.y;
     const int n_seg = (a.new_count + a.segment - 1) / a.segment;
@@ -110,8 +116,7 @@ __global__ __launch_bounds__(256) void segment_topk_kernel(const SelectArgs a)
     const int start = seg * a.segment;
     const int len = active ? min(a.segment, a.new_count - start) : 0;
     const int take = min(a.keep, len);
-    const int slice = padded_length(a.segment);
-    float* sc = lds + wave * slice;
+    float* sc = lds + wave * wave_slice(a.segment);
     const float* base = a.score + (size_t)unit * a.unit_stride;
     int* out = a.sel + (size_t)unit * a.sel_stride + seg * a.keep;
     if (a.ignore_scores) {                         // all equal: the lowest indices win
@@ -119,9 +124,9 @@ __global__ __launch_bounds__(256) void segment_topk_kernel(const SelectArgs a)
         return;
     }
     if (!active) return;                           // no block-wide barrier below: a wave only reads what it wrote
-    for (int e = lane; e < padded_length(len); e += 64) {
+    for (int e = lane; e < len; e += 64) {
         const int row = a.lo + start + e;
-        float v = e < len ? base[a.map.ring_cap ? a.map.phys(row) : row] : -INFINITY;
+        float v = base[a.map.ring_cap ? a.map.phys(row) : row];
         if (v != v) v = -INFINITY;                 // NaN ranks below everything
         sc[e] = v;
     }
@@ -229,7 +234,7 @@ __global__ __launch_bounds__(kTopkBlock) void segment_topk_block_kernel(const Se
 // adds exactly 0 for it.
 __global__ __launch_bounds__(256) void evict_new_rows_kernel(const EvictArgs a)
 {
-    extern __shared__ __attribute__((aligned(16))) float lds[];   // [kSelWaves][padded_length(segment)] scores, [kSelWaves][keep] kept offsets
+    extern __shared__ __attribute__((aligned(16))) float lds[];   // [kSelWaves][wave_slice(segment + keep)]: scores, then kept offsets
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int seg = blockIdx.x * kSelWaves + wave, unit = blockIdx.y;
     const int n_seg = (a.new_count + a.segment - 1) / a.segment;
@@ -237,9 +242,8 @@ __global__ __launch_bounds__(256) void evict_new_rows_kernel(const EvictArgs a)
     const int start = seg * a.segment;
     const int len = min(a.segment, a.new_count - start);
     const int take = min(a.keep, len);
-    const int slice = padded_length(a.segment);
-    float* sc = lds + wave * slice;
-    int* kept = (int*)(lds + kSelWaves * slice) + wave * a.keep;
+    float* sc = lds + wave * wave_slice(a.segment + a.keep);
+    int* kept = (int*)sc + a.segment;
     const size_t ubase = (size_t)unit * a.cap;
     const float* logit_u = a.logit_prev ? a.logit_prev + ubase * a.G : nullptr;
     auto current_score = [&](int ph) {             // the row's score with the pending update applied
@@ -250,8 +254,8 @@ __global__ __launch_bounds__(256) void evict_new_rows_kernel(const EvictArgs a)
                                     a.stat_prev[((size_t)unit * a.G + g) * 2 + 1]);
         return v;
     };
-    for (int e = lane; e < padded_length(len); e += 64) {
-        float v = e >= len ? -INFINITY : a.ignore_scores ? 0.f : current_score(a.map.phys(a.lo + start + e));   // all equal: lowest indices win
+    for (int e = lane; e < len; e += 64) {
+        float v = a.ignore_scores ? 0.f : current_score(a.map.phys(a.lo + start + e));   // all equal: lowest indices win
         if (v != v) v = -INFINITY;                 // NaN ranks below everything
         sc[e] = v;
     }
@@ -356,7 +360,7 @@ hipError_t launch_evict_new_rows(const EvictArgs& a, int units, hipStream_t st, 
     if (n_seg <= 0 || a.keep <= 0) return hipSuccess;
     if (a.row_bytes > 1024 || (a.row_bytes & 15) || 64 % (a.row_bytes >> 4)) return hipErrorInvalidValue;
     const dim3 grid((n_seg + kSelWaves - 1) / kSelWaves, units);
-    const size_t lds = (size_t)kSelWaves * (padded_length(a.segment) + a.keep) * sizeof(float);
+    const size_t lds = (size_t)kSelWaves * wave_slice(a.segment + a.keep) * sizeof(float);
     BUZZ_LAUNCH(evict_new_rows_kernel, grid, dim3(256), lds, st, tm, a);
     return hipGetLastError();
 }
@@ -371,7 +375,7 @@ hipError_t launch_segment_topk(const SelectArgs& a, int units, hipStream_t st, T
         return hipGetLastError();
     }
     dim3 grid((n_seg + kSelWaves - 1) / kSelWaves, units), block(256);
-    const size_t lds = (size_t)kSelWaves * padded_length(a.segment) * sizeof(float);
+    const size_t lds = (size_t)kSelWaves * wave_slice(a.segment) * sizeof(float);
     BUZZ_LAUNCH(segment_topk_kernel, grid, block, lds, st, tm, a);
     return hipGetLastError();
 }

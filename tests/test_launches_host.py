@@ -80,3 +80,18 @@ def test_a_prefill_that_fails_while_it_scores_leaves_no_cache_behind(lib, dtype,
         assert lib.rec_count() == 0
         assert lib.buzz_prefill(h, KP, VP, 600, QP, n_obs, None, None) == 0
     assert lib.buzz_cache_destroy(h) == 0
+
+
+@pytest.mark.parametrize("segment,keep,one", [(4093, 3, True), (4092, 4, True), (4095, 1, True), (3001, 1095, True), (64, 8, True),
+                                              (4093, 4, False), (4094, 3, False), (4096, 1, False)])
+def test_the_one_launch_eviction_takes_every_segment_that_fits_the_lds(lib, segment, keep, one):
+    """Scores and kept offsets of four waves in 64 KB: segment + keep up to 4096 floats per wave, whatever the segment is
+    modulo four."""
+    h = create(lib, config(segment=segment, keep=keep, evict_every=64, window=10, max_context=20000, flags=0))
+    assert lib.buzz_cache_import(h, KP, VP, SP, PP, 4 + 10 + 50, 0, 64, None) == 0
+    lib.rec_reset(-1)
+    assert lib.buzz_evict(h, None) == 0
+    kernels = [k for k, _ in recorded(lib)]
+    assert ["evict_new_rows_kernel" in k for k in kernels] == ([True] if one else [False, False])
+    assert all(lib.rec_value(i, b"lds") <= 65536 for _, i in recorded(lib))
+    assert lib.buzz_cache_destroy(h) == 0
