@@ -254,15 +254,19 @@ __global__ __launch_bounds__(256) void evict_new_rows_kernel(const EvictArgs a)
                                     a.stat_prev[((size_t)unit * a.G + g) * 2 + 1]);
         return v;
     };
-    for (int e = lane; e < len; e += 64) {
-        float v = a.ignore_scores ? 0.f : current_score(a.map.phys(a.lo + start + e));   // all equal: lowest indices win
-        if (v != v) v = -INFINITY;                 // NaN ranks below everything
-        sc[e] = v;
+    if (a.ignore_scores) {                         // all equal: the lowest indices win
+        for (int r = lane; r < take; r += 64) kept[r] = r;
+    } else {
+        for (int e = lane; e < len; e += 64) {
+            float v = current_score(a.map.phys(a.lo + start + e));
+            if (v != v) v = -INFINITY;             // NaN ranks below everything
+            sc[e] = v;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        rank_segment(sc, len, take, lane, [&](int r, int e) { kept[r] = e; });
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    rank_segment(sc, len, take, lane, [&](int r, int e) { kept[r] = e; });
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");

@@ -499,6 +499,14 @@ def test_few_rows_rank_as_fast_in_a_long_segment_as_in_a_short_one():
     assert long <= 2 * short
 
 
+def test_evictions_that_ignore_the_scores_do_not_rank_them():
+    """Interval sampling of the new rows keeps the first rows of every segment: nothing is compared."""
+    from paper_2410_23079_amd import FLAG_INTERVAL_NEW
+    ranked, first = eviction_time(1000, 100, 1000, distinct), eviction_time(1000, 100, 1000, distinct, FLAG_INTERVAL_NEW)
+    print(f"[rank] by score {ranked * 1e3:.1f} us, by index {first * 1e3:.1f} us", flush=True)
+    assert first <= 0.5 * ranked
+
+
 @pytest.mark.parametrize("segment,keep", [(5000, 7), (9000, 300)])
 def test_segments_longer_than_one_wave_can_rank(segment, keep):
     """Segments beyond 4096 rows take the block-wide selection (radix select + prefix sum): two full segments and a
