@@ -161,7 +161,7 @@ struct ObsArgs {               // prefill scoring: causal attention of observed 
     float* score;              // [units][N]   the prompt scores, written by the first pass, added to by later ones
     const float* init;         // [units][N]   starting scores, NULL: zeros
     float* stats;              // [B * Hq][key_parts][t_count][2] (reference, sum) of every query over each part of its keys
-    float* partial;            // [item_parts][units][N] column sums, each over a part of the queries
+    float* partial;            // [item_parts][units][keys that the pass sees] column sums, each over a part of the queries
     size_t stats_cap;          // (reference, sum) pairs the statistics array holds
     size_t partial_cap;        // column sums the partial array holds
     int32_t N, n_obs;
@@ -180,9 +180,11 @@ struct ObsArgs {               // prefill scoring: causal attention of observed 
 constexpr int kObsPassRows = 4096;   // prompt scoring: queries per head and pass
 constexpr int kObsKeyParts = 16;     // ... and the most blocks that share one query group's keys
 constexpr int kObsItemParts = 16;    // ... or one key block's queries
-// Elements of the two arrays that hold the parts' results: what the launch's rule can ask for.  It cuts a step
-// with fewer than 4 blocks (of at most 256 stationary vectors) per compute unit into at most 8 per unit and one remainder
-// per uncut block, so 12 blocks of 256 results per compute unit are enough and never bind.
+// Elements of the two arrays that hold the parts' results: what the launch's rule can ask for.  It cuts a step whose
+// longest block has more than the share of half a compute unit (2 blocks per unit), to parts of a quarter of a unit's.
+// Work falls linearly from the longest block (of at most 256 stationary vectors) on, so on average a block with work has
+// half of the longest's at least: there are fewer than 4 such blocks per unit, and with a remainder each they make
+// at most 8 + 4 times 256 results per unit, in every pass of a prompt.
 constexpr size_t kObsPartElems = (size_t)12 * kDefaultCUs * 256;
 
 // Optional event pair: when both are non-null the launch records the kernel's own begin / end

@@ -86,6 +86,9 @@ __host__ __device__ inline int seeing_chunks(const ObsArgs& a, int j_block, int 
     return *t_lo < t_end ? (t_end - *t_lo + chunk_rows - 1) / chunk_rows : 0;
 }
 
+// The keys that some query of the pass sees are the first visible_keys: the parts' column sums are laid out over these.
+__host__ __device__ inline int visible_keys(const ObsArgs& a) { return a.N - a.n_obs + a.t_begin + a.t_count; }
+
 // The moving rows of one chunk in LDS.  A row occupies its bytes plus 16: with that pitch the 16
 // lanes that read the same piece of 16 different rows fall on 16 different groups of four banks.
 template <int ROWB_>
@@ -394,10 +397,12 @@ __global__ __launch_bounds__(256) void obs_mfma_kernel(const ObsArgs a)
             float c = col[ct] + __shfl_xor(col[ct], 16);
             c += __shfl_xor(c, 32);
             const int key = j_base + 16 * ct + j;
-            if (q == 0 && key < a.N) {
+            if (a.item_parts == 1) {
                 const size_t at = (size_t)unit * a.N + key;
-                if (a.item_parts == 1) a.score[at] = score_so_far(a, at) + c;
-                else a.partial[(size_t)part * a.units * a.N + at] = c;
+                if (q == 0 && key < a.N) a.score[at] = score_so_far(a, at) + c;
+            } else {
+                const int keys = visible_keys(a);
+                if (q == 0 && key < keys) a.partial[((size_t)part * a.units + unit) * keys + key] = c;
             }
         }
     }
@@ -433,12 +438,13 @@ __global__ __launch_bounds__(256) void obs_sum_parts_kernel(const ObsArgs a, int
     const int j = blockIdx.x * 256 + threadIdx.x, unit = blockIdx.y;
     if (j >= a.N) return;
     int t_lo;
-    const int items = seeing_chunks(a, j / cols * cols, chunk_rows, &t_lo) * (a.Hq / a.Hkv);
+    const int keys = visible_keys(a);
+    const int items = j < keys ? seeing_chunks(a, j / cols * cols, chunk_rows, &t_lo) * (a.Hq / a.Hkv) : 0;
     const int parts = (items + a.item_part_len - 1) / a.item_part_len;
-    const size_t at = (size_t)unit * a.N + j;
+    const size_t at = (size_t)unit * a.N + j, sum = (size_t)unit * keys + j;
     float got[kObsItemParts];
 #pragma unroll
-    for (int p = 0; p < kObsItemParts; ++p) got[p] = p < parts ? a.partial[(size_t)p * a.units * a.N + at] : 0.f;
+    for (int p = 0; p < kObsItemParts; ++p) got[p] = p < parts ? a.partial[(size_t)p * a.units * keys + sum] : 0.f;
     float s = score_so_far(a, at);
 #pragma unroll
     for (int p = 0; p < kObsItemParts; ++p) s += got[p];
@@ -452,7 +458,7 @@ hipError_t launch_obs_mfma_t(ObsArgs a, int units, hipStream_t st, Timing tm)
     const int heads = units / a.Hkv * a.Hq, G = a.Hq / a.Hkv;
     a.heads = heads; a.units = units;
     const int q_blocks = (a.t_count + COLS - 1) / COLS;
-    const int k_blocks = (a.N + COLS - 1) / COLS;
+    const int k_seen = (visible_keys(a) + COLS - 1) / COLS;            // blocks of keys with work
     // A step whose longest block is no more than its share of two blocks per compute unit stays whole: the long
     // blocks start first and have the SIMDs more and more to themselves, and parts would only repeat the blocks'
     // prologue (64 heads of 128, 4096 queries: 347 us whole, 385 us cut).  Below that it is cut for four blocks
@@ -476,10 +482,11 @@ hipError_t launch_obs_mfma_t(ObsArgs a, int units, hipStream_t st, Timing tm)
     split(total, longest, most < kObsKeyParts ? (most < 1 ? 1 : most) : kObsKeyParts, &a.key_parts, &a.key_part_len);
     total = 0;
     int t_lo;
-    for (int b = 0; b < k_blocks; ++b) total += (int64_t)seeing_chunks(a, b * COLS, CH, &t_lo) * G * units;
+    for (int b = 0; b < k_seen; ++b) total += (int64_t)seeing_chunks(a, b * COLS, CH, &t_lo) * G * units;
     longest = seeing_chunks(a, 0, CH, &t_lo) * G;
-    most = (int)(a.partial_cap / ((size_t)units * a.N));
+    most = (int)(a.partial_cap / ((size_t)units * visible_keys(a)));
     split(total, longest, most < kObsItemParts ? (most < 1 ? 1 : most) : kObsItemParts, &a.item_parts, &a.item_part_len);
+    const int k_blocks = a.item_parts > 1 ? k_seen : (a.N + COLS - 1) / COLS;   // uncut blocks carry every score over
     const int64_t blocks1 = (int64_t)heads * q_blocks * a.key_parts, blocks2 = (int64_t)units * k_blocks * a.item_parts;
     if (blocks1 > INT32_MAX / 256 || blocks2 > INT32_MAX / 256) return hipErrorInvalidValue;   // (far beyond any GPU's memory)
     const dim3 g1((unsigned)blocks1), g2((unsigned)blocks2);

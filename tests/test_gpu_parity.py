@@ -252,6 +252,34 @@ def test_prompt_scoring_cut_into_parts(dtype, D, G, prompt, n_obs):
     run(wl)
 
 
+@pytest.mark.parametrize("dtype,D,units,G,N,n_obs", [("bf16", 64, 8, 1, 8200, 8200), ("fp16", 128, 12, 1, 9001, 5000),
+                                                     ("fp32", 64, 8, 1, 8193, 4097), ("bf16", 256, 6, 2, 6000, 4400)])
+def test_prompt_scoring_in_several_passes_cut_into_parts(dtype, D, units, G, N, n_obs):
+    """More observed queries than one pass takes, few enough heads that every pass is cut: early passes see a part of the
+    keys only.  The column sums are compared with 64-bit softmax rows; the keys' scores start from the caller's."""
+    from paper_2410_23079_amd import BuzzCache, BuzzConfig
+    dt = {"fp32": torch.float32, "fp16": torch.float16, "bf16": torch.bfloat16}[dtype]
+    g = torch.Generator(device="cuda").manual_seed(N)
+    k = torch.randn(1, units, N, D, generator=g, device="cuda").to(dt)
+    q = torch.randn(1, units * G, n_obs, D, generator=g, device="cuda").to(dt)
+    init = torch.rand(1, units, N, generator=g, device="cuda")
+    print(f"[passes] {dtype} D{D} units {units} G{G} N{N} n_obs{n_obs}", flush=True)
+    c = BuzzCache(BuzzConfig(1, units * G, units, D, dtype, 0, N, 16, 1, 16, N + 1, old_stride=1))
+    c.prefill(k, k, q_obs=q, init_score=init)
+    got = c.export()[2][0].double()
+    c.prefill(k, k, q_obs=q, init_score=init)
+    assert torch.equal(got, c.export()[2][0].double())         # the same bits every time
+    at = torch.arange(N - n_obs, N, device="cuda")
+    hidden = torch.arange(N, device="cuda")[None, :] > at[:, None]
+    for h in range(units):
+        want = init[0, h].double()
+        for j in range(G):
+            s = torch.matmul(q[0, h * G + j].double(), k[0, h].double().t().contiguous()) / D ** 0.5
+            want = want + torch.softmax(s.masked_fill_(hidden, -float("inf")), 1).sum(0)
+        err = ((got[h] - want).abs() / want.clamp(min=1.0)).max().item()
+        assert err <= lockstep().SCORE_TOL, f"head {h}: scores off by {err}"
+
+
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
 @pytest.mark.parametrize("D,G,prompt,n_obs", [(64, 1, 200, 200), (128, 2, 700, 333), (256, 1, 90, 41)])
 def test_a_query_that_is_not_a_number_stays_with_the_keys_it_sees(dtype, D, G, prompt, n_obs):

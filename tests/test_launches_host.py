@@ -82,6 +82,51 @@ def test_a_prefill_that_fails_while_it_scores_leaves_no_cache_behind(lib, dtype,
     assert lib.buzz_cache_destroy(h) == 0
 
 
+def scoring_passes(lib):
+    """Per scoring pass: the launch's own split of both steps, as recorded with the first step's arguments."""
+    names = ("t_begin", "t_count", "heads", "units", "key_parts", "key_part_len", "item_parts", "item_part_len", "stats_cap",
+             "partial_cap")
+    return [{n: lib.rec_value(i, n.encode()) for n in names} for k, i in recorded(lib)
+            if "obs_mfma_kernel" in k and "Li1ELb" in k]
+
+
+@pytest.mark.parametrize("dtype,D", [("bf16", 128), ("fp16", 256), ("fp32", 64), ("fp32", 256)])
+@pytest.mark.parametrize("units,G,N,n_obs", [
+    (16, 4, 8192, 8192), (16, 4, 16384, 16384), (8, 4, 32768, 32768), (16, 1, 131072, 131072), (1, 1, 131072, 131072),
+    (8, 1, 9000, 5001), (3, 7, 20000, 12289), (32, 2, 4097, 4097), (2, 8, 4096, 4096), (1, 8, 50000, 300), (64, 1, 4095, 1), (1, 1, 300, 300),
+    (200, 1, 1000, 1000), (300, 1, 5000, 4500)])
+def test_the_cut_of_the_scoring_steps_is_never_bound_by_its_scratch(lib, dtype, D, units, G, N, n_obs):
+    """Both steps of every pass are cut as the rule says -- parts of a quarter of a compute unit's share, at most 16 per
+    block -- whatever part of the prompt the pass sees, and the parts' results fit the arrays of the workspace."""
+    h = create(lib, config(batch=1, n_q_heads=units * G, n_kv_heads=units, head_dim=D, kv_dtype=dtype, max_context=N,
+                           window=64, evict_every=64, segment=64, keep=1))
+    lib.rec_reset(-1)
+    assert lib.buzz_prefill(h, KP, VP, N, QP, n_obs, None, None) == 0
+    passes = scoring_passes(lib)
+    assert len(passes) == -(-n_obs // 4096)
+    row_bytes = D * (4 if dtype == "fp32" else 2)
+    rows, cols, cus, shift = 64 if row_bytes <= 256 else 16384 // row_bytes, 128 if dtype == "fp32" else 256, 256, N - n_obs
+
+    def check(lengths, blocks_per_length, parts, length):
+        longest, total = max(lengths), sum(lengths) * blocks_per_length
+        cut = longest > -(-total // (2 * cus))
+        assert (parts > 1) == (cut and longest > max(-(-total // (4 * cus)), -(-longest // 16)))
+        assert parts == -(-longest // length)
+        if parts > 1:
+            assert length == max(-(-total // (4 * cus)), -(-longest // 16))
+
+    for p in passes:
+        t0, end = p["t_begin"], p["t_begin"] + p["t_count"]
+        keys = shift + end                                   # some query of the pass sees these
+        check([(shift + min(t + cols, end) - 1) // rows + 1 for t in range(t0, end, cols)], units * G, p["key_parts"], p["key_part_len"])
+        first = [t0 + max(j - shift - t0, 0) // rows * rows for j in range(0, keys, cols)]
+        check([-(-(end - t) // rows) * G for t in first], units, p["item_parts"], p["item_part_len"])
+        assert p["key_parts"] == 1 or p["key_parts"] * p["heads"] * p["t_count"] <= p["stats_cap"]
+        assert p["heads"] * p["t_count"] <= p["stats_cap"]
+        assert p["item_parts"] == 1 or p["item_parts"] * units * keys <= p["partial_cap"]
+    assert lib.buzz_cache_destroy(h) == 0
+
+
 @pytest.mark.parametrize("segment,keep,one", [(4093, 3, True), (4092, 4, True), (4095, 1, True), (3001, 1095, True), (64, 8, True),
                                               (4093, 4, False), (4094, 3, False), (4096, 1, False)])
 def test_the_one_launch_eviction_takes_every_segment_that_fits_the_lds(lib, segment, keep, one):
