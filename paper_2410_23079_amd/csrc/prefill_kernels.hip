@@ -463,9 +463,9 @@ hipError_t launch_obs_mfma_t(ObsArgs a, int units, hipStream_t st, Timing tm)
     // blocks start first and have the SIMDs more and more to themselves, and parts would only repeat the blocks'
     // prologue (64 heads of 128, 4096 queries: 347 us whole, 385 us cut).  Below that it is cut for four blocks
     // per compute unit (16 heads on 4 kv heads, 4001 queries: 622 us whole, 369 us cut; six or eight: the same).
-    auto split = [&](int64_t total, int longest, int most, int* parts, int* len) {
+    auto split = [&](int64_t total, int longest, bool whole, int most, int* parts, int* len) {
         const int64_t cus = a.compute_units;
-        int64_t l = longest <= (total + 2 * cus - 1) / (2 * cus) ? longest : (total + 4 * cus - 1) / (4 * cus);
+        int64_t l = whole && longest <= (total + 2 * cus - 1) / (2 * cus) ? longest : (total + 4 * cus - 1) / (4 * cus);
         if (l < (longest + most - 1) / most) l = (longest + most - 1) / most;
         *len = (int)(l < 1 ? 1 : l);
         *parts = longest > 0 ? (int)((longest + *len - 1) / *len) : 1;
@@ -479,13 +479,20 @@ hipError_t launch_obs_mfma_t(ObsArgs a, int units, hipStream_t st, Timing tm)
         longest = chunks;
     }
     int most = (int)(a.stats_cap / ((size_t)heads * a.t_count));       // what the statistics array holds
-    split(total, longest, most < kObsKeyParts ? (most < 1 ? 1 : most) : kObsKeyParts, &a.key_parts, &a.key_part_len);
+    // A few observed queries leave waves of a block without any.  Up to 1.5 waves with queries per SIMD, step 1 is cut all
+    // the same, where a part is long enough to pay for the merge (5 us): the chunks' latencies are not hidden otherwise
+    // (512 heads of 64, 16 bits, 128 queries, 4096 keys: 116 us whole, 84 + 5 cut; 576 heads of 128: 330 us of prefill
+    // whole, 295 cut).  Rows of 128 need a wave per SIMD for that (512 heads, 64 queries: 188 us whole, 204 cut);
+    // fp32 tiles and rows of 256 keep the matrix pipes busy (no difference, 2% slower).
+    const int64_t waves = (int64_t)heads * ((a.t_count + COLS / 4 - 1) / (COLS / 4)), simds = 4 * (int64_t)a.compute_units;
+    const bool idle = DT != BUZZ_FP32 && 2 * waves < 3 * simds && longest >= 24 && (D == 64 || (D == 128 && waves >= simds));
+    split(total, longest, !idle, most < kObsKeyParts ? (most < 1 ? 1 : most) : kObsKeyParts, &a.key_parts, &a.key_part_len);
     total = 0;
     int t_lo;
     for (int b = 0; b < k_seen; ++b) total += (int64_t)seeing_chunks(a, b * COLS, CH, &t_lo) * G * units;
     longest = seeing_chunks(a, 0, CH, &t_lo) * G;
     most = (int)(a.partial_cap / ((size_t)units * visible_keys(a)));
-    split(total, longest, most < kObsItemParts ? (most < 1 ? 1 : most) : kObsItemParts, &a.item_parts, &a.item_part_len);
+    split(total, longest, true, most < kObsItemParts ? (most < 1 ? 1 : most) : kObsItemParts, &a.item_parts, &a.item_part_len);
     const int k_blocks = a.item_parts > 1 ? k_seen : (a.N + COLS - 1) / COLS;   // uncut blocks carry every score over
     const int64_t blocks1 = (int64_t)heads * q_blocks * a.key_parts, blocks2 = (int64_t)units * k_blocks * a.item_parts;
     if (blocks1 > INT32_MAX / 256 || blocks2 > INT32_MAX / 256) return hipErrorInvalidValue;   // (far beyond any GPU's memory)

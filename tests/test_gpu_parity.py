@@ -253,10 +253,11 @@ def test_prompt_scoring_cut_into_parts(dtype, D, G, prompt, n_obs):
 
 
 @pytest.mark.parametrize("dtype,D,units,G,N,n_obs", [("bf16", 64, 8, 1, 8200, 8200), ("fp16", 128, 12, 1, 9001, 5000),
-                                                     ("fp32", 64, 8, 1, 8193, 4097), ("bf16", 256, 6, 2, 6000, 4400)])
-def test_prompt_scoring_in_several_passes_cut_into_parts(dtype, D, units, G, N, n_obs):
+                                                     ("fp32", 64, 8, 1, 8193, 4097), ("bf16", 256, 6, 2, 6000, 4400),
+                                                     ("fp16", 64, 64, 8, 1537, 1), ("bf16", 128, 64, 8, 1600, 100)])
+def test_prompt_scoring_cut_into_parts_of_a_pass_and_of_idle_waves(dtype, D, units, G, N, n_obs):
     """More observed queries than one pass takes, few enough heads that every pass is cut: early passes see a part of the
-    keys only.  The column sums are compared with 64-bit softmax rows; the keys' scores start from the caller's."""
+    keys only.  Many heads with a few queries each, whose blocks are cut because they leave waves idle.  The column sums are compared with 64-bit softmax rows; the keys' scores start from the caller's."""
     from paper_2410_23079_amd import BuzzCache, BuzzConfig
     dt = {"fp32": torch.float32, "fp16": torch.float16, "bf16": torch.bfloat16}[dtype]
     g = torch.Generator(device="cuda").manual_seed(N)
