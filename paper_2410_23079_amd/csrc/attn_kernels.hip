@@ -438,57 +438,68 @@ __device__ inline float wave_sum(float v)
 
 // The last block of a unit merges the partials of its S splits, 64 output elements (of one head) per wave and group:
 // lane s fetches the (max, sum) pair of split s and turns it into that split's weight, every lane fetches its element
-// of the splits' outputs, GB groups and 8 (GB <= 2: 16) splits at a time in one round of loads without a branch in
+// of the splits' outputs, up to four groups and 8 (16) splits at a time in one round of loads without a branch in
 // between, and the weights reach the lanes as scalars: one exponential per wave and split instead of one per
-// element, half the loads of a pair per element, one round trip for up to 16 splits.  What counts here is the
-// number of instructions the waves have to issue between the ticket and the output: with a branch-free burst of
-// pairs and elements per thread, and two rounds of it, a step of 8 units, 12 splits, 4 heads of 128 took 9.3 us
-// instead of 8.0.  (Spreading the splits over all waves of the block and their sums through LDS: 8.2.)
+// element, half the loads of a pair per element, one round trip for up to 16 splits.  Groups of one head that a wave
+// has anyway share their weights.  What counts here is the number of instructions the waves have to issue between the
+// ticket and the output: with a branch-free burst of pairs and elements per thread, and two rounds of it, a step of 8
+// units, 12 splits, 4 heads of 128 took 9.3 us, with weights for each group 8.0, now 7.3.  (Spreading the splits over
+// all waves of the block and their sums through LDS: 8.2.)  128 units, 2 splits, 7 heads of 256: 29.3, 32.8 and 27.8 us.
+// More than four groups at a time cost the streaming kernels a resident block (300 units, 8 heads of 128: 28 -> 42 us).
 template <int G, int D, int NM>
 __device__ inline void merge_splits(const AttnArgs& a, int unit, int wave, bool poisoned, float* outp)
 {
     constexpr int NG = G * D / 64, NMW = NM / 64;         // groups of 64 elements, merging waves
-    constexpr int PER = (NG + NMW - 1) / NMW, GB = PER < 4 ? PER : 4, CH = GB <= 2 ? 16 : 8;
+    constexpr int PER = (NG + NMW - 1) / NMW;             // groups per wave
+    constexpr int HG = PER >= D / 64 ? D / 64 : PER >= 2 && D >= 128 ? 2 : 1;   // groups of one head that stay together ...
+    constexpr int NH = NG / HG, PERH = (NH + NMW - 1) / NMW;
+    constexpr int HB = PERH * HG <= 4 ? PERH : 4 / HG;    // ... and how many such chunks a wave takes at a time
+    constexpr int GB = HB * HG, CH = GB <= 2 && NMW > 2 ? 16 : 8;
+    static_assert(NG % HG == 0 && (D / 64) % HG == 0, "a chunk lies inside one head");
     const int S = a.n_splits, lane = threadIdx.x & 63;
     const unsigned long long* ml = (const unsigned long long*)(a.part_ml + (size_t)unit * a.s_cap * G * 2);
     const float* po = a.part_o + (size_t)unit * a.s_cap * G * D;
 #pragma unroll 1
-    for (int gr0 = wave; gr0 < NG; gr0 += NMW * GB) {
-        float M[GB], L[GB], o[GB];
+    for (int c0 = wave; c0 < NH; c0 += NMW * HB) {
+        float M[HB], L[HB], o[GB];
 #pragma unroll
-        for (int b = 0; b < GB; ++b) { M[b] = -INFINITY; L[b] = 0.f; o[b] = 0.f; }
+        for (int h = 0; h < HB; ++h) { M[h] = -INFINITY; L[h] = 0.f; }
+#pragma unroll
+        for (int b = 0; b < GB; ++b) o[b] = 0.f;
+        auto chunk = [&](int h) { return min(c0 + h * NMW, NH - 1); };
         // 16 (8) splits per round; the running maximum moves from round to round
 #pragma unroll 1
         for (int s0 = 0; s0 < S; s0 += CH) {
-            unsigned long long pair[GB];
+            unsigned long long pair[HB];
             float xr[GB][CH];
             auto request = [&](auto local) {
                 constexpr bool LOCAL = decltype(local)::value;
 #pragma unroll
-                for (int b = 0; b < GB; ++b)
-                    pair[b] = __hip_atomic_load(ml + min(s0 + (lane & (CH - 1)), S - 1) * G + min(gr0 + b * NMW, NG - 1) * 64 / D, __ATOMIC_RELAXED, merge_scope<LOCAL>());
+                for (int h = 0; h < HB; ++h)
+                    pair[h] = __hip_atomic_load(ml + min(s0 + (lane & (CH - 1)), S - 1) * G + chunk(h) * HG * 64 / D, __ATOMIC_RELAXED, merge_scope<LOCAL>());
 #pragma unroll
                 for (int half = 0; half < CH; half += 8) {
                     if (half > 0 && s0 + half >= S) break;
 #pragma unroll
                     for (int b = 0; b < GB; ++b) {
 #pragma unroll
-                        for (int e = half; e < half + 8; ++e) xr[b][e] = acquire<LOCAL>(po + (size_t)min(s0 + e, S - 1) * (G * D) + min(gr0 + b * NMW, NG - 1) * 64 + lane);
+                        for (int e = half; e < half + 8; ++e) xr[b][e] = acquire<LOCAL>(po + (size_t)min(s0 + e, S - 1) * (G * D) + (chunk(b / HG) * HG + b % HG) * 64 + lane);
                     }
                 }
             };
             if (a.xcd_local) request(std::true_type{}); else request(std::false_type{});
             const bool have = lane < CH && s0 + lane < S;
-            float w[GB];
+            float w[HB];
 #pragma unroll
-            for (int b = 0; b < GB; ++b) {
-                const float m = have ? __uint_as_float((unsigned)pair[b]) : -INFINITY;
-                const float mx = fmaxf(M[b], wave_max(m));   // finite: the appended row is always present
-                const float keep = fast_exp2(M[b] - mx);     // 0 in the first round
-                w[b] = fast_exp2(m - mx);
-                L[b] = fmaf(L[b], keep, wave_sum(have ? w[b] * __uint_as_float((unsigned)(pair[b] >> 32)) : 0.f));
-                o[b] *= keep;
-                M[b] = mx;
+            for (int h = 0; h < HB; ++h) {
+                const float m = have ? __uint_as_float((unsigned)pair[h]) : -INFINITY;
+                const float mx = fmaxf(M[h], wave_max(m));   // finite: the appended row is always present
+                const float keep = fast_exp2(M[h] - mx);     // 0 in the first round
+                w[h] = fast_exp2(m - mx);
+                L[h] = fmaf(L[h], keep, wave_sum(have ? w[h] * __uint_as_float((unsigned)(pair[h] >> 32)) : 0.f));
+#pragma unroll
+                for (int b = h * HG; b < (h + 1) * HG; ++b) o[b] *= keep;
+                M[h] = mx;
             }
 #pragma unroll
             for (int half = 0; half < CH; half += 8) {
@@ -496,18 +507,19 @@ __device__ inline void merge_splits(const AttnArgs& a, int unit, int wave, bool 
 #pragma unroll
                 for (int b = 0; b < GB; ++b) {
 #pragma unroll
-                    for (int e = half; e < half + 8; ++e) o[b] = fmaf(lane_value(w[b], e), s0 + e < S ? xr[b][e] : 0.f, o[b]);
+                    for (int e = half; e < half + 8; ++e) o[b] = fmaf(lane_value(w[b / HG], e), s0 + e < S ? xr[b][e] : 0.f, o[b]);
                 }
             }
         }
 #pragma unroll
-        for (int b = 0; b < GB; ++b) {
-            const int gr = gr0 + b * NMW;
-            if (gr >= NG) continue;
-            outp[gr * 64 + lane] = poisoned ? __builtin_nanf("") : o[b] / L[b];
-            if (gr * 64 % D == 0 && lane == 0) {
-                a.stat[((size_t)unit * G + gr * 64 / D) * 2] = M[b];
-                a.stat[((size_t)unit * G + gr * 64 / D) * 2 + 1] = 1.0f / L[b];
+        for (int h = 0; h < HB; ++h) {
+            const int c = c0 + h * NMW;
+            if (c >= NH) continue;
+#pragma unroll
+            for (int b = 0; b < HG; ++b) outp[(c * HG + b) * 64 + lane] = poisoned ? __builtin_nanf("") : o[h * HG + b] / L[h];
+            if (c * HG * 64 % D == 0 && lane == 0) {
+                a.stat[((size_t)unit * G + c * HG * 64 / D) * 2] = M[h];
+                a.stat[((size_t)unit * G + c * HG * 64 / D) * 2 + 1] = 1.0f / L[h];
             }
         }
     }
@@ -516,7 +528,8 @@ __device__ inline void merge_splits(const AttnArgs& a, int unit, int wave, bool 
 // Everything a block does once its waves have put their (max, sum, unnormalised output) into LDS:
 //   1. merge the waves; the only split of a unit writes the result, else publish the split's partial;
 //   2. wait for the published stores, synchronise, take the ticket;
-//   3. in the block that drew the last ticket the upper half of the waves merges the splits and writes the output;
+//   3. in the block that drew the last ticket the upper half of the waves (all of them for a wide output) merges the
+//      splits and writes the output;
 //   4. side phase: this step's logits leave LDS, the previous step's score update is applied.  (The read
 //      stream of the block is over by then.  Doing the score update at the start of the block instead, under the
 //      latency of the first K/V loads, was measured 8% slower: its writes then compete with the ramping stream.
@@ -602,16 +615,17 @@ __device__ inline void finish_split(const AttnArgs& a, const SplitCtx& x, SideRo
         const int arrival = __builtin_amdgcn_readfirstlane(sm.ticket);
         if ((arrival & 0xffff) == S - 1) {
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-            constexpr int NM = NTHR / 2;                  // merging threads: the lower half starts its side phase
-            if (tid >= NM) {
+            // merging threads: the lower half starts its side phase, unless the block has only 4 waves for a wide output
+            constexpr int NM = G * D >= kWideBlockMaxGD ? NTHR : NTHR / 2;
+            if (tid >= NTHR - NM) {
                 // A die-local merge with a block on an unexpected die may have missed partials: its output is NaN
                 // rather than plausible numbers.
-                merge_splits<G, D, NM>(a, unit, __builtin_amdgcn_readfirstlane((tid - NM) >> 6), (arrival >> 16) != 0, outp);
-                if (tid == NM) {                          // ready for the next step
+                merge_splits<G, D, NM>(a, unit, __builtin_amdgcn_readfirstlane((tid - (NTHR - NM)) >> 6), (arrival >> 16) != 0, outp);
+                if (tid == NTHR - NM) {                   // ready for the next step
                     if (a.xcd_local) __hip_atomic_store(a.ticket + unit, 0, __ATOMIC_RELAXED, merge_scope<true>());
                     else __hip_atomic_store(a.ticket + unit, 0, __ATOMIC_RELAXED, merge_scope<false>());
                 }
-                if (tid == NM) BUZZ_STAMP(5);
+                if (tid == NTHR - NM) BUZZ_STAMP(5);
             }
         }
     }

@@ -120,6 +120,18 @@ def test_split_merge_rounds_and_side_rounds(G, D, dtype, splits, prompt):
 
 
 @pytest.mark.parametrize("device_merge", [False, True])
+@pytest.mark.parametrize("G,D,dtype,splits", [(1, 64, "fp16", 17), (1, 256, "bf16", 9), (2, 256, "fp32", 20), (3, 128, "bf16", 33),
+                                              (4, 128, "fp16", 18), (5, 256, "bf16", 10), (6, 256, "fp16", 9), (7, 256, "bf16", 17),
+                                              (8, 64, "bf16", 40), (8, 256, "fp32", 12)])
+def test_merge_rounds_through_one_die_and_device_memory(G, D, dtype, splits, device_merge):
+    """Merges of more splits than one round of loads covers, with every way the outputs of a unit are dealt to the
+    merging waves (whole heads, parts of a head, more heads than waves), in both forms of the merge."""
+    wl = small(batch=1, n_kv_heads=8, n_q_heads=8 * G, head_dim=D, dtype=dtype, prompt=900, decode_steps=5,
+               sink=3, window=780, segment=16, keep=3, evict_every=16, n_obs=8)
+    run(wl, splits=splits, device_merge=device_merge, units=[(0, 0), (0, 5)])
+
+
+@pytest.mark.parametrize("device_merge", [False, True])
 @pytest.mark.parametrize("G,dtype,heads", [(1, "fp16", 8), (4, "bf16", 8), (2, "fp32", 16), (8, "bf16", 8)])
 def test_split_merge_through_one_die_or_device_memory(G, dtype, heads, device_merge):
     """Units that divide evenly over the 8 dies with several splits each: by default a unit's blocks share a
