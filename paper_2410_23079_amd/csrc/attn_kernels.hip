@@ -221,20 +221,30 @@ __device__ inline SplitCtx make_ctx(const AttnArgs& a)
 
 // The tiles of a split: WROWS consecutive rows each, numbered across its (up to three) stored runs from each run's
 // first row on; the row being appended, which comes from the caller's buffer, is a tile of its own at the end.
+// ANCHOR: the tiles of a run sit on a grid of multiples of WROWS physical rows (`lead` rows before its first row are
+// masked), so that a tile's rows are one aligned piece of the arena.
 // A block's waves do not own fixed tiles: apart from the first one each, a wave claims its next tile from a counter
 // in LDS.  (With fixed round-robin tiles the waves launched first -- which the memory pipeline serves first
 // -- ended 15% earlier than the others, and the block waited for the slowest.)
-struct Tile { int lo, phys, cnt, base; bool fresh; };     // run: first logical and physical row, length; first row in it
+// run: first logical and physical row, length and masked rows (both from the anchor on); first row of the tile in it
+struct Tile { int lo, phys, cnt, lead, base; bool fresh; };
 
-template <int WROWS>
+template <int WROWS, bool ANCHOR>
 struct TileMap {
-    int lo0, lo1, lo2, ph0, ph1, ph2, c0, c1, c2, f1, f2, f3, n_tiles, n;
+    int lo0, lo1, lo2, ph0, ph1, ph2, c0, c1, c2, ld0, ld1, ld2, f1, f2, f3, n_tiles, n;
     __device__ inline TileMap(const AttnArgs& a, const SplitCtx& x)
     {
         n = a.n;
         lo0 = x.j0; ph0 = lo0; c0 = min(x.jl1, a.map.front) - lo0;
         lo1 = max(x.j0, a.map.front); ph1 = a.map.ring_base + a.map.ring_head + (lo1 - a.map.front); c1 = min(x.jl1, x.wrap) - lo1;
         lo2 = max(x.j0, x.wrap); ph2 = a.map.ring_base + (lo2 - x.wrap); c2 = x.jl1 - lo2;
+        ld0 = ld1 = ld2 = 0;
+        if constexpr (ANCHOR) {
+            static_assert((WROWS & (WROWS - 1)) == 0, "tiles anchor at multiples of WROWS");
+            if (c0 > 0) c0 += ld0 = ph0 & (WROWS - 1);
+            if (c1 > 0) c1 += ld1 = ph1 & (WROWS - 1);
+            if (c2 > 0) c2 += ld2 = ph2 & (WROWS - 1);
+        }
         f1 = (max(c0, 0) + WROWS - 1) / WROWS;
         f2 = f1 + (max(c1, 0) + WROWS - 1) / WROWS;
         f3 = f2 + (max(c2, 0) + WROWS - 1) / WROWS;
@@ -251,8 +261,9 @@ struct TileMap {
         k.lo = lo0 + (r1 ? lo1 - lo0 : 0) + (r2 ? lo2 - lo1 : 0);
         k.phys = ph0 + (r1 ? ph1 - ph0 : 0) + (r2 ? ph2 - ph1 : 0);
         k.cnt = c0 + (r1 ? c1 - c0 : 0) + (r2 ? c2 - c1 : 0);
+        k.lead = ld0 + (r1 ? ld1 - ld0 : 0) + (r2 ? ld2 - ld1 : 0);
         k.base = (t - (r1 ? f1 : 0) - (r2 ? f2 - f1 : 0)) * WROWS;
-        if (k.fresh) { k.lo = n - 1; k.cnt = 1; k.base = 0; }
+        if (k.fresh) { k.lo = n - 1; k.cnt = 1; k.lead = 0; k.base = 0; }
         return k;
     }
 };
@@ -688,7 +699,7 @@ __global__ __launch_bounds__(NW * 64, BUZZ_MIN_BLOCKS) void attn_split_kernel(co
     // the block.  Writes that trickle into a saturated read stream were measured to cost ~5% of the kernel per 1% of
     // extra bytes.
     struct Buf { u32x4 k[U], v[U]; };
-    const TileMap<WROWS> tiles(a, x);
+    const TileMap<WROWS, false> tiles(a, x);
     const int total = tiles.total();
     auto load_t = [&](u32x4 (&kr)[U], u32x4 (&vr)[U], int t) {
         const Tile k = tiles.locate(t);
@@ -842,7 +853,7 @@ template <> struct Mma<fp16_t> {
     }
 };
 
-template <typename T, int D, int G, bool NT, int NW>
+template <typename T, int D, int G, bool NT, int NW, bool ANCHOR>
 __global__ __launch_bounds__(NW * 64) void attn_split_mfma_kernel(const AttnArgs a)
 {
     constexpr int ROWB = D * 2;
@@ -887,18 +898,20 @@ __global__ __launch_bounds__(NW * 64) void attn_split_mfma_kernel(const AttnArgs
     }
 
     struct Buf { u32x4 k[QP], v[VS][4]; };
-    const TileMap<WROWS> tiles(a, x);
+    const TileMap<WROWS, ANCHOR> tiles(a, x);
     const int total = tiles.total();
+    // row i of a tile, counted from its run's first row; outside the run its nearest row again
+    auto row = [&](const Tile& k, int i) { return (unsigned)(ANCHOR ? min(max(k.base + i, k.lead), k.cnt - 1) - k.lead : min(k.base + i, k.cnt - 1)); };
     auto load_t = [&](u32x4 (&kk)[QP], u32x4 (&vv)[VS][4], int t) {
         const Tile k = tiles.locate(t);
         const char* kp = k.fresh ? (const char*)a.k_new + (size_t)unit * ROWB : Kb + (size_t)k.phys * ROWB;
         const char* vp = k.fresh ? (const char*)a.v_new + (size_t)unit * ROWB : Vb + (size_t)k.phys * ROWB;
-        const unsigned krow = (unsigned)min(k.base + j, k.cnt - 1) * ROWB;   // past the run's end: its last row again
+        const unsigned krow = row(k, j) * ROWB;
 #pragma unroll
         for (int p = 0; p < QP; ++p) kk[p] = load16<NT>(kp + krow + (4 * p + q) * 16);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const unsigned vrow = (unsigned)min(k.base + 4 * q + e, k.cnt - 1) * ROWB;
+            const unsigned vrow = row(k, 4 * q + e) * ROWB;
 #pragma unroll
             for (int t2 = 0; t2 < VS; ++t2) vv[t2][e] = load16<NT>(vp + vrow + ((16 * t2 + j) % NCH) * 16);
         }
@@ -906,7 +919,7 @@ __global__ __launch_bounds__(NW * 64) void attn_split_mfma_kernel(const AttnArgs
 
     auto compute_t = [&](const u32x4 (&kk)[QP], const u32x4 (&vv)[VS][4], int t) {
         const Tile k = tiles.locate(t);
-        const int stg = k.lo - j0 + k.base;               // staging index (row relative to the split's first row)
+        const int stg = k.lo - j0 + k.base - k.lead;      // staging index (row relative to the split's first row)
         f32x4 sacc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int p = 0; p < QP; ++p) sacc = Mma<T>::qk(kk[p], qb[p], sacc);
@@ -914,7 +927,7 @@ __global__ __launch_bounds__(NW * 64) void attn_split_mfma_kernel(const AttnArgs
         float tmax = -INFINITY;
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            const bool ok = k.base + 4 * q + v < k.cnt;
+            const bool ok = k.base + 4 * q + v < k.cnt && (!ANCHOR || k.base + 4 * q + v >= k.lead);
             const float d = sacc[v] * a.scale_log2;
             s[v] = ok ? d : -INFINITY;
             if (ok && j < G) stage[j * a.rows_per_split + stg + 4 * q + v] = d;
@@ -1020,19 +1033,30 @@ template <int G, bool NT> constexpr int unroll_for()
     return G == 1 ? (NT ? BUZZ_U_G1 : BUZZ_U_G1_CACHED) : (G == 2 ? BUZZ_U_G2 : (G <= 4 ? BUZZ_U_G4 : BUZZ_U_G8));
 }
 
+// Streaming matrix-core kernels anchor their tiles where rows are 256 bytes or more and a split is long enough for the
+// partial tile at each end not to count.  Tiles of 4 KB that straddle two aligned ones were up to 3% slower: 512 units of
+// 2000 rows, 2 heads of 128: 86.8 us anchored, 88.1 not; 32 units of 20000 rows, 4 heads: 76.0 and 78.2.  With 350 rows per
+// split the partial tiles and the masks cost 1%, with rows of 128 bytes 3%, from the last-level cache up to 8%.
+constexpr int kAnchorRows = 1024;
+
 template <typename T, int D, int G>
 hipError_t launch_split_t(const AttnArgs& a, int units, hipStream_t st, Timing tm)
 {
     const dim3 grid = a.xcd_local ? dim3(8, a.n_splits, units / 8) : dim3(a.n_splits, units), block(a.waves * 64);
     const size_t lds = (size_t)G * a.rows_per_split * sizeof(float);   // logit staging
     if constexpr (G >= 2 && !std::is_same<T, float>::value) {   // grouped queries on a 16-bit cache: matrix cores
-        if (a.waves == 8) {
-            if (a.streaming) BUZZ_LAUNCH((attn_split_mfma_kernel<T, D, G, true, 8>), grid, block, lds, st, tm, a);
-            else BUZZ_LAUNCH((attn_split_mfma_kernel<T, D, G, false, 8>), grid, block, lds, st, tm, a);
-        } else {
-            if (a.streaming) BUZZ_LAUNCH((attn_split_mfma_kernel<T, D, G, true, 4>), grid, block, lds, st, tm, a);
-            else BUZZ_LAUNCH((attn_split_mfma_kernel<T, D, G, false, 4>), grid, block, lds, st, tm, a);
-        }
+        auto launch = [&](auto nt, auto nw, auto anchor) {
+            BUZZ_LAUNCH((attn_split_mfma_kernel<T, D, G, decltype(nt)::value, decltype(nw)::value, decltype(anchor)::value>), grid, block, lds, st, tm, a);
+        };
+        auto flavour = [&](auto nw) {
+            if (!a.streaming) { launch(std::false_type{}, nw, std::false_type{}); return; }
+            if constexpr (D >= 128) {
+                if (a.rows_per_split >= kAnchorRows) { launch(std::true_type{}, nw, std::true_type{}); return; }
+            }
+            launch(std::true_type{}, nw, std::false_type{});
+        };
+        if (a.waves == 8) flavour(std::integral_constant<int, 8>{});
+        else flavour(std::integral_constant<int, 4>{});
         return hipGetLastError();
     } else {
         constexpr int RPW = 64 / (D / Elem<T>::VEC);

@@ -119,6 +119,17 @@ def test_split_merge_rounds_and_side_rounds(G, D, dtype, splits, prompt):
     run(wl, splits=splits)
 
 
+@pytest.mark.parametrize("G,D,dtype,sink,T,steps", [(2, 128, "bf16", 3, 16, 40), (4, 128, "fp16", 17, 33, 70), (5, 128, "bf16", 0, 7, 20),
+                                                    (3, 256, "fp16", 5, 50, 55)])
+def test_anchored_tiles_of_long_streaming_splits(G, D, dtype, sink, T, steps):
+    """One split of more than 1024 rows per unit, read with the streaming loads: tiles anchored at multiples of 16 physical
+    rows, runs that start and end anywhere, the ring's wrap inside and between tiles."""
+    n = 1200
+    wl = small(batch=1, n_kv_heads=2, n_q_heads=2 * G, head_dim=D, dtype=dtype, prompt=n, decode_steps=steps, sink=sink,
+               window=n - 70, segment=16, keep=3, evict_every=T, n_obs=8)
+    run(wl, splits=1, kv_loads="streaming")
+
+
 @pytest.mark.parametrize("device_merge", [False, True])
 @pytest.mark.parametrize("G,D,dtype,splits", [(1, 64, "fp16", 17), (1, 256, "bf16", 9), (2, 256, "fp32", 20), (3, 128, "bf16", 33),
                                               (4, 128, "fp16", 18), (5, 256, "bf16", 10), (6, 256, "fp16", 9), (7, 256, "bf16", 17),

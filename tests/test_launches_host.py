@@ -2,6 +2,7 @@
 kernel launches in place of the HIP runtime (tests/launch_recorder.cpp).  Device pointers are made up; nothing runs."""
 import ctypes
 import os
+import re
 import shutil
 import subprocess
 
@@ -144,4 +145,24 @@ def test_the_one_launch_eviction_takes_every_segment_that_fits_the_lds(lib, segm
     kernels = [k for k, _ in recorded(lib)]
     assert ["evict_new_rows_kernel" in k for k in kernels] == ([True] if one else [False, False])
     assert all(lib.rec_value(i, b"lds") <= 65536 for _, i in recorded(lib))
+    assert lib.buzz_cache_destroy(h) == 0
+
+
+def prepared(lib, units, G, D, dtype, rows, flags=0):
+    h = create(lib, config(batch=1, n_q_heads=units * G, n_kv_heads=units, head_dim=D, kv_dtype=dtype, window=rows - 5, segment=8,
+                           evict_every=64, max_context=rows + 200, flags=flags))
+    assert lib.buzz_cache_import(h, KP, VP, SP, PP, rows - 1, 0, rows - 1, None) == 0
+    lib.rec_reset(-1)
+    assert lib.buzz_decode_step(h, QP, KP, VP, OUT, None) == 0
+    assert lib.rec_count() == 1
+    return h, lib.rec_kernel(0).decode()
+
+
+@pytest.mark.parametrize("units,G,D,dtype,rows,flags,anchored", [
+    (512, 2, 128, "bf16", 2000, 0, True), (32, 4, 128, "fp16", 20000, 4, True), (128, 2, 256, "bf16", 4000, 4, True),
+    (512, 2, 128, "bf16", 1000, 4, False), (512, 2, 128, "bf16", 2000, 8, False), (512, 2, 64, "bf16", 4000, 4, False)])
+def test_streaming_steps_of_long_splits_anchor_their_tiles(lib, units, G, D, dtype, rows, flags, anchored):
+    h, kernel = prepared(lib, units, G, D, dtype, rows, flags)
+    streaming, anchor = re.search(r"attn_split_mfma_kernel.*Lb([01])ELi[48]ELb([01])E", kernel).groups()
+    assert anchor == "01"[anchored] and (streaming == "1" or not anchored), kernel
     assert lib.buzz_cache_destroy(h) == 0
