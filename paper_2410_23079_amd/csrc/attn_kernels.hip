@@ -238,8 +238,8 @@ struct TileMap {
         lo0 = x.j0; ph0 = lo0; c0 = min(x.jl1, a.map.front) - lo0;
         lo1 = max(x.j0, a.map.front); ph1 = a.map.ring_base + a.map.ring_head + (lo1 - a.map.front); c1 = min(x.jl1, x.wrap) - lo1;
         lo2 = max(x.j0, x.wrap); ph2 = a.map.ring_base + (lo2 - x.wrap); c2 = x.jl1 - lo2;
-        ld0 = ld1 = ld2 = 0;
         if constexpr (ANCHOR) {
+            ld0 = ld1 = ld2 = 0;
             static_assert((WROWS & (WROWS - 1)) == 0, "tiles anchor at multiples of WROWS");
             if (c0 > 0) c0 += ld0 = ph0 & (WROWS - 1);
             if (c1 > 0) c1 += ld1 = ph1 & (WROWS - 1);
@@ -261,9 +261,10 @@ struct TileMap {
         k.lo = lo0 + (r1 ? lo1 - lo0 : 0) + (r2 ? lo2 - lo1 : 0);
         k.phys = ph0 + (r1 ? ph1 - ph0 : 0) + (r2 ? ph2 - ph1 : 0);
         k.cnt = c0 + (r1 ? c1 - c0 : 0) + (r2 ? c2 - c1 : 0);
-        k.lead = ld0 + (r1 ? ld1 - ld0 : 0) + (r2 ? ld2 - ld1 : 0);
+        if constexpr (ANCHOR) k.lead = ld0 + (r1 ? ld1 - ld0 : 0) + (r2 ? ld2 - ld1 : 0); else k.lead = 0;
         k.base = (t - (r1 ? f1 : 0) - (r2 ? f2 - f1 : 0)) * WROWS;
-        if (k.fresh) { k.lo = n - 1; k.cnt = 1; k.lead = 0; k.base = 0; }
+        if (k.fresh) { k.lo = n - 1; k.cnt = 1; k.base = 0; }
+        if (ANCHOR && k.fresh) k.lead = 0;
         return k;
     }
 };
