@@ -16,6 +16,7 @@
 //  - The block that finishes last for a unit (atomic ticket, nobody waits) merges the split partials
 //    into the attention output and publishes (M, 1/L) for the next step's score update.
 #include <stddef.h>
+#include <algorithm>
 #include <type_traits>
 
 #include "buzz_internal.h"
@@ -1034,6 +1035,45 @@ template <int G, bool NT> constexpr int unroll_for()
     return G == 1 ? (NT ? BUZZ_U_G1 : BUZZ_U_G1_CACHED) : (G == 2 ? BUZZ_U_G2 : (G <= 4 ? BUZZ_U_G4 : BUZZ_U_G8));
 }
 
+// Launches a decode kernel so that its blocks come out even.  Of `fit` blocks that a compute unit holds at a time, two
+// rounds may leave the second one nearly empty, while one block less at a time takes as many rounds of equal work (what
+// bounds the blocks is memory, which fewer of them saturate as well).  Then more LDS is asked for than is used, so that
+// fewer fit.  1024 blocks (512 units, 2 splits of 2500 rows, 2 heads of 128): 3 at a time 268 us, 2 at a time 226; 1000
+// units of 1000 rows: 108 and 95; 1000 units of 800 rows, 5 heads: 92 and 85.  From three rounds on the blocks' ends
+// spread by themselves (2000 units of 300 rows: 65 us, 69 with fewer), and short blocks hide each other's starts and
+// ends (1024 units of 200 rows: 20.9 us, 22.0 with fewer).  On the vector ALU up to 4 heads: 1280 units of 700 fp32 rows,
+// 4 heads of 128: 185 and 172 us; 512 units of 1200, 8 heads of 64, which are not bound by memory: 92, 98 with fewer.
+constexpr int kEvenRows = 512;                             // rows per split from which it counts
+constexpr int kLdsPerUnit = 160 * 1024;                    // bytes of LDS of a compute unit
+
+template <void (*kernel)(AttnArgs)>
+void launch_even(const dim3& grid, const dim3& block, size_t lds, hipStream_t st, Timing tm, const AttnArgs& a)
+{
+    struct Footprint { int fit = 0; int64_t lds = 0; };    // resident blocks by registers, bytes of static LDS
+    static const Footprint own = [&] {
+        Footprint f;
+        hipFuncAttributes attr{};
+        int fit = 0;
+        if (hipFuncGetAttributes(&attr, (const void*)kernel) == hipSuccess &&
+            hipOccupancyMaxActiveBlocksPerMultiprocessor(&fit, (const void*)kernel, (int)block.x, 0) == hipSuccess) {
+            f.fit = fit;
+            f.lds = (int64_t)attr.sharedSizeBytes;
+        }
+        return f;
+    }();
+    const int64_t blocks = (int64_t)grid.x * grid.y * grid.z, per = (blocks + a.compute_units - 1) / a.compute_units;
+    const int64_t fit = std::min<int64_t>(own.fit, kLdsPerUnit / (own.lds + (int64_t)lds + 1));
+    auto share = [&](int64_t at_a_time) { return (per + at_a_time - 1) / at_a_time * at_a_time; };   // of blocks, empty places included
+    if (a.rows_per_split >= kEvenRows && fit > 2 && per > fit && per <= 2 * fit) {
+        int64_t best = fit;
+        for (int64_t n = fit - 1; n >= 2; --n)
+            if (share(n) < share(best)) best = n;
+        const int64_t need = kLdsPerUnit / (best + 1) + 1;   // one block more does not fit
+        if (best < fit && need <= 65536) lds = std::max<int64_t>((int64_t)lds, need - own.lds);
+    }
+    BUZZ_LAUNCH(kernel, grid, block, lds, st, tm, a);
+}
+
 // Streaming matrix-core kernels anchor their tiles where rows are 256 bytes or more and a split is long enough for the
 // partial tile at each end not to count.  Tiles of 4 KB that straddle two aligned ones were up to 3% slower: 512 units of
 // 2000 rows, 2 heads of 128: 86.8 us anchored, 88.1 not; 32 units of 20000 rows, 4 heads: 76.0 and 78.2.  With 350 rows per
@@ -1047,7 +1087,7 @@ hipError_t launch_split_t(const AttnArgs& a, int units, hipStream_t st, Timing t
     const size_t lds = (size_t)G * a.rows_per_split * sizeof(float);   // logit staging
     if constexpr (G >= 2 && !std::is_same<T, float>::value) {   // grouped queries on a 16-bit cache: matrix cores
         auto launch = [&](auto nt, auto nw, auto anchor) {
-            BUZZ_LAUNCH((attn_split_mfma_kernel<T, D, G, decltype(nt)::value, decltype(nw)::value, decltype(anchor)::value>), grid, block, lds, st, tm, a);
+            launch_even<attn_split_mfma_kernel<T, D, G, decltype(nt)::value, decltype(nw)::value, decltype(anchor)::value>>(grid, block, lds, st, tm, a);
         };
         auto flavour = [&](auto nw) {
             if (!a.streaming) { launch(std::false_type{}, nw, std::false_type{}); return; }
@@ -1064,13 +1104,17 @@ hipError_t launch_split_t(const AttnArgs& a, int units, hipStream_t st, Timing t
         // a trip covers at least 4 rows
         constexpr int US = unroll_for<G, true>() * RPW >= 4 ? unroll_for<G, true>() : 4 / RPW;     // streaming loads
         constexpr int UC = unroll_for<G, false>() * RPW >= 4 ? unroll_for<G, false>() : 4 / RPW;   // cached loads
-        if (a.waves == 8) {
-            if (a.streaming) BUZZ_LAUNCH((attn_split_kernel<T, D, G, US, true, 8>), grid, block, lds, st, tm, a);
-            else BUZZ_LAUNCH((attn_split_kernel<T, D, G, UC, false, 8>), grid, block, lds, st, tm, a);
-        } else {
-            if (a.streaming) BUZZ_LAUNCH((attn_split_kernel<T, D, G, US, true, 4>), grid, block, lds, st, tm, a);
-            else BUZZ_LAUNCH((attn_split_kernel<T, D, G, UC, false, 4>), grid, block, lds, st, tm, a);
-        }
+        auto launch = [&](auto nt, auto nw) {
+            constexpr bool NT = decltype(nt)::value;
+            constexpr auto kernel = attn_split_kernel<T, D, G, NT ? US : UC, NT, decltype(nw)::value>;
+            if constexpr (G <= 4) launch_even<kernel>(grid, block, lds, st, tm, a);
+            else BUZZ_LAUNCH(kernel, grid, block, lds, st, tm, a);   // the vector ALU bounds these
+        };
+        auto flavour = [&](auto nw) {
+            if (a.streaming) launch(std::true_type{}, nw); else launch(std::false_type{}, nw);
+        };
+        if (a.waves == 8) flavour(std::integral_constant<int, 8>{});
+        else flavour(std::integral_constant<int, 4>{});
         return hipGetLastError();
     }
 }

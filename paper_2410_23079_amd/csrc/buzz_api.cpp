@@ -732,7 +732,7 @@ int decode_step_impl(buzz_cache_t* c, const void* q, const void* k_new, const vo
         a.new_phys = (int32_t)new_phys;
         a.new_pos = (int32_t)c->tokens_seen;
         a.cap = L.cap;
-        a.Hq = cfg.n_q_heads; a.Hkv = cfg.n_kv_heads;
+        a.compute_units = cus;
         a.s_cap = L.s_cap;
         a.scale_log2 = (float)(c->scale * 1.4426950408889634 * c->log_n_factor(c->tokens_seen + 1));
         const double step_bytes = (double)L.units * (double)n * 2.0 * L.row_bytes;

@@ -85,7 +85,7 @@ struct AttnArgs {
     int32_t rows_per_split;
     int32_t n_splits;
     int32_t s_cap;
-    int32_t Hq, Hkv;
+    int32_t compute_units;
     int32_t waves;       // waves per block: 4, or 8 when every unit is a single split
     int32_t pending;     // 1: the previous step's score update has not been applied yet
     int32_t streaming;   // 1: K/V are read with the non-temporal hint (working set exceeds the last-level cache)

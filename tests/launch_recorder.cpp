@@ -90,6 +90,8 @@ hipError_t hipExtLaunchKernel(const void* fn, dim3 grid, dim3 block, void** args
 hipError_t hipGetLastError() { const hipError_t e = last_error; last_error = hipSuccess; return e; }
 hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
 hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) { *v = kDefaultCUs; return hipSuccess; }
+hipError_t hipFuncGetAttributes(hipFuncAttributes* f, const void*) { *f = hipFuncAttributes{}; f->sharedSizeBytes = 8000; return hipSuccess; }
+hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int* n, const void*, int block, size_t) { *n = 3 * 256 / block; return hipSuccess; }   // 3 waves per SIMD
 hipError_t hipGetSymbolAddress(void** p, const void*) { *p = symbol_memory; return hipSuccess; }
 hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t) { memcpy(d, s, n); return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }

@@ -166,3 +166,16 @@ def test_streaming_steps_of_long_splits_anchor_their_tiles(lib, units, G, D, dty
     streaming, anchor = re.search(r"attn_split_mfma_kernel.*Lb([01])ELi[48]ELb([01])E", kernel).groups()
     assert anchor == "01"[anchored] and (streaming == "1" or not anchored), kernel
     assert lib.buzz_cache_destroy(h) == 0
+
+
+@pytest.mark.parametrize("units,rows,resident", [
+    (1000, 1000, 2), (1024, 600, 2), (512, 5000, 2),         # 4 blocks per compute unit: 2 + 2, not 3 + 1
+    (1300, 600, 3), (1280, 1000, 3),                         # 5 or 6 of them: 3 + 3 as well
+    (768, 1000, 3), (512, 2000, 3), (2000, 700, 3), (1024, 300, 3)])   # one round, many rounds, short blocks: as they come
+def test_two_rounds_of_blocks_come_out_even(lib, units, rows, resident):
+    """The recorder's kernels have three waves per SIMD and 8000 bytes of LDS of their own: the LDS that a step asks for
+    says how many of its 4-wave blocks a compute unit takes at a time."""
+    h, kernel = prepared(lib, units, 2, 64, "bf16", rows, 8)
+    assert lib.rec_value(0, b"block_x") == 256
+    assert min(3, 160 * 1024 // (8000 + lib.rec_value(0, b"lds"))) == resident
+    assert lib.buzz_cache_destroy(h) == 0
