@@ -271,7 +271,8 @@ int buzz_cache_override_die_map(buzz_cache_t* cache, int64_t die_map);
  */
 typedef struct buzz_profile {
     int64_t attn_launches;     /* split decode-attention kernel */
-    int64_t epilogue_launches; /* score flush kernel (pending score update applied before an eviction or export) */
+    int64_t epilogue_launches; /* score flush kernel (pending score update applied to every row before an eviction
+                                  that moves old rows; an export applies it inside its copy, which is not timed) */
     int64_t evictions;         /* whole evictions (all their kernels) */
     double attn_ms, epilogue_ms, evict_ms; /* summed device time */
     double attn_row_bytes;     /* sum over attn launches of units * rows * 2 * head_dim * sizeof(element) */

@@ -148,7 +148,7 @@ template <int LPR> __device__ inline float row_sum(float v) {
 
 __device__ inline float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
-// How split partials travel between the blocks of one launch (finish_split_scoped).
+// How split partials travel between the blocks of one launch (finish_split).
 //
 // Device-wide form (blocks of a unit possibly on different dies, each die with its own L2).  A block writes
 // its partial with relaxed device-scope atomic stores (`sc1`: written through the die's L2 to the memory

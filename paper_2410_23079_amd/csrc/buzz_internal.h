@@ -46,7 +46,7 @@ inline int stage_floats(int G, int D)
     if (f < kStageFloats) f = kStageFloats;
     return f;
 }
-constexpr double kLastLevelCacheBytes = 256.0 * 1024 * 1024;   // Infinity Cache of one MI355X      // segment scores of one wave must fit its LDS slice
+constexpr double kLastLevelCacheBytes = 256.0 * 1024 * 1024;   // Infinity Cache of one MI355X
 
 struct RingMap {
     int32_t front;      // rows [0, front) are stored linearly

@@ -462,7 +462,9 @@ hipError_t launch_obs_mfma_t(ObsArgs a, int units, hipStream_t st, Timing tm)
     // A step whose longest block is no more than its share of two blocks per compute unit stays whole: the long
     // blocks start first and have the SIMDs more and more to themselves, and parts would only repeat the blocks'
     // prologue (64 heads of 128, 4096 queries: 347 us whole, 385 us cut).  Below that it is cut for four blocks
-    // per compute unit (16 heads on 4 kv heads, 4001 queries: 622 us whole, 369 us cut; six or eight: the same).
+    // per compute unit (64 heads of 128 on 16 units, 4001 queries: prefill and export 644 us whole, 342 cut).  Eight or
+    // twelve blocks per unit gave 320 and 323 us there, but 146 instead of 131 us with heads of 256 and 385-390
+    // instead of 378 for 256 heads with 256 queries, so four stays.
     auto split = [&](int64_t total, int longest, bool whole, int most, int* parts, int* len) {
         const int64_t cus = a.compute_units;
         int64_t l = whole && longest <= (total + 2 * cus - 1) / (2 * cus) ? longest : (total + 4 * cus - 1) / (4 * cus);
