@@ -597,6 +597,7 @@ int buzz_prefill(buzz_cache_t* c, const void* kp, const void* vp, int64_t N, con
         if (int rc = probe_die_placement(st)) return rc;
         // prompt scores, one row of N per unit: what the scoring leaves, or the caller's (NULL: all zero)
         const float* ps = n_obs > 0 ? c->at<float>(L.pscore) : init_score;
+        bool placed = false;
         if (n_obs > 0) {
             c->ready = c->pending = false;                      // from here on the scoring overwrites the logits of the last step
             const int max_q = kObsPassRows;                     // queries of one head per pass
@@ -612,10 +613,16 @@ int buzz_prefill(buzz_cache_t* c, const void* kp, const void* vp, int64_t N, con
                 oa.partial = c->at<float>(L.obs_partial);
                 oa.stats_cap = L.obs_stats_cap; oa.partial_cap = L.obs_partial_cap;
                 oa.compute_units = compute_units();
+                // A prompt that is kept whole goes to the cache with its last pass: the keys that the scoring reads are
+                // stored while it computes, and so are the values.
+                if (survivors == 0 && tail_rows == N - sink_rows && t0 + max_q >= n_obs)
+                    oa.place = PromptPlace{1, RingMap{(int32_t)sink_rows, L.ring_base, 0, L.ring_cap}, vp, c->at<char>(L.K), c->at<char>(L.V),
+                                           c->at<float>(L.score), c->at<int32_t>(L.pos), c->at<int32_t>(L.ticket), L.cap};
                 if (hipError_t e = launch_obs_scores(cfg.kv_dtype, cfg.head_dim, oa, L.units, st)) return hip_rc(e);
+                placed = oa.place.on != 0;
             }
         }
-        // one launch places every row: sink, survivors behind it, the tail at the start of the ring
+        // otherwise one launch places every row: sink, survivors behind it, the tail at the start of the ring
         GatherArgs g{};
         g.srcK = kp; g.srcV = vp; g.srcScore = ps;
         g.src_unit_rows = N; g.src_step = 1;
@@ -639,7 +646,8 @@ int buzz_prefill(buzz_cache_t* c, const void* kp, const void* vp, int64_t N, con
             if (hipError_t e = launch_segment_topk(sa, L.units, st)) return hip_rc(e);
             g.sel = c->at<int32_t>(L.sel); g.sel_stride = L.sel_stride; g.sel_step = (int32_t)sel_step;
         }
-        if (hipError_t e = launch_gather_rows(g, L.units, st)) return hip_rc(e);
+        if (!placed)
+            if (hipError_t e = launch_gather_rows(g, L.units, st)) return hip_rc(e);
     }
     c->pending = false;
     c->sink_filled = sink_rows;

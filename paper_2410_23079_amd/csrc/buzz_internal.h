@@ -155,6 +155,18 @@ struct GatherArgs {
     int32_t G;
 };
 
+// Where the scoring puts a prompt that is kept whole: a key's row is map.phys(key).
+struct PromptPlace {
+    int32_t on;                // 0: the scores go to ObsArgs::score and nothing is placed
+    RingMap map;
+    const void* V_from;        // [units][N][D]
+    void* K; void* V;          // [units][rows][D]
+    float* score;              // [units][rows]
+    int32_t* pos;              // [units][rows]
+    int32_t* ticket;           // [units] arrival counters of the decode step to clear
+    int64_t rows;
+};
+
 struct ObsArgs {               // prefill scoring: causal attention of observed prompt queries (one pass)
     const void* K;             // [units][N][D]
     const void* q_obs;         // [B][Hq][n_obs][D]; query t sits at prompt position N - n_obs + t
@@ -175,6 +187,7 @@ struct ObsArgs {               // prefill scoring: causal attention of observed 
     int32_t key_parts, key_part_len, item_parts, item_part_len;
     int32_t heads, units;      // B * Hq, B * Hkv (set by the launch)
     float scale_log2;
+    PromptPlace place;         // on in the last pass of a prompt that is kept whole
 };
 
 constexpr int kObsPassRows = 4096;   // prompt scoring: queries per head and pass

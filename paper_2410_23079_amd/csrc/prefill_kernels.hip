@@ -18,6 +18,16 @@ __device__ inline float score_so_far(const ObsArgs& a, size_t i)
     return a.first_pass ? (a.init ? a.init[i] : 0.f) : a.score[i];
 }
 
+// the pass's result for a key: the prompt score so far, or, where the call places the prompt itself, the cache's row
+__device__ inline void put_score(const ObsArgs& a, int unit, int key, float v)
+{
+    if (!a.place.on) { a.score[(size_t)unit * a.N + key] = v; return; }
+    const size_t to = (size_t)unit * a.place.rows + a.place.map.phys(key);
+    a.place.score[to] = v;
+    a.place.pos[to] = key;
+    if (key == 0) a.place.ticket[unit] = 0;
+}
+
 // ---------------------------------------------------------------------------------------------------
 // One template serves both steps and all types.  A wave keeps 64 (fp32: 32) "stationary" vectors in registers as the
 // B operand (column tiles of 16) and streams tiles of 16 "moving" vectors through the A
@@ -122,12 +132,47 @@ struct MovingChunk {
             *(u32x4*)(buf + row * PITCH + col * 16) = r[k];
         }
     }
+    // the same pieces to their rows of the cache (the unit's rows start at `to`)
+    static __device__ inline void place(char* to, const RingMap& map, const u32x4 (&r)[PER_THREAD], int row0, int last_row)
+    {
+#pragma unroll
+        for (int k = 0; k < PER_THREAD; ++k) {
+            const int piece = threadIdx.x + 256 * k, row = row0 + piece / PIECES, col = piece % PIECES;
+            if (row <= last_row) __builtin_nontemporal_store(r[k], (u32x4*)(to + (size_t)map.phys(row) * ROWB + col * 16));
+        }
+    }
     // A operand of tile `tile` (16 rows) of the chunk for this lane
     static __device__ inline void fetch(u32x4 (&f)[ROWB / 64], const char* buf, int tile, int j, int q)
     {
         const char* row = buf + (16 * tile + j) * PITCH + q * 16;
 #pragma unroll
         for (int p = 0; p < ROWB / 64; ++p) f[p] = *(const u32x4*)(row + p * 64);
+    }
+};
+
+// Value rows j_block .. j_block + ROWS - 1 of a unit on their way to the cache, up to 16 pieces per thread in flight at once.
+template <int ROWB, int ROWS>
+struct ValueRows {
+    static constexpr int PIECES = ROWB / 16, N = ROWS * PIECES / 256, BATCH = N < 16 ? N : 16;   // pieces per row, per thread, at a time
+    static_assert(ROWS * PIECES % 256 == 0 && N % BATCH == 0, "whole rounds");
+    u32x4 r[BATCH];
+    __device__ inline void request(const ObsArgs& a, int unit, int j_block, int k0)
+    {
+        const char* from = (const char*)a.place.V_from + (size_t)unit * a.N * ROWB;
+#pragma unroll
+        for (int k = 0; k < BATCH; ++k) {
+            const int piece = threadIdx.x + 256 * (k0 + k);
+            r[k] = __builtin_nontemporal_load((const u32x4*)(from + (size_t)min(j_block + piece / PIECES, a.N - 1) * ROWB + piece % PIECES * 16));
+        }
+    }
+    __device__ inline void store(const ObsArgs& a, int unit, int j_block, int k0) const
+    {
+        char* to = (char*)a.place.V + (size_t)unit * a.place.rows * ROWB;
+#pragma unroll
+        for (int k = 0; k < BATCH; ++k) {
+            const int piece = threadIdx.x + 256 * (k0 + k), row = j_block + piece / PIECES;
+            if (row < a.N) __builtin_nontemporal_store(r[k], (u32x4*)(to + (size_t)a.place.map.phys(row) * ROWB + piece % PIECES * 16));
+        }
     }
 };
 
@@ -156,11 +201,12 @@ __global__ __launch_bounds__(256) void obs_mfma_kernel(const ObsArgs a)
 
     if constexpr (STEP == 1) {
         // the latest queries see the most keys: their blocks go first, for all heads, so that the launch
-        // ends with the short blocks (the grid is linear, the head advances first, then the part, then the group)
-        const int head = blockIdx.x % a.heads, slot = blockIdx.x / a.heads;   // b * Hq + h
+        // ends with the short blocks (the grid is linear, the head advances first, then the part, then the group).
+        // Heads run over the units first: where these divide evenly over the 8 dies, a unit's heads share one, whose L2
+        // then serves the keys (32 heads on 4 units each, 1535 queries: prefill and export 189 -> 183 us, 64 on 16: 355 -> 352).
+        const int at = blockIdx.x % a.heads, slot = blockIdx.x / a.heads;
+        const int unit = at % a.units, head = unit * G + at / a.units;   // b * Hkv + kvh, b * Hq + h
         const int part = slot % a.key_parts, group = slot / a.key_parts;
-        const int b = head / a.Hq, h = head - b * a.Hq;
-        const int unit = b * a.Hkv + h / G;
         const int t_block = a.t_begin + ((a.t_count - 1) / BLOCK_COLS - group) * BLOCK_COLS;
         const int t_base = t_block + wave * COLS;
         const bool active = t_base < t_end;                // a wave without queries still copies and synchronises
@@ -230,8 +276,15 @@ __global__ __launch_bounds__(256) void obs_mfma_kernel(const ObsArgs a)
                 l[ct] += tile_sum(acc, ct, k0, std::true_type{});
             }
         };
+        // A prompt that is kept whole is placed by the scoring itself, which reads the keys anyway and is not bound by
+        // memory: the blocks of the latest queries of a unit's first head stream every key of the unit once and store it
+        // here, the first blocks of step 2 carry the values (256 heads of 128, 256 queries, 4096 keys: 94 + 96 + 160 us
+        // for the steps and a placement of their own, 120 + 170 so; prefill and export 504 -> 450 us).
+        const bool places = a.place.on && at < a.units && group == 0;
+        char* K_to = (char*)a.place.K + (size_t)unit * a.place.rows * ROWB;
         MC::request(staged, Kb, c_begin * CH, a.N - 1);
         MC::store(sm_rows[c_begin & 1], staged);
+        if (places) MC::place(K_to, a.place.map, staged, c_begin * CH, a.N - 1);
         __syncthreads();
         for (int c = c_begin; c < c_end; ++c) {
             const bool more = c + 1 < c_end;
@@ -276,7 +329,10 @@ __global__ __launch_bounds__(256) void obs_mfma_kernel(const ObsArgs a)
                     }
                 }
             }
-            if (more) MC::store(sm_rows[(c + 1) & 1], staged);
+            if (more) {
+                MC::store(sm_rows[(c + 1) & 1], staged);
+                if (places) MC::place(K_to, a.place.map, staged, (c + 1) * CH, a.N - 1);
+            }
             __syncthreads();
         }
         if (!active) return;
@@ -310,6 +366,16 @@ __global__ __launch_bounds__(256) void obs_mfma_kernel(const ObsArgs a)
         if (part > 0 && item0 >= n_items) return;          // fewer parts here (part 0 carries the scores over)
         const int j_base = j_block + wave * COLS;
         const bool active = j_base < a.N;
+        ValueRows<ROWB, BLOCK_COLS> values;
+        const bool places = a.place.on && part == 0;
+        if (places) {
+#pragma unroll 1
+            for (int k0 = values.BATCH; k0 < values.N; k0 += values.BATCH) {
+                values.request(a, unit, j_block, k0);
+                values.store(a, unit, j_block, k0);
+            }
+        }
+        if (places) values.request(a, unit, j_block, 0);
         const char* Kb = (const char*)a.K + (size_t)unit * a.N * ROWB;
         u32x4 kf[CT][QP];
         float col[CT];
@@ -358,10 +424,13 @@ __global__ __launch_bounds__(256) void obs_mfma_kernel(const ObsArgs a)
                 }
             }
         };
+        if (places) values.store(a, unit, j_block, 0);
         if (item0 < n_items) {
             request(item0);
             store(item0 & 1);
         }
+        __builtin_amdgcn_s_waitcnt(0x0F70);                // vmcnt(0): else the loop waits for the stationary rows, and with
+                                                           // them for the rows it has just requested, in every tile
         __syncthreads();
         for (int item = item0; item < n_items; ++item) {
             const bool more = item + 1 < n_items;
@@ -398,8 +467,7 @@ __global__ __launch_bounds__(256) void obs_mfma_kernel(const ObsArgs a)
             c += __shfl_xor(c, 32);
             const int key = j_base + 16 * ct + j;
             if (a.item_parts == 1) {
-                const size_t at = (size_t)unit * a.N + key;
-                if (q == 0 && key < a.N) a.score[at] = score_so_far(a, at) + c;
+                if (q == 0 && key < a.N) put_score(a, unit, key, score_so_far(a, (size_t)unit * a.N + key) + c);
             } else {
                 const int keys = visible_keys(a);
                 if (q == 0 && key < keys) a.partial[((size_t)part * a.units + unit) * keys + key] = c;
@@ -448,7 +516,7 @@ __global__ __launch_bounds__(256) void obs_sum_parts_kernel(const ObsArgs a, int
     float s = score_so_far(a, at);
 #pragma unroll
     for (int p = 0; p < kObsItemParts; ++p) s += got[p];
-    a.score[at] = s;
+    put_score(a, unit, j, s);
 }
 
 template <int DT, int D>

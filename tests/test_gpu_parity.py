@@ -611,6 +611,38 @@ def test_capacity_error_when_eviction_is_skipped():
     torch.cuda.synchronize()
 
 
+@pytest.mark.parametrize("dtype,D", [("fp32", 64), ("fp32", 256), ("bf16", 64), ("fp16", 128), ("bf16", 256)])
+@pytest.mark.parametrize("units,G,N,n_obs,sink", [(1, 1, 1, 1, 4), (2, 3, 64, 1, 0), (3, 1, 65, 65, 4), (8, 2, 257, 257, 300), (2, 2, 1000, 130, 4),
+                                                  (1, 1, 4200, 4200, 1)])
+def test_a_scored_prompt_that_is_kept_whole_is_placed_by_the_scoring(dtype, D, units, G, N, n_obs, sink):
+    """Rows and positions bit-exact, scores against 64-bit column sums, and a decode step on the cache: the workspace
+    holds garbage before, so whatever the placement leaves out shows.  Bars: scores 1e-5 of their norm (32-bit sums), outputs 1e-4."""
+    from paper_2410_23079_amd import BuzzCache, BuzzConfig
+    print(f"[placement] {dtype} D{D} units{units} G{G} N{N} n_obs{n_obs} sink{sink}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(N * 7 + D)
+    dt = {"fp32": torch.float32, "fp16": torch.float16, "bf16": torch.bfloat16}[dtype]
+    k, v, q, kn, vn, qn = (torch.randn(*shape, D, generator=g, device="cuda").to(dt) for shape in
+                           ((1, units, N), (1, units, N), (1, units * G, n_obs), (1, units), (1, units), (1, units * G)))
+    c = BuzzCache(BuzzConfig(1, units * G, units, D, dtype, sink, 16, 16, 1, N + 16, N + 8, old_stride=1))
+    c.workspace.fill_(0xFF)
+    c.prefill(k, v, q_obs=q)
+    K, V, score, pos = c.export()
+    assert torch.equal(K, k) and torch.equal(V, v)
+    assert torch.equal(pos, torch.arange(N, device="cuda", dtype=torch.int32).expand(1, units, N))
+    s = torch.matmul(q.double().view(units, G * n_obs, D), k[0].double().transpose(1, 2).contiguous()) / D ** 0.5
+    at = torch.arange(N - n_obs, N, device="cuda").repeat(G)
+    s.masked_fill_(torch.arange(N, device="cuda")[None] > at[:, None], -float("inf"))
+    ref = torch.softmax(s, -1).sum(1)
+    assert float((score[0] - ref).norm() / ref.norm()) < 1e-5
+    out = torch.empty(1, units * G, D, device="cuda")
+    for _ in range(2):                                       # the second step finds the counters as the first left them
+        c.decode_step(qn, kn, vn, out)
+    Ka, Va = (torch.cat([x[0].double(), y[0, :, None].double(), y[0, :, None].double()], 1) for x, y in ((k, kn), (v, vn)))
+    p = torch.softmax(torch.matmul(qn.double().view(units, G, D), Ka.transpose(1, 2).contiguous()) / D ** 0.5, -1)
+    want = torch.matmul(p, Va).view(1, units * G, D)
+    assert float((out - want).abs().max() / want.abs().max()) < 1e-4
+
+
 def test_log_n_scale_argument():
     """Sec. 3.5: the log-n variant only changes the softmax scale, which is a configuration argument."""
     import math
