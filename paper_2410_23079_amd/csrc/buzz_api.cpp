@@ -209,6 +209,9 @@ int make_layout(const buzz_config_t* c, Layout* L)
 
 }  // namespace
 
+// What auto_splits prices a step with (us): a row of a split, a split, and what a split saves at least.
+struct SplitModel { double row_us, split_us, whole_us; };
+
 struct buzz_cache {
     uint32_t magic;
     buzz_config_t cfg;
@@ -220,6 +223,7 @@ struct buzz_cache {
     bool ready;
     int64_t sink_filled, n_old, tail, head, tokens_seen;
     int32_t user_splits;
+    SplitModel split_model;
     int64_t die_map_override;   // >= 0: use this instead of the placement probe's record (failure-handling tests)
     // the score update of the last decode step is applied lazily (by the next step or by a flush)
     bool pending;
@@ -513,6 +517,10 @@ int buzz_cache_create(const buzz_config_t* cfg, void* dev_workspace, size_t byte
     c->ready = false;
     c->sink_filled = c->n_old = c->tail = c->head = c->tokens_seen = 0;
     c->user_splits = 0;
+    const bool matrix = L.G >= 2 && cfg->kv_dtype != BUZZ_FP32, die_local = L.units % 8 == 0 && !(cfg->flags & BUZZ_FLAG_DEVICE_MERGE);
+    c->split_model.row_us = (matrix ? 0.0078 : 0.009 * (1.0 + 0.237 * (L.G - 1))) * pow(L.row_bytes / 256.0, 0.63);
+    c->split_model.split_us = (0.0366 + 0.006 * (L.units < 12 ? L.units : 12)) * (1.0 + 0.056 * (L.G - 1));
+    c->split_model.whole_us = die_local ? 1.0 + 0.01 * L.units : 1.6;
     c->die_map_override = -1;
     c->pending = false;
     c->last_buf = 0;
@@ -663,6 +671,36 @@ int buzz_prefill(buzz_cache_t* c, const void* kp, const void* vp, int64_t N, con
 
 namespace {
 
+// Key-range splits of a decode step, the automatic choice.  Few, long blocks amortise the per-block merge, and a block
+// count that fills every compute unit the same number of times avoids a tail: at most one block per compute unit
+// (floor(CUs / units) splits; with at least one unit per compute unit a unit is a single block and nothing is merged
+// across blocks at all).  A short step takes fewer: a block needs row_us per row of its split, whose loads it waits for
+// more than it streams, and the merge split_us per split, more where the partial results are larger or the units many.
+// row_us n / S + split_us S is least at the root below; a cache whose rows take less than the publishing and merging does
+// (whole_us) stays whole, up to 128 rows also one that a split does not save 2.6 us more: the launch that the counters of
+// the static scratch cost, and both entry points split alike.  Beyond 8 splits the merge goes by rounds of 8 and 16
+// loads: the counts between 8 and 16, and between 16 and 24, were slower than the nearer of the two.  Around the root the
+// time is flat to what the model leaves out (the tiles of a split over its waves), so splits of 128 rows, one 16-row tile
+// per wave, stay unless the model gains 0.4 us.  The constants are a fit to 840 shapes (1 to 64 units of 80 to 12000 rows,
+// groups of 1 to 8, heads of 64 to 256, all types, 5 to 23 split counts each): 4% less time on average than with splits of
+// at least 128 rows, none longer; 8 units of 300 rows, one head of 64 in fp32, 6.16 us with 3 splits and 5.46 with 5 or 6;
+// 1 unit of 12000 rows, 4 heads of 128 in bf16, 13.1 us with 94 and 10.7 with 32.
+int64_t auto_splits(const buzz_cache_t* c, int64_t n, int cus)
+{
+    const SplitModel& m = c->split_model;
+    const int64_t units = c->L.units;
+    if (units >= cus) return 1;
+    const double rows_us = m.row_us * (double)n;
+    if (rows_us <= m.whole_us + (n <= 128 ? 2.6 : 0.0)) return 1;
+    const int64_t most = cus / units, long_splits = ceil_div(n, 128) < most ? ceil_div(n, 128) : most;
+    auto us = [&](int64_t s) { return rows_us / (double)s + m.split_us * (double)s; };
+    int64_t S = (int64_t)(sqrt(rows_us / m.split_us) + 0.5);
+    if (S < 2) S = 2;
+    if (S > 8) S = S < 12 ? 8 : S < 22 ? 16 : (S + 4) / 8 * 8;
+    if (S > most) S = most;
+    return long_splits > 1 && us(long_splits) - us(S) < 0.4 ? long_splits : S;
+}
+
 // One decode step.  static_scratch: the split-softmax scratch (arrival counters, per-split partials) is the
 // library's static device array instead of the caller's workspace.
 int decode_step_impl(buzz_cache_t* c, const void* q, const void* k_new, const void* v_new, float* out,
@@ -701,15 +739,9 @@ int decode_step_impl(buzz_cache_t* c, const void* q, const void* k_new, const vo
                 : (new_phys < L.ring_base || new_phys >= (int64_t)L.ring_base + L.ring_cap || new_phys >= L.cap))
         return BUZZ_ECAPACITY;
     if (sink_filled + c->n_old > L.ring_base) return BUZZ_ECAPACITY;
-    // Key-range splits.  Few, long blocks amortise the per-block merge, and a block count that fills every
-    // compute unit the same number of times avoids a tail.  Automatic choice: one block per compute unit, 8
-    // waves wide (floor(CUs / units) splits); with at least one unit per CU a unit is a single block and nothing
-    // is merged across blocks at all.
     const int cus = compute_units();
     const int tile = attn_tile_rows(cfg.kv_dtype, cfg.head_dim, L.G);
-    int64_t S = c->user_splits > 0 ? c->user_splits : (L.units >= cus ? 1 : cus / L.units);
-    // a split of fewer than kMinSplitRows rows costs more in merge latency than it saves in streaming
-    if (c->user_splits == 0 && S > ceil_div(n, kMinSplitRows)) S = ceil_div(n, kMinSplitRows);
+    int64_t S = c->user_splits > 0 ? c->user_splits : auto_splits(c, n, cus);
     if (S < 1) S = 1;
     if (S > L.s_cap) S = L.s_cap;
     int64_t rps = ceil_div(ceil_div(n, S), tile) * tile;

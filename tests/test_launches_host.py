@@ -179,3 +179,30 @@ def test_two_rounds_of_blocks_come_out_even(lib, units, rows, resident):
     assert lib.rec_value(0, b"block_x") == 256
     assert min(3, 160 * 1024 // (8000 + lib.rec_value(0, b"lds"))) == resident
     assert lib.buzz_cache_destroy(h) == 0
+
+
+@pytest.mark.parametrize("dtype,G,D", [("fp32", 1, 64), ("fp32", 8, 256), ("bf16", 4, 128), ("bf16", 8, 64), ("fp16", 1, 128)])
+@pytest.mark.parametrize("units", [1, 7, 8, 16, 32, 255, 256, 300])
+@pytest.mark.parametrize("rows", [17, 90, 130, 400, 1000, 5000, 12000])
+def test_the_automatic_split_count(lib, dtype, G, D, units, rows):
+    """A few rows are not split, a step has at most one block per compute unit unless the logits of a split would not fit
+    the LDS, and the entry point with the static scratch splits the same (its results are the same bits)."""
+    def splits(n, static=False):
+        h = create(lib, config(batch=1, n_q_heads=units * G, n_kv_heads=units, head_dim=D, kv_dtype=dtype, window=n - 5, segment=8,
+                               evict_every=64, max_context=n + 200, flags=0))
+        assert lib.buzz_cache_import(h, KP, VP, SP, PP, n - 1, 0, n - 1, None) == 0
+        lib.rec_reset(-1)
+        assert (lib.buzz_decode_step_static if static else lib.buzz_decode_step)(h, QP, KP, VP, OUT, None) == 0
+        last = lib.rec_count() - 1
+        grid = [lib.rec_value(last, b"grid_" + x) for x in (b"x", b"y", b"z")]
+        s, rest = divmod(grid[0] * grid[1] * grid[2], units)
+        assert rest == 0
+        assert (lib.rec_count() == 2) == (static and s > 1)  # the counters' clearing
+        assert lib.buzz_cache_destroy(h) == 0
+        return s
+    lib.buzz_decode_step_static.argtypes = [ctypes.c_void_p] * 6
+    s = splits(rows)
+    assert s <= max(1, 256 // units) or s <= -(-rows * G // (4096 - 260 * G)) + 1
+    assert rows > 64 or s == 1
+    if units * s * G * (D + 2) * 4 <= 8 << 20:
+        assert splits(rows, True) == s
