@@ -292,9 +292,24 @@ __global__ __launch_bounds__(256) void evict_new_rows_kernel(const EvictArgs a)
 // and one of V, both requested before either is stored; rows are spread over as many blocks as that takes.  That is the
 // shape in which a copy is fastest on this chip (1 GB device to device: one piece per thread 6.2 TB/s, four 5.7,
 // eight 4.2); with 64 rows per block and four dependent load-store rounds per thread this kernel moved 5.0 TB/s.
-// Nothing of a copy is read twice: non-temporal loads and stores (32 units of 7668 rows of 512 bytes, copied in and out:
-// 111 us with ordinary accesses, 102 with non-temporal stores, 98 with both; no size was slower, from 8 x 1512 rows up).
+// Non-temporal accesses where data is not read again before the last-level cache (256 MB) has turned over: what a caller
+// hands in or gets back, and the cache's rows on their way out if they are more than it holds.  Rows that go into the
+// cache are stored normally and stay there for what comes next.  Placed and exported again, both in turn: 228 MB 159 us
+// with non-temporal accesses only, 119 so; 120 MB 87 and 69; 511 MB 339 and 317 (with the rows read back through the
+// last-level cache as well 369); 15 MB 17.4 and 14.8.
 // The block's first threads carry the rows' scores and positions, one row each.
+template <bool NTS> __device__ inline u32x4 load_piece(const char* p)
+{
+    if constexpr (NTS) return __builtin_nontemporal_load((const u32x4*)p);
+    else return *(const u32x4*)p;
+}
+template <bool NTD> __device__ inline void store_piece(char* p, const u32x4& v)
+{
+    if constexpr (NTD) __builtin_nontemporal_store(v, (u32x4*)p);
+    else *(u32x4*)p = v;
+}
+
+template <bool NTS, bool NTD>
 __global__ __launch_bounds__(256) void gather_rows_kernel(const GatherArgs a, const int lpr_log2)
 {
     const int unit = blockIdx.y, tid = threadIdx.x;
@@ -314,10 +329,10 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(const GatherArgs a, co
         const int c = (tid & ((1 << lpr_log2) - 1)) * 16;
         const size_t so = (sbase + sp) * a.row_bytes + c, dof = (dbase + place(r)) * a.row_bytes + c;
         u32x4 k, v;
-        if (a.dstK) k = __builtin_nontemporal_load((const u32x4*)((const char*)a.srcK + so));
-        if (a.dstV) v = __builtin_nontemporal_load((const u32x4*)((const char*)a.srcV + so));
-        if (a.dstK) __builtin_nontemporal_store(k, (u32x4*)((char*)a.dstK + dof));
-        if (a.dstV) __builtin_nontemporal_store(v, (u32x4*)((char*)a.dstV + dof));
+        if (a.dstK) k = load_piece<NTS>((const char*)a.srcK + so);
+        if (a.dstV) v = load_piece<NTS>((const char*)a.srcV + so);
+        if (a.dstK) store_piece<NTD>((char*)a.dstK + dof, k);
+        if (a.dstV) store_piece<NTD>((char*)a.dstV + dof, v);
     }
     if (tid < rows && r0 + tid < a.n_rows) {
         const int src = source(r0 + tid), sp = a.src_map.ring_cap ? a.src_map.phys(src) : src;
@@ -392,7 +407,10 @@ hipError_t launch_gather_rows(const GatherArgs& a, int units, hipStream_t st, Ti
     if ((16 << lpr_log2) != a.row_bytes || lpr_log2 > 6) return hipErrorInvalidValue;
     const int rows = 256 >> lpr_log2;
     dim3 grid(a.n_rows > 0 ? (a.n_rows + rows - 1) / rows : 1, units), block(256);
-    BUZZ_LAUNCH(gather_rows_kernel, grid, block, 0, st, tm, a, lpr_log2);
+    if (a.stream_src && a.stream_dst) BUZZ_LAUNCH((gather_rows_kernel<true, true>), grid, block, 0, st, tm, a, lpr_log2);
+    else if (a.stream_src) BUZZ_LAUNCH((gather_rows_kernel<true, false>), grid, block, 0, st, tm, a, lpr_log2);
+    else if (a.stream_dst) BUZZ_LAUNCH((gather_rows_kernel<false, true>), grid, block, 0, st, tm, a, lpr_log2);
+    else BUZZ_LAUNCH((gather_rows_kernel<false, false>), grid, block, 0, st, tm, a, lpr_log2);
     return hipGetLastError();
 }
 
