@@ -397,7 +397,7 @@ int evict_impl(buzz_cache_t* c, hipStream_t st)
             SelectArgs sa{};
             sa.score = c->at<float>(L.score); sa.unit_stride = L.cap;
             sa.map = c->map(); sa.lo = (int32_t)k; sa.new_count = (int32_t)mid;
-            sa.segment = (int32_t)(mid > kMaxWaveSegment ? mid : kMaxWaveSegment);   // one segment, whatever its length
+            sa.segment = (int32_t)mid;                          // one segment, whatever its length
             sa.keep = L.keep; sa.ignore_scores = 0;
             sa.sel = c->at<int32_t>(L.sel); sa.sel_stride = L.sel_stride;
             if (hipError_t e = launch_segment_topk(sa, L.units, st, prof_pair(c, 2))) return hip_rc(e);
@@ -647,7 +647,7 @@ int buzz_prefill(buzz_cache_t* c, const void* kp, const void* vp, int64_t N, con
             sa.score = ps; sa.unit_stride = N;
             sa.map = RingMap{0, 0, 0, 0};
             sa.lo = (int32_t)k; sa.new_count = (int32_t)M;
-            sa.segment = global ? (int32_t)(M > kMaxWaveSegment ? M : kMaxWaveSegment) : cfg.segment;
+            sa.segment = global ? (int32_t)M : cfg.segment;
             sa.keep = L.keep;
             sa.ignore_scores = ((cfg.flags & BUZZ_FLAG_INTERVAL_NEW) || !ps) ? 1 : 0;   // no scores: all equal
             sa.sel = c->at<int32_t>(L.sel); sa.sel_stride = L.sel_stride;

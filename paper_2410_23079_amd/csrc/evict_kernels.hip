@@ -136,14 +136,18 @@ __global__ __launch_bounds__(256) void segment_topk_kernel(const SelectArgs a)
     rank_segment(sc, len, take, lane, [&](int r, int e) { out[r] = a.lo + start + e; });
 }
 
-// Segments too long for one wave's slice of the LDS (and the single segment of the H2O-style variant, which
-// spans every row between sink and window): one block per (segment, unit) finds the `take` largest scores by a
-// radix select on the order-preserving integer image of the scores -- four passes of a 256-bin histogram in
-// LDS, most significant byte first, each narrowing the candidates to one bin -- which ends with the key of the
-// last survivor and the number of rows with exactly that key that still fit.  A final pass in index order keeps
-// every row with a larger key and the first of the equal ones (ties go to the lowest index), and numbers the
-// survivors with a block-wide prefix sum so that they come out in index order.  Same result as the wave kernel.
-constexpr int kTopkBlock = 1024;
+// Long segments, the single segment of the H2O-style variant among them, which spans every row between sink and window:
+// one block per (segment, unit) finds the `take` largest scores by a radix select on the order-preserving integer image of
+// the scores -- up to three passes of a histogram in LDS, most significant digit first, each narrowing the candidates to
+// one bin -- which ends with the digits of the last survivor's key and the number of rows with these digits that still
+// fit.  Every row above survives and the first of the equal ones do (ties go to the lowest index).  Same result as the wave
+// kernel, whose work grows with the square of the length.
+// A wave takes a contiguous run of the rows, 64 at a time, so that rows are numbered by ballots and two counts per wave,
+// without a barrier per 1024 rows.  Up to 16 of a wave's rounds stay in registers (segments of 16384 rows); longer segments
+// are read again in each pass, 16 rounds in flight.  Digits of 11 bits keep the exponent and two more bits in the first: a
+// prompt's scores then spread over a few dozen bins, where one byte puts nearly all of them into four, on whose counters
+// the lanes of a wave queue.
+constexpr int kTopkBlock = 1024, kTopkWaves = kTopkBlock / 64, kTopkRounds = 16, kTopkBins = 2048;
 
 __device__ inline unsigned score_key(float v)      // larger score <=> larger key; NaN ranks with -inf; -0 == +0
 {
@@ -152,77 +156,101 @@ __device__ inline unsigned score_key(float v)      // larger score <=> larger ke
     return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
 }
 
-// exclusive prefix count of `flag` over the block in thread order, and the block total (both via LDS `tmp`,
-// one slot per wave plus one); every thread of the block must call it
-__device__ inline int block_prefix(bool flag, int* tmp, int& total)
-{
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
-    const unsigned long long m = __ballot(flag);
-    if (lane == 0) tmp[wave] = __popcll(m);
-    __syncthreads();
-    int before = 0, sum = 0;
-    for (int w = 0; w < nw; ++w) { const int c = tmp[w]; before += w < wave ? c : 0; sum += c; }
-    __syncthreads();                               // tmp is reused by the next call
-    total = sum;
-    return before + __popcll(m & ((1ull << lane) - 1ull));
-}
-
+template <bool HELD>
 __global__ __launch_bounds__(kTopkBlock) void segment_topk_block_kernel(const SelectArgs a)
 {
-    __shared__ int hist[256];
-    __shared__ int tmp[kTopkBlock / 64];
+    __shared__ int hist[kTopkBins];
+    __shared__ int wave_sum[kTopkWaves], wave_equal[kTopkWaves];
     __shared__ unsigned sh_prefix;
-    __shared__ int sh_remaining;
-    const int tid = threadIdx.x, seg = blockIdx.x, unit = blockIdx.y;
+    __shared__ int sh_remaining, sh_all;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), seg = blockIdx.x, unit = blockIdx.y;
+    const unsigned long long below = (1ull << lane) - 1ull;
     const long long start = (long long)seg * a.segment;
     const int len = (int)min((long long)a.segment, (long long)a.new_count - start);
     const int take = min(a.keep, len);
     if (take <= 0) return;
     const float* base = a.score + (size_t)unit * a.unit_stride;
+    const int run = ((len + kTopkWaves - 1) / kTopkWaves + 63) & ~63, first = wave * run, last = min(len, first + run);   // this wave's rows
     auto key_of = [&](int e) {
-        const int row = a.lo + (int)start + e;
+        const int row = a.lo + (int)start + min(e, len - 1);
         return a.ignore_scores ? 0x80000000u : score_key(base[a.map.ring_cap ? a.map.phys(row) : row]);
     };
-    // radix select: after the pass for byte b, `prefix` holds the top bytes of the last survivor's key and
-    // `remaining` how many rows are still to be taken among those that share them
+    unsigned held[kTopkRounds];
+    auto load = [&](int e0) {
+#pragma unroll
+        for (int i = 0; i < kTopkRounds; ++i) held[i] = key_of(e0 + 64 * i + lane);
+    };
+    if (HELD) load(first);
+    // f(key, row) for this wave's rows, in order
+    auto for_rows = [&](auto f) {
+#pragma unroll 1
+        for (int e0 = first; e0 < last; e0 += 64 * kTopkRounds) {
+            if (!HELD) load(e0);
+#pragma unroll
+            for (int i = 0; i < kTopkRounds; ++i) {
+                if (e0 + 64 * i >= last) break;
+                f(held[i], e0 + 64 * i + lane);
+            }
+        }
+    };
+    // after the pass for a digit, `prefix` holds the digits so far of the last survivor's key and `remaining` how many
+    // rows are still to be taken among those that share them
     unsigned prefix = 0, mask = 0;
     int remaining = take;
-    for (int shift = 24; shift >= 0; shift -= 8) {
-        if (tid < 256) hist[tid] = 0;
+#pragma unroll 1
+    for (int shift = 21; shift >= -1; shift -= 11) {        // bits 31..21, 20..10, 9..0
+        const int at = max(shift, 0);
+        const unsigned digit = shift < 0 ? 1023u : 2047u;
+        for (int i = tid; i < kTopkBins; i += kTopkBlock) hist[i] = 0;
         __syncthreads();
-        for (int e = tid; e < len; e += kTopkBlock) {
-            const unsigned k = key_of(e);
-            if ((k & mask) == prefix) atomicAdd(&hist[(k >> shift) & 255u], 1);
+        for_rows([&](unsigned k, int e) { if (e < last && (k & mask) == prefix) atomicAdd(&hist[(k >> at) & digit], 1); });
+        __syncthreads();
+        // the bin where the count from the largest digit down reaches `remaining`: a suffix sum, two bins per thread
+        const int low = hist[2 * tid], high = hist[2 * tid + 1];
+        int upto = low + high;                             // this lane's bins and those above, in the wave
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int v = __shfl_down(upto, off);
+            if (lane + off < 64) upto += v;
         }
+        if (lane == 0) wave_sum[wave] = upto;
         __syncthreads();
-        if (tid == 0) {
-            int left = remaining, bin = 255;
-            for (; bin > 0; --bin) {               // from the largest digit down: the bin where the count runs out
-                if (hist[bin] >= left) break;
-                left -= hist[bin];
-            }
-            sh_prefix = prefix | ((unsigned)bin << shift);
-            sh_remaining = left;
+        for (int w = wave + 1; w < kTopkWaves; ++w) upto += wave_sum[w];
+        const int above = upto - low - high;
+        if (above < remaining && remaining <= upto) {
+            const bool in_high = above + high >= remaining;
+            sh_prefix = prefix | ((unsigned)(2 * tid + (in_high ? 1 : 0)) << at);
+            sh_remaining = remaining - above - (in_high ? 0 : high);
+            sh_all = sh_remaining == (in_high ? high : low);
         }
         __syncthreads();
         prefix = sh_prefix; remaining = sh_remaining;
-        mask |= 255u << shift;
-        __syncthreads();
+        mask |= digit << at;
+        if (sh_all) break;                                 // every row of the bin survives
     }
-    // prefix = key of the last survivor; `remaining` (>= 1) rows with that key survive, the lowest indices first
-    int ties_seen = 0, kept_seen = 0;
+    // rows with larger digits and the first `remaining` with equal ones
+    int n_larger = 0, n_equal = 0;
+    for_rows([&](unsigned k, int e) {
+        n_larger += __popcll(__ballot(e < last && (k & mask) > prefix));
+        n_equal += __popcll(__ballot(e < last && (k & mask) == prefix));
+    });
+    __syncthreads();                                       // wave_sum is read above
+    if (lane == 0) { wave_sum[wave] = n_larger; wave_equal[wave] = n_equal; }
+    __syncthreads();
+    int equal = 0, kept = 0;                               // before this wave's run
+    for (int w = 0; w < wave; ++w) {
+        kept += wave_sum[w] + min(max(remaining - equal, 0), wave_equal[w]);
+        equal += wave_equal[w];
+    }
     int* out = a.sel + (size_t)unit * a.sel_stride + (size_t)seg * a.keep;
-    for (int e0 = 0; e0 < len; e0 += kTopkBlock) {
-        const int e = e0 + tid;
-        const unsigned k = e < len ? key_of(e) : 0u;
-        const bool eq = e < len && k == prefix, gt = e < len && k > prefix;
-        int n_eq, n_kp;
-        const int eq_before = ties_seen + block_prefix(eq, tmp, n_eq);
-        const bool kp = gt || (eq && eq_before < remaining);
-        const int pos = kept_seen + block_prefix(kp, tmp, n_kp);
-        if (kp) out[pos] = a.lo + (int)start + e;
-        ties_seen += n_eq; kept_seen += n_kp;
-    }
+    for_rows([&](unsigned k, int e) {
+        const unsigned long long ties = __ballot(e < last && (k & mask) == prefix);
+        const bool keeps = e < last && ((k & mask) > prefix || ((k & mask) == prefix && equal + __popcll(ties & below) < remaining));
+        const unsigned long long kept_here = __ballot(keeps);
+        if (keeps) out[kept + __popcll(kept_here & below)] = a.lo + (int)start + e;
+        kept += __popcll(kept_here);
+        equal += __popcll(ties);
+    });
 }
 
 // Eviction of the new rows in one launch, for caches whose old rows stay in place.  A wave ranks one segment
@@ -384,13 +412,21 @@ hipError_t launch_evict_new_rows(const EvictArgs& a, int units, hipStream_t st, 
     return hipGetLastError();
 }
 
-hipError_t launch_segment_topk(const SelectArgs& a, int units, hipStream_t st, Timing tm)
+hipError_t launch_segment_topk(SelectArgs a, int units, hipStream_t st, Timing tm)
 {
     const int n_seg = (a.new_count + a.segment - 1) / a.segment;
     if (n_seg <= 0) return hipSuccess;
-    if (a.segment > kMaxWaveSegment) {             // a segment's scores no longer fit a wave's slice of the LDS
-        if (n_seg > 65535) return hipErrorInvalidValue;
-        BUZZ_LAUNCH(segment_topk_block_kernel, dim3(n_seg, units), dim3(kTopkBlock), 0, st, tm, a);
+    if (n_seg == 1) a.segment = a.new_count;       // no longer than what there is
+    // A wave per segment takes 1.35e-4 us times the square of the length, however few there are; a block per segment 3 us,
+    // and 0.022 us per block where there are many.  (Prefill and export, wave / block: 4 units, 300 rows 24.9 / 17.5 us,
+    // 1000 rows 159 / 17.4, 4000 rows 2307 / 17.5; 32 units and 8192 rows in segments of 300, 400 and 700: 29.1 / 38.2,
+    // 40.7 / 32.2, 87 / 27.8; 32768 rows in segments of 300 and 700: 66 / 123, 118 / 80.)
+    const double length = a.segment, block_us = 3.0 + 0.022 * (double)n_seg * units;
+    if (a.segment > kMaxWaveSegment || (a.segment >= 256 && block_us < 1.35e-4 * length * length)) {
+        if ((int64_t)n_seg * kTopkBlock > UINT32_MAX) return hipErrorInvalidValue;
+        const dim3 grid(n_seg, units), block(kTopkBlock);
+        if (a.segment <= kTopkWaves * 64 * kTopkRounds) BUZZ_LAUNCH(segment_topk_block_kernel<true>, grid, block, 0, st, tm, a);
+        else BUZZ_LAUNCH(segment_topk_block_kernel<false>, grid, block, 0, st, tm, a);
         return hipGetLastError();
     }
     dim3 grid((n_seg + kSelWaves - 1) / kSelWaves, units), block(256);

@@ -567,6 +567,45 @@ def test_segments_longer_than_one_wave_can_rank(segment, keep):
               evict_every=segment + 1000, n_obs=16))
 
 
+@pytest.mark.parametrize("segment,rows,keep,global_topk", [(255, 600, 31, False), (256, 773, 1, False), (256, 773, 255, False), (300, 2999, 40, False),
+                                                           (1023, 1023, 100, False), (1025, 1025, 1024, False), (4000, 9000, 3, False),
+                                                           (16384, 16384, 2000, False), (16385, 16385, 2000, False), (64, 40001, 5000, True),
+                                                           (64, 257, 200, True)])
+@pytest.mark.parametrize("values", ["distinct", "three", "equal", "odd"])
+def test_selection_of_long_segments(segment, rows, keep, global_topk, values):
+    """Whole segments, remainders and the lengths at which the selection changes its kernel or the place of its keys,
+    against a stable sort on the CPU: score descending, ties to the lowest index, NaN lowest, -0 equal to +0."""
+    from paper_2410_23079_amd import FLAG_GLOBAL_TOPK, BuzzCache, BuzzConfig
+    print(f"[selection] segment {segment} rows {rows} keep {keep} global {global_topk} {values}", flush=True)
+    sink, window, units, D, N = 3, 7, 2, 64, rows + 10
+    g = torch.Generator().manual_seed(segment + rows)
+    score = torch.exp(torch.randn(1, units, N, generator=g))
+    if values == "three":
+        score = torch.floor(torch.rand(1, units, N, generator=g) * 3.0)
+    elif values == "equal":
+        score = torch.full((1, units, N), -2.5)
+    elif values == "odd":
+        odd = torch.tensor([float("nan"), float("inf"), -float("inf"), 0.0, -0.0, -1.0, 1e-40, -1e-40])
+        score = odd[torch.randint(0, 8, (1, units, N), generator=g)]
+    k = torch.randn(1, units, N, D, generator=g).to("cuda", torch.bfloat16)
+    c = BuzzCache(BuzzConfig(1, units, units, D, "bf16", sink, window, segment, keep, rows, N, old_stride=1,
+                             flags=FLAG_GLOBAL_TOPK if global_topk else 0))
+    c.prefill(k, k, init_score=score.cuda())
+    K, _, _, pos = c.export()
+    s = score.double()
+    s = torch.where(s.isnan(), torch.full_like(s, -float("inf")), s)[0]
+    step, want = rows if global_topk else segment, []
+    for u in range(units):
+        kept = list(range(sink))
+        for lo in range(sink, sink + rows, step):
+            hi = min(lo + step, sink + rows)
+            kept += sorted((torch.sort(s[u, lo:hi], descending=True, stable=True).indices[:keep] + lo).tolist())
+        want.append(kept + list(range(N - window, N)))
+    want = torch.tensor(want, dtype=torch.int32)
+    assert torch.equal(pos[0].cpu(), want)
+    assert torch.equal(K[0], torch.gather(k[0], 1, want.long().cuda()[..., None].expand(-1, -1, D)))
+
+
 def test_long_segments_with_nan_and_infinite_scores():
     st = run(small(prompt=11000, decode_steps=4, sink=4, window=64, segment=5000, keep=40, evict_every=6000, n_obs=12),
              plant=plant_odd_scores)
