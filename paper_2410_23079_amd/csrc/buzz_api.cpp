@@ -651,11 +651,11 @@ int buzz_prefill(buzz_cache_t* c, const void* kp, const void* vp, int64_t N, con
             sa.keep = L.keep;
             sa.ignore_scores = ((cfg.flags & BUZZ_FLAG_INTERVAL_NEW) || !ps) ? 1 : 0;   // no scores: all equal
             sa.sel = c->at<int32_t>(L.sel); sa.sel_stride = L.sel_stride;
-            if (hipError_t e = launch_segment_topk(sa, L.units, st)) return hip_rc(e);
             g.sel = c->at<int32_t>(L.sel); g.sel_stride = L.sel_stride; g.sel_step = (int32_t)sel_step;
-        }
-        if (!placed)
+            if (hipError_t e = launch_place_sampled(sa, g, L.units, st)) return hip_rc(e);
+        } else if (!placed) {
             if (hipError_t e = launch_gather_rows(g, L.units, st)) return hip_rc(e);
+        }
     }
     c->pending = false;
     c->sink_filled = sink_rows;

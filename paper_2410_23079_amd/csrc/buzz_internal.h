@@ -213,6 +213,7 @@ struct Timing { hipEvent_t begin = nullptr, end = nullptr; };
 hipError_t launch_attn_split(int dtype, int D, int G, const AttnArgs& a, int units, hipStream_t st, Timing tm = {});
 hipError_t launch_flush_scores(int G, const AttnArgs& a, int units, hipStream_t st, Timing tm = {});
 hipError_t launch_segment_topk(SelectArgs a, int units, hipStream_t st, Timing tm = {});
+hipError_t launch_place_sampled(SelectArgs a, const GatherArgs& g, int units, hipStream_t st);
 hipError_t launch_gather_rows(const GatherArgs& a, int units, hipStream_t st, Timing tm = {});
 hipError_t launch_clear_f32(float* dst, int64_t n, hipStream_t st);
 hipError_t launch_plain_copy(void* dst, const void* src, size_t bytes, hipStream_t st);

@@ -337,12 +337,11 @@ template <bool NTD> __device__ inline void store_piece(char* p, const u32x4& v)
     else *(u32x4*)p = v;
 }
 
-template <bool NTS, bool NTD>
-__global__ __launch_bounds__(256) void gather_rows_kernel(const GatherArgs a, const int lpr_log2)
+// The copy of rows row_of(i0), row_of(i0 + 1), ... by one block, as many as it has threads for; row_of(i) >= n_rows: none.
+template <bool NTS, bool NTD, typename RowOf>
+__device__ inline void copy_rows(const GatherArgs& a, int lpr_log2, int unit, int i0, RowOf row_of)
 {
-    const int unit = blockIdx.y, tid = threadIdx.x;
-    const int rows = 256 >> lpr_log2;              // rows per block, 1 << lpr_log2 pieces each
-    const int r0 = blockIdx.x * rows;
+    const int tid = threadIdx.x, rows = 256 >> lpr_log2;   // rows per block, 1 << lpr_log2 pieces each
     const size_t sbase = (size_t)unit * a.src_unit_rows, dbase = (size_t)unit * a.dst_unit_rows;
     auto source = [&](int r) {
         if (a.sel && r >= a.sel_lo && r < a.sel_hi)
@@ -350,8 +349,7 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(const GatherArgs a, co
         return a.src_start + r * a.src_step + (r >= a.sel_hi ? a.tail_shift : 0);
     };
     auto place = [&](int r) { return a.dst_map.ring_cap ? a.dst_map.phys(a.dst_start + r) : a.dst_start + r; };
-    if (a.ticket && blockIdx.x == 0 && tid == 0) a.ticket[unit] = 0;
-    const int r = r0 + (tid >> lpr_log2);
+    const int r = row_of(i0 + (tid >> lpr_log2));
     if (r < a.n_rows) {
         const int src = source(r), sp = a.src_map.ring_cap ? a.src_map.phys(src) : src;
         const int c = (tid & ((1 << lpr_log2) - 1)) * 16;
@@ -362,9 +360,11 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(const GatherArgs a, co
         if (a.dstK) store_piece<NTD>((char*)a.dstK + dof, k);
         if (a.dstV) store_piece<NTD>((char*)a.dstV + dof, v);
     }
-    if (tid < rows && r0 + tid < a.n_rows) {
-        const int src = source(r0 + tid), sp = a.src_map.ring_cap ? a.src_map.phys(src) : src;
-        const size_t d = dbase + place(r0 + tid);
+    if (tid >= rows) return;
+    const int rs = row_of(i0 + tid);
+    if (rs < a.n_rows) {
+        const int src = source(rs), sp = a.src_map.ring_cap ? a.src_map.phys(src) : src;
+        const size_t d = dbase + place(rs);
         if (a.dstScore) {
             float v = a.srcScore ? a.srcScore[sbase + sp] : 0.f;
             if (a.logit_prev)
@@ -374,6 +374,76 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(const GatherArgs a, co
             a.dstScore[d] = v;
         }
         if (a.dstPos) a.dstPos[d] = a.srcPos ? a.srcPos[sbase + sp] : src;
+    }
+}
+
+template <bool NTS, bool NTD>
+__global__ __launch_bounds__(256) void gather_rows_kernel(const GatherArgs a, const int lpr_log2)
+{
+    if (a.ticket && blockIdx.x == 0 && threadIdx.x == 0) a.ticket[blockIdx.y] = 0;
+    copy_rows<NTS, NTD>(a, lpr_log2, blockIdx.y, blockIdx.x * (256 >> lpr_log2), [](int i) { return i; });
+}
+
+// Placement of a sampled prompt in one launch: the first `seg_blocks` blocks of a unit give a wave to each segment, which
+// ranks it and moves its survivors, as many pieces per lane in flight as four passes have; the others copy sink and window
+// rows meanwhile.  Bound by memory traffic; a launch of its own for the ranking left the memory idle while it
+// ran and read its list back (32 units of 32768 rows, 64 per segment, 8 kept, a window of 4096: prefill and export 87.9 us, 82.5 so).
+__global__ __launch_bounds__(256) void place_sampled_kernel(const SelectArgs a, const GatherArgs g, const int lpr_log2, const int seg_blocks)
+{
+    extern __shared__ __attribute__((aligned(16))) float lds[];   // [kSelWaves][wave_slice(segment + keep)]: scores, then kept offsets
+    const int unit = blockIdx.y;
+    if (g.ticket && blockIdx.x == 0 && threadIdx.x == 0) g.ticket[unit] = 0;
+    if ((int)blockIdx.x >= seg_blocks) {
+        const int sampled = g.sel_hi - g.sel_lo;
+        copy_rows<true, false>(g, lpr_log2, unit, (blockIdx.x - seg_blocks) * (256 >> lpr_log2), [&](int i) { return i < g.sel_lo ? i : i + sampled; });
+        return;
+    }
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, seg = blockIdx.x * kSelWaves + wave;
+    const int n_seg = (a.new_count + a.segment - 1) / a.segment;
+    if (seg >= n_seg) return;                      // no block-wide barrier below: a wave only reads what it wrote
+    const int start = seg * a.segment, len = min(a.segment, a.new_count - start), take = min(a.keep, len);
+    float* sc = lds + wave * wave_slice(a.segment + a.keep);
+    int* kept = (int*)sc + a.segment;
+    const float* base = a.score + (size_t)unit * a.unit_stride + a.lo + start;
+    if (a.ignore_scores) {                         // all equal: the lowest indices win
+        for (int r = lane; r < take; r += 64) kept[r] = r;
+    } else {
+        for (int e = lane; e < len; e += 64) {
+            const float v = base[e];
+            sc[e] = v != v ? -INFINITY : v;        // NaN ranks below everything
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        rank_segment(sc, len, take, lane, [&](int r, int e) { kept[r] = e; });
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    constexpr int U = 4;
+    const int rows = 64 >> lpr_log2, rr = lane >> lpr_log2, c = (lane & ((1 << lpr_log2) - 1)) * 16;   // rows per pass, this lane's
+    const size_t from = ((size_t)unit * g.src_unit_rows + a.lo + start) * g.row_bytes + c;
+    const size_t to_row = (size_t)unit * g.dst_unit_rows + g.sel_lo + (size_t)seg * a.keep, to = to_row * g.row_bytes + c;
+    for (int r0 = rr; r0 < take; r0 += U * rows) {
+        u32x4 k[U], v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (r0 + u * rows >= take) break;
+            const size_t at = from + (size_t)kept[r0 + u * rows] * g.row_bytes;
+            k[u] = load_piece<true>((const char*)g.srcK + at);
+            v[u] = load_piece<true>((const char*)g.srcV + at);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (r0 + u * rows >= take) break;
+            const size_t at = to + (size_t)(r0 + u * rows) * g.row_bytes;
+            store_piece<false>((char*)g.dstK + at, k[u]);
+            store_piece<false>((char*)g.dstV + at, v[u]);
+        }
+    }
+    for (int r = lane; r < take; r += 64) {
+        g.dstScore[to_row + r] = g.srcScore ? base[kept[r]] : 0.f;
+        g.dstPos[to_row + r] = a.lo + start + kept[r];
     }
 }
 
@@ -412,17 +482,22 @@ hipError_t launch_evict_new_rows(const EvictArgs& a, int units, hipStream_t st, 
     return hipGetLastError();
 }
 
+// Whether a block per segment selects faster than a wave per segment.  The latter takes 1.35e-4 us times the square of the
+// length, however few there are; a block 3 us, and 0.022 us per block where there are many.  (Prefill and export, wave /
+// block: 4 units, 300 rows 24.9 / 17.5 us, 1000 rows 159 / 17.4, 4000 rows 2307 / 17.5; 32 units and 8192 rows in segments
+// of 300, 400 and 700: 29.1 / 38.2, 40.7 / 32.2, 87 / 27.8; 32768 rows in segments of 300 and 700: 66 / 123, 118 / 80.)
+static bool block_selects(int segment, int n_seg, int units)
+{
+    const double length = segment, block_us = 3.0 + 0.022 * (double)n_seg * units;
+    return segment > kMaxWaveSegment || (segment >= 256 && block_us < 1.35e-4 * length * length);
+}
+
 hipError_t launch_segment_topk(SelectArgs a, int units, hipStream_t st, Timing tm)
 {
     const int n_seg = (a.new_count + a.segment - 1) / a.segment;
     if (n_seg <= 0) return hipSuccess;
     if (n_seg == 1) a.segment = a.new_count;       // no longer than what there is
-    // A wave per segment takes 1.35e-4 us times the square of the length, however few there are; a block per segment 3 us,
-    // and 0.022 us per block where there are many.  (Prefill and export, wave / block: 4 units, 300 rows 24.9 / 17.5 us,
-    // 1000 rows 159 / 17.4, 4000 rows 2307 / 17.5; 32 units and 8192 rows in segments of 300, 400 and 700: 29.1 / 38.2,
-    // 40.7 / 32.2, 87 / 27.8; 32768 rows in segments of 300 and 700: 66 / 123, 118 / 80.)
-    const double length = a.segment, block_us = 3.0 + 0.022 * (double)n_seg * units;
-    if (a.segment > kMaxWaveSegment || (a.segment >= 256 && block_us < 1.35e-4 * length * length)) {
+    if (block_selects(a.segment, n_seg, units)) {
         if ((int64_t)n_seg * kTopkBlock > UINT32_MAX) return hipErrorInvalidValue;
         const dim3 grid(n_seg, units), block(kTopkBlock);
         if (a.segment <= kTopkWaves * 64 * kTopkRounds) BUZZ_LAUNCH(segment_topk_block_kernel<true>, grid, block, 0, st, tm, a);
@@ -435,12 +510,40 @@ hipError_t launch_segment_topk(SelectArgs a, int units, hipStream_t st, Timing t
     return hipGetLastError();
 }
 
+// 16-byte pieces per row: a power of two, at most 64; its logarithm, or -1
+static int pieces_log2(int row_bytes)
+{
+    int lpr_log2 = 0;
+    while ((16 << lpr_log2) < row_bytes) ++lpr_log2;
+    return (16 << lpr_log2) == row_bytes && lpr_log2 <= 6 ? lpr_log2 : -1;
+}
+
+// Selection and placement of a sampled prompt.  One launch where waves rank the segments, every survivor is kept and the
+// survivors of a segment are at most what a wave moves at a time, 256 pieces (64 units of 4096 rows of 512 bytes, 25 of 200
+// kept: 52 us in one launch, 47 in two), else two launches.  Many segments with one survivor or less than half a wave's pieces
+// take two as well (32 units of 32768 rows of 256 bytes, 1 of 5 kept: 130 and 120 us; 2 of 16 kept: 69 and 76.5); few save the launch.
+hipError_t launch_place_sampled(SelectArgs a, const GatherArgs& g, int units, hipStream_t st)
+{
+    const int n_seg = (a.new_count + a.segment - 1) / a.segment, lpr_log2 = pieces_log2(g.row_bytes);
+    if (n_seg == 1) a.segment = a.new_count;
+    const size_t lds = (size_t)kSelWaves * (size_t)wave_slice(a.segment + a.keep) * sizeof(float);   // segment and keep are below 2^28
+    if (lpr_log2 < 0) return hipErrorInvalidValue;
+    const int64_t pieces = (int64_t)a.keep << lpr_log2, waves = (int64_t)n_seg * units;
+    if (g.sel_step != 1 || block_selects(a.segment, n_seg, units) || pieces > 256 || ((pieces < 32 || a.keep < 2) && waves > 4096) || lds > 65536) {
+        if (hipError_t e = launch_segment_topk(a, units, st)) return e;
+        return launch_gather_rows(g, units, st);
+    }
+    const int seg_blocks = (n_seg + kSelWaves - 1) / kSelWaves, rows = 256 >> lpr_log2;
+    const int others = g.n_rows - (g.sel_hi - g.sel_lo);
+    hipLaunchKernelGGL(place_sampled_kernel, dim3(seg_blocks + (others + rows - 1) / rows, units), dim3(256), lds, st, a, g, lpr_log2, seg_blocks);
+    return hipGetLastError();
+}
+
 hipError_t launch_gather_rows(const GatherArgs& a, int units, hipStream_t st, Timing tm)
 {
     if (a.n_rows <= 0 && !a.ticket) return hipSuccess;
-    int lpr_log2 = 0;                              // 16-byte pieces per row: a power of two, at most 64
-    while ((16 << lpr_log2) < a.row_bytes) ++lpr_log2;
-    if ((16 << lpr_log2) != a.row_bytes || lpr_log2 > 6) return hipErrorInvalidValue;
+    const int lpr_log2 = pieces_log2(a.row_bytes);
+    if (lpr_log2 < 0) return hipErrorInvalidValue;
     const int rows = 256 >> lpr_log2;
     dim3 grid(a.n_rows > 0 ? (a.n_rows + rows - 1) / rows : 1, units), block(256);
     if (a.stream_src && a.stream_dst) BUZZ_LAUNCH((gather_rows_kernel<true, true>), grid, block, 0, st, tm, a, lpr_log2);

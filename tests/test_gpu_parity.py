@@ -606,6 +606,44 @@ def test_selection_of_long_segments(segment, rows, keep, global_topk, values):
     assert torch.equal(K[0], torch.gather(k[0], 1, want.long().cuda()[..., None].expand(-1, -1, D)))
 
 
+@pytest.mark.parametrize("dtype,D", [("bf16", 64), ("fp16", 128), ("fp32", 256)])
+@pytest.mark.parametrize("units,segment,keep,rows,window", [(1, 16, 1, 16, 0), (3, 16, 2, 331, 5), (2, 64, 8, 1000, 70), (1, 64, 16, 64, 1),
+                                                            (5, 7, 7, 100, 16), (2, 250, 5, 777, 300), (40, 5, 1, 2003, 9), (2, 64, 33, 640, 33)])
+@pytest.mark.parametrize("scored", [True, False])
+def test_sampled_prompts_are_placed_in_one_launch_or_two(dtype, D, units, segment, keep, rows, window, scored):
+    """Either way of the rule, at its edges: rows, scores and positions against a stable sort on the CPU, from a workspace
+    that holds garbage; without scores the first rows of a segment survive."""
+    from paper_2410_23079_amd import BuzzCache, BuzzConfig
+    print(f"[sampled] {dtype} D{D} units{units} s{segment} c{keep} rows{rows} w{window} scored{scored}", flush=True)
+    sink, N = 2, 2 + rows + window
+    g = torch.Generator().manual_seed(segment * 1000 + rows + D)
+    score = torch.floor(torch.randn(1, units, N, generator=g) * 8.0)
+    dt = {"fp32": torch.float32, "fp16": torch.float16, "bf16": torch.bfloat16}[dtype]
+    k, v = (torch.randn(1, units, N, D, generator=g).to("cuda", dt) for _ in range(2))
+    c = BuzzCache(BuzzConfig(1, units, units, D, dtype, sink, window, segment, keep, rows, N + 4, old_stride=1))
+    c.workspace.fill_(0xFF)
+    c.prefill(k, v, init_score=score.cuda() if scored else None)
+    K, V, S, pos = c.export()
+    want = []
+    for u in range(units):
+        kept = list(range(sink))
+        for lo in range(sink, sink + rows, segment):
+            s = score[0, u, lo:min(lo + segment, sink + rows)] if scored else torch.zeros(min(segment, sink + rows - lo))
+            kept += sorted((torch.sort(s, descending=True, stable=True).indices[:keep] + lo).tolist())
+        want.append(kept + list(range(N - window, N)))
+    want = torch.tensor(want)
+    assert torch.equal(pos[0].cpu(), want.int())
+    at = want.cuda()[..., None].expand(-1, -1, D)
+    assert torch.equal(K[0], torch.gather(k[0], 1, at)) and torch.equal(V[0], torch.gather(v[0], 1, at))
+    assert torch.equal(S[0].cpu(), torch.gather(score[0], 1, want) if scored else torch.zeros_like(want, dtype=torch.float32))
+    out, q = torch.empty(1, units, D, device="cuda"), torch.randn(1, units, D, generator=g).to("cuda", dt)
+    c.decode_step(q, q, q, out)                              # the arrival counters are clear
+    Ka, Va = (torch.cat([x[0].double(), q[0, :, None].double()], 1) for x in (K, V))
+    p = torch.softmax(torch.matmul(Ka, q[0, :, :, None].double())[..., 0] / D ** 0.5, -1)
+    o = torch.matmul(p[:, None], Va)[:, 0]
+    assert float((out[0] - o).abs().max() / o.abs().max()) < 1e-4
+
+
 def test_long_segments_with_nan_and_infinite_scores():
     st = run(small(prompt=11000, decode_steps=4, sink=4, window=64, segment=5000, keep=40, evict_every=6000, n_obs=12),
              plant=plant_odd_scores)
