@@ -143,11 +143,11 @@ __global__ __launch_bounds__(256) void segment_topk_kernel(const SelectArgs a)
 // fit.  Every row above survives and the first of the equal ones do (ties go to the lowest index).  Same result as the wave
 // kernel, whose work grows with the square of the length.
 // A wave takes a contiguous run of the rows, 64 at a time, so that rows are numbered by ballots and two counts per wave,
-// without a barrier per 1024 rows.  Up to 16 of a wave's rounds stay in registers (segments of 16384 rows); longer segments
-// are read again in each pass, 16 rounds in flight.  Digits of 11 bits keep the exponent and two more bits in the first: a
+// without a barrier per 1024 rows.  Up to 32 of a wave's rounds stay in registers (segments of 32768 rows; 21688 rows in 16
+// units, prefill and export: 66.7 us so, 81 read again in each pass); longer segments are read again, 16 rounds in flight.  Digits of 11 bits keep the exponent and two more bits in the first: a
 // prompt's scores then spread over a few dozen bins, where one byte puts nearly all of them into four, on whose counters
 // the lanes of a wave queue.
-constexpr int kTopkBlock = 1024, kTopkWaves = kTopkBlock / 64, kTopkRounds = 16, kTopkBins = 2048;
+constexpr int kTopkBlock = 1024, kTopkWaves = kTopkBlock / 64, kTopkBins = 2048;
 
 __device__ inline unsigned score_key(float v)      // larger score <=> larger key; NaN ranks with -inf; -0 == +0
 {
@@ -156,7 +156,7 @@ __device__ inline unsigned score_key(float v)      // larger score <=> larger ke
     return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
 }
 
-template <bool HELD>
+template <int ROUNDS, bool HELD>
 __global__ __launch_bounds__(kTopkBlock) void segment_topk_block_kernel(const SelectArgs a)
 {
     __shared__ int hist[kTopkBins];
@@ -175,19 +175,19 @@ __global__ __launch_bounds__(kTopkBlock) void segment_topk_block_kernel(const Se
         const int row = a.lo + (int)start + min(e, len - 1);
         return a.ignore_scores ? 0x80000000u : score_key(base[a.map.ring_cap ? a.map.phys(row) : row]);
     };
-    unsigned held[kTopkRounds];
+    unsigned held[ROUNDS];
     auto load = [&](int e0) {
 #pragma unroll
-        for (int i = 0; i < kTopkRounds; ++i) held[i] = key_of(e0 + 64 * i + lane);
+        for (int i = 0; i < ROUNDS; ++i) held[i] = key_of(e0 + 64 * i + lane);
     };
     if (HELD) load(first);
     // f(key, row) for this wave's rows, in order
     auto for_rows = [&](auto f) {
 #pragma unroll 1
-        for (int e0 = first; e0 < last; e0 += 64 * kTopkRounds) {
+        for (int e0 = first; e0 < last; e0 += 64 * ROUNDS) {
             if (!HELD) load(e0);
 #pragma unroll
-            for (int i = 0; i < kTopkRounds; ++i) {
+            for (int i = 0; i < ROUNDS; ++i) {
                 if (e0 + 64 * i >= last) break;
                 f(held[i], e0 + 64 * i + lane);
             }
@@ -483,12 +483,13 @@ hipError_t launch_evict_new_rows(const EvictArgs& a, int units, hipStream_t st, 
 }
 
 // Whether a block per segment selects faster than a wave per segment.  The latter takes 1.35e-4 us times the square of the
-// length, however few there are; a block 3 us, and 0.022 us per block where there are many.  (Prefill and export, wave /
-// block: 4 units, 300 rows 24.9 / 17.5 us, 1000 rows 159 / 17.4, 4000 rows 2307 / 17.5; 32 units and 8192 rows in segments
-// of 300, 400 and 700: 29.1 / 38.2, 40.7 / 32.2, 87 / 27.8; 32768 rows in segments of 300 and 700: 66 / 123, 118 / 80.)
+// length, however few there are; a block 3 us, and 0.008 us per block where there are many.  (Prefill and export, wave /
+// block: 4 units, 300 rows 24.9 / 17.4 us, 1000 rows 159 / 17.4, 4000 rows 2307 / 17.3; 32 units and 8192 rows in segments
+// of 300, 400 and 700: 28.7 / 23.9, 40.7 / 22.6, 87 / 19.5; 32768 rows in segments of 400, 512 and 700: 81 / not measured,
+// 83 / 62.8, 118 / 55.8.)
 static bool block_selects(int segment, int n_seg, int units)
 {
-    const double length = segment, block_us = 3.0 + 0.022 * (double)n_seg * units;
+    const double length = segment, block_us = 3.0 + 0.008 * (double)n_seg * units;
     return segment > kMaxWaveSegment || (segment >= 256 && block_us < 1.35e-4 * length * length);
 }
 
@@ -500,8 +501,11 @@ hipError_t launch_segment_topk(SelectArgs a, int units, hipStream_t st, Timing t
     if (block_selects(a.segment, n_seg, units)) {
         if ((int64_t)n_seg * kTopkBlock > UINT32_MAX) return hipErrorInvalidValue;
         const dim3 grid(n_seg, units), block(kTopkBlock);
-        if (a.segment <= kTopkWaves * 64 * kTopkRounds) BUZZ_LAUNCH(segment_topk_block_kernel<true>, grid, block, 0, st, tm, a);
-        else BUZZ_LAUNCH(segment_topk_block_kernel<false>, grid, block, 0, st, tm, a);
+        constexpr int round = kTopkBlock;              // rows
+        if (a.segment <= 4 * round) BUZZ_LAUNCH((segment_topk_block_kernel<4, true>), grid, block, 0, st, tm, a);
+        else if (a.segment <= 16 * round) BUZZ_LAUNCH((segment_topk_block_kernel<16, true>), grid, block, 0, st, tm, a);
+        else if (a.segment <= 32 * round) BUZZ_LAUNCH((segment_topk_block_kernel<32, true>), grid, block, 0, st, tm, a);
+        else BUZZ_LAUNCH((segment_topk_block_kernel<16, false>), grid, block, 0, st, tm, a);
         return hipGetLastError();
     }
     dim3 grid((n_seg + kSelWaves - 1) / kSelWaves, units), block(256);
@@ -518,10 +522,13 @@ static int pieces_log2(int row_bytes)
     return (16 << lpr_log2) == row_bytes && lpr_log2 <= 6 ? lpr_log2 : -1;
 }
 
-// Selection and placement of a sampled prompt.  One launch where waves rank the segments, every survivor is kept and the
-// survivors of a segment are at most what a wave moves at a time, 256 pieces (64 units of 4096 rows of 512 bytes, 25 of 200
-// kept: 52 us in one launch, 47 in two), else two launches.  Many segments with one survivor or less than half a wave's pieces
-// take two as well (32 units of 32768 rows of 256 bytes, 1 of 5 kept: 130 and 120 us; 2 of 16 kept: 69 and 76.5); few save the launch.
+// Selection and placement of a sampled prompt, in one launch or two.  One takes that every survivor is kept.  With many
+// segments it gains the time that the ranking would leave the memory idle, if a wave moves its survivors at a time (256
+// pieces: 64 units of 4096 rows of 512 bytes, 25 of 200 kept, 52 us in one launch, 47 in two) and has two and half its
+// lanes' pieces at least (32 units of 32768 rows of 256 bytes, 1 of 5 kept: 130 and 120 us; 2 of 16 kept: 69 and 76.5).  With few
+// it saves a launch, 2.5 of 17 us, up to 128 pieces (16 units of 4239 rows of 512 bytes, 8 of 64 kept: 18 and 17 us).
+// In between all waves rank and then all of them copy, in one launch as in two (32 units of 8192 rows of 128 bytes, 12 of
+// 100 kept: 18.4 and 17.3 us).
 hipError_t launch_place_sampled(SelectArgs a, const GatherArgs& g, int units, hipStream_t st)
 {
     const int n_seg = (a.new_count + a.segment - 1) / a.segment, lpr_log2 = pieces_log2(g.row_bytes);
@@ -529,7 +536,8 @@ hipError_t launch_place_sampled(SelectArgs a, const GatherArgs& g, int units, hi
     const size_t lds = (size_t)kSelWaves * (size_t)wave_slice(a.segment + a.keep) * sizeof(float);   // segment and keep are below 2^28
     if (lpr_log2 < 0) return hipErrorInvalidValue;
     const int64_t pieces = (int64_t)a.keep << lpr_log2, waves = (int64_t)n_seg * units;
-    if (g.sel_step != 1 || block_selects(a.segment, n_seg, units) || pieces > 256 || ((pieces < 32 || a.keep < 2) && waves > 4096) || lds > 65536) {
+    const bool one = waves >= 4096 ? pieces >= 32 && pieces <= 256 && a.keep >= 2 : waves <= 512 && pieces <= 128;
+    if (g.sel_step != 1 || block_selects(a.segment, n_seg, units) || !one || lds > 65536) {
         if (hipError_t e = launch_segment_topk(a, units, st)) return e;
         return launch_gather_rows(g, units, st);
     }

@@ -569,7 +569,8 @@ def test_segments_longer_than_one_wave_can_rank(segment, keep):
 
 @pytest.mark.parametrize("segment,rows,keep,global_topk", [(255, 600, 31, False), (256, 773, 1, False), (256, 773, 255, False), (300, 2999, 40, False),
                                                            (1023, 1023, 100, False), (1025, 1025, 1024, False), (4000, 9000, 3, False),
-                                                           (16384, 16384, 2000, False), (16385, 16385, 2000, False), (64, 40001, 5000, True),
+                                                           (4096, 4096, 9, False), (4097, 4097, 9, False), (16384, 16384, 2000, False),
+                                                           (16385, 16385, 2000, False), (32768, 32768, 40, False), (32769, 32769, 4000, False), (64, 40001, 5000, True),
                                                            (64, 257, 200, True)])
 @pytest.mark.parametrize("values", ["distinct", "three", "equal", "odd"])
 def test_selection_of_long_segments(segment, rows, keep, global_topk, values):
