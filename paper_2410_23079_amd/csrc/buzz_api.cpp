@@ -306,6 +306,12 @@ void prof_clear(buzz_cache_t* c)
 }
 inline int hip_rc(hipError_t e) { return e == hipSuccess ? BUZZ_OK : BUZZ_EHIP; }
 
+// Whether n rows per unit are more than the last-level cache holds: then nothing is gained by keeping them there.
+bool exceeds_last_level_cache(const buzz_cache_t* c, int64_t n)
+{
+    return (double)c->L.units * (double)n * 2.0 * c->L.row_bytes > kLastLevelCacheBytes;
+}
+
 GatherArgs cache_gather_base(const buzz_cache_t* c)
 {
     GatherArgs g{};
@@ -642,6 +648,7 @@ int buzz_prefill(buzz_cache_t* c, const void* kp, const void* vp, int64_t N, con
         g.n_rows = (int32_t)(sink_rows + survivors + tail_rows);
         g.sel_lo = (int32_t)sink_rows; g.sel_hi = (int32_t)(sink_rows + survivors);
         g.tail_shift = (int32_t)(N - tail_rows - sink_rows - survivors);
+        g.stream_dst = exceeds_last_level_cache(c, g.n_rows);
         if (survivors > 0) {
             SelectArgs sa{};
             sa.score = ps; sa.unit_stride = N;
@@ -854,8 +861,7 @@ int buzz_cache_export(buzz_cache_t* c, void* k, void* v, float* score, int32_t* 
         g.G = c->L.G;
     }
     g.dstK = k; g.dstV = v; g.dstScore = score; g.dstPos = pos;
-    g.stream_dst = 1;
-    g.stream_src = (double)c->L.units * (double)c->n() * 2.0 * c->L.row_bytes > kLastLevelCacheBytes;
+    g.stream_src = g.stream_dst = 1;
     g.dst_unit_rows = c->n(); g.dst_start = 0; g.n_rows = (int32_t)c->n();
     return hip_rc(launch_gather_rows(g, c->L.units, (hipStream_t)hip_stream));
 }
@@ -878,7 +884,7 @@ int buzz_cache_import(buzz_cache_t* c, const void* k, const void* v, const float
         if (int rc = probe_die_placement(st)) return rc;
         GatherArgs g{};
         g.srcK = k; g.srcV = v; g.srcScore = score; g.srcPos = pos;
-        g.src_unit_rows = n; g.src_step = 1; g.stream_src = 1;
+        g.src_unit_rows = n; g.src_step = 1; g.stream_src = 1; g.stream_dst = exceeds_last_level_cache(c, n);
         g.dstK = c->at<char>(L.K); g.dstV = c->at<char>(L.V);
         g.dstScore = c->at<float>(L.score); g.dstPos = c->at<int32_t>(L.pos);
         g.dst_unit_rows = L.cap; g.row_bytes = L.row_bytes;

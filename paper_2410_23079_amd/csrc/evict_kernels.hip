@@ -321,10 +321,11 @@ __global__ __launch_bounds__(256) void evict_new_rows_kernel(const EvictArgs a)
 // shape in which a copy is fastest on this chip (1 GB device to device: one piece per thread 6.2 TB/s, four 5.7,
 // eight 4.2); with 64 rows per block and four dependent load-store rounds per thread this kernel moved 5.0 TB/s.
 // Non-temporal accesses where data is not read again before the last-level cache (256 MB) has turned over: what a caller
-// hands in or gets back, and the cache's rows on their way out if they are more than it holds.  Rows that go into the
-// cache are stored normally and stay there for what comes next.  Placed and exported again, both in turn: 228 MB 159 us
-// with non-temporal accesses only, 119 so; 120 MB 87 and 69; 511 MB 339 and 317 (with the rows read back through the
-// last-level cache as well 369); 15 MB 17.4 and 14.8.
+// hands in or gets back, the cache's rows on their way out, and on their way in if they are more than it holds.  Other rows
+// that go into the cache are stored normally and stay there for what comes next.  Other rows each time: a prompt of which
+// 126 MB are kept, placed and exported, 93.5 us with non-temporal stores into the cache, 81.9 so, 87 if the export reads
+// with ordinary loads as well; 126 MB imported, 64 steps, exported 1558, 1552 and 1567; 1 GB 10833 us with non-temporal
+// accesses only, 10906 with normal stores into the cache: what they leave behind is written back under the decode steps.
 // The block's first threads carry the rows' scores and positions, one row each.
 template <bool NTS> __device__ inline u32x4 load_piece(const char* p)
 {
@@ -388,6 +389,7 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(const GatherArgs a, co
 // ranks it and moves its survivors, as many pieces per lane in flight as four passes have; the others copy sink and window
 // rows meanwhile.  Bound by memory traffic; a launch of its own for the ranking left the memory idle while it
 // ran and read its list back (32 units of 32768 rows, 64 per segment, 8 kept, a window of 4096: prefill and export 87.9 us, 82.5 so).
+template <bool NTD>
 __global__ __launch_bounds__(256) void place_sampled_kernel(const SelectArgs a, const GatherArgs g, const int lpr_log2, const int seg_blocks)
 {
     extern __shared__ __attribute__((aligned(16))) float lds[];   // [kSelWaves][wave_slice(segment + keep)]: scores, then kept offsets
@@ -395,7 +397,7 @@ __global__ __launch_bounds__(256) void place_sampled_kernel(const SelectArgs a, 
     if (g.ticket && blockIdx.x == 0 && threadIdx.x == 0) g.ticket[unit] = 0;
     if ((int)blockIdx.x >= seg_blocks) {
         const int sampled = g.sel_hi - g.sel_lo;
-        copy_rows<true, false>(g, lpr_log2, unit, (blockIdx.x - seg_blocks) * (256 >> lpr_log2), [&](int i) { return i < g.sel_lo ? i : i + sampled; });
+        copy_rows<true, NTD>(g, lpr_log2, unit, (blockIdx.x - seg_blocks) * (256 >> lpr_log2), [&](int i) { return i < g.sel_lo ? i : i + sampled; });
         return;
     }
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, seg = blockIdx.x * kSelWaves + wave;
@@ -437,8 +439,8 @@ __global__ __launch_bounds__(256) void place_sampled_kernel(const SelectArgs a, 
         for (int u = 0; u < U; ++u) {
             if (r0 + u * rows >= take) break;
             const size_t at = to + (size_t)(r0 + u * rows) * g.row_bytes;
-            store_piece<false>((char*)g.dstK + at, k[u]);
-            store_piece<false>((char*)g.dstV + at, v[u]);
+            store_piece<NTD>((char*)g.dstK + at, k[u]);
+            store_piece<NTD>((char*)g.dstV + at, v[u]);
         }
     }
     for (int r = lane; r < take; r += 64) {
@@ -543,7 +545,9 @@ hipError_t launch_place_sampled(SelectArgs a, const GatherArgs& g, int units, hi
     }
     const int seg_blocks = (n_seg + kSelWaves - 1) / kSelWaves, rows = 256 >> lpr_log2;
     const int others = g.n_rows - (g.sel_hi - g.sel_lo);
-    hipLaunchKernelGGL(place_sampled_kernel, dim3(seg_blocks + (others + rows - 1) / rows, units), dim3(256), lds, st, a, g, lpr_log2, seg_blocks);
+    const dim3 grid(seg_blocks + (others + rows - 1) / rows, units);
+    if (g.stream_dst) hipLaunchKernelGGL(place_sampled_kernel<true>, grid, dim3(256), lds, st, a, g, lpr_log2, seg_blocks);
+    else hipLaunchKernelGGL(place_sampled_kernel<false>, grid, dim3(256), lds, st, a, g, lpr_log2, seg_blocks);
     return hipGetLastError();
 }
 
