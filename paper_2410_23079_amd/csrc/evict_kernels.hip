@@ -1,6 +1,8 @@
 // BeeHive eviction kernels (Sec. 3.3; the eviction branch of Alg. 1, Alg. 2):
 //   segment_topk : one wavefront per (segment, unit) ranks the segment's accumulated scores and
-//                  emits the top min(keep, len) rows in index order (ties -> lowest index, NaN lowest);
+//                  emits the top min(keep, len) rows in index order (ties -> lowest index, NaN lowest),
+//                  one block per (segment, unit) where segments are long;
+//   place_sampled: the same and the placement of a prompt in one launch;
 //   gather_rows  : packs K, V, score and position of selected rows into their destination
 //                  (survivors behind the old region, sink / window at prefill, export in cache order).
 // Every segment yields min(keep, len) rows, so a survivor's destination is
@@ -503,10 +505,10 @@ hipError_t launch_segment_topk(SelectArgs a, int units, hipStream_t st, Timing t
     if (block_selects(a.segment, n_seg, units)) {
         if ((int64_t)n_seg * kTopkBlock > UINT32_MAX) return hipErrorInvalidValue;
         const dim3 grid(n_seg, units), block(kTopkBlock);
-        constexpr int round = kTopkBlock;              // rows
-        if (a.segment <= 4 * round) BUZZ_LAUNCH((segment_topk_block_kernel<4, true>), grid, block, 0, st, tm, a);
-        else if (a.segment <= 16 * round) BUZZ_LAUNCH((segment_topk_block_kernel<16, true>), grid, block, 0, st, tm, a);
-        else if (a.segment <= 32 * round) BUZZ_LAUNCH((segment_topk_block_kernel<32, true>), grid, block, 0, st, tm, a);
+        constexpr int per_round = kTopkBlock;          // rows
+        if (a.segment <= 4 * per_round) BUZZ_LAUNCH((segment_topk_block_kernel<4, true>), grid, block, 0, st, tm, a);
+        else if (a.segment <= 16 * per_round) BUZZ_LAUNCH((segment_topk_block_kernel<16, true>), grid, block, 0, st, tm, a);
+        else if (a.segment <= 32 * per_round) BUZZ_LAUNCH((segment_topk_block_kernel<32, true>), grid, block, 0, st, tm, a);
         else BUZZ_LAUNCH((segment_topk_block_kernel<16, false>), grid, block, 0, st, tm, a);
         return hipGetLastError();
     }
