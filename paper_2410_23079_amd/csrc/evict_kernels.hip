@@ -537,9 +537,9 @@ hipError_t launch_place_sampled(SelectArgs a, const GatherArgs& g, int units, hi
 {
     const int n_seg = (a.new_count + a.segment - 1) / a.segment, lpr_log2 = pieces_log2(g.row_bytes);
     if (n_seg == 1) a.segment = a.new_count;
-    const size_t lds = (size_t)kSelWaves * (size_t)wave_slice(a.segment + a.keep) * sizeof(float);   // segment and keep are below 2^28
     if (lpr_log2 < 0) return hipErrorInvalidValue;
     const int64_t pieces = (int64_t)a.keep << lpr_log2, waves = (int64_t)n_seg * units;
+    const int64_t lds = ((int64_t)a.segment + a.keep + 3) / 4 * 4 * kSelWaves * (int64_t)sizeof(float);
     const bool one = waves >= 4096 ? pieces >= 32 && pieces <= 256 && a.keep >= 2 : waves <= 512 && pieces <= 128;
     if (g.sel_step != 1 || block_selects(a.segment, n_seg, units) || !one || lds > 65536) {
         if (hipError_t e = launch_segment_topk(a, units, st)) return e;
@@ -548,8 +548,8 @@ hipError_t launch_place_sampled(SelectArgs a, const GatherArgs& g, int units, hi
     const int seg_blocks = (n_seg + kSelWaves - 1) / kSelWaves, rows = 256 >> lpr_log2;
     const int others = g.n_rows - (g.sel_hi - g.sel_lo);
     const dim3 grid(seg_blocks + (others + rows - 1) / rows, units);
-    if (g.stream_dst) hipLaunchKernelGGL(place_sampled_kernel<true>, grid, dim3(256), lds, st, a, g, lpr_log2, seg_blocks);
-    else hipLaunchKernelGGL(place_sampled_kernel<false>, grid, dim3(256), lds, st, a, g, lpr_log2, seg_blocks);
+    if (g.stream_dst) hipLaunchKernelGGL(place_sampled_kernel<true>, grid, dim3(256), (size_t)lds, st, a, g, lpr_log2, seg_blocks);
+    else hipLaunchKernelGGL(place_sampled_kernel<false>, grid, dim3(256), (size_t)lds, st, a, g, lpr_log2, seg_blocks);
     return hipGetLastError();
 }
 
