@@ -394,7 +394,7 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(const GatherArgs a, co
 template <bool NTD>
 __global__ __launch_bounds__(256) void place_sampled_kernel(const SelectArgs a, const GatherArgs g, const int lpr_log2, const int seg_blocks)
 {
-    extern __shared__ __attribute__((aligned(16))) float lds[];   // [kSelWaves][wave_slice(segment + keep)]: scores, then kept offsets
+    extern __shared__ __attribute__((aligned(16))) float lds[];   // [kSelWaves][wave_slice(scores + keep)]: scores, if any, then kept offsets
     const int unit = blockIdx.y;
     if (g.ticket && blockIdx.x == 0 && threadIdx.x == 0) g.ticket[unit] = 0;
     if ((int)blockIdx.x >= seg_blocks) {
@@ -406,8 +406,9 @@ __global__ __launch_bounds__(256) void place_sampled_kernel(const SelectArgs a, 
     const int n_seg = (a.new_count + a.segment - 1) / a.segment;
     if (seg >= n_seg) return;                      // no block-wide barrier below: a wave only reads what it wrote
     const int start = seg * a.segment, len = min(a.segment, a.new_count - start), take = min(a.keep, len);
-    float* sc = lds + wave * wave_slice(a.segment + a.keep);
-    int* kept = (int*)sc + a.segment;
+    const int scores = a.ignore_scores ? 0 : a.segment;
+    float* sc = lds + wave * wave_slice(scores + a.keep);
+    int* kept = (int*)sc + scores;
     const float* base = a.score + (size_t)unit * a.unit_stride + a.lo + start;
     if (a.ignore_scores) {                         // all equal: the lowest indices win
         for (int r = lane; r < take; r += 64) kept[r] = r;
@@ -491,8 +492,13 @@ hipError_t launch_evict_new_rows(const EvictArgs& a, int units, hipStream_t st, 
 // block: 4 units, 300 rows 24.9 / 17.4 us, 1000 rows 159 / 17.4, 4000 rows 2307 / 17.3; 32 units and 8192 rows in segments
 // of 300, 400 and 700: 28.7 / 23.9, 40.7 / 22.6, 87 / 19.5; 32768 rows in segments of 400, 512 and 700: 81 / not measured,
 // 83 / 62.8, 118 / 55.8.)
-static bool block_selects(int segment, int n_seg, int units)
+// Without scores to compare (interval sampling, a prompt that has none) a wave writes its segment's first rows, whatever
+// the length: the block would search keys that are all equal, every lane on one counter (prefill, wave / block: 4 units,
+// one segment of 1000 rows 5.9 / 12.7 us; 32 units, 4000 rows 8.5 / 24.5; 32 units of 32768 rows in segments of 512 27 / 64).
+static bool block_selects(const SelectArgs& a, int n_seg, int units)
 {
+    const int segment = a.segment;
+    if (a.ignore_scores) return false;
     const double length = segment, block_us = 3.0 + 0.008 * (double)n_seg * units;
     return segment > kMaxWaveSegment || (segment >= 256 && block_us < 1.35e-4 * length * length);
 }
@@ -502,7 +508,7 @@ hipError_t launch_segment_topk(SelectArgs a, int units, hipStream_t st, Timing t
     const int n_seg = (a.new_count + a.segment - 1) / a.segment;
     if (n_seg <= 0) return hipSuccess;
     if (n_seg == 1) a.segment = a.new_count;       // no longer than what there is
-    if (block_selects(a.segment, n_seg, units)) {
+    if (block_selects(a, n_seg, units)) {
         if ((int64_t)n_seg * kTopkBlock > UINT32_MAX) return hipErrorInvalidValue;
         const dim3 grid(n_seg, units), block(kTopkBlock);
         constexpr int per_round = kTopkBlock;          // rows
@@ -513,7 +519,7 @@ hipError_t launch_segment_topk(SelectArgs a, int units, hipStream_t st, Timing t
         return hipGetLastError();
     }
     dim3 grid((n_seg + kSelWaves - 1) / kSelWaves, units), block(256);
-    const size_t lds = (size_t)kSelWaves * wave_slice(a.segment) * sizeof(float);
+    const size_t lds = a.ignore_scores ? 0 : (size_t)kSelWaves * wave_slice(a.segment) * sizeof(float);
     BUZZ_LAUNCH(segment_topk_kernel, grid, block, lds, st, tm, a);
     return hipGetLastError();
 }
@@ -539,9 +545,9 @@ hipError_t launch_place_sampled(SelectArgs a, const GatherArgs& g, int units, hi
     if (n_seg == 1) a.segment = a.new_count;
     if (lpr_log2 < 0) return hipErrorInvalidValue;
     const int64_t pieces = (int64_t)a.keep << lpr_log2, waves = (int64_t)n_seg * units;
-    const int64_t lds = ((int64_t)a.segment + a.keep + 3) / 4 * 4 * kSelWaves * (int64_t)sizeof(float);
+    const int64_t lds = ((int64_t)(a.ignore_scores ? 0 : a.segment) + a.keep + 3) / 4 * 4 * kSelWaves * (int64_t)sizeof(float);
     const bool one = waves >= 4096 ? pieces >= 32 && pieces <= 256 && a.keep >= 2 : waves <= 512 && pieces <= 128;
-    if (g.sel_step != 1 || block_selects(a.segment, n_seg, units) || !one || lds > 65536) {
+    if (g.sel_step != 1 || block_selects(a, n_seg, units) || !one || lds > 65536) {
         if (hipError_t e = launch_segment_topk(a, units, st)) return e;
         return launch_gather_rows(g, units, st);
     }

@@ -8,7 +8,7 @@ import subprocess
 
 import pytest
 
-from paper_2410_23079_amd import FLAG_AUTO_EVICT, BuzzConfig
+from paper_2410_23079_amd import FLAG_AUTO_EVICT, FLAG_INTERVAL_NEW, BuzzConfig
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 HERE = os.path.join(ROOT, "tests")
@@ -206,3 +206,26 @@ def test_the_automatic_split_count(lib, dtype, G, D, units, rows):
     assert rows > 64 or s == 1
     if units * s * G * (D + 2) * 4 <= 8 << 20:
         assert splits(rows, True) == s
+
+
+@pytest.mark.parametrize("segment,keep", [(64, 8), (255, 31), (1000, 100), (4096, 500), (5000, 600), (90000, 20000)])
+@pytest.mark.parametrize("why", ["no scores", "interval"])
+def test_a_selection_that_compares_nothing_ranks_nothing(lib, segment, keep, why):
+    """Prompts without scores and interval sampling keep the first rows of every segment: no block-wide selection, whose
+    lanes would all queue on one counter, at prefill and in evictions that thin the old rows, whatever the length."""
+    h = create(lib, config(n_q_heads=2, segment=segment, keep=keep, evict_every=32, window=10, max_context=2 * segment + 200, old_stride=2,
+                           flags=FLAG_INTERVAL_NEW if why == "interval" else 0))
+    for rows in (segment + 40, 2 * segment + 40):
+        lib.rec_reset(-1)
+        assert lib.buzz_prefill(h, KP, VP, rows, None, 0, SP if why == "interval" else None, None) == 0
+        names = [k for k, _ in recorded(lib)]
+        assert names and not any("segment_topk_block" in k for k in names)
+        assert all(lib.rec_value(i, b"lds") <= 65536 for _, i in recorded(lib))
+    if why == "interval":
+        for _ in range(32):
+            assert lib.buzz_decode_step(h, QP, KP, VP, OUT, None) == 0
+        lib.rec_reset(-1)
+        assert lib.buzz_evict(h, None) == 0
+        names = [k for k, _ in recorded(lib)]
+        assert any("segment_topk_kernel" in k for k in names) and not any("segment_topk_block" in k for k in names)
+    assert lib.buzz_cache_destroy(h) == 0
