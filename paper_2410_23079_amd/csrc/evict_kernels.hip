@@ -488,10 +488,11 @@ hipError_t launch_evict_new_rows(const EvictArgs& a, int units, hipStream_t st, 
 }
 
 // Whether a block per segment selects faster than a wave per segment.  The latter takes 1.35e-4 us times the square of the
-// length, however few there are; a block 3 us, and 0.008 us per block where there are many.  (Prefill and export, wave /
-// block: 4 units, 300 rows 24.9 / 17.4 us, 1000 rows 159 / 17.4, 4000 rows 2307 / 17.3; 32 units and 8192 rows in segments
-// of 300, 400 and 700: 28.7 / 23.9, 40.7 / 22.6, 87 / 19.5; 32768 rows in segments of 400, 512 and 700: 81 / not measured,
-// 83 / 62.8, 118 / 55.8.)
+// length, however few there are, and as many times longer as there are more than 2700 waves (two to three per SIMD share
+// it); a block 3 us, and 0.008 us per block where there are many.  Prefill and export of heads of 64, an eighth kept, wave /
+// block: 16 segments of 256 rows 17.0 / 11.7 us, of 800 rows 108 / 12.6; 1024 of 256 24.3 / 25.5, of 320 30.1 / 25.2; 2048 of
+// 320 38.4 / 44.0, of 400 54.7 / 47.8; 4096 of 360 76.6 / 83.5, of 450 110 / 92.4; 8192 of 400 160 / 162, of 450 191 / 171;
+// 16384 of 360 249 / 299.  Below 256 rows a block gains a microsecond at most (16 segments of 192 12.3 / 11.6 us).
 // Without scores to compare (interval sampling, a prompt that has none) a wave writes its segment's first rows, whatever
 // the length: the block would search keys that are all equal, every lane on one counter (prefill, wave / block: 4 units,
 // one segment of 1000 rows 5.9 / 12.7 us; 32 units, 4000 rows 8.5 / 24.5; 32 units of 32768 rows in segments of 512 27 / 64).
@@ -499,8 +500,8 @@ static bool block_selects(const SelectArgs& a, int n_seg, int units)
 {
     const int segment = a.segment;
     if (a.ignore_scores) return false;
-    const double length = segment, block_us = 3.0 + 0.008 * (double)n_seg * units;
-    return segment > kMaxWaveSegment || (segment >= 256 && block_us < 1.35e-4 * length * length);
+    const double length = segment, count = (double)n_seg * units, crowd = count > 2700.0 ? count / 2700.0 : 1.0;
+    return segment > kMaxWaveSegment || (segment >= 256 && 3.0 + 0.008 * count < 1.35e-4 * length * length * crowd);
 }
 
 hipError_t launch_segment_topk(SelectArgs a, int units, hipStream_t st, Timing tm)

@@ -229,3 +229,19 @@ def test_a_selection_that_compares_nothing_ranks_nothing(lib, segment, keep, why
         names = [k for k, _ in recorded(lib)]
         assert any("segment_topk_kernel" in k for k in names) and not any("segment_topk_block" in k for k in names)
     assert lib.buzz_cache_destroy(h) == 0
+
+
+@pytest.mark.parametrize("segments,segment,block", [
+    (1, 255, False), (16, 256, True), (16, 4097, True), (1024, 256, False), (1024, 320, True), (2048, 320, False), (2048, 400, True),
+    (4096, 360, False), (4096, 450, True), (4096, 512, True), (8192, 360, False), (8192, 450, True), (16384, 360, False)])
+@pytest.mark.parametrize("units", [1, 8])
+def test_segments_are_ranked_by_what_was_faster(lib, segments, segment, block, units):
+    """A wave per segment or a block per segment, at measured shapes on either side of the line."""
+    n_seg = -(-segments // units)
+    h = create(lib, config(batch=1, n_q_heads=units, n_kv_heads=units, head_dim=64, segment=segment, keep=4, evict_every=segment,
+                           window=64, max_context=n_seg * segment + 68))
+    lib.rec_reset(-1)
+    assert lib.buzz_prefill(h, KP, VP, n_seg * segment + 68, None, 0, SP, None) == 0
+    names = [k for k, _ in recorded(lib)]
+    assert any("segment_topk_block" in k for k in names) == block, names
+    assert lib.buzz_cache_destroy(h) == 0
