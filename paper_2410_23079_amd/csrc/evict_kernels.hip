@@ -323,7 +323,8 @@ __global__ __launch_bounds__(256) void evict_new_rows_kernel(const EvictArgs a)
 // shape in which a copy is fastest on this chip (1 GB device to device: one piece per thread 6.2 TB/s, four 5.7,
 // eight 4.2); with 64 rows per block and four dependent load-store rounds per thread this kernel moved 5.0 TB/s.
 // Non-temporal accesses where data is not read again before the last-level cache (256 MB) has turned over: what a caller
-// hands in or gets back, the cache's rows on their way out, and on their way in if they are more than it holds.  Other rows
+// hands in or gets back, the cache's rows on their way out, and on their way in if they are more than it holds or the caller
+// has set BUZZ_FLAG_STREAMING.  Other rows
 // that go into the cache are stored normally and stay there for what comes next.  Other rows each time: a prompt of which
 // 126 MB are kept, placed and exported, 93.5 us with non-temporal stores into the cache, 81.9 so, 87 if the export reads
 // with ordinary loads as well; 126 MB imported, 64 steps, exported 1558, 1552 and 1567; 1 GB 10833 us with non-temporal

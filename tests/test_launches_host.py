@@ -8,7 +8,7 @@ import subprocess
 
 import pytest
 
-from paper_2410_23079_amd import FLAG_AUTO_EVICT, FLAG_INTERVAL_NEW, BuzzConfig
+from paper_2410_23079_amd import FLAG_AUTO_EVICT, FLAG_CACHED, FLAG_INTERVAL_NEW, FLAG_STREAMING, BuzzConfig
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 HERE = os.path.join(ROOT, "tests")
@@ -244,4 +244,24 @@ def test_segments_are_ranked_by_what_was_faster(lib, segments, segment, block, u
     assert lib.buzz_prefill(h, KP, VP, n_seg * segment + 68, None, 0, SP, None) == 0
     names = [k for k, _ in recorded(lib)]
     assert any("segment_topk_block" in k for k in names) == block, names
+    assert lib.buzz_cache_destroy(h) == 0
+
+
+@pytest.mark.parametrize("flags,rows,past", [(0, 1000, False), (0, 9000, True), (FLAG_STREAMING, 1000, True), (FLAG_STREAMING, 9000, True),
+                                             (FLAG_CACHED, 1000, False), (FLAG_CACHED, 9000, True)])
+@pytest.mark.parametrize("call", ["import", "prefill", "sampled"])
+def test_rows_go_into_the_cache_past_the_last_level_cache_or_not(lib, flags, rows, past, call):
+    """64 units of 512-byte rows: 33 MB and 590 MB.  More than 256 MB, or a caller who has said that nothing survives there."""
+    sampled = call == "sampled"
+    h = create(lib, config(batch=1, n_q_heads=64, n_kv_heads=64, window=rows // 2, segment=64, keep=64 if sampled else 8,
+                           evict_every=64 if sampled else rows, max_context=rows, flags=flags))
+    lib.rec_reset(-1)
+    if call == "import":
+        assert lib.buzz_cache_import(h, KP, VP, SP, PP, rows, 0, rows, None) == 0
+    else:
+        assert lib.buzz_prefill(h, KP, VP, rows, None, 0, SP, None) == 0
+    into = re.findall(r"gather_rows_kernelILb1ELb([01])E|place_sampled_kernelILb([01])E", lib.rec_kernel(lib.rec_count() - 1).decode())
+    assert "".join(into[0]) == "01"[past]
+    lib.rec_reset(-1)
+    assert lib.buzz_cache_export(h, KP, VP, SP, PP, None) == 0 and "gather_rows_kernelILb1ELb1E" in lib.rec_kernel(0).decode()
     assert lib.buzz_cache_destroy(h) == 0
