@@ -325,6 +325,7 @@ GatherArgs cache_gather_base(const buzz_cache_t* c)
     g.dstScore = c->at<float>(c->L.score); g.dstPos = c->at<int32_t>(c->L.pos);
     g.dst_unit_rows = c->L.cap;
     g.row_bytes = c->L.row_bytes;
+    g.stream_dst = 1;
     return g;
 }
 
@@ -641,7 +642,7 @@ int buzz_prefill(buzz_cache_t* c, const void* kp, const void* vp, int64_t N, con
         // otherwise one launch places every row: sink, survivors behind it, the tail at the start of the ring
         GatherArgs g{};
         g.srcK = kp; g.srcV = vp; g.srcScore = ps;
-        g.src_unit_rows = N; g.src_step = 1; g.stream_src = 1;
+        g.src_unit_rows = N; g.src_step = 1;
         g.dstK = c->at<char>(L.K); g.dstV = c->at<char>(L.V);
         g.dstScore = c->at<float>(L.score); g.dstPos = c->at<int32_t>(L.pos);
         g.dst_unit_rows = L.cap; g.row_bytes = L.row_bytes;
@@ -863,7 +864,6 @@ int buzz_cache_export(buzz_cache_t* c, void* k, void* v, float* score, int32_t* 
         g.G = c->L.G;
     }
     g.dstK = k; g.dstV = v; g.dstScore = score; g.dstPos = pos;
-    g.stream_src = g.stream_dst = 1;
     g.dst_unit_rows = c->n(); g.dst_start = 0; g.n_rows = (int32_t)c->n();
     return hip_rc(launch_gather_rows(g, c->L.units, (hipStream_t)hip_stream));
 }
@@ -886,7 +886,7 @@ int buzz_cache_import(buzz_cache_t* c, const void* k, const void* v, const float
         if (int rc = probe_die_placement(st)) return rc;
         GatherArgs g{};
         g.srcK = k; g.srcV = v; g.srcScore = score; g.srcPos = pos;
-        g.src_unit_rows = n; g.src_step = 1; g.stream_src = 1; g.stream_dst = streams_into_cache(c, n);
+        g.src_unit_rows = n; g.src_step = 1; g.stream_dst = streams_into_cache(c, n);
         g.dstK = c->at<char>(L.K); g.dstV = c->at<char>(L.V);
         g.dstScore = c->at<float>(L.score); g.dstPos = c->at<int32_t>(L.pos);
         g.dst_unit_rows = L.cap; g.row_bytes = L.row_bytes;

@@ -152,7 +152,7 @@ struct GatherArgs {
     int32_t n_rows;
     int32_t row_bytes;         // D * sizeof(element)
     int32_t G;
-    int32_t stream_src, stream_dst;   // 1: that side's rows are not read again soon (non-temporal accesses)
+    int32_t stream_dst;        // 1: the copies are stored past the last-level cache (non-temporal)
 };
 
 // Where the scoring puts a prompt that is kept whole: a key's row is map.phys(key).

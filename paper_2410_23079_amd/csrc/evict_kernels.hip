@@ -322,19 +322,16 @@ __global__ __launch_bounds__(256) void evict_new_rows_kernel(const EvictArgs a)
 // and one of V, both requested before either is stored; rows are spread over as many blocks as that takes.  That is the
 // shape in which a copy is fastest on this chip (1 GB device to device: one piece per thread 6.2 TB/s, four 5.7,
 // eight 4.2); with 64 rows per block and four dependent load-store rounds per thread this kernel moved 5.0 TB/s.
-// Non-temporal accesses where data is not read again before the last-level cache (256 MB) has turned over: what a caller
-// hands in or gets back, the cache's rows on their way out, and on their way in if they are more than it holds or the caller
-// has set BUZZ_FLAG_STREAMING.  Other rows
-// that go into the cache are stored normally and stay there for what comes next.  Other rows each time: a prompt of which
-// 126 MB are kept, placed and exported, 93.5 us with non-temporal stores into the cache, 81.9 so, 87 if the export reads
-// with ordinary loads as well; 126 MB imported, 64 steps, exported 1558, 1552 and 1567; 1 GB 10833 us with non-temporal
-// accesses only, 10906 with normal stores into the cache: what they leave behind is written back under the decode steps.
+// Rows are loaded past the last-level cache (256 MB), and stored past it (non-temporal) unless they come in from a caller: a
+// prompt or an import that it holds is stored normally and stays there for what comes next, if the caller has not set
+// BUZZ_FLAG_STREAMING.  Other rows each time: a prompt of which 126 MB are kept, placed and exported, 93.5 us with
+// non-temporal stores into the cache, 81.9 so, 87 if the export loads normally as well; 126 MB imported, 64 steps, exported
+// 1558, 1552 and 1567; 1 GB 10833 us with non-temporal accesses only, 10906 with normal stores into the cache: what they leave
+// behind is written back under the decode steps.  So are the rows that evictions move: with normal accesses there, 8 caches
+// of 74 MB in turn, an eviction (31 MB through the staging rows) and 3 steps each, 796 us instead of 765, 8 of 235 MB 1770
+// instead of 1638; one cache alone, 128 MB moved, the eviction 111 instead of 118 us and no difference with 8 steps after it.
 // The block's first threads carry the rows' scores and positions, one row each.
-template <bool NTS> __device__ inline u32x4 load_piece(const char* p)
-{
-    if constexpr (NTS) return __builtin_nontemporal_load((const u32x4*)p);
-    else return *(const u32x4*)p;
-}
+__device__ inline u32x4 load_piece(const char* p) { return __builtin_nontemporal_load((const u32x4*)p); }
 template <bool NTD> __device__ inline void store_piece(char* p, const u32x4& v)
 {
     if constexpr (NTD) __builtin_nontemporal_store(v, (u32x4*)p);
@@ -342,7 +339,7 @@ template <bool NTD> __device__ inline void store_piece(char* p, const u32x4& v)
 }
 
 // The copy of rows row_of(i0), row_of(i0 + 1), ... by one block, as many as it has threads for; row_of(i) >= n_rows: none.
-template <bool NTS, bool NTD, typename RowOf>
+template <bool NTD, typename RowOf>
 __device__ inline void copy_rows(const GatherArgs& a, int lpr_log2, int unit, int i0, RowOf row_of)
 {
     const int tid = threadIdx.x, rows = 256 >> lpr_log2;   // rows per block, 1 << lpr_log2 pieces each
@@ -359,8 +356,8 @@ __device__ inline void copy_rows(const GatherArgs& a, int lpr_log2, int unit, in
         const int c = (tid & ((1 << lpr_log2) - 1)) * 16;
         const size_t so = (sbase + sp) * a.row_bytes + c, dof = (dbase + place(r)) * a.row_bytes + c;
         u32x4 k, v;
-        if (a.dstK) k = load_piece<NTS>((const char*)a.srcK + so);
-        if (a.dstV) v = load_piece<NTS>((const char*)a.srcV + so);
+        if (a.dstK) k = load_piece((const char*)a.srcK + so);
+        if (a.dstV) v = load_piece((const char*)a.srcV + so);
         if (a.dstK) store_piece<NTD>((char*)a.dstK + dof, k);
         if (a.dstV) store_piece<NTD>((char*)a.dstV + dof, v);
     }
@@ -381,11 +378,11 @@ __device__ inline void copy_rows(const GatherArgs& a, int lpr_log2, int unit, in
     }
 }
 
-template <bool NTS, bool NTD>
+template <bool NTD>
 __global__ __launch_bounds__(256) void gather_rows_kernel(const GatherArgs a, const int lpr_log2)
 {
     if (a.ticket && blockIdx.x == 0 && threadIdx.x == 0) a.ticket[blockIdx.y] = 0;
-    copy_rows<NTS, NTD>(a, lpr_log2, blockIdx.y, blockIdx.x * (256 >> lpr_log2), [](int i) { return i; });
+    copy_rows<NTD>(a, lpr_log2, blockIdx.y, blockIdx.x * (256 >> lpr_log2), [](int i) { return i; });
 }
 
 // Placement of a sampled prompt in one launch: the first `seg_blocks` blocks of a unit give a wave to each segment, which
@@ -400,7 +397,7 @@ __global__ __launch_bounds__(256) void place_sampled_kernel(const SelectArgs a, 
     if (g.ticket && blockIdx.x == 0 && threadIdx.x == 0) g.ticket[unit] = 0;
     if ((int)blockIdx.x >= seg_blocks) {
         const int sampled = g.sel_hi - g.sel_lo;
-        copy_rows<true, NTD>(g, lpr_log2, unit, (blockIdx.x - seg_blocks) * (256 >> lpr_log2), [&](int i) { return i < g.sel_lo ? i : i + sampled; });
+        copy_rows<NTD>(g, lpr_log2, unit, (blockIdx.x - seg_blocks) * (256 >> lpr_log2), [&](int i) { return i < g.sel_lo ? i : i + sampled; });
         return;
     }
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, seg = blockIdx.x * kSelWaves + wave;
@@ -436,8 +433,8 @@ __global__ __launch_bounds__(256) void place_sampled_kernel(const SelectArgs a, 
         for (int u = 0; u < U; ++u) {
             if (r0 + u * rows >= take) break;
             const size_t at = from + (size_t)kept[r0 + u * rows] * g.row_bytes;
-            k[u] = load_piece<true>((const char*)g.srcK + at);
-            v[u] = load_piece<true>((const char*)g.srcV + at);
+            k[u] = load_piece((const char*)g.srcK + at);
+            v[u] = load_piece((const char*)g.srcV + at);
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -568,10 +565,8 @@ hipError_t launch_gather_rows(const GatherArgs& a, int units, hipStream_t st, Ti
     if (lpr_log2 < 0) return hipErrorInvalidValue;
     const int rows = 256 >> lpr_log2;
     dim3 grid(a.n_rows > 0 ? (a.n_rows + rows - 1) / rows : 1, units), block(256);
-    if (a.stream_src && a.stream_dst) BUZZ_LAUNCH((gather_rows_kernel<true, true>), grid, block, 0, st, tm, a, lpr_log2);
-    else if (a.stream_src) BUZZ_LAUNCH((gather_rows_kernel<true, false>), grid, block, 0, st, tm, a, lpr_log2);
-    else if (a.stream_dst) BUZZ_LAUNCH((gather_rows_kernel<false, true>), grid, block, 0, st, tm, a, lpr_log2);
-    else BUZZ_LAUNCH((gather_rows_kernel<false, false>), grid, block, 0, st, tm, a, lpr_log2);
+    if (a.stream_dst) BUZZ_LAUNCH(gather_rows_kernel<true>, grid, block, 0, st, tm, a, lpr_log2);
+    else BUZZ_LAUNCH(gather_rows_kernel<false>, grid, block, 0, st, tm, a, lpr_log2);
     return hipGetLastError();
 }
 

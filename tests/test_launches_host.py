@@ -8,7 +8,7 @@ import subprocess
 
 import pytest
 
-from paper_2410_23079_amd import FLAG_AUTO_EVICT, FLAG_CACHED, FLAG_INTERVAL_NEW, FLAG_STREAMING, BuzzConfig
+from paper_2410_23079_amd import FLAG_AUTO_EVICT, FLAG_CACHED, FLAG_GLOBAL_TOPK, FLAG_INTERVAL_NEW, FLAG_STREAMING, BuzzConfig
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 HERE = os.path.join(ROOT, "tests")
@@ -260,8 +260,25 @@ def test_rows_go_into_the_cache_past_the_last_level_cache_or_not(lib, flags, row
         assert lib.buzz_cache_import(h, KP, VP, SP, PP, rows, 0, rows, None) == 0
     else:
         assert lib.buzz_prefill(h, KP, VP, rows, None, 0, SP, None) == 0
-    into = re.findall(r"gather_rows_kernelILb1ELb([01])E|place_sampled_kernelILb([01])E", lib.rec_kernel(lib.rec_count() - 1).decode())
+    into = re.findall(r"gather_rows_kernelILb([01])E|place_sampled_kernelILb([01])E", lib.rec_kernel(lib.rec_count() - 1).decode())
     assert "".join(into[0]) == "01"[past]
     lib.rec_reset(-1)
-    assert lib.buzz_cache_export(h, KP, VP, SP, PP, None) == 0 and "gather_rows_kernelILb1ELb1E" in lib.rec_kernel(0).decode()
+    assert lib.buzz_cache_export(h, KP, VP, SP, PP, None) == 0 and "gather_rows_kernelILb1E" in lib.rec_kernel(0).decode()
+    assert lib.buzz_cache_destroy(h) == 0
+
+
+@pytest.mark.parametrize("rows", [200, 2048, 4400])
+@pytest.mark.parametrize("kind", ["thinned", "global"])
+def test_rows_that_an_eviction_moves_do_not_stay_in_the_last_level_cache(lib, rows, kind):
+    """Stored normally they are written back under the next steps, of this cache or of the others that take their turn."""
+    moved = rows // 2
+    h = create(lib, config(batch=1, n_q_heads=256, n_kv_heads=256, window=64, segment=32, keep=moved if kind == "global" else 4, evict_every=256,
+                           max_context=40000, old_stride=2, flags=FLAG_GLOBAL_TOPK if kind == "global" else 0,
+                           capacity=0 if kind == "global" else 4 + 64 + 256 + 2 * rows))
+    n_old = moved if kind == "global" else rows
+    assert lib.buzz_cache_import(h, KP, VP, SP, PP, 4 + 64 + n_old + 255, n_old, 30000, None) == 0
+    lib.rec_reset(-1)
+    assert lib.buzz_evict(h, None) == 0
+    names = [k for k, _ in recorded(lib) if "gather_rows" in k]
+    assert len(names) == (2 if kind == "global" else 3) and all("ILb1E" in k and "ILb0E" not in k and "ELb0E" not in k for k in names), names
     assert lib.buzz_cache_destroy(h) == 0
