@@ -150,26 +150,29 @@ struct MovingChunk {
     }
 };
 
-// Value rows j_block .. j_block + ROWS - 1 of a unit on their way to the cache, up to 16 pieces per thread in flight at once.
+// Value rows j_block .. j_block + ROWS - 1 of a unit on their way to the cache: N pieces per thread, up to BATCH of them in
+// flight at once.  ALL: a whole batch from k0 on; else pieces k0 .. k1 - 1, at most a batch.
 template <int ROWB, int ROWS>
 struct ValueRows {
     static constexpr int PIECES = ROWB / 16, N = ROWS * PIECES / 256, BATCH = N < 16 ? N : 16;   // pieces per row, per thread, at a time
-    static_assert(ROWS * PIECES % 256 == 0 && N % BATCH == 0, "whole rounds");
+    static_assert(ROWS * PIECES % 256 == 0 && N % BATCH == 0 && (N + 1) / 2 <= BATCH, "whole rounds; half a block's pieces are a batch");
     u32x4 r[BATCH];
-    __device__ inline void request(const ObsArgs& a, int unit, int j_block, int k0)
+    template <bool ALL> __device__ inline void request(const ObsArgs& a, int unit, int j_block, int k0, int k1)
     {
         const char* from = (const char*)a.place.V_from + (size_t)unit * a.N * ROWB;
 #pragma unroll
         for (int k = 0; k < BATCH; ++k) {
+            if (!ALL && k0 + k >= k1) break;
             const int piece = threadIdx.x + 256 * (k0 + k);
             r[k] = __builtin_nontemporal_load((const u32x4*)(from + (size_t)min(j_block + piece / PIECES, a.N - 1) * ROWB + piece % PIECES * 16));
         }
     }
-    __device__ inline void store(const ObsArgs& a, int unit, int j_block, int k0) const
+    template <bool ALL> __device__ inline void store(const ObsArgs& a, int unit, int j_block, int k0, int k1) const
     {
         char* to = (char*)a.place.V + (size_t)unit * a.place.rows * ROWB;
 #pragma unroll
         for (int k = 0; k < BATCH; ++k) {
+            if (!ALL && k0 + k >= k1) break;
             const int piece = threadIdx.x + 256 * (k0 + k), row = j_block + piece / PIECES;
             if (row < a.N) __builtin_nontemporal_store(r[k], (u32x4*)(to + (size_t)a.place.map.phys(row) * ROWB + piece % PIECES * 16));
         }
@@ -278,8 +281,8 @@ __global__ __launch_bounds__(256) void obs_mfma_kernel(const ObsArgs a)
         };
         // A prompt that is kept whole is placed by the scoring itself, which reads the keys anyway and is not bound by
         // memory: the blocks of the latest queries of a unit's first head stream every key of the unit once and store it
-        // here, the first blocks of step 2 carry the values (256 heads of 128, 256 queries, 4096 keys: 94 + 96 + 160 us
-        // for the steps and a placement of their own, 120 + 170 so; prefill and export 504 -> 450 us).
+        // here, the blocks of step 2 carry the values (256 heads of 128, 256 queries, 4096 keys: 94 + 96 + 160 us
+        // for the steps and a placement of their own, 120 + 165 so; prefill and export 505 -> 472 us).
         const bool places = a.place.on && at < a.units && group == 0;
         char* K_to = (char*)a.place.K + (size_t)unit * a.place.rows * ROWB;
         MC::request(staged, Kb, c_begin * CH, a.N - 1);
@@ -366,16 +369,22 @@ __global__ __launch_bounds__(256) void obs_mfma_kernel(const ObsArgs a)
         if (part > 0 && item0 >= n_items) return;          // fewer parts here (part 0 carries the scores over)
         const int j_base = j_block + wave * COLS;
         const bool active = j_base < a.N;
+        // The parts of a cut step share the block's value rows: a launch of about four short blocks per compute unit ends with
+        // whoever carries them alone (prefill and export, bf16, 2 heads on each of 4 units, D 256, 500 queries, 3000 keys: 48.8 us
+        // with a copy of its own, 57.4 with all rows in part 0, 47.5 so; of 8 units, D 128, 256 queries, 2000 keys: 31.9, 33.2, 30.1).
         ValueRows<ROWB, BLOCK_COLS> values;
-        const bool places = a.place.on && part == 0;
-        if (places) {
+        const int parts_here = max(1, (n_chunks * G + a.item_part_len - 1) / a.item_part_len);
+        const int piece0 = part * values.N / parts_here, piece1 = (part + 1) * values.N / parts_here;   // this part's share
+        const bool places_all = a.place.on && parts_here == 1, places_some = a.place.on && parts_here > 1;
+        if (places_all) {
 #pragma unroll 1
             for (int k0 = values.BATCH; k0 < values.N; k0 += values.BATCH) {
-                values.request(a, unit, j_block, k0);
-                values.store(a, unit, j_block, k0);
+                values.template request<true>(a, unit, j_block, k0, 0);
+                values.template store<true>(a, unit, j_block, k0, 0);
             }
+            values.template request<true>(a, unit, j_block, 0, 0);
         }
-        if (places) values.request(a, unit, j_block, 0);
+        if (places_some) values.template request<false>(a, unit, j_block, piece0, piece1);
         const char* Kb = (const char*)a.K + (size_t)unit * a.N * ROWB;
         u32x4 kf[CT][QP];
         float col[CT];
@@ -424,7 +433,8 @@ __global__ __launch_bounds__(256) void obs_mfma_kernel(const ObsArgs a)
                 }
             }
         };
-        if (places) values.store(a, unit, j_block, 0);
+        if (places_all) values.template store<true>(a, unit, j_block, 0, 0);
+        if (places_some) values.template store<false>(a, unit, j_block, piece0, piece1);
         if (item0 < n_items) {
             request(item0);
             store(item0 & 1);

@@ -763,6 +763,41 @@ def test_a_scored_prompt_that_is_kept_whole_is_placed_by_the_scoring(dtype, D, u
     assert float((out - want).abs().max() / want.abs().max()) < 1e-4
 
 
+@pytest.mark.parametrize("dtype,D,units,G,N,n_obs,sink", [("bf16", 64, 2, 3, 771, 300, 4), ("fp32", 128, 3, 1, 1999, 1999, 0), ("fp16", 256, 5, 2, 515, 250, 4),
+                                                          ("fp32", 256, 2, 5, 130, 129, 1), ("bf16", 128, 64, 1, 400, 3, 4), ("bf16", 256, 70, 1, 300, 2, 0),
+                                                          ("fp32", 256, 66, 2, 257, 40, 4), ("fp32", 64, 130, 1, 129, 1, 4)])
+def test_value_rows_of_a_scored_prompt_are_shared_by_the_parts(dtype, D, units, G, N, n_obs, sink):
+    """Steps cut into few and into many parts, more parts than pieces per thread, and whole ones: every row arrives."""
+    test_a_scored_prompt_that_is_kept_whole_is_placed_by_the_scoring(dtype, D, units, G, N, n_obs, sink)
+
+
+@pytest.mark.parametrize("dtype,D,units,G,N,n_obs", [("bf16", 256, 4, 2, 3000, 500), ("bf16", 256, 4, 2, 2000, 256), ("fp32", 128, 8, 2, 700, 256),
+                                                     ("bf16", 128, 32, 2, 700, 256)])
+def test_placing_a_prompt_under_its_scoring_costs_less_than_copying_it(dtype, D, units, G, N, n_obs):
+    """The same prompt, scored, all of its rows kept: placed by the scoring, or by a launch of its own (interval sampling
+    that keeps whole segments).  The former saves two launches, 11 to 16% of the call when measured; with the value rows in the
+    hands of few blocks it took 6% less to 12% more."""
+    from paper_2410_23079_amd import FLAG_INTERVAL_NEW, BuzzCache, BuzzConfig
+    dt = {"fp32": torch.float32, "bf16": torch.bfloat16}[dtype]
+    k, v = (torch.randn(1, units, N, D, device="cuda").to(dt) for _ in range(2))
+    q = torch.randn(1, units * G, n_obs, D, device="cuda").to(dt)
+    caches = {name: BuzzCache(BuzzConfig(1, units * G, units, D, dtype, 4, 16, 64, 64, T, N + 8, old_stride=1, flags=FLAG_INTERVAL_NEW))
+              for name, T in (("placed", N), ("copied", N - 64))}
+    best = {}
+    for name in ("placed", "copied") * 5:
+        c, a, b = caches[name], torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        c.prefill(k, v, q_obs=q)
+        assert c.lengths()[0] == N
+        a.record()
+        for _ in range(30):
+            c.prefill(k, v, q_obs=q)
+        b.record()
+        b.synchronize()
+        best[name] = min(best.get(name, 1e9), a.elapsed_time(b) / 30)
+    print(f"[placement] {dtype} D{D} units{units} N{N}: {best['placed'] * 1e3:.1f} us, copied {best['copied'] * 1e3:.1f} us", flush=True)
+    assert best["placed"] <= 0.93 * best["copied"]
+
+
 def test_log_n_scale_argument():
     """Sec. 3.5: the log-n variant only changes the softmax scale, which is a configuration argument."""
     import math
