@@ -630,13 +630,12 @@ int buzz_prefill(buzz_cache_t* c, const void* kp, const void* vp, int64_t N, con
                 oa.partial = c->at<float>(L.obs_partial);
                 oa.stats_cap = L.obs_stats_cap; oa.partial_cap = L.obs_partial_cap;
                 oa.compute_units = compute_units();
-                // A prompt that is kept whole goes to the cache with its last pass: the keys that the scoring reads are
-                // stored while it computes, and so are the values.
+                // A prompt that is kept whole may go to the cache with its last pass: the keys that the scoring reads are
+                // stored while it computes, and so are the values.  Its launch says whether they were.
                 if (survivors == 0 && tail_rows == N - sink_rows && t0 + max_q >= n_obs)
                     oa.place = PromptPlace{1, RingMap{(int32_t)sink_rows, L.ring_base, 0, L.ring_cap}, vp, c->at<char>(L.K), c->at<char>(L.V),
                                            c->at<float>(L.score), c->at<int32_t>(L.pos), c->at<int32_t>(L.ticket), L.cap};
-                if (hipError_t e = launch_obs_scores(cfg.kv_dtype, cfg.head_dim, oa, L.units, st)) return hip_rc(e);
-                placed = oa.place.on != 0;
+                if (hipError_t e = launch_obs_scores(cfg.kv_dtype, cfg.head_dim, oa, L.units, &placed, st)) return hip_rc(e);
             }
         }
         // otherwise one launch places every row: sink, survivors behind it, the tail at the start of the ring

@@ -157,7 +157,7 @@ struct GatherArgs {
 
 // Where the scoring puts a prompt that is kept whole: a key's row is map.phys(key).
 struct PromptPlace {
-    int32_t on;                // 0: the scores go to ObsArgs::score and nothing is placed
+    int32_t on;                // 0: the scores go to ObsArgs::score and nothing is placed (the launch may clear it)
     RingMap map;
     const void* V_from;        // [units][N][D]
     void* K; void* V;          // [units][rows][D]
@@ -218,7 +218,7 @@ hipError_t launch_gather_rows(const GatherArgs& a, int units, hipStream_t st, Ti
 hipError_t launch_clear_f32(float* dst, int64_t n, hipStream_t st);
 hipError_t launch_plain_copy(void* dst, const void* src, size_t bytes, hipStream_t st);
 hipError_t launch_evict_new_rows(const EvictArgs& a, int units, hipStream_t st, Timing tm = {});
-hipError_t launch_obs_scores(int dtype, int D, const ObsArgs& a, int units, hipStream_t st, Timing tm = {});
+hipError_t launch_obs_scores(int dtype, int D, const ObsArgs& a, int units, bool* placed, hipStream_t st, Timing tm = {});
 int attn_tile_rows(int dtype, int D, int G);   // rows one block consumes per loop trip (split sizes are multiples)
 bool attn_supported(int dtype, int D, int G);
 

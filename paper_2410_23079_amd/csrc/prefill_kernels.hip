@@ -530,7 +530,7 @@ __global__ __launch_bounds__(256) void obs_sum_parts_kernel(const ObsArgs a, int
 }
 
 template <int DT, int D>
-hipError_t launch_obs_mfma_t(ObsArgs a, int units, hipStream_t st, Timing tm)
+hipError_t launch_obs_mfma_t(ObsArgs a, int units, bool* placed, hipStream_t st, Timing tm)
 {
     constexpr int CH = MovingChunk<D * (DT == BUZZ_FP32 ? 4 : 2)>::ROWS, COLS = block_cols<DT>();
     const int heads = units / a.Hkv * a.Hq, G = a.Hq / a.Hkv;
@@ -573,6 +573,21 @@ hipError_t launch_obs_mfma_t(ObsArgs a, int units, hipStream_t st, Timing tm)
     longest = seeing_chunks(a, 0, CH, &t_lo) * G;
     most = (int)(a.partial_cap / ((size_t)units * visible_keys(a)));
     split(total, longest, true, most < kObsItemParts ? (most < 1 ? 1 : most) : kObsItemParts, &a.item_parts, &a.item_part_len);
+    // Whether the steps place a prompt that is kept whole, or a copy of its own does.  They save its launch and its waits, if
+    // enough blocks carry the rows: a block of step 2 has 32, 64 or 128 KB of values before its first tile, a block of step 1
+    // stores all the chunks of its part.  With 32 KB they always do.  With more, whole (uncut) blocks have to be 8 (64 KB), or
+    // half as many as compute units (128 KB): prefill and export, copy / steps, bf16 heads of 256, 16 queries, 48 blocks (16
+    // units of 700 keys) 27.0 / 28.5 us, 96 (32 of 700) 36.3 / 37.4, 128 (16 of 2000) 43.8 / 42.8, 256 (32 of 2000) 67 / 63;
+    // of 128, 3 blocks (1 unit of 700 keys) 18.4 / 18.5, 8 (8 of 200) 18.7 / 18.5, 16 (16 of 200) 19.3 / 19.0.  And fewer than
+    // 32 blocks of step 1 must not have 8 chunks or more each (1 unit of 12000 keys: heads of 128 39.3 / 40.6, of 256 51.4 / 55.9).
+    if (a.place.on) {
+        constexpr int value_bytes = COLS * D * (DT == BUZZ_FP32 ? 4 : 2);
+        const int64_t blocks = (int64_t)units * ((a.N + COLS - 1) / COLS);
+        const bool few = a.item_parts == 1 && blocks < (value_bytes > 65536 ? a.compute_units / 2 : 8);
+        const bool long_parts = (int64_t)units * a.key_parts < 32 && a.key_part_len >= 8;
+        if (value_bytes > 32768 && (few || long_parts)) a.place.on = 0;
+    }
+    *placed = a.place.on != 0;
     const int k_blocks = a.item_parts > 1 ? k_seen : (a.N + COLS - 1) / COLS;   // uncut blocks carry every score over
     const int64_t blocks1 = (int64_t)heads * q_blocks * a.key_parts, blocks2 = (int64_t)units * k_blocks * a.item_parts;
     if (blocks1 > INT32_MAX / 256 || blocks2 > INT32_MAX / 256) return hipErrorInvalidValue;   // (far beyond any GPU's memory)
@@ -595,12 +610,12 @@ hipError_t launch_obs_mfma_t(ObsArgs a, int units, hipStream_t st, Timing tm)
 }
 
 template <int DT>
-hipError_t launch_obs_mfma_d(int D, const ObsArgs& a, int units, hipStream_t st, Timing tm)
+hipError_t launch_obs_mfma_d(int D, const ObsArgs& a, int units, bool* placed, hipStream_t st, Timing tm)
 {
     switch (D) {
-        case 64: return launch_obs_mfma_t<DT, 64>(a, units, st, tm);
-        case 128: return launch_obs_mfma_t<DT, 128>(a, units, st, tm);
-        case 256: return launch_obs_mfma_t<DT, 256>(a, units, st, tm);
+        case 64: return launch_obs_mfma_t<DT, 64>(a, units, placed, st, tm);
+        case 128: return launch_obs_mfma_t<DT, 128>(a, units, placed, st, tm);
+        case 256: return launch_obs_mfma_t<DT, 256>(a, units, placed, st, tm);
     }
     return hipErrorInvalidValue;
 }
@@ -608,13 +623,14 @@ hipError_t launch_obs_mfma_d(int D, const ObsArgs& a, int units, hipStream_t st,
 }  // namespace
 
 
-hipError_t launch_obs_scores(int dtype, int D, const ObsArgs& a, int units, hipStream_t st, Timing tm)
+hipError_t launch_obs_scores(int dtype, int D, const ObsArgs& a, int units, bool* placed, hipStream_t st, Timing tm)
 {
+    *placed = false;
     if (a.N <= 0 || a.t_count <= 0) return hipSuccess;
     switch (dtype) {
-        case BUZZ_FP32: return launch_obs_mfma_d<BUZZ_FP32>(D, a, units, st, tm);
-        case BUZZ_FP16: return launch_obs_mfma_d<BUZZ_FP16>(D, a, units, st, tm);
-        case BUZZ_BF16: return launch_obs_mfma_d<BUZZ_BF16>(D, a, units, st, tm);
+        case BUZZ_FP32: return launch_obs_mfma_d<BUZZ_FP32>(D, a, units, placed, st, tm);
+        case BUZZ_FP16: return launch_obs_mfma_d<BUZZ_FP16>(D, a, units, placed, st, tm);
+        case BUZZ_BF16: return launch_obs_mfma_d<BUZZ_BF16>(D, a, units, placed, st, tm);
     }
     return hipErrorInvalidValue;
 }

@@ -71,6 +71,7 @@ long long rec_value(int i, const char* what)
     if (w == "units") return l.obs.units;
     if (w == "stats_cap") return (long long)l.obs.stats_cap;
     if (w == "partial_cap") return (long long)l.obs.partial_cap;
+    if (w == "places") return l.obs.place.on;
     return -1;
 }
 
