@@ -578,13 +578,15 @@ hipError_t launch_obs_mfma_t(ObsArgs a, int units, bool* placed, hipStream_t st,
     // stores all the chunks of its part.  With 32 KB they always do.  With more, whole (uncut) blocks have to be 8 (64 KB), or
     // half as many as compute units (128 KB): prefill and export, copy / steps, bf16 heads of 256, 16 queries, 48 blocks (16
     // units of 700 keys) 27.0 / 28.5 us, 96 (32 of 700) 36.3 / 37.4, 128 (16 of 2000) 43.8 / 42.8, 256 (32 of 2000) 67 / 63;
-    // of 128, 3 blocks (1 unit of 700 keys) 18.4 / 18.5, 8 (8 of 200) 18.7 / 18.5, 16 (16 of 200) 19.3 / 19.0.  And fewer than
-    // 32 blocks of step 1 must not have 8 chunks or more each (1 unit of 12000 keys: heads of 128 39.3 / 40.6, of 256 51.4 / 55.9).
+    // of 128, 3 blocks (1 unit of 700 keys) 18.4 / 18.5, 8 (8 of 200) 18.7 / 18.5, 16 (16 of 200) 19.3 / 19.0.  And step 1
+    // must not be up to 32 blocks of 8 chunks or more each (1 unit of 12000 keys: heads of 128 39.3 / 40.6, of 256 51.4 / 55.9);
+    // a larger one hides the stores (4 units of 10512 keys 47.6 / 45.7), however few of its blocks have some (64 heads of 128 on
+    // 16 units, 4001 queries 351 / 340).
     if (a.place.on) {
         constexpr int value_bytes = COLS * D * (DT == BUZZ_FP32 ? 4 : 2);
         const int64_t blocks = (int64_t)units * ((a.N + COLS - 1) / COLS);
         const bool few = a.item_parts == 1 && blocks < (value_bytes > 65536 ? a.compute_units / 2 : 8);
-        const bool long_parts = (int64_t)units * a.key_parts < 32 && a.key_part_len >= 8;
+        const bool long_parts = (int32_t)heads * q_blocks * a.key_parts <= 32 && a.key_part_len >= 8;
         if (value_bytes > 32768 && (few || long_parts)) a.place.on = 0;
     }
     *placed = a.place.on != 0;

@@ -287,9 +287,10 @@ def test_rows_that_an_eviction_moves_do_not_stay_in_the_last_level_cache(lib, ro
 @pytest.mark.parametrize("dtype,D,units,G,N,n_obs,steps_place", [
     ("bf16", 256, 16, 1, 700, 16, False), ("bf16", 256, 32, 1, 700, 16, False), ("bf16", 256, 16, 1, 2000, 16, True), ("bf16", 256, 32, 1, 2000, 16, True),
     ("fp32", 256, 4, 1, 700, 16, False), ("fp32", 256, 16, 1, 2000, 16, True),
-    ("bf16", 256, 4, 2, 3000, 500, True), ("bf16", 256, 1, 2, 12000, 256, False), ("fp32", 256, 1, 2, 5000, 256, False), ("bf16", 256, 1, 1, 2000, 2000, True),
+    ("bf16", 256, 4, 2, 3000, 500, True), ("bf16", 256, 1, 2, 12000, 256, False), ("bf16", 256, 1, 1, 2000, 2000, True),
     ("bf16", 128, 1, 1, 700, 16, False), ("bf16", 128, 8, 1, 200, 16, True), ("bf16", 128, 1, 1, 12000, 16, False), ("bf16", 128, 8, 1, 12000, 16, True),
     ("fp32", 128, 1, 1, 12000, 16, False), ("fp32", 128, 8, 2, 700, 256, True), ("fp16", 128, 256, 1, 4096, 256, True),
+    ("bf16", 128, 16, 4, 4001, 4001, True), ("bf16", 128, 1, 1, 12000, 12000, True), ("fp16", 128, 4, 1, 10512, 2, True), ("bf16", 256, 4, 1, 12000, 16, True),
     ("fp16", 64, 1, 1, 200, 16, True), ("fp32", 64, 1, 1, 12000, 16, True), ("fp32", 64, 8, 1, 2048, 2048, True)])
 def test_a_scored_prompt_that_is_kept_whole_is_placed_where_that_was_faster(lib, dtype, D, units, G, N, n_obs, steps_place):
     """By the scoring steps or by a copy of its own, at measured shapes on either side of the line."""
@@ -298,5 +299,6 @@ def test_a_scored_prompt_that_is_kept_whole_is_placed_where_that_was_faster(lib,
     assert lib.buzz_prefill(h, KP, VP, N, QP, n_obs, None, None) == 0
     names = [k for k, _ in recorded(lib)]
     assert "obs_" in names[0] and any("gather_rows" in k for k in names) == (not steps_place), names
-    assert all(lib.rec_value(i, b"places") == steps_place for k, i in recorded(lib) if "obs_" in k)
+    places = [lib.rec_value(i, b"places") for k, i in recorded(lib) if "obs_mfma" in k]
+    assert places[-2:] == [steps_place] * 2 and not any(places[:-2])        # the last pass
     assert lib.buzz_cache_destroy(h) == 0
