@@ -529,7 +529,7 @@ int buzz_cache_create(const buzz_config_t* cfg, void* dev_workspace, size_t byte
     const bool matrix = L.G >= 2 && cfg->kv_dtype != BUZZ_FP32, die_local = L.units % 8 == 0 && !(cfg->flags & BUZZ_FLAG_DEVICE_MERGE);
     c->split_model.row_us = (matrix ? 0.0078 : 0.009 * (1.0 + 0.237 * (L.G - 1))) * pow(L.row_bytes / 256.0, 0.63);
     c->split_model.split_us = (0.0366 + 0.006 * (L.units < 12 ? L.units : 12)) * (1.0 + 0.056 * (L.G - 1));
-    c->split_model.whole_us = die_local ? 1.0 + 0.01 * L.units : 1.6;
+    c->split_model.whole_us = die_local ? 1.0 + 0.01 * (L.units < 52 ? L.units : 52) : 1.6;
     c->die_map_override = -1;
     c->pending = false;
     c->last_buf = 0;
@@ -684,16 +684,19 @@ namespace {
 // count that fills every compute unit the same number of times avoids a tail: at most one block per compute unit
 // (floor(CUs / units) splits; with at least one unit per compute unit a unit is a single block and nothing is merged
 // across blocks at all).  A short step takes fewer: a block needs row_us per row of its split, whose loads it waits for
-// more than it streams, and the merge split_us per split, more where the partial results are larger or the units many.
-// row_us n / S + split_us S is least at the root below; a cache whose rows take less than the publishing and merging does
-// (whole_us) stays whole, up to 128 rows also one that a split does not save 2.6 us more: the launch that the counters of
-// the static scratch cost, and both entry points split alike.  Beyond 8 splits the merge goes by rounds of 8 and 16
-// loads: the counts between 8 and 16, and between 16 and 24, were slower than the nearer of the two.  Around the root the
-// time is flat to what the model leaves out (the tiles of a split over its waves), so splits of 128 rows, one 16-row tile
-// per wave, stay unless the model gains 0.4 us.  The constants are a fit to 840 shapes (1 to 64 units of 80 to 12000 rows,
-// groups of 1 to 8, heads of 64 to 256, all types, 5 to 23 split counts each): 4% less time on average than with splits of
-// at least 128 rows, none longer; 8 units of 300 rows, one head of 64 in fp32, 6.16 us with 3 splits and 5.46 with 5 or 6;
-// 1 unit of 12000 rows, 4 heads of 128 in bf16, 13.1 us with 94 and 10.7 with 32.
+// more than it streams (5 to 57 ns over the supported shapes), and the merge split_us per split, more where the partial
+// results are larger or the units many (43 to 151 ns).  row_us n / S + split_us S is least at the root below; a cache whose
+// rows take less than the publishing and merging does (whole_us) stays whole, up to 128 rows also one that a split does not
+// save 2.6 us more: the launch that the counters of the static scratch cost, and both entry points split alike.  Beyond 8
+// splits the merge goes by rounds of 8 and 16 loads: a root of more than 8 is rounded to 8, 16 or a larger multiple of 8.
+// Around the root the time is flat to what the model leaves out (the tiles of a split over its waves), so splits of 128
+// rows, one 16-row tile per wave, stay, whatever their number, unless the model gains 0.4 us: 8 units of 300 rows of one
+// fp32 head of 64 stay at 3 splits, 6.2 us, though 6 take 5.5; 8 of 1512 rows of 4 bf16 heads of 128 at 12, 7.3 us, as 8 do.
+// The constants are a fit to 1 to 64 units of 80 to 12000 rows, groups of 1 to 8, heads of 64 to 256, all types.  Against
+// splits of at least 128 rows, on 220 random shapes of that range 4% less time on average, on 120 of 65 to 255 units 0.7%, on
+// 67 of 12000 to 120000 rows 3%, none longer by more than 2% (whole_us ends to grow at 52 units: at 80 and 120 it left steps
+// whole that took 3-4% longer so).  1 unit of 12000 rows, 4 heads of 128 in bf16, 13.0 us with 94 splits, 10.9 with 40; 3 of
+// 175, 4 fp32 heads of 256, 14.2 with 2, 8.2 with 8; 100 of 154, 8 fp16 heads of 64, 7.7 with 2, 5.4 whole.
 int64_t auto_splits(const buzz_cache_t* c, int64_t n, int cus)
 {
     const SplitModel& m = c->split_model;

@@ -302,3 +302,16 @@ def test_a_scored_prompt_that_is_kept_whole_is_placed_where_that_was_faster(lib,
     places = [lib.rec_value(i, b"places") for k, i in recorded(lib) if "obs_mfma" in k]
     assert places[-2:] == [steps_place] * 2 and not any(places[:-2])        # the last pass
     assert lib.buzz_cache_destroy(h) == 0
+
+
+@pytest.mark.parametrize("units,rows,G,dtype,D,splits", [
+    (8, 110, 1, "fp32", 64, 1), (100, 154, 8, "fp16", 64, 1), (72, 140, 2, "fp16", 128, 1), (256, 5000, 1, "bf16", 128, 1),      # whole
+    (8, 300, 1, "fp32", 64, 3), (8, 1512, 4, "bf16", 128, 12), (8, 846, 4, "fp32", 64, 7),                                       # of 128 rows
+    (3, 175, 4, "fp32", 256, 8), (12, 431, 4, "fp32", 256, 8),                                                                   # shorter
+    (1, 12000, 4, "bf16", 128, 40), (1, 16000, 1, "bf16", 128, 56), (2, 20000, 4, "bf16", 64, 40), (3, 22272, 1, "fp16", 128, 85),  # longer
+    (80, 320, 2, "fp16", 64, 3), (120, 220, 1, "fp32", 64, 2), (64, 286, 4, "fp16", 64, 1), (48, 262, 4, "bf16", 64, 1)])          # many units
+def test_the_automatic_split_count_at_measured_shapes(lib, units, rows, G, dtype, D, splits):
+    h, _ = prepared(lib, units, G, D, dtype, rows)
+    grid = [lib.rec_value(0, b"grid_" + x) for x in (b"x", b"y", b"z")]
+    assert grid[0] * grid[1] * grid[2] == units * splits
+    assert lib.buzz_cache_destroy(h) == 0
