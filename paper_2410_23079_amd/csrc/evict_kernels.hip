@@ -531,13 +531,15 @@ static int pieces_log2(int row_bytes)
     return (16 << lpr_log2) == row_bytes && lpr_log2 <= 6 ? lpr_log2 : -1;
 }
 
-// Selection and placement of a sampled prompt, in one launch or two.  One takes that every survivor is kept.  With many
-// segments it gains the time that the ranking would leave the memory idle, if a wave moves its survivors at a time (256
-// pieces: 64 units of 4096 rows of 512 bytes, 25 of 200 kept, 52 us in one launch, 47 in two) and has two and half its
-// lanes' pieces at least (32 units of 32768 rows of 256 bytes, 1 of 5 kept: 130 and 120 us; 2 of 16 kept: 69 and 76.5).  With few
-// it saves a launch, 2.5 of 17 us, up to 128 pieces (16 units of 4239 rows of 512 bytes, 8 of 64 kept: 18 and 17 us).
-// In between all waves rank and then all of them copy, in one launch as in two (32 units of 8192 rows of 128 bytes, 12 of
-// 100 kept: 18.4 and 17.3 us).
+// Selection and placement of a sampled prompt, in one launch or two.  One takes that every survivor is kept (no thinning).
+// It saves a launch, and where segments are many the time that the ranking would leave the memory idle; two spread the copy
+// over all blocks, however unevenly segments and survivors are spread.  The line encloses shapes where one launch was never
+// the slower of the two, of 256 measured (4 to 128 units of 2048 to 32768 rows of 128 to 512 bytes, 1 of 5 to 32 of 128 kept):
+// at least 4096 segments of 32 to 256 pieces, two rows or more (prefill and export, two / one: 32 units of 32768 rows of 256
+// bytes, 8 of 64 kept, 87.9 / 82.5 us; 128 of 4096, 2 of 16 kept, 52.8 / 45.4), and at most 512 segments of up to 128 pieces
+// (8 units of 4096 rows of 256 bytes, 8 of 64 kept, 10.6 / 9.8).  Outside it goes either way and two launches stay: 8 units of
+// 4096 rows, 4 of 32 kept, 10.3 / 8.3; 32 of 8192, 8 of 64, 27.9 / 24.6; but, of 128 bytes, 4 of 32768, 1 of 5, 16.4 / 20.0,
+// 32 of 8192, 12 of 100, 19.2 / 21.1.
 hipError_t launch_place_sampled(SelectArgs a, const GatherArgs& g, int units, hipStream_t st)
 {
     const int n_seg = (a.new_count + a.segment - 1) / a.segment, lpr_log2 = pieces_log2(g.row_bytes);

@@ -315,3 +315,24 @@ def test_the_automatic_split_count_at_measured_shapes(lib, units, rows, G, dtype
     grid = [lib.rec_value(0, b"grid_" + x) for x in (b"x", b"y", b"z")]
     assert grid[0] * grid[1] * grid[2] == units * splits
     assert lib.buzz_cache_destroy(h) == 0
+
+
+@pytest.mark.parametrize("units,rows,D,dtype,segment,keep,one", [
+    (32, 32768, 128, "bf16", 64, 8, True), (128, 4096, 128, "bf16", 16, 2, True), (32, 32768, 64, "bf16", 32, 4, True), (8, 4096, 128, "bf16", 64, 8, True),
+    (1, 1000, 64, "fp32", 16, 1, True), (4, 32768, 64, "bf16", 5, 1, False), (32, 8192, 64, "bf16", 100, 12, False), (8, 4096, 256, "bf16", 100, 12, False),
+    (32, 32768, 128, "bf16", 5, 1, False), (8, 4096, 128, "bf16", 32, 4, False), (4, 4096, 128, "bf16", 1000, 8, False)])
+@pytest.mark.parametrize("thinned", [False, True])
+def test_a_sampled_prompt_is_placed_in_one_launch_or_two(lib, units, rows, D, dtype, segment, keep, one, thinned):
+    """At measured shapes on either side of the line; two launches where the survivors are thinned before they are placed."""
+    window = rows // 8
+    h = create(lib, config(batch=1, n_q_heads=units, n_kv_heads=units, head_dim=D, kv_dtype=dtype, window=window, segment=segment, keep=keep,
+                           evict_every=segment, max_context=rows, old_stride=2 if thinned else 1,
+                           capacity=4 + window + segment + (rows - window) * keep // segment // 2 + keep + 8 if thinned else 0))
+    lib.rec_reset(-1)
+    assert lib.buzz_prefill(h, KP, VP, rows, None, 0, SP, None) == 0
+    names = [k for k, _ in recorded(lib)]
+    if one and not thinned:
+        assert len(names) == 1 and "place_sampled" in names[0]
+    else:
+        assert len(names) == 2 and "segment_topk" in names[0] and "gather_rows" in names[1]
+    assert lib.buzz_cache_destroy(h) == 0
