@@ -308,10 +308,13 @@ inline int hip_rc(hipError_t e) { return e == hipSuccess ? BUZZ_OK : BUZZ_EHIP; 
 
 // Whether n rows per unit that go into the cache go past the last-level cache: it does not hold them, or the caller has said
 // that nothing survives in it until they are read.  What is left there otherwise is written back under the decode steps: 8
-// layers of 62 MB imported, then 4 steps of each, 700 us with normal stores and 683 so, of 93 MB 994 and 957.
+// layers of 62 MB imported, then 4 steps of each, 700 us with normal stores and 683 so, of 93 MB 994 and 957.  A few rows go
+// past it too: what reading them from there saves is less than their launch waits at its end for the caches of the dies.
+// Imported, 4 steps, exported, normal stores / past it: 4 MB 36.3 / 35.5 us, 6 MB 41.5 / 40.8, 17 MB 53.4 / 54.9, 32 MB 66.5 / 72.2.
 bool streams_into_cache(const buzz_cache_t* c, int64_t n)
 {
-    return (c->cfg.flags & BUZZ_FLAG_STREAMING) || (double)c->L.units * (double)n * 2.0 * c->L.row_bytes > kLastLevelCacheBytes;
+    const double bytes = (double)c->L.units * (double)n * 2.0 * c->L.row_bytes;
+    return (c->cfg.flags & BUZZ_FLAG_STREAMING) || bytes > kLastLevelCacheBytes || bytes < 1.0e7;
 }
 
 GatherArgs cache_gather_base(const buzz_cache_t* c)

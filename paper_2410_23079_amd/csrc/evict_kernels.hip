@@ -323,8 +323,8 @@ __global__ __launch_bounds__(256) void evict_new_rows_kernel(const EvictArgs a)
 // shape in which a copy is fastest on this chip (1 GB device to device: one piece per thread 6.2 TB/s, four 5.7,
 // eight 4.2); with 64 rows per block and four dependent load-store rounds per thread this kernel moved 5.0 TB/s.
 // Rows are loaded past the last-level cache (256 MB), and stored past it (non-temporal) unless they come in from a caller: a
-// prompt or an import that it holds is stored normally and stays there for what comes next, if the caller has not set
-// BUZZ_FLAG_STREAMING.  Other rows each time: a prompt of which 126 MB are kept, placed and exported, 93.5 us with
+// prompt or an import of 10 MB or more that it holds is stored normally and stays there for what comes next, if the caller has
+// not set BUZZ_FLAG_STREAMING.  Other rows each time: a prompt of which 126 MB are kept, placed and exported, 93.5 us with
 // non-temporal stores into the cache, 81.9 so, 87 if the export loads normally as well; 126 MB imported, 64 steps, exported
 // 1558, 1552 and 1567; 1 GB 10833 us with non-temporal accesses only, 10906 with normal stores into the cache: what they leave
 // behind is written back under the decode steps.  So are the rows that evictions move: with normal accesses there, 8 caches

@@ -247,11 +247,12 @@ def test_segments_are_ranked_by_what_was_faster(lib, segments, segment, block, u
     assert lib.buzz_cache_destroy(h) == 0
 
 
-@pytest.mark.parametrize("flags,rows,past", [(0, 1000, False), (0, 9000, True), (FLAG_STREAMING, 1000, True), (FLAG_STREAMING, 9000, True),
+@pytest.mark.parametrize("flags,rows,past", [(0, 200, True), (0, 1000, False), (0, 9000, True), (FLAG_CACHED, 200, True), (FLAG_STREAMING, 1000, True), (FLAG_STREAMING, 9000, True),
                                              (FLAG_CACHED, 1000, False), (FLAG_CACHED, 9000, True)])
 @pytest.mark.parametrize("call", ["import", "prefill", "sampled"])
 def test_rows_go_into_the_cache_past_the_last_level_cache_or_not(lib, flags, rows, past, call):
-    """64 units of 512-byte rows: 33 MB and 590 MB.  More than 256 MB, or a caller who has said that nothing survives there."""
+    """64 units of 512-byte rows: 7, 33 and 590 MB (the sampled prompt keeps all rows).  Fewer than 10 MB, more than 256 MB, or a
+    caller who has said that nothing survives there."""
     sampled = call == "sampled"
     h = create(lib, config(batch=1, n_q_heads=64, n_kv_heads=64, window=rows // 2, segment=64, keep=64 if sampled else 8,
                            evict_every=64 if sampled else rows, max_context=rows, flags=flags))
