@@ -26,9 +26,9 @@ __host__ __device__ inline int wave_slice(int floats) { return (floats + 3) & ~3
 // the kernel.  That count keeps too many rows only where equal scores straddle the boundary.  The last survivor's score
 // is then the one that the most rows are larger than among the kept, its equals share the places that the larger rows
 // leave, and a pass that only compares with that score numbers them: a tie costs one step per 64 rows.
-// 448 segments of 64 in each of 32 units: 12.7 us with the tie-breaker in every comparison, 9 us now.  Prefill of 16
-// segments of 1000 in each of 32 units: 253 us with distinct scores, 716 with equal ones when ties took a second pass of
-// comparisons, 165 with either now.
+// 448 segments of 64 in each of 32 units: 12.7 us with the tie-breaker in every comparison, 9 us now.  One segment of 1000
+// rows in each of 32 units, evicted in place: 175 us with distinct scores and with equal ones, for which ties took 2.8 times
+// as long when they were a second pass of comparisons.  (Where a launch of its own selects, a block takes such segments.)
 template <typename Emit>
 __device__ inline void rank_segment(const float* sc, int len, int take, int lane, Emit emit)
 {
@@ -146,9 +146,10 @@ __global__ __launch_bounds__(256) void segment_topk_kernel(const SelectArgs a)
 // kernel, whose work grows with the square of the length.
 // A wave takes a contiguous run of the rows, 64 at a time, so that rows are numbered by ballots and two counts per wave,
 // without a barrier per 1024 rows.  Up to 32 of a wave's rounds stay in registers (segments of 32768 rows; 21688 rows in 16
-// units, prefill and export: 66.7 us so, 81 read again in each pass); longer segments are read again, 16 rounds in flight.  Digits of 11 bits keep the exponent and two more bits in the first: a
-// prompt's scores then spread over a few dozen bins, where one byte puts nearly all of them into four, on whose counters
-// the lanes of a wave queue.
+// units, prefill and export: 66.7 us so, 81 read again in each pass); longer segments are read again, 16 rounds in flight.
+// Digits of 11 bits keep the exponent and two more bits in the first: a prompt's scores then spread over a few dozen bins,
+// where one byte puts nearly all of them into four, on whose counters the lanes of a wave queue.  (32 units of 4000 rows in
+// one segment, prefill: 20.5 us with scores of three values, 26 with equal ones.)
 constexpr int kTopkBlock = 1024, kTopkWaves = kTopkBlock / 64, kTopkBins = 2048;
 
 __device__ inline unsigned score_key(float v)      // larger score <=> larger key; NaN ranks with -inf; -0 == +0
