@@ -62,7 +62,8 @@ enum {
     /* How the decode kernel reads K and V.  Default (neither flag): streaming loads when one step of this
        cache reads more than the GPU's 256 MB last-level cache, cached loads otherwise.  A caller that runs many
        layers (so that nothing survives in cache between two steps of one layer) should set STREAMING: prefill and
-       import then write their rows past that cache as well, as they do by themselves with more than it holds. */
+       import then write their rows past that cache as well, as they do by themselves with more than it holds or
+       less than 10 MB. */
     BUZZ_FLAG_STREAMING = 4u,
     BUZZ_FLAG_CACHED = 8u,
     /* Log-n scaled attention (Sec. 3.5): the softmax scale of a query is multiplied by log(n)/log(512),
