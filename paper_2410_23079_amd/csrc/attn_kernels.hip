@@ -199,6 +199,20 @@ struct SplitCtx {
     size_t ubase;
 };
 
+// The arguments, in scalar registers from the start.  Left to itself the compiler fetches each where it is first used: a
+// dozen fetches one after the other in front of the stream and half as many in the tail, each a wait, the first on each of
+// four cache lines a wait for memory.  Asked for at once they are one wait (what is fetched again later finds its line).
+// (256 steps of 8 units of 110 rows of one fp32 head of 64: 1396 -> 1288 us, half of that from request_fresh_row; 256 steps of
+// 256 units of 1240 rows of one fp16 head of 128 5453 -> 5288; 64 steps of 8 units of 1540 rows, 4 bf16 heads of 128, 478 -> 470.)
+__device__ inline void hold_arguments(const AttnArgs& a)
+{
+    asm volatile("" :: "s"(a.q), "s"(a.k_new), "s"(a.v_new), "s"(a.K), "s"(a.V), "s"(a.score), "s"(a.logit), "s"(a.logit_prev),
+                 "s"(a.part_ml), "s"(a.part_o), "s"(a.stat), "s"(a.stat_prev), "s"(a.ticket), "s"(a.out),
+                 "s"(a.map.front), "s"(a.map.ring_base), "s"(a.map.ring_head), "s"(a.map.ring_cap), "s"(a.n), "s"(a.cap),
+                 "s"(a.rows_per_split), "s"(a.n_splits), "s"(a.s_cap), "s"(a.pending), "s"(a.fixed_tiles), "s"(a.xcd_local),
+                 "s"(a.die_map), "s"(a.scale_log2), "s"(a.units_per_die), "s"(a.new_phys));
+}
+
 __device__ inline SplitCtx make_ctx(const AttnArgs& a)
 {
     SplitCtx x;
@@ -210,7 +224,7 @@ __device__ inline SplitCtx make_ctx(const AttnArgs& a)
         // unit share b mod 8 = blockIdx.x (units is a multiple of 8 here) and die d gets units d * units/8 ...
         x.home = blockIdx.x;
         x.split = blockIdx.y;
-        x.unit = blockIdx.x * gridDim.z + blockIdx.z;
+        x.unit = blockIdx.x * a.units_per_die + blockIdx.z;
     }
     x.j0 = x.split * a.rows_per_split;
     x.j1 = min(a.n, x.j0 + a.rows_per_split);
@@ -349,7 +363,11 @@ __device__ inline void request_fresh_row(const AttnArgs& a, const SplitCtx& x, S
 {
     constexpr int P = ROWB / 16;
     const int i = threadIdx.x;
-    if (fresh_piece<ROWB>(a, x)) p.fresh = *(const u32x4*)((const char*)(i < P ? a.k_new : a.v_new) + (size_t)x.unit * ROWB + (i < P ? i : i - P) * 16);
+    // (the arguments as values: selected in place, the compiler fetched them with a load per lane and waited for everything
+    // requested so far, in front of the stream)
+    const char* k = (const char*)a.k_new + (size_t)x.unit * ROWB;
+    const char* v = (const char*)a.v_new + (size_t)x.unit * ROWB - ROWB;
+    if (fresh_piece<ROWB>(a, x)) p.fresh = *(const u32x4*)((i < P ? k : v) + i * 16);
 }
 template <int ROWB, int G>
 __device__ inline void store_fresh_row(const AttnArgs& a, const SplitCtx& x, const SideRows<G>& p)
@@ -668,6 +686,7 @@ __global__ __launch_bounds__(NW * 64, BUZZ_MIN_BLOCKS) void attn_split_kernel(co
     __shared__ WaveResults<G, D, NW> sm;
     static_assert(alignof(decltype(sm)) >= 16 && offsetof(decltype(sm), acc) % 16 == 0 && D % 4 == 0, "16-byte stores into acc");
 
+    hold_arguments(a);
     const SplitCtx x = make_ctx(a);
     const int unit = x.unit, j0 = x.j0;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -869,6 +888,7 @@ __global__ __launch_bounds__(NW * 64) void attn_split_mfma_kernel(const AttnArgs
     __shared__ WaveResults<G, D, NW> sm;
     static_assert(alignof(decltype(sm)) >= 16 && offsetof(decltype(sm), acc) % 16 == 0 && D % 4 == 0, "16-byte stores into acc");
 
+    hold_arguments(a);
     const SplitCtx x = make_ctx(a);
     const int unit = x.unit, j0 = x.j0;
     const int tid = threadIdx.x, lane = tid & 63;

@@ -816,6 +816,7 @@ int decode_step_impl(buzz_cache_t* c, const void* q, const void* k_new, const vo
         // the 8 dies
         a.xcd_local = (a.n_splits > 1 && L.units % 8 == 0 && !(cfg.flags & BUZZ_FLAG_DEVICE_MERGE) &&
                        die_local_ok(&a.die_map)) ? 1 : 0;
+        a.units_per_die = L.units / 8;
         if (a.xcd_local && c->die_map_override >= 0) a.die_map = (uint32_t)c->die_map_override;
         if (hipError_t e = launch_attn_split(cfg.kv_dtype, cfg.head_dim, L.G, a, L.units, st,
                                              static_scratch ? Timing{} : prof_pair(c, 0)))
