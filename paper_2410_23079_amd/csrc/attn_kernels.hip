@@ -36,6 +36,7 @@ typedef _Float16 f16x4_t __attribute__((ext_vector_type(4)));
 typedef short s16x4_t __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+typedef int i32x4 __attribute__((ext_vector_type(4)));
 
 // Build-time tuning knobs (defaults are the measured best; a sweep overrides them with -D).
 // 16-byte loads of K (and of V) per lane and tile.  Group size 1 keeps two tiles in flight; small tiles win
@@ -135,14 +136,31 @@ template <int CTRL> __device__ inline float dpp_move(float v) {
     return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, false));
 }
 
+// The two values that lanes l and l ^ 16 (32) hold, in both of them: `a` the one of the lane with that bit clear.
+struct LanePair { float a, b; };
+template <int BIT> __device__ inline LanePair lane_pair(float v)
+{
+    static_assert(BIT == 16 || BIT == 32, "rows of 16 lanes or halves of a wave");
+    const unsigned x = __builtin_bit_cast(unsigned, v);
+    if constexpr (BIT == 16) {
+        const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+        return {__uint_as_float(r[0]), __uint_as_float(r[1])};
+    } else {
+        const auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+        return {__uint_as_float(r[0]), __uint_as_float(r[1])};
+    }
+}
+template <int BIT> __device__ inline float pair_sum(float v) { const LanePair p = lane_pair<BIT>(v); return p.a + p.b; }
+template <int BIT> __device__ inline float pair_max(float v) { const LanePair p = lane_pair<BIT>(v); return fmaxf(p.a, p.b); }
+
 // Sum over the LPR consecutive lanes that share a cache row; every lane of the group gets the total.
 template <int LPR> __device__ inline float row_sum(float v) {
     v += dpp_move<0xB1>(v);                 // quad_perm [1,0,3,2]
     v += dpp_move<0x4E>(v);                 // quad_perm [2,3,0,1]
-    if (LPR >= 8) v += dpp_move<0x141>(v);  // row_half_mirror
-    if (LPR >= 16) v += dpp_move<0x140>(v); // row_mirror
-    if (LPR >= 32) v += __shfl_xor(v, 16);
-    if (LPR >= 64) v += __shfl_xor(v, 32);
+    if constexpr (LPR >= 8) v += dpp_move<0x141>(v);  // row_half_mirror
+    if constexpr (LPR >= 16) v += dpp_move<0x140>(v); // row_mirror
+    if constexpr (LPR >= 32) v = pair_sum<16>(v);
+    if constexpr (LPR >= 64) v = pair_sum<32>(v);
     return v;
 }
 
@@ -208,7 +226,7 @@ __device__ inline void hold_arguments(const AttnArgs& a)
 {
     asm volatile("" :: "s"(a.q), "s"(a.k_new), "s"(a.v_new), "s"(a.K), "s"(a.V), "s"(a.score), "s"(a.logit), "s"(a.logit_prev),
                  "s"(a.part_ml), "s"(a.part_o), "s"(a.stat), "s"(a.stat_prev), "s"(a.ticket), "s"(a.out),
-                 "s"(a.map.front), "s"(a.map.ring_base), "s"(a.map.ring_head), "s"(a.map.ring_cap), "s"(a.n), "s"(a.cap),
+                 "s"(__builtin_bit_cast(i32x4, a.map)), "s"(a.n), "s"(a.cap),
                  "s"(a.rows_per_split), "s"(a.n_splits), "s"(a.s_cap), "s"(a.pending), "s"(a.fixed_tiles), "s"(a.xcd_local),
                  "s"(a.die_map), "s"(a.scale_log2), "s"(a.units_per_die), "s"(a.new_phys));
 }
@@ -284,6 +302,24 @@ struct TileMap {
     }
 };
 
+// A tile of a short split (one or two tiles for each wave of the block): WROWS logical rows, wherever they are stored.  Short
+// steps are bound by latency and by the instructions in front of the first load and behind the last.  All of the split's
+// rows are requested at once, at their own 32-bit offsets from the unit's first row, so there are no runs to cut tiles at (the
+// linear region's end, the ring's wrap and the new row each began another tile, and often a second round of loads for the
+// whole block), no tiles to claim, and no barrier before the stream.  256 steps of 8 units of 110 rows, one fp32 head of
+// 64: 1233 -> 970 us; 64 steps of 8 units of 1540 rows in 13 splits, 4 bf16 heads of 128, 470 -> 449; 48 of 8 of 1060 in 9, 4 fp32
+// heads of 64, 384 -> 356; per step, 8 units of 600 rows in 5 splits, one bf16 head of 128, 6.5 -> 5.0 us.
+template <int WROWS>
+struct ShortTile {
+    int j0, cnt, base;
+    __device__ inline ShortTile(const SplitCtx& x, int t) : j0(x.j0), cnt(x.j1 - x.j0), base(t * WROWS) {}
+    __device__ inline bool exists() const { return base < cnt; }
+    __device__ inline bool last(const SplitCtx& x, int n) const { return x.j1 == n && base + WROWS >= cnt; }   // has the new row
+    // its logical row i, or the split's last
+    __device__ inline int row(int i) const { return j0 + min(base + i, cnt - 1); }
+    __device__ inline Tile tile() const { Tile k; k.lo = j0; k.phys = 0; k.cnt = cnt; k.lead = 0; k.base = base; k.fresh = false; return k; }
+};
+
 __device__ inline int claim_tile(int* counter)
 {
     int t = 0;
@@ -298,19 +334,32 @@ __device__ inline int next_tile(const AttnArgs& a, int* counter, int last, int n
     return a.fixed_tiles ? last + nw : claim_tile(counter);
 }
 
+// A barrier that orders LDS only: loads from memory that are in flight stay in flight across it.
+__device__ inline void lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 // A wave's way through the tiles.  TWO: two tile buffers, the next tile's loads are issued before the current tile is
 // consumed.  (The compiler waits for both at once, because the next tile may not exist.  With the loads
 // issued unconditionally, and the loop shaped so that it waits for the older half only, the stream was no faster -- 52
 // us of 62 on one sequence of 23.6k rows by 32 heads, 7.4 TB/s either way -- and waves with one tile paid for loads of
-// tiles that do not exist: 8 units of 1500 rows, 4 heads each, 10.1 instead of 8.0 us per step.)
-template <bool TWO, typename Buf, typename Load, typename Compute>
-__device__ inline void stream_tiles(const AttnArgs& a, int* counter, int wave, int nw, int total, Load load, Compute compute)
+// tiles that do not exist: 8 units of 1500 rows, 4 heads each, 10.1 instead of 8.0 us per step.)  The side requests come
+// behind the first tile's loads and before the second's: 64 steps of 512 units of 3900 rows, one bf16 head of 128, 10580 us,
+// 10800 with the side requests first, 10760 with both tiles first.  With one buffer they come first: with the first tile's
+// loads hoisted over them the loop copies its registers, 64 steps of 32 units of 7800 rows, 4 heads of 128, 1550 -> 1576 us.
+template <bool TWO, typename Buf, typename Load, typename Requests, typename Compute>
+__device__ inline void stream_tiles(const AttnArgs& a, int* counter, int wave, int nw, int total, Load load, Requests requests, Compute compute)
 {
     int t = wave;
     if constexpr (TWO) {
         Buf first, second;
+        int tn = t + nw;
         if (t < total) load(first, t);
-        int tn = next_tile(a, counter, t, nw);
+        requests();
+        lds_barrier();                                    // the counter is set
         while (t < total) {
             if (tn < total) load(second, tn);
             int t2 = next_tile(a, counter, tn, nw);
@@ -323,6 +372,8 @@ __device__ inline void stream_tiles(const AttnArgs& a, int* counter, int wave, i
             t = tn; tn = t2;
         }
     } else {
+        requests();
+        lds_barrier();                                    // the counter is set
         while (t < total) {
             Buf buf;
             load(buf, t);
@@ -333,14 +384,6 @@ __device__ inline void stream_tiles(const AttnArgs& a, int* counter, int wave, i
     }
 }
 
-// A barrier that orders LDS only: loads from memory that are in flight stay in flight across it.
-__device__ inline void lds_barrier()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 // The side phase: per row of the split, this step's logits out, and the score with the previous step's probability
 // added (one step late, because a probability needs the maximum and sum over all splits).  A thread takes the rows
 // tid, tid + NTHR, ...: every access of a wave is one contiguous piece whatever the row's place in the arena is.
@@ -348,9 +391,9 @@ __device__ inline void lds_barrier()
 // their latency is never exposed; longer splits take further rounds of SR rows.
 template <int G> constexpr int side_rows() { return G == 1 ? 8 : (G <= 4 ? 4 : 2); }
 
-template <int G> struct SideRows {
+template <int G, int SR> struct SideRows {
     float M[G], iL[G];                                    // the previous step's softmax statistics of the unit
-    float sc[side_rows<G>()], lp[side_rows<G>()][G];      // old scores and the previous step's logits
+    float sc[SR], lp[SR][G];                              // old scores and the previous step's logits
     u32x4 fresh;                                          // one of the new row's pieces (K's, then V's), last split only
 };
 
@@ -358,8 +401,8 @@ template <int G> struct SideRows {
 // side phase (stores between the streaming loop's loads would make the compiler wait for more than it needs).
 template <int ROWB>
 __device__ inline bool fresh_piece(const AttnArgs& a, const SplitCtx& x) { return x.j1 == a.n && x.j0 < a.n && (int)threadIdx.x < 2 * (ROWB / 16); }
-template <int ROWB, int G>
-__device__ inline void request_fresh_row(const AttnArgs& a, const SplitCtx& x, SideRows<G>& p)
+template <int ROWB, int G, int SR>
+__device__ inline void request_fresh_row(const AttnArgs& a, const SplitCtx& x, SideRows<G, SR>& p)
 {
     constexpr int P = ROWB / 16;
     const int i = threadIdx.x;
@@ -369,8 +412,8 @@ __device__ inline void request_fresh_row(const AttnArgs& a, const SplitCtx& x, S
     const char* v = (const char*)a.v_new + (size_t)x.unit * ROWB - ROWB;
     if (fresh_piece<ROWB>(a, x)) p.fresh = *(const u32x4*)((i < P ? k : v) + i * 16);
 }
-template <int ROWB, int G>
-__device__ inline void store_fresh_row(const AttnArgs& a, const SplitCtx& x, const SideRows<G>& p)
+template <int ROWB, int G, int SR>
+__device__ inline void store_fresh_row(const AttnArgs& a, const SplitCtx& x, const SideRows<G, SR>& p)
 {
     constexpr int P = ROWB / 16;
     const int i = threadIdx.x;
@@ -383,8 +426,8 @@ __device__ inline void store_fresh_row(const AttnArgs& a, const SplitCtx& x, con
 // element i of an array that starts at a wave-uniform address: a scalar base and a 32-bit offset per lane
 __device__ inline float* lane_element(const float* base, unsigned i) { return (float*)((char*)base + i * 4u); }
 
-template <int G, int NTHR>
-__device__ inline void request_side_rows(const AttnArgs& a, const SplitCtx& x, int first, SideRows<G>& p)
+template <int G, int NTHR, int SR>
+__device__ inline void request_side_rows(const AttnArgs& a, const SplitCtx& x, int first, SideRows<G, SR>& p)
 {
     const float* score_u = a.score + x.ubase;
     const float* logit_prev_u = a.logit_prev + x.ubase * G;
@@ -400,7 +443,7 @@ __device__ inline void request_side_rows(const AttnArgs& a, const SplitCtx& x, i
     // against 508 us per 64 steps).
     if (G > 1 && !a.pending) return;
 #pragma unroll
-    for (int i = 0; i < side_rows<G>(); ++i) {
+    for (int i = 0; i < SR; ++i) {
         if (x.j0 + first + i * NTHR >= x.jl1 && (G > 1 || i > 0)) break;
         const int j = x.j0 + first + (int)threadIdx.x + i * NTHR;
         if constexpr (G == 1) request(i, max(min(j, x.jl1 - 1), 0));
@@ -408,8 +451,8 @@ __device__ inline void request_side_rows(const AttnArgs& a, const SplitCtx& x, i
     }
 }
 
-template <int G>
-__device__ inline void request_prev_stat(const AttnArgs& a, int unit, SideRows<G>& p)
+template <int G, int SR>
+__device__ inline void request_prev_stat(const AttnArgs& a, int unit, SideRows<G, SR>& p)
 {
 #pragma unroll
     for (int g = 0; g < G; ++g) {
@@ -418,13 +461,13 @@ __device__ inline void request_prev_stat(const AttnArgs& a, int unit, SideRows<G
     }
 }
 
-template <int G, int NTHR>
-__device__ inline void store_side_rows(const AttnArgs& a, const SplitCtx& x, int first, const SideRows<G>& p, const float* stage)
+template <int G, int NTHR, int SR>
+__device__ inline void store_side_rows(const AttnArgs& a, const SplitCtx& x, int first, const SideRows<G, SR>& p, const float* stage)
 {
     float* score_u = a.score + x.ubase;
     float* logit_u = a.logit + x.ubase * G;               // [G][cap] for this unit, written by this step
 #pragma unroll
-    for (int i = 0; i < side_rows<G>(); ++i) {
+    for (int i = 0; i < SR; ++i) {
         if (x.j0 + first + i * NTHR >= x.j1) break;
         const int r = first + (int)threadIdx.x + i * NTHR, j = x.j0 + r;
         if (j < x.j1) {
@@ -565,8 +608,8 @@ __device__ inline void merge_splits(const AttnArgs& a, int unit, int wave, bool 
 //      stream of the block is over by then.  Doing the score update at the start of the block instead, under the
 //      latency of the first K/V loads, was measured 8% slower: its writes then compete with the ramping stream.
 //      Between 1 and 2 it delays the tickets: 8 units, 12 splits: 8.4 instead of 8.0 us per step.)
-template <int G, int D, int NW, int ROWB>
-__device__ inline void finish_split(const AttnArgs& a, const SplitCtx& x, SideRows<G>& side, const float* stage, WaveResults<G, D, NW>& sm)
+template <int G, int D, int NW, int ROWB, bool ONE_ROUND, int SR>
+__device__ inline void finish_split(const AttnArgs& a, const SplitCtx& x, SideRows<G, SR>& side, const float* stage, WaveResults<G, D, NW>& sm)
 {
     constexpr int NTHR = NW * 64;                         // threads per block
     const int tid = threadIdx.x, unit = x.unit;
@@ -646,8 +689,10 @@ __device__ inline void finish_split(const AttnArgs& a, const SplitCtx& x, SideRo
         const int arrival = __builtin_amdgcn_readfirstlane(sm.ticket);
         if ((arrival & 0xffff) == S - 1) {
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-            // merging threads: the lower half starts its side phase, unless the block has only 4 waves for a wide output
-            constexpr int NM = G * D >= kWideBlockMaxGD ? NTHR : NTHR / 2;
+            // merging threads: the lower half starts its side phase, unless the block has only 4 waves for a wide output, or a
+            // short split's side phase and more groups of outputs than waves (2 units, 32 splits of 125 rows, 8 heads of 128: 10.1
+            // us per step, 9.25 so; with 4 heads 8 units, 13 splits, half of them: 6.82, all 6.91)
+            constexpr int NM = G * D >= kWideBlockMaxGD || (ONE_ROUND && G * D / 64 > NW) ? NTHR : NTHR / 2;
             if (tid >= NTHR - NM) {
                 // A die-local merge with a block on an unexpected die may have missed partials: its output is NaN
                 // rather than plausible numbers.
@@ -660,18 +705,20 @@ __device__ inline void finish_split(const AttnArgs& a, const SplitCtx& x, SideRo
             }
         }
     }
-    store_fresh_row<ROWB, G>(a, x, side);
+    store_fresh_row<ROWB>(a, x, side);
     store_side_rows<G, NTHR>(a, x, 0, side, stage);
+    if constexpr (!ONE_ROUND) {
 #pragma unroll 1
-    for (int first = side_rows<G>() * NTHR; x.j0 + first < x.j1; first += side_rows<G>() * NTHR) {
-        request_side_rows<G, NTHR>(a, x, first, side);
-        store_side_rows<G, NTHR>(a, x, first, side, stage);
+        for (int first = SR * NTHR; x.j0 + first < x.j1; first += SR * NTHR) {
+            request_side_rows<G, NTHR>(a, x, first, side);
+            store_side_rows<G, NTHR>(a, x, first, side, stage);
+        }
     }
     if (tid == 0) BUZZ_STAMP(3);
 }
 
 // Vector-ALU streaming kernel (any dtype; the choice for one query head per kv head).
-template <typename T, int D, int G, int U, bool NT, int NW>
+template <typename T, int D, int G, int U, bool NT, int NW, int SHORT>
 __global__ __launch_bounds__(NW * 64, BUZZ_MIN_BLOCKS) void attn_split_kernel(const AttnArgs a)
 {
     using E = Elem<T>;
@@ -693,7 +740,8 @@ __global__ __launch_bounds__(NW * 64, BUZZ_MIN_BLOCKS) void attn_split_kernel(co
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // tile numbers and addresses stay in scalar registers
     const int c = lane % LPR, rs = lane / LPR;
     if (tid == 0) { BUZZ_STAMP(0); BUZZ_STAMP_VALUE(6, __builtin_amdgcn_s_getreg((31 << 11) | 4)); BUZZ_STAMP_VALUE(7, __builtin_amdgcn_s_getreg((31 << 11) | 20)); }
-    if (tid == 0) sm.next_tile = NW;                      // tiles 0 .. NW-1 are the waves' first tiles
+    constexpr bool TWO = G == 1;
+    if (!SHORT && tid == 0) sm.next_tile = TWO ? 2 * NW : NW;       // the waves' first tiles are not claimed
 
     u32x4 qr[G];                                          // this lane's 16 bytes of every query head, raw
     {
@@ -721,7 +769,6 @@ __global__ __launch_bounds__(NW * 64, BUZZ_MIN_BLOCKS) void attn_split_kernel(co
     // extra bytes.
     struct Buf { u32x4 k[U], v[U]; };
     const TileMap<WROWS, false> tiles(a, x);
-    const int total = tiles.total();
     auto load_t = [&](u32x4 (&kr)[U], u32x4 (&vr)[U], int t) {
         const Tile k = tiles.locate(t);
         const char* kp = k.fresh ? (const char*)a.k_new + (size_t)unit * ROWB : Kb + (size_t)k.phys * ROWB;
@@ -734,8 +781,7 @@ __global__ __launch_bounds__(NW * 64, BUZZ_MIN_BLOCKS) void attn_split_kernel(co
         }
     };
 
-    auto compute_t = [&](const u32x4 (&kr)[U], const u32x4 (&vr)[U], int t) {
-        const Tile k = tiles.locate(t);
+    auto compute_t = [&](const u32x4 (&kr)[U], const u32x4 (&vr)[U], const Tile& k) {
         const int stg = k.lo - j0 + k.base;               // staging index (row relative to the split's first row)
         float s[G][U];
 #pragma unroll
@@ -780,34 +826,81 @@ __global__ __launch_bounds__(NW * 64, BUZZ_MIN_BLOCKS) void attn_split_kernel(co
         }
     };
 
-    SideRows<G> side;
-    request_side_rows<G, NW * 64>(a, x, 0, side);
-    request_prev_stat<G>(a, unit, side);
-    request_fresh_row<ROWB, G>(a, x, side);
-    lds_barrier();                                        // next_tile is set
-    stream_tiles<G == 1, Buf>(a, &sm.next_tile, wave, NW, total, [&](Buf& b, int t) { load_t(b.k, b.v, t); }, [&](Buf& b, int t) { compute_t(b.k, b.v, t); });
+    SideRows<G, SHORT ? (SHORT * WROWS + 63) / 64 : side_rows<G>()> side;
+    auto requests = [&] {
+        request_side_rows<G, NW * 64>(a, x, 0, side);
+        request_prev_stat(a, unit, side);
+        request_fresh_row<ROWB>(a, x, side);
+    };
+    if constexpr (SHORT) {
+        const char* kn = (const char*)a.k_new + (size_t)unit * ROWB;
+        const char* vn = (const char*)a.v_new + (size_t)unit * ROWB;
+        Buf b[SHORT];
+#pragma unroll
+        for (int i = 0; i < SHORT; ++i) {
+            const ShortTile<WROWS> own(x, wave + i * NW);
+            if (!own.exists()) break;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const unsigned off = (unsigned)a.map.phys(own.row(u * RPW + rs)) * ROWB + lane_off;
+                b[i].k[u] = load16<NT>(Kb + off);
+                b[i].v[u] = load16<NT>(Vb + off);
+            }
+            if (own.last(x, a.n)) {                       // the new row is still the caller's
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    if (own.row(u * RPW + rs) == a.n - 1) {
+                        b[i].k[u] = load16<NT>(kn + lane_off);
+                        b[i].v[u] = load16<NT>(vn + lane_off);
+                    }
+                }
+            }
+        }
+        requests();
+#pragma unroll
+        for (int i = 0; i < SHORT; ++i) {
+            const ShortTile<WROWS> own(x, wave + i * NW);
+            if (own.exists()) compute_t(b[i].k, b[i].v, own.tile());
+        }
+    } else {
+        stream_tiles<TWO, Buf>(a, &sm.next_tile, wave, NW, tiles.total(), [&](Buf& b, int t) { load_t(b.k, b.v, t); }, requests, [&](Buf& b, int t) { compute_t(b.k, b.v, tiles.locate(t)); });
+    }
 
     if (lane == 0) BUZZ_STAMP(8 + (wave & 7));
 
     // merge the RPW lane groups of this wave (same columns, different rows)
-#pragma unroll
-    for (int off = LPR; off < 64; off <<= 1) {
+    auto merge_groups = [&](auto bit) {
+        constexpr int BIT = decltype(bit)::value;
 #pragma unroll
         for (int g = 0; g < G; ++g) {
-            const float mo = __shfl_xor(m[g], off);
-            const float lo = __shfl_xor(l[g], off);
+            const LanePair mp = lane_pair<BIT>(m[g]), lp = lane_pair<BIT>(l[g]);
+            const float mn = fmaxf(mp.a, mp.b);
+            const float mref = (mn == -INFINITY) ? 0.f : mn;
+            const float wa = fast_exp2(mp.a - mref), wb = fast_exp2(mp.b - mref);
+            l[g] = lp.a * wa + lp.b * wb;
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) {
+                const LanePair ap = lane_pair<BIT>(acc[g][v]);
+                acc[g][v] = ap.a * wa + ap.b * wb;
+            }
+            m[g] = mn;
+        }
+    };
+    if constexpr (LPR <= 8) {
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            const float mo = dpp_move<0x128>(m[g]), lo = dpp_move<0x128>(l[g]);   // row_ror 8: the row's other half
             const float mn = fmaxf(m[g], mo);
             const float mref = (mn == -INFINITY) ? 0.f : mn;
             const float wa = fast_exp2(m[g] - mref), wb = fast_exp2(mo - mref);
             l[g] = l[g] * wa + lo * wb;
 #pragma unroll
-            for (int v = 0; v < VEC; ++v) {
-                const float ao = __shfl_xor(acc[g][v], off);
-                acc[g][v] = acc[g][v] * wa + ao * wb;
-            }
+            for (int v = 0; v < VEC; ++v) acc[g][v] = acc[g][v] * wa + dpp_move<0x128>(acc[g][v]) * wb;
             m[g] = mn;
         }
     }
+    if constexpr (LPR <= 16) merge_groups(std::integral_constant<int, 16>{});
+    if constexpr (LPR <= 32) merge_groups(std::integral_constant<int, 32>{});
 
     // this wave's result into LDS
     if (rs == 0) {
@@ -822,7 +915,7 @@ __global__ __launch_bounds__(NW * 64, BUZZ_MIN_BLOCKS) void attn_split_kernel(co
             for (int g = 0; g < G; ++g) sm.ml[g][wave] = make_float2(m[g], l[g]);
         }
     }
-    finish_split<G, D, NW, ROWB>(a, x, side, stage, sm);
+    finish_split<G, D, NW, ROWB, SHORT != 0>(a, x, side, stage, sm);
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -838,7 +931,7 @@ __global__ __launch_bounds__(NW * 64, BUZZ_MIN_BLOCKS) void attn_split_kernel(co
 //  * K operand: lane (j, q) holds row j of the tile, 16-byte chunks 4p + q, p = 0 .. D/32-1 (one load
 //    instruction fetches 64 contiguous bytes of each of 16 rows).  The contraction index may be permuted
 //    freely as long as Q uses the same permutation: lane (j, q) of the Q operand holds head j, the same
-//    chunks (zero for j >= G).
+//    chunks (for j >= G those of the last head again; their products are not used).
 //  * S comes out with lane (j, q) holding head j, rows 4q .. 4q+3: exactly the layout the P operand of
 //    the second contraction needs, so softmax results go straight back into the matrix core.
 //    P is split into a 16-bit head and a 16-bit remainder (two MFMAs) to keep ~16 bits of it.
@@ -874,7 +967,7 @@ template <> struct Mma<fp16_t> {
     }
 };
 
-template <typename T, int D, int G, bool NT, int NW, bool ANCHOR>
+template <typename T, int D, int G, bool NT, int NW, bool ANCHOR, int SHORT>
 __global__ __launch_bounds__(NW * 64) void attn_split_mfma_kernel(const AttnArgs a)
 {
     constexpr int ROWB = D * 2;
@@ -895,17 +988,12 @@ __global__ __launch_bounds__(NW * 64) void attn_split_mfma_kernel(const AttnArgs
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // tile numbers and addresses stay in scalar registers
     const int j = lane & 15, q = lane >> 4;
     if (tid == 0) { BUZZ_STAMP(0); BUZZ_STAMP_VALUE(6, __builtin_amdgcn_s_getreg((31 << 11) | 4)); BUZZ_STAMP_VALUE(7, __builtin_amdgcn_s_getreg((31 << 11) | 20)); }
-    if (tid == 0) sm.next_tile = NW;                      // tiles 0 .. NW-1 are the waves' first tiles
-    SideRows<G> side;
-    request_prev_stat<G>(a, unit, side);
-    request_side_rows<G, NW * 64>(a, x, 0, side);
-    request_fresh_row<ROWB, G>(a, x, side);
+    if (!SHORT && tid == 0) sm.next_tile = NW;            // tiles 0 .. NW-1 are the waves' first tiles
 
-    u32x4 qb[QP];                                         // Q operand: head j, chunks 4p + q
+    u32x4 qb[QP];                                         // Q operand: head j (slots without one repeat the last), chunks 4p + q
 #pragma unroll
     for (int p = 0; p < QP; ++p) {
-        qb[p] = u32x4{0u, 0u, 0u, 0u};
-        if (j < G) qb[p] = *(const u32x4*)((const char*)a.q + (size_t)(unit * G + j) * ROWB + (4 * p + q) * 16);
+        qb[p] = *(const u32x4*)((const char*)a.q + (size_t)unit * G * ROWB + (unsigned)(min(j, G - 1) * ROWB + (4 * p + q) * 16));
     }
 
     char* Kb = (char*)a.K + x.ubase * ROWB;
@@ -921,7 +1009,6 @@ __global__ __launch_bounds__(NW * 64) void attn_split_mfma_kernel(const AttnArgs
 
     struct Buf { u32x4 k[QP], v[VS][4]; };
     const TileMap<WROWS, ANCHOR> tiles(a, x);
-    const int total = tiles.total();
     // row i of a tile, counted from its run's first row; outside the run its nearest row again
     auto row = [&](const Tile& k, int i) { return (unsigned)(ANCHOR ? min(max(k.base + i, k.lead), k.cnt - 1) - k.lead : min(k.base + i, k.cnt - 1)); };
     auto load_t = [&](u32x4 (&kk)[QP], u32x4 (&vv)[VS][4], int t) {
@@ -930,17 +1017,16 @@ __global__ __launch_bounds__(NW * 64) void attn_split_mfma_kernel(const AttnArgs
         const char* vp = k.fresh ? (const char*)a.v_new + (size_t)unit * ROWB : Vb + (size_t)k.phys * ROWB;
         const unsigned krow = row(k, j) * ROWB;
 #pragma unroll
-        for (int p = 0; p < QP; ++p) kk[p] = load16<NT>(kp + krow + (4 * p + q) * 16);
+        for (int p = 0; p < QP; ++p) kk[p] = load16<NT>(kp + (unsigned)(krow + (4 * p + q) * 16));
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const unsigned vrow = row(k, 4 * q + e) * ROWB;
 #pragma unroll
-            for (int t2 = 0; t2 < VS; ++t2) vv[t2][e] = load16<NT>(vp + vrow + ((16 * t2 + j) % NCH) * 16);
+            for (int t2 = 0; t2 < VS; ++t2) vv[t2][e] = load16<NT>(vp + (unsigned)(vrow + ((16 * t2 + j) % NCH) * 16));
         }
     };
 
-    auto compute_t = [&](const u32x4 (&kk)[QP], const u32x4 (&vv)[VS][4], int t) {
-        const Tile k = tiles.locate(t);
+    auto compute_t = [&](const u32x4 (&kk)[QP], const u32x4 (&vv)[VS][4], const Tile& k) {
         const int stg = k.lo - j0 + k.base - k.lead;      // staging index (row relative to the split's first row)
         f32x4 sacc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -955,8 +1041,7 @@ __global__ __launch_bounds__(NW * 64) void attn_split_mfma_kernel(const AttnArgs
             if (ok && j < G) stage[j * a.rows_per_split + stg + 4 * q + v] = d;
             tmax = fmaxf(tmax, s[v]);
         }
-        tmax = fmaxf(tmax, __shfl_xor(tmax, 16));
-        tmax = fmaxf(tmax, __shfl_xor(tmax, 32));
+        tmax = pair_max<32>(pair_max<16>(tmax));
         const float mn = fmaxf(m_run, tmax);
         const float mref = (mn == -INFINITY) ? 0.f : mn;
         const float alpha = fast_exp2(m_run - mref);
@@ -1000,13 +1085,56 @@ __global__ __launch_bounds__(NW * 64) void attn_split_mfma_kernel(const AttnArgs
         }
     };
 
-    lds_barrier();
-    stream_tiles<false, Buf>(a, &sm.next_tile, wave, NW, total, [&](Buf& b, int t) { load_t(b.k, b.v, t); }, [&](Buf& b, int t) { compute_t(b.k, b.v, t); });
+    SideRows<G, SHORT ? 1 : side_rows<G>()> side;
+    auto requests = [&] {
+        request_prev_stat(a, unit, side);
+        request_side_rows<G, NW * 64>(a, x, 0, side);
+        request_fresh_row<ROWB>(a, x, side);
+    };
+    if constexpr (SHORT) {
+        const char* kn = (const char*)a.k_new + (size_t)unit * ROWB;
+        const char* vn = (const char*)a.v_new + (size_t)unit * ROWB;
+        Buf b[SHORT];
+#pragma unroll
+        for (int i = 0; i < SHORT; ++i) {
+            const ShortTile<WROWS> own(x, wave + i * NW);
+            if (!own.exists()) break;
+            const unsigned koff = (unsigned)a.map.phys(own.row(j)) * ROWB + q * 16;
+#pragma unroll
+            for (int p = 0; p < QP; ++p) b[i].k[p] = load16<NT>(Kb + (unsigned)(koff + p * 64));
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const unsigned voff = (unsigned)a.map.phys(own.row(4 * q + e)) * ROWB;
+#pragma unroll
+                for (int t2 = 0; t2 < VS; ++t2) b[i].v[t2][e] = load16<NT>(Vb + (unsigned)(voff + ((16 * t2 + j) % NCH) * 16));
+            }
+            if (own.last(x, a.n)) {                       // the new row is still the caller's
+                if (own.row(j) == a.n - 1) {
+#pragma unroll
+                    for (int p = 0; p < QP; ++p) b[i].k[p] = load16<NT>(kn + (unsigned)(q * 16 + p * 64));
+                }
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    if (own.row(4 * q + e) == a.n - 1) {
+#pragma unroll
+                        for (int t2 = 0; t2 < VS; ++t2) b[i].v[t2][e] = load16<NT>(vn + (unsigned)((16 * t2 + j) % NCH * 16));
+                    }
+                }
+            }
+        }
+        requests();
+#pragma unroll
+        for (int i = 0; i < SHORT; ++i) {
+            const ShortTile<WROWS> own(x, wave + i * NW);
+            if (own.exists()) compute_t(b[i].k, b[i].v, own.tile());
+        }
+    } else {
+        stream_tiles<false, Buf>(a, &sm.next_tile, wave, NW, tiles.total(), [&](Buf& b, int t) { load_t(b.k, b.v, t); }, requests, [&](Buf& b, int t) { compute_t(b.k, b.v, tiles.locate(t)); });
+    }
 
     if (lane == 0) BUZZ_STAMP(8 + (wave & 7));
     // this wave's result into LDS
-    float l_tot = l_run + __shfl_xor(l_run, 16);
-    l_tot += __shfl_xor(l_tot, 32);
+    const float l_tot = pair_sum<32>(pair_sum<16>(l_run));
     if (q == 0 && j < G) sm.ml[j][wave] = make_float2(m_run, l_tot);
 #pragma unroll
     for (int t2 = 0; t2 < VS; ++t2) {
@@ -1021,7 +1149,7 @@ __global__ __launch_bounds__(NW * 64) void attn_split_mfma_kernel(const AttnArgs
             }
         }
     }
-    finish_split<G, D, NW, ROWB>(a, x, side, stage, sm);
+    finish_split<G, D, NW, ROWB, SHORT != 0>(a, x, side, stage, sm);
 }
 
 constexpr int kScoreRowsPerBlock = 2048;
@@ -1105,11 +1233,14 @@ hipError_t launch_split_t(const AttnArgs& a, int units, hipStream_t st, Timing t
 {
     const dim3 grid = a.xcd_local ? dim3(8, a.n_splits, units / 8) : dim3(a.n_splits, units), block(a.waves * 64);
     const size_t lds = (size_t)G * a.rows_per_split * sizeof(float);   // logit staging
+    const bool may_be_short = !a.streaming && (uint64_t)a.cap * D * sizeof(T) <= UINT32_MAX;   // 32-bit offsets into a unit
     if constexpr (G >= 2 && !std::is_same<T, float>::value) {   // grouped queries on a 16-bit cache: matrix cores
         auto launch = [&](auto nt, auto nw, auto anchor) {
-            launch_even<attn_split_mfma_kernel<T, D, G, decltype(nt)::value, decltype(nw)::value, decltype(anchor)::value>>(grid, block, lds, st, tm, a);
+            launch_even<attn_split_mfma_kernel<T, D, G, decltype(nt)::value, decltype(nw)::value, decltype(anchor)::value, 0>>(grid, block, lds, st, tm, a);
         };
         auto flavour = [&](auto nw) {
+            constexpr int NW = decltype(nw)::value;
+            if (may_be_short && a.rows_per_split <= NW * 16) { BUZZ_LAUNCH((attn_split_mfma_kernel<T, D, G, false, NW, false, 1>), grid, block, lds, st, tm, a); return; }
             if (!a.streaming) { launch(std::false_type{}, nw, std::false_type{}); return; }
             if constexpr (D >= 128) {
                 if (a.rows_per_split >= kAnchorRows) { launch(std::true_type{}, nw, std::true_type{}); return; }
@@ -1124,14 +1255,21 @@ hipError_t launch_split_t(const AttnArgs& a, int units, hipStream_t st, Timing t
         // a trip covers at least 4 rows
         constexpr int US = unroll_for<G, true>() * RPW >= 4 ? unroll_for<G, true>() : 4 / RPW;     // streaming loads
         constexpr int UC = unroll_for<G, false>() * RPW >= 4 ? unroll_for<G, false>() : 4 / RPW;   // cached loads
-        auto launch = [&](auto nt, auto nw) {
-            constexpr bool NT = decltype(nt)::value;
-            constexpr auto kernel = attn_split_kernel<T, D, G, NT ? US : UC, NT, decltype(nw)::value>;
+        // short splits: tiles of 16 rows, 8 where a row takes a whole wave and for the vector work of more than 4 heads, which is to
+        // reach all waves (32 units of 128 rows in 3 splits, 6 fp32 heads of 128: 9.3 us per step with tiles of 16)
+        constexpr int SHORT_ROWS = G > 4 || RPW == 1 ? 8 : 16, UH = SHORT_ROWS / RPW;
+        constexpr bool TWO_TILES = G == 1 || G > 4;
+        auto launch = [&](auto nt, auto nw, auto u) {
+            constexpr auto kernel = attn_split_kernel<T, D, G, decltype(u)::value, decltype(nt)::value, decltype(nw)::value, 0>;
             if constexpr (G <= 4) launch_even<kernel>(grid, block, lds, st, tm, a);
             else BUZZ_LAUNCH(kernel, grid, block, lds, st, tm, a);   // the vector ALU bounds these
         };
         auto flavour = [&](auto nw) {
-            if (a.streaming) launch(std::true_type{}, nw); else launch(std::false_type{}, nw);
+            constexpr int NW = decltype(nw)::value;
+            if (a.streaming) launch(std::true_type{}, nw, std::integral_constant<int, US>{});
+            else if (may_be_short && a.rows_per_split <= UH * RPW * NW) BUZZ_LAUNCH((attn_split_kernel<T, D, G, UH, false, NW, 1>), grid, block, lds, st, tm, a);
+            else if (TWO_TILES && NW == 8 && may_be_short && a.rows_per_split <= 2 * UH * RPW * NW) BUZZ_LAUNCH((attn_split_kernel<T, D, G, UH, false, NW, TWO_TILES && NW == 8 ? 2 : 1>), grid, block, lds, st, tm, a);
+            else launch(std::false_type{}, nw, std::integral_constant<int, UC>{});
         };
         if (a.waves == 8) flavour(std::integral_constant<int, 8>{});
         else flavour(std::integral_constant<int, 4>{});

@@ -130,6 +130,17 @@ def test_anchored_tiles_of_long_streaming_splits(G, D, dtype, sink, T, steps):
     run(wl, splits=1, kv_loads="streaming")
 
 
+@pytest.mark.parametrize("G,D,dtype", [(1, 64, "fp32"), (1, 128, "bf16"), (1, 64, "fp16"), (1, 256, "fp32"), (4, 64, "fp32"), (3, 256, "fp32"),
+                                       (4, 128, "bf16"), (8, 128, "fp16"), (2, 64, "bf16"), (8, 256, "bf16")])
+@pytest.mark.parametrize("rows,splits", [(0, 1), (15, 1), (60, 1), (63, 2), (126, 1), (120, 3), (250, 1), (255, 2), (390, 4)])
+def test_short_splits(G, D, dtype, rows, splits):
+    """Splits whose rows are all requested at once: one row, tiles and blocks that are just full or just not, the ring's wrap and
+    the linear region's end inside a tile, the new row alone in the last split, and the first size that is streamed instead."""
+    wl = small(batch=1, n_kv_heads=2, n_q_heads=2 * G, head_dim=D, dtype=dtype, prompt=rows, decode_steps=14, sink=3,
+               window=max(1, rows - 20), segment=4, keep=1, evict_every=7, n_obs=min(rows, 5))
+    run(wl, splits=splits, check_auto=False)
+
+
 @pytest.mark.parametrize("device_merge", [False, True])
 @pytest.mark.parametrize("G,D,dtype,splits", [(1, 64, "fp16", 17), (1, 256, "bf16", 9), (2, 256, "fp32", 20), (3, 128, "bf16", 33),
                                               (4, 128, "fp16", 18), (5, 256, "bf16", 10), (6, 256, "fp16", 9), (7, 256, "bf16", 17),
