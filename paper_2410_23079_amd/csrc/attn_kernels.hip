@@ -346,20 +346,22 @@ __device__ inline void lds_barrier()
 // consumed.  (The compiler waits for both at once, because the next tile may not exist.  With the loads
 // issued unconditionally, and the loop shaped so that it waits for the older half only, the stream was no faster -- 52
 // us of 62 on one sequence of 23.6k rows by 32 heads, 7.4 TB/s either way -- and waves with one tile paid for loads of
-// tiles that do not exist: 8 units of 1500 rows, 4 heads each, 10.1 instead of 8.0 us per step.)  The side requests come
-// behind the first tile's loads and before the second's: 64 steps of 512 units of 3900 rows, one bf16 head of 128, 10580 us,
-// 10800 with the side requests first, 10760 with both tiles first.  With one buffer they come first: with the first tile's
-// loads hoisted over them the loop copies its registers, 64 steps of 32 units of 7800 rows, 4 heads of 128, 1550 -> 1576 us.
-template <bool TWO, typename Buf, typename Load, typename Requests, typename Compute>
+// tiles that do not exist: 8 units of 1500 rows, 4 heads each, 10.1 instead of 8.0 us per step.)  TILE_FIRST:
+// the first tile's loads go before the side requests, per step, so and after them: 512 units of 3900 bf16 rows of 128 in 4-wave
+// blocks 154.1 / 156.7 us, 1000 of 3000 rows of 64 127.6 / 133.5 (400 of 3000: 98.9 / 97.2), 256 of 1450 cached rows 28.8 / 29.1; streaming
+// in 8-wave blocks they come behind: 200 of 2630 44.9 / 41.7, 96 of 4663 rows of 256 77.0 / 70.4 (32 of 23600 in 8 splits 61.4 / 62.2).  With
+// one buffer they come behind, too: hoisted, the loop copies its registers, 64 steps of 32 units of 7800 rows, 4 heads, 1550 -> 1576 us.
+template <bool TWO, bool TILE_FIRST, typename Buf, typename Load, typename Requests, typename Compute>
 __device__ inline void stream_tiles(const AttnArgs& a, int* counter, int wave, int nw, int total, Load load, Requests requests, Compute compute)
 {
     int t = wave;
     if constexpr (TWO) {
         Buf first, second;
         int tn = t + nw;
-        if (t < total) load(first, t);
+        if (TILE_FIRST && t < total) load(first, t);
         requests();
         lds_barrier();                                    // the counter is set
+        if (!TILE_FIRST && t < total) load(first, t);
         while (t < total) {
             if (tn < total) load(second, tn);
             int t2 = next_tile(a, counter, tn, nw);
@@ -454,10 +456,13 @@ __device__ inline void request_side_rows(const AttnArgs& a, const SplitCtx& x, i
 template <int G, int SR>
 __device__ inline void request_prev_stat(const AttnArgs& a, int unit, SideRows<G, SR>& p)
 {
+    // Through the constant address space: no launch writes what it reads here, and scalar registers hold it.  (In vector
+    // registers it costs wide groups a resident block: 256 units of 3800 rows, 6 fp16 heads of 64, 53 -> 71 us.)
+    const auto* prev = (const __attribute__((address_space(4))) float*)(a.stat_prev + (size_t)unit * G * 2);
 #pragma unroll
     for (int g = 0; g < G; ++g) {
-        p.M[g] = a.stat_prev[((size_t)unit * G + g) * 2];       // (read but not used where nothing is pending)
-        p.iL[g] = a.stat_prev[((size_t)unit * G + g) * 2 + 1];
+        p.M[g] = prev[2 * g];                                   // (read but not used where nothing is pending)
+        p.iL[g] = prev[2 * g + 1];
     }
 }
 
@@ -863,7 +868,7 @@ __global__ __launch_bounds__(NW * 64, BUZZ_MIN_BLOCKS) void attn_split_kernel(co
             if (own.exists()) compute_t(b[i].k, b[i].v, own.tile());
         }
     } else {
-        stream_tiles<TWO, Buf>(a, &sm.next_tile, wave, NW, tiles.total(), [&](Buf& b, int t) { load_t(b.k, b.v, t); }, requests, [&](Buf& b, int t) { compute_t(b.k, b.v, tiles.locate(t)); });
+        stream_tiles<TWO, !NT || NW == 4, Buf>(a, &sm.next_tile, wave, NW, tiles.total(), [&](Buf& b, int t) { load_t(b.k, b.v, t); }, requests, [&](Buf& b, int t) { compute_t(b.k, b.v, tiles.locate(t)); });
     }
 
     if (lane == 0) BUZZ_STAMP(8 + (wave & 7));
@@ -1129,7 +1134,7 @@ __global__ __launch_bounds__(NW * 64) void attn_split_mfma_kernel(const AttnArgs
             if (own.exists()) compute_t(b[i].k, b[i].v, own.tile());
         }
     } else {
-        stream_tiles<false, Buf>(a, &sm.next_tile, wave, NW, tiles.total(), [&](Buf& b, int t) { load_t(b.k, b.v, t); }, requests, [&](Buf& b, int t) { compute_t(b.k, b.v, tiles.locate(t)); });
+        stream_tiles<false, false, Buf>(a, &sm.next_tile, wave, NW, tiles.total(), [&](Buf& b, int t) { load_t(b.k, b.v, t); }, requests, [&](Buf& b, int t) { compute_t(b.k, b.v, tiles.locate(t)); });
     }
 
     if (lane == 0) BUZZ_STAMP(8 + (wave & 7));
@@ -1258,7 +1263,7 @@ hipError_t launch_split_t(const AttnArgs& a, int units, hipStream_t st, Timing t
         // short splits: tiles of 16 rows, 8 where a row takes a whole wave and for the vector work of more than 4 heads, which is to
         // reach all waves (32 units of 128 rows in 3 splits, 6 fp32 heads of 128: 9.3 us per step with tiles of 16)
         constexpr int SHORT_ROWS = G > 4 || RPW == 1 ? 8 : 16, UH = SHORT_ROWS / RPW;
-        constexpr bool TWO_TILES = G == 1 || G > 4;
+        constexpr bool TWO_TILES = G == 1 || (G > 4 && RPW > 1);   // (64 units of 391 rows, 5 fp32 heads of 256: 20.7 us with two, 18.6 streamed)
         auto launch = [&](auto nt, auto nw, auto u) {
             constexpr auto kernel = attn_split_kernel<T, D, G, decltype(u)::value, decltype(nt)::value, decltype(nw)::value, 0>;
             if constexpr (G <= 4) launch_even<kernel>(grid, block, lds, st, tm, a);

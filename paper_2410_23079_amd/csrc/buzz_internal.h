@@ -78,21 +78,22 @@ struct AttnArgs {
     float* out;          // [B][Hq][D]
     RingMap map;
     int32_t n;           // retained rows including the one being appended (logical index n-1)
-    int32_t new_phys;    // physical row the appended token is written to
-    int32_t new_pos;     // its original token index
     int32_t cap;
     int32_t rows_per_split;
     int32_t n_splits;
     int32_t s_cap;
-    int32_t compute_units;
-    int32_t waves;       // waves per block: 4, or 8 when every unit is a single split
     int32_t pending;     // 1: the previous step's score update has not been applied yet
-    int32_t streaming;   // 1: K/V are read with the non-temporal hint (working set exceeds the last-level cache)
     int32_t fixed_tiles; // 1: waves take tiles in a fixed round-robin (bitwise reproducible results)
     int32_t xcd_local;   // 1: blocks are renumbered so that a unit's splits share one die, and merge through its L2
     int32_t units_per_die;  // ... (the grid's z)
     uint32_t die_map;    // ... and the die (4 bits each) that serves launch-order block numbers 0..7 mod 8
     float scale_log2;    // softmax scale * log2(e)
+    int32_t new_phys;    // physical row the appended token is written to
+    int32_t new_pos;     // its original token index
+    // what the kernels read ends within three cache lines; the launch only:
+    int32_t compute_units;
+    int32_t waves;       // waves per block: 4, or 8 when every unit is a single split
+    int32_t streaming;   // 1: K/V are read with the non-temporal hint (working set exceeds the last-level cache)
 };
 
 // The lazy score update of one row and head: score + exp2(logit - max) / sum of the step that left it pending.
