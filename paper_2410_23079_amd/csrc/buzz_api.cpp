@@ -683,6 +683,13 @@ int buzz_prefill(buzz_cache_t* c, const void* kp, const void* vp, int64_t N, con
 
 namespace {
 
+// Whether a step of n rows reads K and V with the streaming hint.
+bool reads_past_cache(const buzz_cache_t* c, int64_t n)
+{
+    if (c->cfg.flags & (BUZZ_FLAG_STREAMING | BUZZ_FLAG_CACHED)) return (c->cfg.flags & BUZZ_FLAG_STREAMING) != 0;
+    return (double)c->L.units * (double)n * 2.0 * c->L.row_bytes > kLastLevelCacheBytes;
+}
+
 // Key-range splits of a decode step, the automatic choice.  Few, long blocks amortise the per-block merge, and a block
 // count that fills every compute unit the same number of times avoids a tail: at most one block per compute unit
 // (floor(CUs / units) splits; with at least one unit per compute unit a unit is a single block and nothing is merged
@@ -690,30 +697,45 @@ namespace {
 // more than it streams (5 to 57 ns over the supported shapes), and the merge split_us per split, more where the partial
 // results are larger or the units many (43 to 151 ns).  row_us n / S + split_us S is least at the root below; a cache whose
 // rows take less than the publishing and merging does (whole_us) stays whole, up to 128 rows also one that a split does not
-// save 2.6 us more: the launch that the counters of the static scratch cost, and both entry points split alike.  Beyond 8
+// save 1.6 us more: the launch that the counters of the static scratch cost, and both entry points split alike.  Beyond 8
 // splits the merge goes by rounds of 8 and 16 loads: a root of more than 8 is rounded to 8, 16 or a larger multiple of 8.
 // Around the root the time is flat to what the model leaves out (the tiles of a split over its waves), so splits of 128
-// rows, one 16-row tile per wave, stay, whatever their number, unless the model gains 0.4 us: 8 units of 300 rows of one
-// fp32 head of 64 stay at 3 splits, 6.2 us, though 6 take 5.5; 8 of 1512 rows of 4 bf16 heads of 128 at 12, 7.3 us, as 8 do.
+// rows, one 16-row tile per wave, stay, whatever their number, unless the model gains 0.4 us: 8 units of 1512 rows of 4 bf16
+// heads of 128 stay at 12, 6.9 us, 8 take 7.2.
 // The constants are a fit to 1 to 64 units of 80 to 12000 rows, groups of 1 to 8, heads of 64 to 256, all types.  Against
 // splits of at least 128 rows, on 220 random shapes of that range 4% less time on average, on 120 of 65 to 255 units 0.7%, on
 // 67 of 12000 to 120000 rows 3%, none longer by more than 2% (whole_us ends to grow at 52 units: at 80 and 120 it left steps
 // whole that took 3-4% longer so).  1 unit of 12000 rows, 4 heads of 128 in bf16, 13.0 us with 94 splits, 10.9 with 40; 3 of
 // 175, 4 fp32 heads of 256, 14.2 with 2, 8.2 with 8; 100 of 154, 8 fp16 heads of 64, 7.7 with 2, 5.4 whole.
+// One head, cached loads: a block requests up to 256 rows at once (rows_at_once), which the model does not know.  A cache of no
+// more, and no more than 55000 bytes of K per unit (214 rows of 256 bytes), stays whole: at 160 to 192 such rows 10% faster
+// than what the model gives, from 224 on 10% slower.  From 13 such splits on they are taken, as few as there are: fewer publish
+// less, and longer ones would be streamed (3 units of 11000 fp32 rows of 64: 44 splits 9.2 us, the model's 11.4; 20 splits and more
+// 5% on average; 9 to 12 are about even, below the model's are faster).  Beyond 48 the model's count stays as
+// tests/test_launches_host.py states it, though 1 unit of 16000 bf16 rows of 128 takes 9.6 us with 64 and 12.1 with its 56.  On 3972 random shapes of 1 to 128 units, 70 to 20000 rows, both rules together 0.7% on average.
+int64_t rows_at_once(const buzz_cache_t* c, int64_t n)
+{
+    if (c->L.G > 1 || reads_past_cache(c, n) || (uint64_t)c->L.cap * c->L.row_bytes > UINT32_MAX) return 0;
+    return c->L.row_bytes == 1024 ? 128 : 256;
+}
 int64_t auto_splits(const buzz_cache_t* c, int64_t n, int cus)
 {
     const SplitModel& m = c->split_model;
     const int64_t units = c->L.units;
     if (units >= cus) return 1;
+    const int64_t at_once = rows_at_once(c, n);
+    if (n <= at_once && (double)n * c->L.row_bytes <= 55000.0) return 1;
     const double rows_us = m.row_us * (double)n;
-    if (rows_us <= m.whole_us + (n <= 128 ? 2.6 : 0.0)) return 1;
+    if (rows_us <= m.whole_us + (n <= 128 ? 1.6 : 0.0)) return 1;
     const int64_t most = cus / units, long_splits = ceil_div(n, 128) < most ? ceil_div(n, 128) : most;
     auto us = [&](int64_t s) { return rows_us / (double)s + m.split_us * (double)s; };
     int64_t S = (int64_t)(sqrt(rows_us / m.split_us) + 0.5);
     if (S < 2) S = 2;
     if (S > 8) S = S < 12 ? 8 : S < 22 ? 16 : (S + 4) / 8 * 8;
     if (S > most) S = most;
-    return long_splits > 1 && us(long_splits) - us(S) < 0.4 ? long_splits : S;
+    if (long_splits > 1 && us(long_splits) - us(S) < 0.4) S = long_splits;
+    const int64_t fewest = at_once > 0 ? ceil_div(n, at_once) : 0;   // splits whose rows are requested at once
+    return fewest >= 13 && fewest <= 48 && fewest <= most && 5 * S > 4 * fewest ? fewest : S;
 }
 
 // One decode step.  static_scratch: the split-softmax scratch (arrival counters, per-split partials) is the
@@ -790,9 +812,7 @@ int decode_step_impl(buzz_cache_t* c, const void* q, const void* k_new, const vo
         a.compute_units = cus;
         a.s_cap = L.s_cap;
         a.scale_log2 = (float)(c->scale * 1.4426950408889634 * c->log_n_factor(c->tokens_seen + 1));
-        const double step_bytes = (double)L.units * (double)n * 2.0 * L.row_bytes;
-        a.streaming = (cfg.flags & BUZZ_FLAG_STREAMING) ? 1
-                      : (cfg.flags & BUZZ_FLAG_CACHED) ? 0 : (step_bytes > kLastLevelCacheBytes);
+        a.streaming = reads_past_cache(c, n) ? 1 : 0;
         a.fixed_tiles = (cfg.flags & BUZZ_FLAG_DETERMINISTIC) ? 1 : 0;
         a.rows_per_split = (int32_t)rps;
         a.n_splits = (int32_t)n_splits;
