@@ -263,6 +263,11 @@ __global__ __launch_bounds__(kTopkBlock) void segment_topk_block_kernel(const Se
 // and the next decode step applies the update there as it would have without an eviction.  A survivor arrives
 // with its updated score, and its entry in that step's logit buffer is set to -inf so that the next step
 // adds exactly 0 for it.
+// Bound by latency: a chain of round trips to memory.  All of a row's logits are requested with its score, the statistics
+// once per wave, and the survivors' scores are those that were ranked.  (With a loop over the heads each logit waited for
+// the one before it, once to rank and again to move: 8 units, 32 rows, 8 heads of 128, 4.6 us per eviction, now 3.0; 32
+// units of 64 rows, 4 heads, 6.4 and 4.2; 8 of 16 rows, one head of 64, 3.3 and 3.0.)
+template <int G>
 __global__ __launch_bounds__(256) void evict_new_rows_kernel(const EvictArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) float lds[];   // [kSelWaves][wave_slice(segment + keep)]: scores, then kept offsets
@@ -276,13 +281,19 @@ __global__ __launch_bounds__(256) void evict_new_rows_kernel(const EvictArgs a)
     float* sc = lds + wave * wave_slice(a.segment + a.keep);
     int* kept = (int*)sc + a.segment;
     const size_t ubase = (size_t)unit * a.cap;
-    const float* logit_u = a.logit_prev ? a.logit_prev + ubase * a.G : nullptr;
+    const float* logit_u = a.logit_prev + ubase * G;
+    float stat[2 * G];
+#pragma unroll
+    for (int i = 0; i < 2 * G; ++i) stat[i] = a.stat_prev[(size_t)unit * 2 * G + i];   // (read but not used where nothing is pending)
     auto current_score = [&](int ph) {             // the row's score with the pending update applied
         float v = a.score[ubase + ph];
-        if (logit_u)
-            for (int g = 0; g < a.G; ++g)
-                v = add_probability(v, logit_u[(size_t)g * a.cap + ph], a.stat_prev[((size_t)unit * a.G + g) * 2],
-                                    a.stat_prev[((size_t)unit * a.G + g) * 2 + 1]);
+        if (a.logit_prev) {
+            float logit[G];
+#pragma unroll
+            for (int g = 0; g < G; ++g) logit[g] = logit_u[(size_t)g * a.cap + ph];
+#pragma unroll
+            for (int g = 0; g < G; ++g) v = add_probability(v, logit[g], stat[2 * g], stat[2 * g + 1]);
+        }
         return v;
     };
     if (a.ignore_scores) {                         // all equal: the lowest indices win
@@ -308,13 +319,20 @@ __global__ __launch_bounds__(256) void evict_new_rows_kernel(const EvictArgs a)
         const int sp = a.map.phys(a.lo + start + kept[r]);
         const int dp = a.dst_start + seg * a.keep + r;
         const size_t so = (ubase + sp) * a.row_bytes + c * 16, dof = (ubase + dp) * a.row_bytes + c * 16;
-        *(uint4*)((char*)a.K + dof) = *(const uint4*)((const char*)a.K + so);
-        *(uint4*)((char*)a.V + dof) = *(const uint4*)((const char*)a.V + so);
-        if (c == 0) {
-            a.score[ubase + dp] = current_score(sp);
-            a.pos[ubase + dp] = a.pos[ubase + sp];
-            if (a.logit_prev)
-                for (int g = 0; g < a.G; ++g) a.logit_prev[ubase * a.G + (size_t)g * a.cap + dp] = -INFINITY;
+        const uint4 k = *(const uint4*)((const char*)a.K + so), v = *(const uint4*)((const char*)a.V + so);
+        *(uint4*)((char*)a.K + dof) = k;
+        *(uint4*)((char*)a.V + dof) = v;
+    }
+    for (int r = lane; r < take; r += 64) {
+        const int sp = a.map.phys(a.lo + start + kept[r]), dp = a.dst_start + seg * a.keep + r;
+        // the score that was ranked; what ranks lowest may have been NaN
+        float v = a.ignore_scores ? -INFINITY : sc[kept[r]];
+        if (v == -INFINITY) v = current_score(sp);
+        a.score[ubase + dp] = v;
+        a.pos[ubase + dp] = a.pos[ubase + sp];
+        if (a.logit_prev) {
+#pragma unroll
+            for (int g = 0; g < G; ++g) a.logit_prev[ubase * G + (size_t)g * a.cap + dp] = -INFINITY;
         }
     }
 }
@@ -483,7 +501,17 @@ hipError_t launch_evict_new_rows(const EvictArgs& a, int units, hipStream_t st, 
     if (a.row_bytes > 1024 || (a.row_bytes & 15) || 64 % (a.row_bytes >> 4)) return hipErrorInvalidValue;
     const dim3 grid((n_seg + kSelWaves - 1) / kSelWaves, units);
     const size_t lds = (size_t)kSelWaves * wave_slice(a.segment + a.keep) * sizeof(float);
-    BUZZ_LAUNCH(evict_new_rows_kernel, grid, dim3(256), lds, st, tm, a);
+    switch (a.G) {
+        case 1: BUZZ_LAUNCH((evict_new_rows_kernel<1>), grid, dim3(256), lds, st, tm, a); break;
+        case 2: BUZZ_LAUNCH((evict_new_rows_kernel<2>), grid, dim3(256), lds, st, tm, a); break;
+        case 3: BUZZ_LAUNCH((evict_new_rows_kernel<3>), grid, dim3(256), lds, st, tm, a); break;
+        case 4: BUZZ_LAUNCH((evict_new_rows_kernel<4>), grid, dim3(256), lds, st, tm, a); break;
+        case 5: BUZZ_LAUNCH((evict_new_rows_kernel<5>), grid, dim3(256), lds, st, tm, a); break;
+        case 6: BUZZ_LAUNCH((evict_new_rows_kernel<6>), grid, dim3(256), lds, st, tm, a); break;
+        case 7: BUZZ_LAUNCH((evict_new_rows_kernel<7>), grid, dim3(256), lds, st, tm, a); break;
+        case 8: BUZZ_LAUNCH((evict_new_rows_kernel<8>), grid, dim3(256), lds, st, tm, a); break;
+        default: return hipErrorInvalidValue;
+    }
     return hipGetLastError();
 }
 
