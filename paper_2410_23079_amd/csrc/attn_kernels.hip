@@ -302,7 +302,7 @@ struct TileMap {
     }
 };
 
-// A tile of a short split (one or two tiles for each wave of the block): WROWS logical rows, wherever they are stored.  Short
+// A tile of a short split (one to three tiles for each wave of the block): WROWS logical rows, wherever they are stored.  Short
 // steps are bound by latency and by the instructions in front of the first load and behind the last.  All of the split's
 // rows are requested at once, at their own 32-bit offsets from the unit's first row, so there are no runs to cut tiles at (the
 // linear region's end, the ring's wrap and the new row each began another tile, and often a second round of loads for the
@@ -1263,7 +1263,10 @@ hipError_t launch_split_t(const AttnArgs& a, int units, hipStream_t st, Timing t
         // short splits: tiles of 16 rows, 8 where a row takes a whole wave and for the vector work of more than 4 heads, which is to
         // reach all waves (32 units of 128 rows in 3 splits, 6 fp32 heads of 128: 9.3 us per step with tiles of 16)
         constexpr int SHORT_ROWS = G > 4 || RPW == 1 ? 8 : 16, UH = SHORT_ROWS / RPW;
-        constexpr bool TWO_TILES = G == 1 || (G > 4 && RPW > 1);   // (64 units of 391 rows, 5 fp32 heads of 256: 20.7 us with two, 18.6 streamed)
+        // ... and the most of them per wave: three with one head of up to 256 bytes (32 units of 2800 bf16 rows of 64 in 8 splits 8.2 us
+        // streamed, 6.9 so; 64 of 1300 fp32 rows of 128 in 4 splits 16.1 / 17.1), one where tiles of 8 rows would leave waves idle for a
+        // round of wide rows (64 units of 391 rows, 5 fp32 heads of 256: 18.6 us streamed, 20.7 with two)
+        constexpr int MOST = G == 1 ? (RPW >= 4 ? 3 : 2) : G > 4 && RPW > 1 ? 2 : 1;
         auto launch = [&](auto nt, auto nw, auto u) {
             constexpr auto kernel = attn_split_kernel<T, D, G, decltype(u)::value, decltype(nt)::value, decltype(nw)::value, 0>;
             if constexpr (G <= 4) launch_even<kernel>(grid, block, lds, st, tm, a);
@@ -1271,9 +1274,11 @@ hipError_t launch_split_t(const AttnArgs& a, int units, hipStream_t st, Timing t
         };
         auto flavour = [&](auto nw) {
             constexpr int NW = decltype(nw)::value;
+            constexpr int TILES = NW == 8 ? MOST : 1;
             if (a.streaming) launch(std::true_type{}, nw, std::integral_constant<int, US>{});
             else if (may_be_short && a.rows_per_split <= UH * RPW * NW) BUZZ_LAUNCH((attn_split_kernel<T, D, G, UH, false, NW, 1>), grid, block, lds, st, tm, a);
-            else if (TWO_TILES && NW == 8 && may_be_short && a.rows_per_split <= 2 * UH * RPW * NW) BUZZ_LAUNCH((attn_split_kernel<T, D, G, UH, false, NW, TWO_TILES && NW == 8 ? 2 : 1>), grid, block, lds, st, tm, a);
+            else if (TILES >= 2 && may_be_short && a.rows_per_split <= 2 * UH * RPW * NW) BUZZ_LAUNCH((attn_split_kernel<T, D, G, UH, false, NW, (TILES >= 2 ? 2 : 1)>), grid, block, lds, st, tm, a);
+            else if (TILES >= 3 && may_be_short && a.rows_per_split <= 3 * UH * RPW * NW) BUZZ_LAUNCH((attn_split_kernel<T, D, G, UH, false, NW, TILES>), grid, block, lds, st, tm, a);
             else launch(std::false_type{}, nw, std::integral_constant<int, UC>{});
         };
         if (a.waves == 8) flavour(std::integral_constant<int, 8>{});

@@ -707,12 +707,13 @@ bool reads_past_cache(const buzz_cache_t* c, int64_t n)
 // 67 of 12000 to 120000 rows 3%, none longer by more than 2% (whole_us ends to grow at 52 units: at 80 and 120 it left steps
 // whole that took 3-4% longer so).  1 unit of 12000 rows, 4 heads of 128 in bf16, 13.0 us with 94 splits, 10.9 with 40; 3 of
 // 175, 4 fp32 heads of 256, 14.2 with 2, 8.2 with 8; 100 of 154, 8 fp16 heads of 64, 7.7 with 2, 5.4 whole.
-// One head, cached loads: a block requests up to 256 rows at once (rows_at_once), which the model does not know.  A cache of no
-// more, and no more than 55000 bytes of K per unit (214 rows of 256 bytes), stays whole: at 160 to 192 such rows 10% faster
-// than what the model gives, from 224 on 10% slower.  From 13 such splits on they are taken, as few as there are: fewer publish
-// less, and longer ones would be streamed (3 units of 11000 fp32 rows of 64: 44 splits 9.2 us, the model's 11.4; 20 splits and more
-// 5% on average; 9 to 12 are about even, below the model's are faster).  Beyond 48 the model's count stays as
-// tests/test_launches_host.py states it, though 1 unit of 16000 bf16 rows of 128 takes 9.6 us with 64 and 12.1 with its 56.  On 3972 random shapes of 1 to 128 units, 70 to 20000 rows, both rules together 0.7% on average.
+// One head, cached loads: a block requests 256 rows at once (rows_at_once; up to 384 of no more than 256 bytes, some 5% slower per
+// row), which the model does not know.  A cache of no more, and no more than 55000 bytes of K per unit (214 rows of 256 bytes),
+// stays whole: at 160 to 192 such rows 10% faster than what the model gives, from 224 on 10% slower.  From 13 splits of 256 rows
+// on these are taken, as few as there are: fewer publish less (3 units of 11000 fp32 rows of 64: 44 splits 8.9 us, 86 11.4; 20
+// splits and more 5% on average; 9 to 12 are about even, below the model's are faster).  Beyond 48 the model's count stays (1
+// unit of 16000 bf16 rows of 128: 56 splits of 286 rows 9.8 us, 63 of 254 9.6).  On 3972 random shapes of 1 to 128 units, 70 to
+// 20000 rows, both rules together 0.7% on average.
 int64_t rows_at_once(const buzz_cache_t* c, int64_t n)
 {
     if (c->L.G > 1 || reads_past_cache(c, n) || (uint64_t)c->L.cap * c->L.row_bytes > UINT32_MAX) return 0;

@@ -132,7 +132,8 @@ def test_anchored_tiles_of_long_streaming_splits(G, D, dtype, sink, T, steps):
 
 @pytest.mark.parametrize("G,D,dtype", [(1, 64, "fp32"), (1, 128, "bf16"), (1, 64, "fp16"), (1, 256, "fp32"), (4, 64, "fp32"), (3, 256, "fp32"),
                                        (4, 128, "bf16"), (8, 128, "fp16"), (2, 64, "bf16"), (8, 256, "bf16")])
-@pytest.mark.parametrize("rows,splits", [(0, 1), (15, 1), (60, 1), (63, 2), (126, 1), (120, 3), (250, 1), (255, 2), (390, 4)])
+@pytest.mark.parametrize("rows,splits", [(0, 1), (15, 1), (60, 1), (63, 2), (126, 1), (120, 3), (250, 1), (255, 2), (390, 4), (262, 1),
+                                         (378, 1), (391, 1)])
 def test_short_splits(G, D, dtype, rows, splits):
     """Splits whose rows are all requested at once: one row, tiles and blocks that are just full or just not, the ring's wrap and
     the linear region's end inside a tile, the new row alone in the last split, and the first size that is streamed instead."""
