@@ -256,8 +256,8 @@ __device__ inline SplitCtx make_ctx(const AttnArgs& a)
 // first row on; the row being appended, which comes from the caller's buffer, is a tile of its own at the end.
 // ANCHOR: the tiles of a run sit on a grid of multiples of WROWS physical rows (`lead` rows before its first row are
 // masked), so that a tile's rows are one aligned piece of the arena.
-// A block's waves do not own fixed tiles: apart from the first one each, a wave claims its next tile from a counter
-// in LDS.  (With fixed round-robin tiles the waves launched first -- which the memory pipeline serves first
+// A block's waves do not own fixed tiles: apart from the first one each (two with two buffers), a wave claims its next tile
+// from a counter in LDS.  (With fixed round-robin tiles the waves launched first -- which the memory pipeline serves first
 // -- ended 15% earlier than the others, and the block waited for the slowest.)
 // run: first logical and physical row, length and masked rows (both from the anchor on); first row of the tile in it
 struct Tile { int lo, phys, cnt, lead, base; bool fresh; };
