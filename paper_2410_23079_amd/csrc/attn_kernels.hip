@@ -346,11 +346,23 @@ __device__ inline void lds_barrier()
 // consumed.  (The compiler waits for both at once, because the next tile may not exist.  With the loads
 // issued unconditionally, and the loop shaped so that it waits for the older half only, the stream was no faster -- 52
 // us of 62 on one sequence of 23.6k rows by 32 heads, 7.4 TB/s either way -- and waves with one tile paid for loads of
-// tiles that do not exist: 8 units of 1500 rows, 4 heads each, 10.1 instead of 8.0 us per step.)  TILE_FIRST:
-// the first tile's loads go before the side requests, per step, so and after them: 512 units of 3900 bf16 rows of 128 in 4-wave
-// blocks 154.1 / 156.7 us, 1000 of 3000 rows of 64 127.6 / 133.5 (400 of 3000: 98.9 / 97.2), 256 of 1450 cached rows 28.8 / 29.1; streaming
-// in 8-wave blocks they come behind: 200 of 2630 44.9 / 41.7, 96 of 4663 rows of 256 77.0 / 70.4 (32 of 23600 in 8 splits 61.4 / 62.2).  With
-// one buffer they come behind, too: hoisted, the loop copies its registers, 64 steps of 32 units of 7800 rows, 4 heads, 1550 -> 1576 us.
+// tiles that do not exist: 8 units of 1500 rows, 4 heads each, 10.1 instead of 8.0 us per step.)
+// TILE_FIRST: the first tile's loads go before the side requests.  The step starts earlier, but the stream gets thinner: the compiler
+// knows of two loads behind the first tile for certain (row 0 of the side phase), and the wait that this allows before a tile
+// is consumed stands in the loop, where it lets two loads of the next tile stay in flight and waits for the others.  Nothing is lost
+// where a tile is two loads (K and V of cached rows of up to 256 bytes: 256 units of 1450 28.8 us per step, 29.1 with the
+// side requests first).  Where it is four, the loop waits twice as often for half as much; first / behind:
+//   cached, 8-wave blocks     144 units of 1711 bf16 rows of 256 48.9 / 42.5, 144 of 1769 fp32 rows of 128 47.6 / 41.3; half a percent
+//                             for the side requests over 2100 random steps, at most 3% against
+//   streaming, 4-wave blocks  272 units of 2872 bf16 rows of 128 86.5 / 74.7, 400 of 1953 66.1 / 63.9; but where 1.6 to 4 blocks on a
+//                             compute unit crowd the memory the thinner stream is the faster one: 480 of 1627 62.4 / 63.8, 560 of
+//                             1395 69.0 / 72.8, 600 of 2929 150.5 / 157.9, 900 of 868 66.9 / 68.7; 1100 of 710 71.9 / 71.1
+//   cached, 4-wave blocks     the same: 300 units of 874 bf16 rows of 256 55.0 / 50.0, 560 of 375 35.7 / 37.8, 1100 units +3%
+//   streaming, 8-wave blocks  behind: 200 of 2630 44.9 / 41.7, 96 of 4663 rows of 256 77.0 / 70.4
+// Rows of 1024 bytes (eight loads): first, 272 units of 799 79.3 / 90.8, 8-wave blocks 0 to 1.5%, but in 4-wave blocks from 1.6 of
+// them on a compute unit on behind: 560 units +3%.  (The first tile consumed in front of the loop, so that no wait in it depends on what
+// follows that tile: 272 units 78.3, 512 of 3900 155.8, first 154.2.)  With one buffer they come behind, too: hoisted, the loop
+// copies its registers, 64 steps of 32 units of 7800 rows, 4 heads, 1550 -> 1576 us.
 template <bool TWO, bool TILE_FIRST, typename Buf, typename Load, typename Requests, typename Compute>
 __device__ inline void stream_tiles(const AttnArgs& a, int* counter, int wave, int nw, int total, Load load, Requests requests, Compute compute)
 {
@@ -723,7 +735,7 @@ __device__ inline void finish_split(const AttnArgs& a, const SplitCtx& x, SideRo
 }
 
 // Vector-ALU streaming kernel (any dtype; the choice for one query head per kv head).
-template <typename T, int D, int G, int U, bool NT, int NW, int SHORT>
+template <typename T, int D, int G, int U, bool NT, int NW, int SHORT, bool TILE_FIRST>
 __global__ __launch_bounds__(NW * 64, BUZZ_MIN_BLOCKS) void attn_split_kernel(const AttnArgs a)
 {
     using E = Elem<T>;
@@ -868,7 +880,7 @@ __global__ __launch_bounds__(NW * 64, BUZZ_MIN_BLOCKS) void attn_split_kernel(co
             if (own.exists()) compute_t(b[i].k, b[i].v, own.tile());
         }
     } else {
-        stream_tiles<TWO, !NT || NW == 4, Buf>(a, &sm.next_tile, wave, NW, tiles.total(), [&](Buf& b, int t) { load_t(b.k, b.v, t); }, requests, [&](Buf& b, int t) { compute_t(b.k, b.v, tiles.locate(t)); });
+        stream_tiles<TWO, TILE_FIRST, Buf>(a, &sm.next_tile, wave, NW, tiles.total(), [&](Buf& b, int t) { load_t(b.k, b.v, t); }, requests, [&](Buf& b, int t) { compute_t(b.k, b.v, tiles.locate(t)); });
     }
 
     if (lane == 0) BUZZ_STAMP(8 + (wave & 7));
@@ -1267,19 +1279,32 @@ hipError_t launch_split_t(const AttnArgs& a, int units, hipStream_t st, Timing t
         // streamed, 6.9 so; 64 of 1300 fp32 rows of 128 in 4 splits 16.1 / 17.1), one where tiles of 8 rows would leave waves idle for a
         // round of wide rows (64 units of 391 rows, 5 fp32 heads of 256: 18.6 us streamed, 20.7 with two)
         constexpr int MOST = G == 1 ? (RPW >= 4 ? 3 : 2) : G > 4 && RPW > 1 ? 2 : 1;
-        auto launch = [&](auto nt, auto nw, auto u) {
-            constexpr auto kernel = attn_split_kernel<T, D, G, decltype(u)::value, decltype(nt)::value, decltype(nw)::value, 0>;
+        auto launch = [&](auto nt, auto nw, auto u, auto tile_first) {
+            constexpr auto kernel = attn_split_kernel<T, D, G, decltype(u)::value, decltype(nt)::value, decltype(nw)::value, 0, decltype(tile_first)::value>;
             if constexpr (G <= 4) launch_even<kernel>(grid, block, lds, st, tm, a);
             else BUZZ_LAUNCH(kernel, grid, block, lds, st, tm, a);   // the vector ALU bounds these
         };
         auto flavour = [&](auto nw) {
             constexpr int NW = decltype(nw)::value;
             constexpr int TILES = NW == 8 ? MOST : 1;
-            if (a.streaming) launch(std::true_type{}, nw, std::integral_constant<int, US>{});
-            else if (may_be_short && a.rows_per_split <= UH * RPW * NW) BUZZ_LAUNCH((attn_split_kernel<T, D, G, UH, false, NW, 1>), grid, block, lds, st, tm, a);
-            else if (TILES >= 2 && may_be_short && a.rows_per_split <= 2 * UH * RPW * NW) BUZZ_LAUNCH((attn_split_kernel<T, D, G, UH, false, NW, (TILES >= 2 ? 2 : 1)>), grid, block, lds, st, tm, a);
-            else if (TILES >= 3 && may_be_short && a.rows_per_split <= 3 * UH * RPW * NW) BUZZ_LAUNCH((attn_split_kernel<T, D, G, UH, false, NW, TILES>), grid, block, lds, st, tm, a);
-            else launch(std::false_type{}, nw, std::integral_constant<int, UC>{});
+            // whether the first tile's loads go before the side requests: figures on both sides of each line at stream_tiles
+            auto stream = [&](auto nt, auto u) {
+                constexpr bool NT = decltype(nt)::value, TWO_LOADS = decltype(u)::value == 1, WIDEST = RPW == 1;
+                if constexpr (G > 1) launch(nt, nw, u, std::false_type{});
+                else if constexpr (TWO_LOADS) launch(nt, nw, u, std::true_type{});
+                else if constexpr (NW == 8) launch(nt, nw, u, std::bool_constant<WIDEST && !NT>{});
+                else {
+                    const int64_t blocks = (int64_t)grid.x * grid.y * grid.z;
+                    const bool crowd = 5 * blocks >= 8 * a.compute_units;
+                    if (WIDEST ? !crowd : crowd && blocks <= 4 * a.compute_units) launch(nt, nw, u, std::true_type{});
+                    else launch(nt, nw, u, std::false_type{});
+                }
+            };
+            if (a.streaming) stream(std::true_type{}, std::integral_constant<int, US>{});
+            else if (may_be_short && a.rows_per_split <= UH * RPW * NW) BUZZ_LAUNCH((attn_split_kernel<T, D, G, UH, false, NW, 1, false>), grid, block, lds, st, tm, a);
+            else if (TILES >= 2 && may_be_short && a.rows_per_split <= 2 * UH * RPW * NW) BUZZ_LAUNCH((attn_split_kernel<T, D, G, UH, false, NW, (TILES >= 2 ? 2 : 1), false>), grid, block, lds, st, tm, a);
+            else if (TILES >= 3 && may_be_short && a.rows_per_split <= 3 * UH * RPW * NW) BUZZ_LAUNCH((attn_split_kernel<T, D, G, UH, false, NW, TILES, false>), grid, block, lds, st, tm, a);
+            else stream(std::false_type{}, std::integral_constant<int, UC>{});
         };
         if (a.waves == 8) flavour(std::integral_constant<int, 8>{});
         else flavour(std::integral_constant<int, 4>{});

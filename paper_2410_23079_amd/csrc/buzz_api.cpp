@@ -687,7 +687,7 @@ namespace {
 bool reads_past_cache(const buzz_cache_t* c, int64_t n)
 {
     if (c->cfg.flags & (BUZZ_FLAG_STREAMING | BUZZ_FLAG_CACHED)) return (c->cfg.flags & BUZZ_FLAG_STREAMING) != 0;
-    return (double)c->L.units * (double)n * 2.0 * c->L.row_bytes > kLastLevelCacheBytes;
+    return step_bytes(c->L.units, n, c->L.row_bytes) > kLastLevelCacheBytes;
 }
 
 // Key-range splits of a decode step, the automatic choice.  Few, long blocks amortise the per-block merge, and a block

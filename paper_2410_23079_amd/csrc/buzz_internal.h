@@ -47,6 +47,9 @@ inline int stage_floats(int G, int D)
 }
 constexpr double kLastLevelCacheBytes = 256.0 * 1024 * 1024;   // Infinity Cache of one MI355X
 
+// Bytes of K and V that a decode step of n rows per unit reads.
+inline double step_bytes(int64_t units, int64_t n, int row_bytes) { return (double)units * (double)n * 2.0 * row_bytes; }
+
 struct RingMap {
     int32_t front;      // rows [0, front) are stored linearly
     int32_t ring_base;  // first physical row of the ring

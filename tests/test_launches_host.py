@@ -168,6 +168,24 @@ def test_streaming_steps_of_long_splits_anchor_their_tiles(lib, units, G, D, dty
     assert lib.buzz_cache_destroy(h) == 0
 
 
+@pytest.mark.parametrize("units,D,dtype,rows,flags,waves,first", [
+    (256, 128, "bf16", 1450, 0, 8, True), (250, 64, "fp32", 1500, 0, 8, True), (600, 64, "fp16", 900, 0, 4, True),   # a tile is two loads
+    (144, 256, "bf16", 1711, 0, 8, False), (144, 128, "fp32", 1769, 0, 8, False), (160, 256, "fp16", 1399, 0, 8, False),
+    (300, 256, "bf16", 840, 0, 4, False), (560, 256, "fp16", 375, 0, 4, True), (1100, 256, "bf16", 220, 0, 4, False),
+    (200, 128, "bf16", 2700, 0, 8, False), (96, 256, "bf16", 4663, 0, 8, False), (8, 128, "fp16", 9000, FLAG_STREAMING, 8, False),
+    (272, 128, "bf16", 2872, 0, 4, False), (300, 64, "bf16", 5000, 0, 4, False), (400, 128, "bf16", 1953, 0, 4, False),
+    (100, 64, "bf16", 19548, 0, 4, False),                                                                          # 3 blocks per unit
+    (430, 128, "bf16", 1775, 0, 4, True), (512, 128, "bf16", 3900, 0, 4, True), (1024, 128, "fp32", 800, 0, 4, True), (1100, 128, "bf16", 1000, 0, 4, False),
+    (96, 256, "fp32", 1000, 0, 8, True), (272, 256, "fp32", 799, 0, 4, True), (272, 256, "fp32", 200, 0, 4, True), (560, 256, "fp32", 300, 0, 4, False),
+    (64, 256, "fp32", 4200, 0, 8, False)])
+def test_the_first_tile_goes_first_where_that_was_faster(lib, units, D, dtype, rows, flags, waves, first):
+    """One head: in front of the side requests it thins the stream wherever a tile is more loads than are certain to follow it."""
+    h, kernel = prepared(lib, units, 1, D, dtype, rows, flags)
+    nw, short, tile_first = re.search(r"attn_split_kernelI.*ELi([48])ELi([0-3])ELb([01])E", kernel).groups()
+    assert (int(nw), short, tile_first) == (waves, "0", "01"[first]), kernel
+    assert lib.buzz_cache_destroy(h) == 0
+
+
 @pytest.mark.parametrize("units,rows,resident", [
     (1000, 1000, 2), (1024, 600, 2), (512, 5000, 2),         # 4 blocks per compute unit: 2 + 2, not 3 + 1
     (1300, 600, 3), (1280, 1000, 3),                         # 5 or 6 of them: 3 + 3 as well
