@@ -1250,14 +1250,17 @@ hipError_t launch_split_t(const AttnArgs& a, int units, hipStream_t st, Timing t
 {
     const dim3 grid = a.xcd_local ? dim3(8, a.n_splits, units / 8) : dim3(a.n_splits, units), block(a.waves * 64);
     const size_t lds = (size_t)G * a.rows_per_split * sizeof(float);   // logit staging
-    const bool may_be_short = !a.streaming && (uint64_t)a.cap * D * sizeof(T) <= UINT32_MAX;   // 32-bit offsets into a unit
-    if constexpr (G >= 2 && !std::is_same<T, float>::value) {   // grouped queries on a 16-bit cache: matrix cores
+    constexpr bool MATRIX = G >= 2 && !std::is_same<T, float>::value;   // grouped queries on a 16-bit cache: matrix cores
+    constexpr int ROWB = D * (int)sizeof(T), TILE = short_tile_rows(MATRIX, G, ROWB);
+    const int at_once = short_rows(MATRIX, G, D, ROWB, a.waves, step_bytes(units, a.n, ROWB), a.cap, a.streaming);
+    auto is_short = [&](int tiles) { return a.rows_per_split <= at_once && a.rows_per_split <= tiles * TILE * a.waves; };
+    if constexpr (MATRIX) {
         auto launch = [&](auto nt, auto nw, auto anchor) {
             launch_even<attn_split_mfma_kernel<T, D, G, decltype(nt)::value, decltype(nw)::value, decltype(anchor)::value, 0>>(grid, block, lds, st, tm, a);
         };
         auto flavour = [&](auto nw) {
             constexpr int NW = decltype(nw)::value;
-            if (may_be_short && a.rows_per_split <= NW * 16) { BUZZ_LAUNCH((attn_split_mfma_kernel<T, D, G, false, NW, false, 1>), grid, block, lds, st, tm, a); return; }
+            if (is_short(1)) { BUZZ_LAUNCH((attn_split_mfma_kernel<T, D, G, false, NW, false, 1>), grid, block, lds, st, tm, a); return; }
             if (!a.streaming) { launch(std::false_type{}, nw, std::false_type{}); return; }
             if constexpr (D >= 128) {
                 if (a.rows_per_split >= kAnchorRows) { launch(std::true_type{}, nw, std::true_type{}); return; }
@@ -1272,13 +1275,7 @@ hipError_t launch_split_t(const AttnArgs& a, int units, hipStream_t st, Timing t
         // a trip covers at least 4 rows
         constexpr int US = unroll_for<G, true>() * RPW >= 4 ? unroll_for<G, true>() : 4 / RPW;     // streaming loads
         constexpr int UC = unroll_for<G, false>() * RPW >= 4 ? unroll_for<G, false>() : 4 / RPW;   // cached loads
-        // short splits: tiles of 16 rows, 8 where a row takes a whole wave and for the vector work of more than 4 heads, which is to
-        // reach all waves (32 units of 128 rows in 3 splits, 6 fp32 heads of 128: 9.3 us per step with tiles of 16)
-        constexpr int SHORT_ROWS = G > 4 || RPW == 1 ? 8 : 16, UH = SHORT_ROWS / RPW;
-        // ... and the most of them per wave: three with one head of up to 256 bytes (32 units of 2800 bf16 rows of 64 in 8 splits 8.2 us
-        // streamed, 6.9 so; 64 of 1300 fp32 rows of 128 in 4 splits 16.1 / 17.1), one where tiles of 8 rows would leave waves idle for a
-        // round of wide rows (64 units of 391 rows, 5 fp32 heads of 256: 18.6 us streamed, 20.7 with two)
-        constexpr int MOST = G == 1 ? (RPW >= 4 ? 3 : 2) : G > 4 && RPW > 1 ? 2 : 1;
+        constexpr int UH = TILE / RPW;                    // short splits
         auto launch = [&](auto nt, auto nw, auto u, auto tile_first) {
             constexpr auto kernel = attn_split_kernel<T, D, G, decltype(u)::value, decltype(nt)::value, decltype(nw)::value, 0, decltype(tile_first)::value>;
             if constexpr (G <= 4) launch_even<kernel>(grid, block, lds, st, tm, a);
@@ -1286,7 +1283,7 @@ hipError_t launch_split_t(const AttnArgs& a, int units, hipStream_t st, Timing t
         };
         auto flavour = [&](auto nw) {
             constexpr int NW = decltype(nw)::value;
-            constexpr int TILES = NW == 8 ? MOST : 1;
+            constexpr int TILES = short_tiles(MATRIX, G, ROWB, NW);
             // whether the first tile's loads go before the side requests: figures on both sides of each line at stream_tiles
             auto stream = [&](auto nt, auto u) {
                 constexpr bool NT = decltype(nt)::value, TWO_LOADS = decltype(u)::value == 1, WIDEST = RPW == 1;
@@ -1301,9 +1298,9 @@ hipError_t launch_split_t(const AttnArgs& a, int units, hipStream_t st, Timing t
                 }
             };
             if (a.streaming) stream(std::true_type{}, std::integral_constant<int, US>{});
-            else if (may_be_short && a.rows_per_split <= UH * RPW * NW) BUZZ_LAUNCH((attn_split_kernel<T, D, G, UH, false, NW, 1, false>), grid, block, lds, st, tm, a);
-            else if (TILES >= 2 && may_be_short && a.rows_per_split <= 2 * UH * RPW * NW) BUZZ_LAUNCH((attn_split_kernel<T, D, G, UH, false, NW, (TILES >= 2 ? 2 : 1), false>), grid, block, lds, st, tm, a);
-            else if (TILES >= 3 && may_be_short && a.rows_per_split <= 3 * UH * RPW * NW) BUZZ_LAUNCH((attn_split_kernel<T, D, G, UH, false, NW, TILES, false>), grid, block, lds, st, tm, a);
+            else if (is_short(1)) BUZZ_LAUNCH((attn_split_kernel<T, D, G, UH, false, NW, 1, false>), grid, block, lds, st, tm, a);
+            else if (TILES >= 2 && is_short(2)) BUZZ_LAUNCH((attn_split_kernel<T, D, G, UH, false, NW, (TILES >= 2 ? 2 : 1), false>), grid, block, lds, st, tm, a);
+            else if (TILES >= 3 && is_short(3)) BUZZ_LAUNCH((attn_split_kernel<T, D, G, UH, false, NW, TILES, false>), grid, block, lds, st, tm, a);
             else stream(std::false_type{}, std::integral_constant<int, UC>{});
         };
         if (a.waves == 8) flavour(std::integral_constant<int, 8>{});

@@ -716,8 +716,10 @@ bool reads_past_cache(const buzz_cache_t* c, int64_t n)
 // 20000 rows, both rules together 0.7% on average.
 int64_t rows_at_once(const buzz_cache_t* c, int64_t n)
 {
-    if (c->L.G > 1 || reads_past_cache(c, n) || (uint64_t)c->L.cap * c->L.row_bytes > UINT32_MAX) return 0;
-    return c->L.row_bytes == 1024 ? 128 : 256;
+    if (c->L.G > 1) return 0;
+    // (also where the step is too large for two tiles of wide rows: 4 units of 9259 fp32 rows of 128 in 37 splits 11.6 us, in 64 13.6)
+    const int most = short_rows(false, 1, c->cfg.head_dim, c->L.row_bytes, 8, 0.0, c->L.cap, reads_past_cache(c, n));
+    return most < 256 ? most : 256;
 }
 int64_t auto_splits(const buzz_cache_t* c, int64_t n, int cus)
 {

@@ -50,6 +50,31 @@ constexpr double kLastLevelCacheBytes = 256.0 * 1024 * 1024;   // Infinity Cache
 // Bytes of K and V that a decode step of n rows per unit reads.
 inline double step_bytes(int64_t units, int64_t n, int row_bytes) { return (double)units * (double)n * 2.0 * row_bytes; }
 
+// Splits of a decode step whose rows a block requests at once (cached loads), a wave in 1 to 3 tiles.
+// Rows of a tile: 16, 8 where a row takes a whole wave and for the vector work of more than 4 heads, which is to reach all
+// waves (32 units of 128 rows in 3 splits, 6 fp32 heads of 128: 9.3 us per step with tiles of 16).
+constexpr int short_tile_rows(bool matrix, int G, int row_bytes) { return !matrix && (G > 4 || row_bytes == 1024) ? 8 : 16; }
+// The most tiles of a wave: in 8-wave blocks three with one head of up to 256 bytes (32 units of 2800 bf16 rows of 64 in 8 splits
+// 8.2 us streamed, 6.9 so; 64 of 1300 fp32 rows of 128 in 4 splits 16.1 / 17.1), one where tiles of 8 rows would leave waves idle
+// for a round of wide rows (64 units of 391 rows, 5 fp32 heads of 256: 18.6 us streamed, 20.7 with two).
+constexpr int short_tiles(bool matrix, int G, int row_bytes, int waves)
+{
+    if (matrix || waves != 8) return 1;
+    if (G == 1) return row_bytes <= 256 ? 3 : 2;
+    return G > 4 && row_bytes < 1024 ? 2 : 1;
+}
+// The rows of such a split at most; 0: none.  Its addresses are 32-bit offsets into a unit.  One head's rows of 512 bytes are taken in
+// two tiles only while about the L2 caches of the dies (32 MB together) hold the step; from then on streaming them is faster, two
+// tiles / streamed: 64 units of 784 bf16 rows of 256 (49 MB) 12.5 / 11.6 us; against the time without short splits, 192 units of
+// 149 (28 MB) 0.88 / 0.95, 32 of 1104 (34 MB) 1.00 / 0.955, 240 of 214 (50 MB) 1.02 / 0.98.  Over 1500 random steps the lines lie at 33
+// MB (16 bit) and 38 MB (fp32); narrower and wider rows have none.
+inline int short_rows(bool matrix, int G, int D, int row_bytes, int waves, double bytes_of_step, int64_t cap, bool streaming)
+{
+    if (streaming || (uint64_t)cap * row_bytes > UINT32_MAX) return 0;
+    const bool one = G == 1 && row_bytes == 512 && bytes_of_step > (D == 128 ? 38.0 : 33.0) * 1024 * 1024;
+    return (one ? 1 : short_tiles(matrix, G, row_bytes, waves)) * short_tile_rows(matrix, G, row_bytes) * waves;
+}
+
 struct RingMap {
     int32_t front;      // rows [0, front) are stored linearly
     int32_t ring_base;  // first physical row of the ring

@@ -186,6 +186,30 @@ def test_the_first_tile_goes_first_where_that_was_faster(lib, units, D, dtype, r
     assert lib.buzz_cache_destroy(h) == 0
 
 
+def split_kernel(kernel):
+    """(waves per block, tiles of a short split or 0) of a decode kernel's name."""
+    m = re.search(r"attn_split_kernelI.*ELi([48])ELi([0-3])ELb[01]E", kernel) or re.search(r"attn_split_mfma_kernelI.*Lb[01]ELi([48])ELb[01]ELi([01])E", kernel)
+    return tuple(map(int, m.groups()))
+
+
+@pytest.mark.parametrize("units,D,dtype,rows,splits,tiles", [
+    (64, 256, "bf16", 500, 4, 1), (64, 256, "bf16", 784, 4, 0), (192, 256, "bf16", 149, 1, 2), (240, 256, "fp16", 214, 1, 0), (8, 256, "bf16", 3000, 24, 1),
+    (16, 256, "fp16", 2000, 8, 2), (16, 256, "fp16", 2300, 10, 0), (256, 256, "bf16", 131, 1, 2), (256, 256, "bf16", 133, 1, 0),   # 33 MB: 132 rows
+    (256, 128, "fp32", 151, 1, 2), (256, 128, "fp32", 153, 1, 0),                                                                  # 38 MB: 152 rows
+    (224, 128, "bf16", 250, 1, 2), (256, 128, "bf16", 380, 1, 3), (256, 64, "fp32", 380, 1, 3), (256, 256, "fp32", 120, 1, 2)])
+def test_wide_rows_are_requested_at_once_while_the_dies_caches_hold_them(lib, units, D, dtype, rows, splits, tiles):
+    """Two tiles per wave of one head's 512-byte rows: up to 33 MB (16 bit) and 38 MB (fp32) of K and V per step; other rows
+    have no such line."""
+    h = create(lib, config(batch=1, n_q_heads=units, n_kv_heads=units, head_dim=D, kv_dtype=dtype, window=rows - 5, segment=8, evict_every=64,
+                           max_context=rows + 200, flags=0))
+    assert lib.buzz_cache_set_splits(h, splits) == 0
+    assert lib.buzz_cache_import(h, KP, VP, SP, PP, rows - 1, 0, rows - 1, None) == 0
+    lib.rec_reset(-1)
+    assert lib.buzz_decode_step(h, QP, KP, VP, OUT, None) == 0
+    assert split_kernel(lib.rec_kernel(0).decode()) == (8, tiles), lib.rec_kernel(0)
+    assert lib.buzz_cache_destroy(h) == 0
+
+
 @pytest.mark.parametrize("units,rows,resident", [
     (1000, 1000, 2), (1024, 600, 2), (512, 5000, 2),         # 4 blocks per compute unit: 2 + 2, not 3 + 1
     (1300, 600, 3), (1280, 1000, 3),                         # 5 or 6 of them: 3 + 3 as well
