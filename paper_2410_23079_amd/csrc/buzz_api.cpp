@@ -697,7 +697,9 @@ bool reads_past_cache(const buzz_cache_t* c, int64_t n)
 // more than it streams (5 to 57 ns over the supported shapes), and the merge split_us per split, more where the partial
 // results are larger or the units many (43 to 151 ns).  row_us n / S + split_us S is least at the root below; a cache whose
 // rows take less than the publishing and merging does (whole_us) stays whole, up to 128 rows also one that a split does not
-// save 1.6 us more: the launch that the counters of the static scratch cost, and both entry points split alike.  Beyond 8
+// save 1.6 us more, because both entry points split alike and the static scratch's counters cost a launch.  Over 2200 random such steps
+// between 1.6 and 2.6 us a split takes 24% less time than the whole, 9% with the static scratch; of the latter 13% are slower, by up
+// to 29% (2 splits, 96 units and more), though none slower than before short splits had a kernel of their own.  Beyond 8
 // splits the merge goes by rounds of 8 and 16 loads: a root of more than 8 is rounded to 8, 16 or a larger multiple of 8.
 // Around the root the time is flat to what the model leaves out (the tiles of a split over its waves), so splits of 128
 // rows, one 16-row tile per wave, stay, whatever their number, unless the model gains 0.4 us: 8 units of 1512 rows of 4 bf16
@@ -707,13 +709,16 @@ bool reads_past_cache(const buzz_cache_t* c, int64_t n)
 // 67 of 12000 to 120000 rows 3%, none longer by more than 2% (whole_us ends to grow at 52 units: at 80 and 120 it left steps
 // whole that took 3-4% longer so).  1 unit of 12000 rows, 4 heads of 128 in bf16, 13.0 us with 94 splits, 10.9 with 40; 3 of
 // 175, 4 fp32 heads of 256, 14.2 with 2, 8.2 with 8; 100 of 154, 8 fp16 heads of 64, 7.7 with 2, 5.4 whole.
-// One head, cached loads: a block requests 256 rows at once (rows_at_once; up to 384 of no more than 256 bytes, some 5% slower per
-// row), which the model does not know.  A cache of no more, and no more than 55000 bytes of K per unit (214 rows of 256 bytes),
-// stays whole: at 160 to 192 such rows 10% faster than what the model gives, from 224 on 10% slower.  From 13 splits of 256 rows
-// on these are taken, as few as there are: fewer publish less (3 units of 11000 fp32 rows of 64: 44 splits 8.9 us, 86 11.4; 20
-// splits and more 5% on average; 9 to 12 are about even, below the model's are faster).  Beyond 48 the model's count stays (1
-// unit of 16000 bf16 rows of 128: 56 splits of 286 rows 9.8 us, 63 of 254 9.6).  On 3972 random shapes of 1 to 128 units, 70 to
-// 20000 rows, both rules together 0.7% on average.
+// One head, cached loads: a block requests 256 rows at once (128 of 1024 bytes; up to 384 of no more than 256 bytes, some 5%
+// slower per row), which the model does not know.  A cache of no more, and no more than 55000 bytes of K per unit (214 rows of 256
+// bytes), stays whole: 1900 such steps took 8% less time than with what the model gives (22% less to 17% more), from 224 rows on 10%
+// more.  From 13 splits of 256 rows on these are taken where they are fewer than the model's: fewer publish less, 8 units of 4200
+// bf16 rows of 128 in 17 splits 7.5 us, in 32 8.3; but a longer split waits longer for its rows, the more the wider they are, 2 units
+// of 4053 fp32 rows of 128 in 16 splits 7.8 us, in 32 7.3.  So what the merge saves, split_us (S - fewest), must be 0.6 of what the model
+// says that the rows cost, row_us n (1 / fewest - 1 / S), or more: 5100 random steps of 1 to 16 units that the rule changes take 6.4%
+// less time, 2% of them over 2% more (with the line at 0.5 9%).  The count is never raised to such splits: 1 unit of 9000 bf16 rows of 64
+// takes 7.1 us in the model's 32, 7.6 in 36.  Beyond 48 the model's count stays (1 unit of 16000 bf16 rows of 128: 56 splits of 286
+// rows 9.8 us, 63 of 254 9.6).
 int64_t rows_at_once(const buzz_cache_t* c, int64_t n)
 {
     if (c->L.G > 1) return 0;
@@ -738,7 +743,7 @@ int64_t auto_splits(const buzz_cache_t* c, int64_t n, int cus)
     if (S > most) S = most;
     if (long_splits > 1 && us(long_splits) - us(S) < 0.4) S = long_splits;
     const int64_t fewest = at_once > 0 ? ceil_div(n, at_once) : 0;   // splits whose rows are requested at once
-    return fewest >= 13 && fewest <= 48 && fewest <= most && 5 * S > 4 * fewest ? fewest : S;
+    return fewest >= 13 && fewest <= 48 && fewest < S && m.split_us * (double)(fewest * S) >= 0.6 * rows_us ? fewest : S;
 }
 
 // One decode step.  static_scratch: the split-softmax scratch (arrival counters, per-split partials) is the

@@ -352,7 +352,16 @@ def test_a_scored_prompt_that_is_kept_whole_is_placed_where_that_was_faster(lib,
     (8, 300, 1, "fp32", 64, 3), (8, 1512, 4, "bf16", 128, 12), (8, 846, 4, "fp32", 64, 7),                                       # of 128 rows
     (3, 175, 4, "fp32", 256, 8), (12, 431, 4, "fp32", 256, 8),                                                                   # shorter
     (1, 12000, 4, "bf16", 128, 40), (1, 16000, 1, "bf16", 128, 56), (2, 20000, 4, "bf16", 64, 40), (3, 22272, 1, "fp16", 128, 85),  # longer
-    (80, 320, 2, "fp16", 64, 3), (120, 220, 1, "fp32", 64, 2), (64, 286, 4, "fp16", 64, 1), (48, 262, 4, "bf16", 64, 1)])          # many units
+    (80, 320, 2, "fp16", 64, 3), (120, 220, 1, "fp32", 64, 2), (64, 286, 4, "fp16", 64, 1), (48, 262, 4, "bf16", 64, 1),           # many units
+    # one head: as few splits as request their rows at once, where the merge saves more than the longer splits cost
+    (8, 4200, 1, "bf16", 128, 17), (6, 5500, 1, "fp32", 128, 22), (10, 4000, 1, "fp16", 256, 16), (8, 4000, 1, "fp32", 64, 16),
+    (2, 4053, 1, "fp32", 128, 32), (2, 4700, 1, "bf16", 256, 37), (1, 2000, 1, "fp32", 256, 32),                                   # wide rows, few units
+    (1, 12000, 1, "bf16", 64, 40), (1, 9000, 1, "bf16", 64, 32), (3, 11000, 1, "fp32", 64, 40), (4, 12288, 1, "bf16", 128, 40),    # never more
+    (8, 3072, 1, "bf16", 128, 24), (8, 3073, 1, "bf16", 128, 13),                                                                  # from 13 on
+    (5, 12288, 1, "fp32", 128, 48), (5, 12289, 1, "fp32", 128, 51),                                                                # up to 48
+    # whole: one head up to 55000 bytes of K per unit; up to 128 rows unless a split saves 1.6 us
+    (8, 214, 1, "bf16", 128, 1), (8, 215, 1, "bf16", 128, 2), (8, 107, 1, "fp32", 128, 1), (8, 256, 1, "bf16", 64, 1),
+    (8, 111, 8, "fp32", 64, 1), (8, 112, 8, "fp32", 64, 5), (8, 128, 4, "bf16", 128, 1), (8, 88, 6, "fp32", 128, 1), (8, 89, 6, "fp32", 128, 5)])
 def test_the_automatic_split_count_at_measured_shapes(lib, units, rows, G, dtype, D, splits):
     h, _ = prepared(lib, units, G, D, dtype, rows)
     grid = [lib.rec_value(0, b"grid_" + x) for x in (b"x", b"y", b"z")]
