@@ -63,11 +63,12 @@ constexpr int short_tiles(bool matrix, int G, int row_bytes, int waves)
     if (G == 1) return row_bytes <= 256 ? 3 : 2;
     return G > 4 && row_bytes < 1024 ? 2 : 1;
 }
-// The rows of such a split at most; 0: none.  Its addresses are 32-bit offsets into a unit.  One head's rows of 512 bytes are taken in
-// two tiles only while about the L2 caches of the dies (32 MB together) hold the step; from then on streaming them is faster, two
-// tiles / streamed: 64 units of 784 bf16 rows of 256 (49 MB) 12.5 / 11.6 us; against the time without short splits, 192 units of
-// 149 (28 MB) 0.88 / 0.95, 32 of 1104 (34 MB) 1.00 / 0.955, 240 of 214 (50 MB) 1.02 / 0.98.  Over 1500 random steps the lines lie at 33
-// MB (16 bit) and 38 MB (fp32); narrower and wider rows have none.
+// The rows of such a split at most; 0: none.  Its addresses are 32-bit offsets into a unit (500 MB is the most that the split limit
+// lets a unit have; checked all the same).  One head's rows of 512 bytes are taken in two tiles only while about the L2 caches of the
+// dies (32 MB together) hold the step; from then on streaming them is faster, two tiles / streamed: 64 units of 784 bf16 rows of
+// 256 (49 MB) 12.5 / 11.6 us; against the time without short splits, 192 units of 149 (28 MB) 0.88 / 0.95, 32 of 1104 (34 MB) 1.00 /
+// 0.955, 240 of 214 (50 MB) 1.02 / 0.98.  Over 1500 random steps the lines lie at 33 MB (16 bit) and 38 MB (fp32); narrower and
+// wider rows have none.
 inline int short_rows(bool matrix, int G, int D, int row_bytes, int waves, double bytes_of_step, int64_t cap, bool streaming)
 {
     if (streaming || (uint64_t)cap * row_bytes > UINT32_MAX) return 0;

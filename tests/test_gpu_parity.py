@@ -8,6 +8,7 @@ import numpy as np
 import pytest
 import torch
 
+from tests.test_launches_host import NEW_ROW_ALONE
 from workloads import decode_inputs, get_workload, prompt_inputs
 
 pytestmark = pytest.mark.gpu
@@ -131,15 +132,57 @@ def test_anchored_tiles_of_long_streaming_splits(G, D, dtype, sink, T, steps):
 
 
 @pytest.mark.parametrize("G,D,dtype", [(1, 64, "fp32"), (1, 128, "bf16"), (1, 64, "fp16"), (1, 256, "fp32"), (4, 64, "fp32"), (3, 256, "fp32"),
-                                       (4, 128, "bf16"), (8, 128, "fp16"), (2, 64, "bf16"), (8, 256, "bf16")])
+                                       (4, 128, "bf16"), (8, 128, "fp16"), (2, 64, "bf16"), (8, 256, "bf16"), (1, 128, "fp32"), (1, 256, "bf16"),
+                                       (5, 128, "fp32"), (8, 128, "fp32")])
 @pytest.mark.parametrize("rows,splits", [(0, 1), (15, 1), (60, 1), (63, 2), (126, 1), (120, 3), (250, 1), (255, 2), (390, 4), (262, 1),
                                          (378, 1), (391, 1)])
 def test_short_splits(G, D, dtype, rows, splits):
     """Splits whose rows are all requested at once: one row, tiles and blocks that are just full or just not, the ring's wrap and
-    the linear region's end inside a tile, the new row alone in the last split, and the first size that is streamed instead."""
+    the linear region's end inside a tile, and the first size that is streamed instead."""
     wl = small(batch=1, n_kv_heads=2, n_q_heads=2 * G, head_dim=D, dtype=dtype, prompt=rows, decode_steps=14, sink=3,
                window=max(1, rows - 20), segment=4, keep=1, evict_every=7, n_obs=min(rows, 5))
     run(wl, splits=splits, check_auto=False)
+
+
+@pytest.mark.parametrize("heads", [2, 8])
+@pytest.mark.parametrize("G,D,dtype,n,splits", NEW_ROW_ALONE)
+def test_the_new_row_alone_in_the_last_split(G, D, dtype, n, splits, heads):
+    """The last block has no stored row: every lane takes the caller's, and there are no side rows.  Step 5 has n rows (that
+    this leaves one for the last split is checked where the launch is looked at on the host); the cache grows through it."""
+    wl = small(batch=1, n_kv_heads=heads, n_q_heads=heads * G, head_dim=D, dtype=dtype, prompt=n - 5, decode_steps=8, sink=3,
+               window=n + 20, segment=4, keep=1, evict_every=16, n_obs=5)
+    run(wl, splits=splits, check_auto=False)
+
+
+@pytest.mark.parametrize("rows", [20, 40, 70])
+@pytest.mark.parametrize("G,dtype", [(1, "fp32"), (1, "bf16"), (4, "bf16"), (6, "fp32"), (8, "fp16")])
+def test_short_splits_of_more_units_than_compute_units(G, dtype, rows):
+    """320 units: 4-wave blocks of one split each, requested at once up to 64 rows (32 with 6 fp32 heads), streamed beyond."""
+    wl = small(batch=5, n_kv_heads=64, n_q_heads=64 * G, head_dim=64, dtype=dtype, prompt=rows, decode_steps=9, sink=3, window=rows - 10,
+               segment=4, keep=1, evict_every=7, n_obs=5)
+    run(wl, units=[(0, 0), (2, 17), (4, 63)])
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "fp16", "bf16"])
+@pytest.mark.parametrize("D", [64, 128, 256])
+@pytest.mark.parametrize("G", [1, 2, 3, 4, 5, 6, 7, 8])
+def test_shapes_of_cached_splits_that_are_streamed(dtype, D, G):
+    """Whole caches of more rows than a block requests at once: runs up to the linear region's end, the ring's wrap and the new
+    row, tiles that the waves claim, further rounds of side rows."""
+    wl = small(batch=1, n_kv_heads=2, n_q_heads=2 * G, head_dim=D, dtype=dtype, prompt=600, decode_steps=12, sink=3, window=420, segment=7, keep=2,
+               evict_every=10, n_obs=9)
+    run(wl, splits=1, kv_loads="cached", check_auto=False)
+
+
+@pytest.mark.parametrize("device_merge", [False, True])
+@pytest.mark.parametrize("G,D,dtype,splits,rows", [(5, 256, "bf16", 9, 1500), (5, 128, "fp16", 9, 1500), (8, 256, "fp32", 9, 1500), (6, 128, "fp32", 10, 1600),
+                                                   (3, 64, "fp32", 9, 1500), (1, 128, "bf16", 9, 3700), (1, 256, "fp32", 9, 1500)])
+def test_merges_of_long_splits(G, D, dtype, splits, rows, device_merge):
+    """More splits than a round of loads covers, each longer than a block requests at once: half of the block merges while the
+    other half starts the side phase."""
+    wl = small(batch=1, n_kv_heads=8, n_q_heads=8 * G, head_dim=D, dtype=dtype, prompt=rows, decode_steps=3, sink=3, window=rows - 120, segment=16,
+               keep=3, evict_every=16, n_obs=8)
+    run(wl, splits=splits, device_merge=device_merge, units=[(0, 0), (0, 5)])
 
 
 @pytest.mark.parametrize("device_merge", [False, True])

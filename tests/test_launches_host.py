@@ -14,6 +14,10 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 HERE = os.path.join(ROOT, "tests")
 WS, KP, VP, QP, SP, PP, OUT = (0x100000 * i for i in (1, 2, 3, 4, 5, 6, 7))     # made-up device addresses
 
+# (query heads per kv head, head_dim, type, rows, splits): one row is left for the last split, the one that the step appends
+NEW_ROW_ALONE = [(1, 64, "fp32", 25, 3), (1, 128, "bf16", 61, 6), (1, 256, "bf16", 25, 3), (1, 256, "fp32", 17, 5), (4, 128, "bf16", 33, 3), (8, 128, "fp16", 513, 9),
+                 (2, 64, "bf16", 129, 9), (4, 64, "fp32", 33, 3), (8, 128, "fp32", 25, 3), (3, 256, "fp32", 61, 6), (5, 128, "fp32", 25, 3), (1, 64, "fp16", 57, 8)]
+
 pytestmark = pytest.mark.skipif(shutil.which("hipcc") is None, reason="hipcc not on PATH")
 
 
@@ -208,6 +212,45 @@ def test_wide_rows_are_requested_at_once_while_the_dies_caches_hold_them(lib, un
     assert lib.buzz_decode_step(h, QP, KP, VP, OUT, None) == 0
     assert split_kernel(lib.rec_kernel(0).decode()) == (8, tiles), lib.rec_kernel(0)
     assert lib.buzz_cache_destroy(h) == 0
+
+
+@pytest.mark.parametrize("units", [2, 8])
+@pytest.mark.parametrize("G,D,dtype,n,splits", NEW_ROW_ALONE)
+def test_the_new_row_can_be_alone_in_the_last_split(lib, G, D, dtype, n, splits, units):
+    h = create(lib, config(batch=1, n_q_heads=units * G, n_kv_heads=units, head_dim=D, kv_dtype=dtype, window=n, flags=0))
+    assert lib.buzz_cache_set_splits(h, splits) == 0
+    assert lib.buzz_cache_import(h, KP, VP, SP, PP, n - 1, 0, n - 1, None) == 0
+    lib.rec_reset(-1)
+    assert lib.buzz_decode_step(h, QP, KP, VP, OUT, None) == 0
+    assert split_kernel(lib.rec_kernel(0).decode())[1] >= 1
+    assert [lib.rec_value(0, b"grid_" + x) for x in (b"x", b"y", b"z")] in ([splits, units, 1], [8, splits, units // 8])
+    rows_per_split = lib.rec_value(0, b"lds") // (4 * G)     # the staged logits
+    assert n - (splits - 1) * rows_per_split == 1
+    assert lib.buzz_cache_destroy(h) == 0
+
+
+@pytest.mark.parametrize("G,D,dtype,waves,rows", [
+    (1, 64, "bf16", 8, (128, 256, 384)), (1, 128, "fp16", 8, (128, 256, 384)), (1, 64, "fp32", 8, (128, 256, 384)), (1, 128, "fp32", 8, (128, 256)),
+    (1, 256, "bf16", 8, (128, 256)), (1, 256, "fp32", 8, (64, 128)), (2, 64, "bf16", 8, (128,)), (4, 128, "fp16", 8, (128,)), (8, 128, "bf16", 8, (128,)),
+    (4, 64, "fp32", 8, (128,)), (3, 128, "fp32", 8, (128,)), (4, 256, "fp32", 8, (64,)), (5, 64, "fp32", 8, (64, 128)), (8, 128, "fp32", 8, (64, 128)),
+    (5, 256, "fp32", 8, (64,)), (8, 256, "bf16", 4, (64,)), (8, 256, "fp32", 4, (32,)), (1, 128, "bf16", 4, (64,)), (1, 256, "fp32", 4, (32,)),
+    (4, 128, "bf16", 4, (64,)), (6, 64, "fp32", 4, (32,))])
+@pytest.mark.parametrize("flags", [0, FLAG_STREAMING])
+def test_which_splits_are_requested_at_once(lib, G, D, dtype, waves, rows, flags):
+    """Up to so many rows per split in one, two and three tiles per wave; one row more takes the next kernel."""
+    units = 4 if G * D >= 1505 or waves == 8 else 300
+    def kernel(n):
+        h = create(lib, config(batch=1, n_q_heads=units * G, n_kv_heads=units, head_dim=D, kv_dtype=dtype, window=n, flags=flags))
+        assert lib.buzz_cache_set_splits(h, 1) == 0
+        assert lib.buzz_cache_import(h, KP, VP, SP, PP, n - 1, 0, n - 1, None) == 0
+        lib.rec_reset(-1)
+        assert lib.buzz_decode_step(h, QP, KP, VP, OUT, None) == 0
+        assert lib.rec_value(0, b"grid_x") * lib.rec_value(0, b"grid_y") == units and lib.buzz_cache_destroy(h) == 0
+        return split_kernel(lib.rec_kernel(0).decode())
+    for tiles, n in enumerate(rows, 1):
+        assert kernel(n) == (waves, 0 if flags else tiles)
+        assert kernel(n + 1) == (waves, 0 if flags or tiles == len(rows) else tiles + 1)
+    assert kernel(1) == (waves, 0 if flags else 1)
 
 
 @pytest.mark.parametrize("units,rows,resident", [
