@@ -190,7 +190,7 @@ class BuzzCache:
 
     def _step(self, entry, what, q, k_new, v_new, out, stream):
         # A short step takes the GPU 4 us, and the host has to keep up: without the general helpers' calls per argument
-        # one step costs it 1.2 us less.
+        # one step costs it 0.1 to 0.5 us less, by machine (0.70 -> 0.60 us with a stream handle given and nothing launched).
         try:
             q, k_new, v_new, out = q.data_ptr(), k_new.data_ptr(), v_new.data_ptr(), out.data_ptr()
         except AttributeError:                             # None among them

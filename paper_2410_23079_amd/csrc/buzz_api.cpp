@@ -703,7 +703,7 @@ bool reads_past_cache(const buzz_cache_t* c, int64_t n)
 // splits the merge goes by rounds of 8 and 16 loads: a root of more than 8 is rounded to 8, 16 or a larger multiple of 8.
 // Around the root the time is flat to what the model leaves out (the tiles of a split over its waves), so splits of 128
 // rows, one 16-row tile per wave, stay, whatever their number, unless the model gains 0.4 us: 8 units of 1512 rows of 4 bf16
-// heads of 128 stay at 12, 6.9 us, 8 take 7.2.
+// heads of 128 stay at 12, 6.8 us, 8 take 6.9.
 // The constants are a fit to 1 to 64 units of 80 to 12000 rows, groups of 1 to 8, heads of 64 to 256, all types.  Against
 // splits of at least 128 rows, on 220 random shapes of that range 4% less time on average, on 120 of 65 to 255 units 0.7%, on
 // 67 of 12000 to 120000 rows 3%, none longer by more than 2% (whole_us ends to grow at 52 units: at 80 and 120 it left steps
