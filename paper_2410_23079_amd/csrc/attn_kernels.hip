@@ -153,14 +153,15 @@ template <int BIT> __device__ inline LanePair lane_pair(float v)
 template <int BIT> __device__ inline float pair_sum(float v) { const LanePair p = lane_pair<BIT>(v); return p.a + p.b; }
 template <int BIT> __device__ inline float pair_max(float v) { const LanePair p = lane_pair<BIT>(v); return fmaxf(p.a, p.b); }
 
-// Sum over the LPR consecutive lanes that share a cache row; every lane of the group gets the total.
-template <int LPR> __device__ inline float row_sum(float v) {
+// Sum over the LPR consecutive lanes that share a cache row; every lane of the group gets the total.  VIA_LDS: rows of 16 lanes
+// exchange through LDS, which paces the loop (see launch_split_t).
+template <int LPR, bool VIA_LDS> __device__ inline float row_sum(float v) {
     v += dpp_move<0xB1>(v);                 // quad_perm [1,0,3,2]
     v += dpp_move<0x4E>(v);                 // quad_perm [2,3,0,1]
     if constexpr (LPR >= 8) v += dpp_move<0x141>(v);  // row_half_mirror
     if constexpr (LPR >= 16) v += dpp_move<0x140>(v); // row_mirror
-    if constexpr (LPR >= 32) v = pair_sum<16>(v);
-    if constexpr (LPR >= 64) v = pair_sum<32>(v);
+    if constexpr (LPR >= 32) v = VIA_LDS ? v + __shfl_xor(v, 16) : pair_sum<16>(v);
+    if constexpr (LPR >= 64) v = VIA_LDS ? v + __shfl_xor(v, 32) : pair_sum<32>(v);
     return v;
 }
 
@@ -523,7 +524,7 @@ __device__ inline float wave_max(float v)
 }
 __device__ inline float wave_sum(float v)
 {
-    v = row_sum<16>(v);
+    v = row_sum<16, false>(v);
     return (lane_value(v, 0) + lane_value(v, 16)) + (lane_value(v, 32) + lane_value(v, 48));
 }
 
@@ -735,7 +736,7 @@ __device__ inline void finish_split(const AttnArgs& a, const SplitCtx& x, SideRo
 }
 
 // Vector-ALU streaming kernel (any dtype; the choice for one query head per kv head).
-template <typename T, int D, int G, int U, bool NT, int NW, int SHORT, bool TILE_FIRST>
+template <typename T, int D, int G, int U, bool NT, int NW, int SHORT, bool TILE_FIRST, bool VIA_LDS>
 __global__ __launch_bounds__(NW * 64, BUZZ_MIN_BLOCKS) void attn_split_kernel(const AttnArgs a)
 {
     using E = Elem<T>;
@@ -806,7 +807,7 @@ __global__ __launch_bounds__(NW * 64, BUZZ_MIN_BLOCKS) void attn_split_kernel(co
             const bool ok = k.base + u * RPW + rs < k.cnt;
 #pragma unroll
             for (int g = 0; g < G; ++g) {
-                const float d = row_sum<LPR>(E::dot(qr[g], kr[u])) * a.scale_log2;
+                const float d = row_sum<LPR, VIA_LDS>(E::dot(qr[g], kr[u])) * a.scale_log2;
                 s[g][u] = ok ? d : -INFINITY;
                 if (c == 0 && ok) stage[g * a.rows_per_split + stg + u * RPW + rs] = d;
             }
@@ -1279,10 +1280,22 @@ hipError_t launch_split_t(const AttnArgs& a, int units, hipStream_t st, Timing t
         constexpr int US = unroll_for<G, true>() * RPW >= 4 ? unroll_for<G, true>() : 4 / RPW;     // streaming loads
         constexpr int UC = unroll_for<G, false>() * RPW >= 4 ? unroll_for<G, false>() : 4 / RPW;   // cached loads
         constexpr int UH = TILE / RPW;                    // short splits
-        auto launch = [&](auto nt, auto nw, auto u, auto tile_first) {
-            constexpr auto kernel = attn_split_kernel<T, D, G, decltype(u)::value, decltype(nt)::value, decltype(nw)::value, 0, decltype(tile_first)::value>;
+        const int64_t blocks = (int64_t)grid.x * grid.y * grid.z;
+        auto launch_as = [&](auto nt, auto nw, auto u, auto tile_first, auto via_lds) {
+            constexpr auto kernel = attn_split_kernel<T, D, G, decltype(u)::value, decltype(nt)::value, decltype(nw)::value, 0, decltype(tile_first)::value, decltype(via_lds)::value>;
             if constexpr (G <= 4) launch_even<kernel>(grid, block, lds, st, tm, a);
             else BUZZ_LAUNCH(kernel, grid, block, lds, st, tm, a);   // the vector ALU bounds these
+        };
+        auto launch = [&](auto nt, auto nw, auto u, auto tile_first) {
+            // Of 2 to 2.5 blocks per compute unit, those that are three on one end last, the more the less time a block's loop takes beside
+            // its loads.  Where memory and arithmetic are about even the lanes' exchange through LDS evens them: 516 to 600 units of
+            // 3 fp32 heads of 256 take 3 to 10% less time so (520 of 319 rows 72.8 -> 62.8 us), of 4 of 128 2 to 5% (560 of 809 94.3 ->
+            // 86.7); 512 units 5 and 3% more, 700 1%, 4 heads of 256 on 560 units 6%; 3 of 128 1% either way, 2 heads 1 to 3% more;
+            // splits of less than 64 KB of K 1% more.
+            if constexpr (decltype(nw)::value == 4 && (G == 3 || G == 4) && G * D >= 512 && G * D < 1024) {
+                if (blocks > 2 * a.compute_units && 2 * blocks <= 5 * a.compute_units && a.rows_per_split * ROWB >= 65536) { launch_as(nt, nw, u, tile_first, std::true_type{}); return; }
+            }
+            launch_as(nt, nw, u, tile_first, std::false_type{});
         };
         auto flavour = [&](auto nw) {
             constexpr int NW = decltype(nw)::value;
@@ -1294,16 +1307,15 @@ hipError_t launch_split_t(const AttnArgs& a, int units, hipStream_t st, Timing t
                 else if constexpr (TWO_LOADS) launch(nt, nw, u, std::true_type{});
                 else if constexpr (NW == 8) launch(nt, nw, u, std::bool_constant<WIDEST && !NT>{});
                 else {
-                    const int64_t blocks = (int64_t)grid.x * grid.y * grid.z;
                     const bool crowd = 5 * blocks >= 8 * a.compute_units;
                     if (WIDEST ? !crowd : crowd && blocks <= 4 * a.compute_units) launch(nt, nw, u, std::true_type{});
                     else launch(nt, nw, u, std::false_type{});
                 }
             };
             if (a.streaming) stream(std::true_type{}, std::integral_constant<int, US>{});
-            else if (is_short(1)) BUZZ_LAUNCH((attn_split_kernel<T, D, G, UH, false, NW, 1, false>), grid, block, lds, st, tm, a);
-            else if (TILES >= 2 && is_short(2)) BUZZ_LAUNCH((attn_split_kernel<T, D, G, UH, false, NW, (TILES >= 2 ? 2 : 1), false>), grid, block, lds, st, tm, a);
-            else if (TILES >= 3 && is_short(3)) BUZZ_LAUNCH((attn_split_kernel<T, D, G, UH, false, NW, TILES, false>), grid, block, lds, st, tm, a);
+            else if (is_short(1)) BUZZ_LAUNCH((attn_split_kernel<T, D, G, UH, false, NW, 1, false, false>), grid, block, lds, st, tm, a);
+            else if (TILES >= 2 && is_short(2)) BUZZ_LAUNCH((attn_split_kernel<T, D, G, UH, false, NW, (TILES >= 2 ? 2 : 1), false, false>), grid, block, lds, st, tm, a);
+            else if (TILES >= 3 && is_short(3)) BUZZ_LAUNCH((attn_split_kernel<T, D, G, UH, false, NW, TILES, false, false>), grid, block, lds, st, tm, a);
             else stream(std::false_type{}, std::integral_constant<int, UC>{});
         };
         if (a.waves == 8) flavour(std::integral_constant<int, 8>{});

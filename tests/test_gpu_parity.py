@@ -163,6 +163,14 @@ def test_short_splits_of_more_units_than_compute_units(G, dtype, rows):
     run(wl, units=[(0, 0), (2, 17), (4, 63)])
 
 
+@pytest.mark.parametrize("G,D,rows", [(3, 256, 90), (4, 128, 150)])
+def test_blocks_paced_by_their_row_sums(G, D, rows):
+    """520 units: two to three 4-wave blocks per compute unit, whose row sums exchange through LDS."""
+    wl = small(batch=65, n_kv_heads=8, n_q_heads=8 * G, head_dim=D, dtype="fp32", prompt=rows, decode_steps=9, sink=3, window=rows - 10, segment=4,
+               keep=1, evict_every=7, n_obs=3)
+    run(wl, units=[(0, 0), (31, 3), (64, 7)])
+
+
 @pytest.mark.parametrize("dtype", ["fp32", "fp16", "bf16"])
 @pytest.mark.parametrize("D", [64, 128, 256])
 @pytest.mark.parametrize("G", [1, 2, 3, 4, 5, 6, 7, 8])

@@ -185,14 +185,14 @@ def test_streaming_steps_of_long_splits_anchor_their_tiles(lib, units, G, D, dty
 def test_the_first_tile_goes_first_where_that_was_faster(lib, units, D, dtype, rows, flags, waves, first):
     """One head: in front of the side requests it thins the stream wherever a tile is more loads than are certain to follow it."""
     h, kernel = prepared(lib, units, 1, D, dtype, rows, flags)
-    nw, short, tile_first = re.search(r"attn_split_kernelI.*ELi([48])ELi([0-3])ELb([01])E", kernel).groups()
+    nw, short, tile_first = re.search(r"attn_split_kernelI.*ELi([48])ELi([0-3])ELb([01])ELb[01]E", kernel).groups()
     assert (int(nw), short, tile_first) == (waves, "0", "01"[first]), kernel
     assert lib.buzz_cache_destroy(h) == 0
 
 
 def split_kernel(kernel):
     """(waves per block, tiles of a short split or 0) of a decode kernel's name."""
-    m = re.search(r"attn_split_kernelI.*ELi([48])ELi([0-3])ELb[01]E", kernel) or re.search(r"attn_split_mfma_kernelI.*Lb[01]ELi([48])ELb[01]ELi([01])E", kernel)
+    m = re.search(r"attn_split_kernelI.*ELi([48])ELi([0-3])ELb[01]ELb[01]E", kernel) or re.search(r"attn_split_mfma_kernelI.*Lb[01]ELi([48])ELb[01]ELi([01])E", kernel)
     return tuple(map(int, m.groups()))
 
 
@@ -251,6 +251,20 @@ def test_which_splits_are_requested_at_once(lib, G, D, dtype, waves, rows, flags
         assert kernel(n) == (waves, 0 if flags else tiles)
         assert kernel(n + 1) == (waves, 0 if flags or tiles == len(rows) else tiles + 1)
     assert kernel(1) == (waves, 0 if flags else 1)
+
+
+@pytest.mark.parametrize("units,G,D,rows,paced", [
+    (520, 3, 256, 319, True), (640, 3, 256, 200, True), (560, 4, 128, 800, True), (280, 4, 128, 2500, True),   # the last: 2 splits per unit
+    (512, 3, 256, 319, False), (512, 4, 128, 800, False), (641, 4, 128, 600, False), (300, 3, 256, 300, False),
+    (560, 3, 256, 64, True), (560, 3, 256, 60, False), (560, 4, 128, 128, True), (560, 4, 128, 120, False),
+    (560, 4, 256, 300, False), (560, 3, 128, 500, False), (560, 2, 256, 300, False), (560, 5, 128, 300, False), (560, 4, 64, 800, False)])
+def test_uneven_blocks_are_paced_where_that_was_faster(lib, units, G, D, rows, paced):
+    """2 to 2.5 blocks per compute unit, 3 heads of 256 or 4 of 128 in fp32, 64 KB of K per split: the sum over a row's lanes goes
+    through LDS."""
+    h, kernel = prepared(lib, units, G, D, "fp32", rows)
+    nw, short, first, via_lds = re.search(r"attn_split_kernelI.*ELi([48])ELi([0-3])ELb([01])ELb([01])E", kernel).groups()
+    assert (nw, short, first, via_lds) == ("4", "0", "0", "01"[paced]), kernel
+    assert lib.buzz_cache_destroy(h) == 0
 
 
 @pytest.mark.parametrize("units,rows,resident", [
