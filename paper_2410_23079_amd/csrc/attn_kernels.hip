@@ -354,7 +354,7 @@ __device__ inline void lds_barrier()
 // where a tile is two loads (K and V of cached rows of up to 256 bytes: 256 units of 1450 28.8 us per step, 29.1 with the
 // side requests first).  Where it is four, the loop waits twice as often for half as much; first / behind:
 //   cached, 8-wave blocks     144 units of 1711 bf16 rows of 256 48.9 / 42.5, 144 of 1769 fp32 rows of 128 47.6 / 41.3; half a percent
-//                             for the side requests over 2100 random steps, at most 3% against
+//                             for the side requests over 2100 random steps, at most 4% against
 //   streaming, 4-wave blocks  272 units of 2872 bf16 rows of 128 86.5 / 74.7, 400 of 1953 66.1 / 63.9; but where 1.6 to 4 blocks on a
 //                             compute unit crowd the memory the thinner stream is the faster one: 480 of 1627 62.4 / 63.8, 560 of
 //                             1395 69.0 / 72.8, 600 of 2929 150.5 / 157.9, 900 of 868 66.9 / 68.7; 1100 of 710 71.9 / 71.1
